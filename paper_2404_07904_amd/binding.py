@@ -1,7 +1,8 @@
-"""Thin ctypes binding of libhgrn2.so: same entry-point names as include/hgrn2.h, argument
-marshalling only.  PyTorch is used for device memory and the current stream, nothing else; every
-step of the computation runs in the HIP kernels.  There is no fallback: if the library is missing
-or a call fails, an exception is raised.
+"""Thin binding of libhgrn2.so: same entry-point names as include/hgrn2.h, argument marshalling only.
+PyTorch is used for device memory and the current stream, nothing else; every step of the
+computation runs in the HIP kernels.  The calls a training or serving loop makes go through the
+native call path _host.so (csrc/host.cpp); the rest, and the C ABI itself (``lib()``), through ctypes.
+There is no fallback: if a library is missing or a call fails, an exception is raised.
 """
 from __future__ import annotations
 
@@ -146,6 +147,24 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_host = None
+
+
+def native():
+    """The native call path (csrc/host.cpp, built next to the library); fails loudly if absent."""
+    global _host
+    if _host is None:
+        lib()                                    # the library itself first: its absence has its own message
+        try:
+            from . import _host as module
+        except ImportError as e:
+            raise RuntimeError("the native call path _host.so is missing or does not load (%s): run "
+                               "`python -m paper_2404_07904_amd.build`" % e) from e
+        module.set_error(Hgrn2Error)
+        _host = module
+    return _host
+
+
 def status_string(status: int) -> str:
     return lib().hgrn2_status_string(int(status)).decode()
 
@@ -205,71 +224,25 @@ def _workspace(nbytes, device, workspace):
 def hgrn2_fwd(q, f, v, h0=None, *, want_hT=True, chunk=0, o=None, hT=None, workspace=None,
               layout=HGRN2_LAYOUT_BHND, domain_flag=None):
     """o, hT = chunkwise forward of the recurrence.  q, f: [B,H,N,dk]; v: [B,H,N,dv]; h0 fp32."""
-    shape = _flagged(make_shape(q, v, f, chunk, layout), domain_flag)
-    assert v.dtype == q.dtype and f.shape == q.shape
-    if o is None:
-        o = torch.empty_like(v)
-    if hT is None and want_hT:
-        hT = torch.empty((shape.B, shape.H, shape.dk, shape.dv), dtype=torch.float32, device=q.device)
-    nbytes = hgrn2_fwd_workspace_bytes(shape)
-    ws = _workspace(nbytes, q.device, workspace)
-    rc = lib().hgrn2_fwd(ctypes.byref(shape), _ptr(q), _ptr(f), _ptr(v), _ptr(h0), _ptr(o), _ptr(hT),
-                         _ptr(ws), ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn2_fwd")
-    return o, hT
+    return (_host or native()).fwd(q, f, None, False, v, h0, want_hT, o, hT, workspace, layout, chunk, domain_flag)
 
 
 def hgrn2_bwd(q, f, v, grad_o, h0=None, grad_hT=None, *, want_grad_h0=False, chunk=0, workspace=None,
               grad_q=None, grad_f=None, grad_v=None, grad_h0=None, layout=HGRN2_LAYOUT_BHND, domain_flag=None):
     """grad_q, grad_f, grad_v, grad_h0 of L = sum(o*grad_o) + sum(hT*grad_hT)."""
-    shape = _flagged(make_shape(q, v, f, chunk, layout), domain_flag)
-    grad_q = torch.empty_like(q) if grad_q is None else grad_q
-    grad_f = torch.empty_like(q) if grad_f is None else grad_f
-    grad_v = torch.empty_like(v) if grad_v is None else grad_v
-    if grad_h0 is None and want_grad_h0:
-        grad_h0 = torch.empty((shape.B, shape.H, shape.dk, shape.dv), dtype=torch.float32, device=q.device)
-    nbytes = hgrn2_bwd_workspace_bytes(shape)
-    ws = _workspace(nbytes, q.device, workspace)
-    rc = lib().hgrn2_bwd(ctypes.byref(shape), _ptr(q), _ptr(f), _ptr(v), _ptr(h0), _ptr(grad_o),
-                         _ptr(grad_hT), _ptr(grad_q), _ptr(grad_f), _ptr(grad_v), _ptr(grad_h0),
-                         _ptr(ws), ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn2_bwd")
-    return grad_q, grad_f, grad_v, grad_h0
+    return (_host or native()).bwd(0, q, f, None, v, h0, grad_o, grad_hT, want_grad_h0, grad_q, grad_f, None, grad_v, grad_h0,
+                                   workspace, layout, chunk, domain_flag)
 
 
 def hgru2_proj_fwd(x, w3, b3, *, keep_av=True, z=None, v=None, q=None, av=None):
     """z, v, q (and av) of the three input projections of the HGRU2 token mixer (Eq. 1).  x: bf16
     [..., d] (any leading shape, contiguous); w3: bf16 [3d, d] (rows of U, V, W); b3: fp32 [3d]."""
-    d = x.shape[-1]
-    M = x.numel() // d if d else 0
-    assert tuple(w3.shape) == (3 * d, d) and w3.dtype == torch.bfloat16 and x.dtype == torch.bfloat16
-    assert b3.dtype == torch.float32 and b3.numel() == 3 * d
-    z = torch.empty_like(x) if z is None else z
-    v = torch.empty_like(x) if v is None else v
-    q = torch.empty_like(x) if q is None else q
-    if av is None and keep_av:
-        av = torch.empty_like(x)
-    rc = lib().hgru2_proj_fwd(M, d, _ptr(x), _ptr(w3), _ptr(b3), _ptr(z), _ptr(v), _ptr(q), _ptr(av), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgru2_proj_fwd")
-    return z, v, q, av
+    return (_host or native()).proj_fwd(x, w3, b3, keep_av, z, v, q, av)
 
 
 def hgru2_proj_bwd(x, w3, q, av, grad_z, grad_v, grad_q, *, workspace=None, grad_x=None, grad_w3=None, grad_b3=None):
     """grad_x (bf16), grad_w3 (fp32 [3d, d]), grad_b3 (fp32 [3d]) of the three projections."""
-    d = x.shape[-1]
-    M = x.numel() // d if d else 0
-    grad_x = torch.empty_like(x) if grad_x is None else grad_x
-    grad_w3 = torch.empty((3 * d, d), dtype=torch.float32, device=x.device) if grad_w3 is None else grad_w3
-    grad_b3 = torch.empty((3 * d,), dtype=torch.float32, device=x.device) if grad_b3 is None else grad_b3
-    ws = _workspace(int(lib().hgru2_proj_bwd_workspace_bytes(M, d)), x.device, workspace)
-    rc = lib().hgru2_proj_bwd(M, d, _ptr(x), _ptr(w3), _ptr(q), _ptr(av), _ptr(grad_z), _ptr(grad_v), _ptr(grad_q),
-                              _ptr(grad_x), _ptr(grad_w3), _ptr(grad_b3), _ptr(ws), ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgru2_proj_bwd")
-    return grad_x, grad_w3, grad_b3
+    return (_host or native()).proj_bwd(x, w3, q, av, grad_z, grad_v, grad_q, workspace, grad_x, grad_w3, grad_b3)
 
 
 def hgrn2_probe_copy(dst, src):
@@ -303,19 +276,7 @@ def hgrn2_fwd_saving(q, f, v, h0=None, *, beta=None, want_hT=True, o=None, hT=No
                      layout=HGRN2_LAYOUT_BHND, domain_flag=None, chunk=0):
     """hgrn2_fwd (or hgrn2_fwd_gated when beta is given) that also keeps the per-chunk states for
     hgrn2_bwd_saved.  Returns o, hT, saved_states (a uint8 device buffer)."""
-    shape = _flagged(make_shape(q, v, f, chunk, layout), domain_flag)
-    if o is None:
-        o = torch.empty_like(v)
-    if hT is None and want_hT:
-        hT = torch.empty((shape.B, shape.H, shape.dk, shape.dv), dtype=torch.float32, device=q.device)
-    if saved_states is None:
-        saved_states = torch.empty(max(hgrn2_saved_states_bytes(shape), 256), dtype=torch.uint8, device=q.device)
-    ws = _workspace(hgrn2_fwd_workspace_bytes(shape), q.device, workspace)
-    rc = lib().hgrn2_fwd_saving(ctypes.byref(shape), _ptr(q), _ptr(f), _ptr(beta), _ptr(v), _ptr(h0), _ptr(o), _ptr(hT),
-                                _ptr(saved_states), saved_states.numel(), _ptr(ws), ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn2_fwd_saving")
-    return o, hT, saved_states
+    return (_host or native()).fwd_saving(q, f, beta, v, h0, want_hT, o, hT, saved_states, workspace, layout, chunk, domain_flag)
 
 
 def hgrn2_bwd_saved(q, f, v, saved_states, grad_o, grad_hT=None, *, beta=None, want_grad_h0=False, workspace=None,
@@ -323,20 +284,8 @@ def hgrn2_bwd_saved(q, f, v, saved_states, grad_o, grad_hT=None, *, beta=None, w
                     chunk=0):
     """hgrn2_bwd (hgrn2_bwd_gated when beta is given) from the states hgrn2_fwd_saving kept.  Returns
     grad_q, grad_f, grad_v, grad_h0 and, with beta, grad_beta as a fifth value."""
-    shape = _flagged(make_shape(q, v, f, chunk, layout), domain_flag)
-    grad_q = torch.empty_like(q) if grad_q is None else grad_q
-    grad_f = torch.empty_like(q) if grad_f is None else grad_f
-    grad_v = torch.empty_like(v) if grad_v is None else grad_v
-    if grad_h0 is None and want_grad_h0:
-        grad_h0 = torch.empty((shape.B, shape.H, shape.dk, shape.dv), dtype=torch.float32, device=q.device)
-    gb = torch.empty_like(beta) if beta is not None else None
-    ws = _workspace(hgrn2_bwd_saved_workspace_bytes(shape, beta is not None), q.device, workspace)
-    rc = lib().hgrn2_bwd_saved(ctypes.byref(shape), _ptr(q), _ptr(f), _ptr(beta), _ptr(v), _ptr(saved_states),
-                               saved_states.numel(), _ptr(grad_o), _ptr(grad_hT), _ptr(grad_q), _ptr(grad_f), _ptr(gb),
-                               _ptr(grad_v), _ptr(grad_h0), _ptr(ws), ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn2_bwd_saved")
-    return (grad_q, grad_f, grad_v, grad_h0) if beta is None else (grad_q, grad_f, grad_v, grad_h0, gb)
+    return (_host or native()).bwd(2, q, f, beta, v, saved_states, grad_o, grad_hT, want_grad_h0, grad_q, grad_f, None, grad_v,
+                                   grad_h0, workspace, layout, chunk, domain_flag)
 
 
 def hgrn2_noalloc_workspace_limit() -> int:
@@ -363,38 +312,15 @@ def hgrn2_fwd_gated(q, z, beta, v, h0=None, *, want_hT=True, o=None, hT=None, wo
                     layout=HGRN2_LAYOUT_BHND, chunk=0, domain_flag=None):
     """hgrn2_fwd with the gate f = beta + (1 - beta) sigmoid(z) formed inside the kernels.
     z: [B,H,N,dk]; beta: fp32 [H,dk]."""
-    shape = _flagged(make_shape(q, v, z, chunk, layout), domain_flag)
-    assert beta.dtype == torch.float32 and tuple(beta.shape) == (shape.H, shape.dk)
-    if o is None:
-        o = torch.empty_like(v)
-    if hT is None and want_hT:
-        hT = torch.empty((shape.B, shape.H, shape.dk, shape.dv), dtype=torch.float32, device=q.device)
-    ws = _workspace(hgrn2_fwd_workspace_bytes(shape), q.device, workspace)
-    rc = lib().hgrn2_fwd_gated(ctypes.byref(shape), _ptr(q), _ptr(z), _ptr(beta), _ptr(v), _ptr(h0), _ptr(o),
-                               _ptr(hT), _ptr(ws), ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn2_fwd_gated")
-    return o, hT
+    return (_host or native()).fwd(q, z, beta, True, v, h0, want_hT, o, hT, workspace, layout, chunk, domain_flag)
 
 
 def hgrn2_bwd_gated(q, z, beta, v, grad_o, h0=None, grad_hT=None, *, want_grad_h0=False, workspace=None,
                     grad_q=None, grad_z=None, grad_beta=None, grad_v=None, grad_h0=None,
                     layout=HGRN2_LAYOUT_BHND, chunk=0, domain_flag=None):
     """grad_q, grad_z, grad_beta, grad_v, grad_h0 of L = sum(o*grad_o) + sum(hT*grad_hT)."""
-    shape = _flagged(make_shape(q, v, z, chunk, layout), domain_flag)
-    grad_q = torch.empty_like(q) if grad_q is None else grad_q
-    grad_z = torch.empty_like(q) if grad_z is None else grad_z
-    grad_v = torch.empty_like(v) if grad_v is None else grad_v
-    grad_beta = torch.empty_like(beta) if grad_beta is None else grad_beta
-    if grad_h0 is None and want_grad_h0:
-        grad_h0 = torch.empty((shape.B, shape.H, shape.dk, shape.dv), dtype=torch.float32, device=q.device)
-    ws = _workspace(hgrn2_bwd_gated_workspace_bytes(shape), q.device, workspace)
-    rc = lib().hgrn2_bwd_gated(ctypes.byref(shape), _ptr(q), _ptr(z), _ptr(beta), _ptr(v), _ptr(h0), _ptr(grad_o),
-                               _ptr(grad_hT), _ptr(grad_q), _ptr(grad_z), _ptr(grad_beta), _ptr(grad_v),
-                               _ptr(grad_h0), _ptr(ws), ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn2_bwd_gated")
-    return grad_q, grad_z, grad_beta, grad_v, grad_h0
+    return (_host or native()).bwd(1, q, z, beta, v, h0, grad_o, grad_hT, want_grad_h0, grad_q, grad_z, grad_beta, grad_v,
+                                   grad_h0, workspace, layout, chunk, domain_flag)
 
 
 def make_shape_varlen(q, v, f, n_seq, chunk=0) -> hgrn2_shape:
@@ -421,25 +347,8 @@ def hgrn2_fwd_varlen(q, f, v, cu_seqlens, h0=None, *, beta=None, want_hT=True, o
     int32 device tensor [n_seq + 1]; h0, hT: fp32 [n_seq,H,dk,dv].  With beta [H,dk] fp32, f holds the
     gates' pre-activations (Eq. 2).  With saved_states (a uint8 device tensor of
     hgrn2_saved_states_varlen_bytes bytes) the call is hgrn2_fwd_varlen_saving."""
-    assert cu_seqlens.dtype == torch.int32 and cu_seqlens.is_contiguous()
-    shape = _flagged(make_shape_varlen(q, v, f, cu_seqlens.numel() - 1, chunk), domain_flag)
-    if o is None:
-        o = torch.empty_like(v)
-    if hT is None and want_hT:
-        hT = torch.empty((shape.B, shape.H, shape.dk, shape.dv), dtype=torch.float32, device=q.device)
-    ws = _workspace(hgrn2_fwd_varlen_workspace_bytes(shape), q.device, workspace)
-    if saved_states is not None:
-        rc = lib().hgrn2_fwd_varlen_saving(ctypes.byref(shape), _ptr(cu_seqlens), _ptr(q), _ptr(f), _ptr(beta), _ptr(v),
-                                           _ptr(h0), _ptr(o), _ptr(hT), _ptr(saved_states), saved_states.numel(),
-                                           _ptr(ws), ws.numel(), _stream())
-        if rc != 0:
-            raise Hgrn2Error(rc, "hgrn2_fwd_varlen_saving")
-        return o, hT
-    rc = lib().hgrn2_fwd_varlen(ctypes.byref(shape), _ptr(cu_seqlens), _ptr(q), _ptr(f), _ptr(beta), _ptr(v), _ptr(h0),
-                                _ptr(o), _ptr(hT), _ptr(ws), ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn2_fwd_varlen")
-    return o, hT
+    return (_host or native()).fwd_varlen(q, f, beta, v, cu_seqlens, h0, want_hT, o, hT, saved_states, workspace, chunk,
+                                          domain_flag)
 
 
 def hgrn2_bwd_varlen(q, f, v, grad_o, cu_seqlens, h0=None, grad_hT=None, *, beta=None, want_grad_h0=False,
@@ -447,28 +356,8 @@ def hgrn2_bwd_varlen(q, f, v, grad_o, cu_seqlens, h0=None, grad_hT=None, *, beta
     """grad_q, grad_f, grad_v, grad_h0 for sequences packed along the token axis; with beta also
     grad_beta (returned as a fifth value), and grad_f is then the gradient of the pre-activations.
     With saved_states (filled by hgrn2_fwd_varlen of the same arguments) the call is hgrn2_bwd_varlen_saved."""
-    assert cu_seqlens.dtype == torch.int32 and cu_seqlens.is_contiguous()
-    shape = _flagged(make_shape_varlen(q, v, f, cu_seqlens.numel() - 1, chunk), domain_flag)
-    gq = torch.empty_like(q) if grad_q is None else grad_q
-    gf = torch.empty_like(q) if grad_f is None else grad_f
-    gv = torch.empty_like(v) if grad_v is None else grad_v
-    gh0 = (torch.empty((shape.B, shape.H, shape.dk, shape.dv), dtype=torch.float32, device=q.device)
-           if want_grad_h0 else None)
-    gb = torch.empty((shape.H, shape.dk), dtype=torch.float32, device=q.device) if beta is not None else None
-    ws = _workspace(hgrn2_bwd_varlen_workspace_bytes(shape), q.device, workspace)
-    if saved_states is not None:
-        rc = lib().hgrn2_bwd_varlen_saved(ctypes.byref(shape), _ptr(cu_seqlens), _ptr(q), _ptr(f), _ptr(beta), _ptr(v),
-                                          _ptr(h0), _ptr(saved_states), saved_states.numel(), _ptr(grad_o), _ptr(grad_hT),
-                                          _ptr(gq), _ptr(gf), _ptr(gb), _ptr(gv), _ptr(gh0), _ptr(ws), ws.numel(), _stream())
-        name = "hgrn2_bwd_varlen_saved"
-    else:
-        rc = lib().hgrn2_bwd_varlen(ctypes.byref(shape), _ptr(cu_seqlens), _ptr(q), _ptr(f), _ptr(beta), _ptr(v), _ptr(h0),
-                                    _ptr(grad_o), _ptr(grad_hT), _ptr(gq), _ptr(gf), _ptr(gb), _ptr(gv), _ptr(gh0), _ptr(ws),
-                                    ws.numel(), _stream())
-        name = "hgrn2_bwd_varlen"
-    if rc != 0:
-        raise Hgrn2Error(rc, name)
-    return (gq, gf, gv, gh0) if beta is None else (gq, gf, gv, gh0, gb)
+    return (_host or native()).bwd_varlen(q, f, beta, v, cu_seqlens, h0, saved_states, grad_o, grad_hT, want_grad_h0, grad_q,
+                                          grad_f, grad_v, workspace, chunk, domain_flag)
 
 
 def hgrn2_min_gate_product(f, beta=None, layout=HGRN2_LAYOUT_BHND, chunk=0):
@@ -515,97 +404,36 @@ def hgrn1_workspace_bytes(B, N, d) -> int:
 def hgrn1_fwd(f, i, o, h0=None, *, want_hN=True, y=None, hN=None, workspace=None):
     """y, hN of the element-wise recurrence h_t = f_t h_{t-1} + (1 - f_t) i_t, y_t = h_t o_t.
     f, i, o: [B,N,d] (i, o bf16; f bf16 or fp32); h0: fp32 [B,d] or None."""
-    B, N, d = i.shape
-    y = torch.empty_like(i) if y is None else y
-    if hN is None and want_hN:
-        hN = torch.empty((B, d), dtype=torch.float32, device=i.device)
-    ws = _workspace(hgrn1_workspace_bytes(B, N, d), i.device, workspace)
-    rc = lib().hgrn1_fwd(B, N, d, _dt(i), _dt(f), _ptr(f), _ptr(i), _ptr(o), _ptr(h0), _ptr(y), _ptr(hN), _ptr(ws),
-                         ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn1_fwd")
-    return y, hN
+    return (_host or native()).hgrn1_fwd(f, i, o, None, h0, want_hN, y, hN, workspace)
 
 
 def hgrn1_bwd(f, i, o, grad_y, h0=None, grad_hN=None, *, want_grad_h0=False, workspace=None, saved=False):
     """grad_f, grad_i, grad_o, grad_h0 of L = sum(y*grad_y) + sum(hN*grad_hN).  saved=True calls
     hgrn1_bwd_saved: `workspace` is then the one hgrn1_fwd of the same inputs was given."""
-    B, N, d = i.shape
-    gf, gi, go = torch.empty_like(i), torch.empty_like(i), torch.empty_like(i)
-    gh0 = torch.empty((B, d), dtype=torch.float32, device=i.device) if want_grad_h0 else None
-    assert workspace is not None or not saved
-    ws = _workspace(hgrn1_workspace_bytes(B, N, d), i.device, workspace)
-    fn = lib().hgrn1_bwd_saved if saved else lib().hgrn1_bwd
-    rc = fn(B, N, d, _dt(i), _dt(f), _ptr(f), _ptr(i), _ptr(o), _ptr(h0), _ptr(grad_y), _ptr(grad_hN),
-            _ptr(gf), _ptr(gi), _ptr(go), _ptr(gh0), _ptr(ws), ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn1_bwd_saved" if saved else "hgrn1_bwd")
-    return gf, gi, go, gh0
+    return (_host or native()).hgrn1_bwd(f, i, o, None, grad_y, h0, grad_hN, want_grad_h0, workspace, saved)
 
 
 def hgrn1_fwd_act(zf, zi, zo, beta, h0=None, *, want_hN=True, y=None, hN=None, workspace=None):
     """y, hN of the element-wise recurrence from the pre-activations of Eq. 1 and the lower bounds
     beta [d] of Eq. 2.  zf, zi, zo: [B,N,d]."""
-    B, N, d = zf.shape
-    assert zi.shape == zf.shape and zo.shape == zf.shape and beta.dtype == torch.float32 and beta.numel() == d
-    if y is None:
-        y = torch.empty_like(zi)
-    if hN is None and want_hN:
-        hN = torch.empty((B, d), dtype=torch.float32, device=zf.device)
-    ws = _workspace(hgrn1_workspace_bytes(B, N, d), zf.device, workspace)
-    rc = lib().hgrn1_fwd_act(B, N, d, _dt(zi), _dt(zf), _ptr(zf), _ptr(zi), _ptr(zo), _ptr(beta), _ptr(h0), _ptr(y),
-                             _ptr(hN), _ptr(ws), ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn1_fwd_act")
-    return y, hN
+    return (_host or native()).hgrn1_fwd_act(zf, zi, zo, beta, h0, want_hN, y, hN, workspace)
 
 
 def hgrn1_bwd_act(zf, zi, zo, beta, grad_y, h0=None, grad_hN=None, *, want_grad_h0=False, workspace=None, saved=False):
     """grad_zf, grad_zi, grad_zo, grad_beta, grad_h0 of L = sum(y*grad_y) + sum(hN*grad_hN).  saved=True
     calls hgrn1_bwd_act_saved: `workspace` is then the one hgrn1_fwd_act of the same inputs was given."""
-    B, N, d = zf.shape
-    assert workspace is not None or not saved
-    gf, gi, go = torch.empty_like(zi), torch.empty_like(zi), torch.empty_like(zi)
-    gb = torch.empty((d,), dtype=torch.float32, device=zf.device)
-    gh0 = torch.empty((B, d), dtype=torch.float32, device=zf.device) if want_grad_h0 else None
-    ws = _workspace(hgrn1_workspace_bytes(B, N, d), zf.device, workspace)
-    fn = lib().hgrn1_bwd_act_saved if saved else lib().hgrn1_bwd_act
-    rc = fn(B, N, d, _dt(zi), _dt(zf), _ptr(zf), _ptr(zi), _ptr(zo), _ptr(beta), _ptr(h0),
-            _ptr(grad_y), _ptr(grad_hN), _ptr(gf), _ptr(gi), _ptr(go), _ptr(gb), _ptr(gh0), _ptr(ws),
-            ws.numel(), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn1_bwd_act_saved" if saved else "hgrn1_bwd_act")
-    return gf, gi, go, gb, gh0
+    return (_host or native()).hgrn1_bwd_act(zf, zi, zo, beta, grad_y, h0, grad_hN, want_grad_h0, workspace, saved)
 
 
 def hgrn2_step(q_t, f_t, v_t, state, o_t=None):
     """One decode step; `state` [B,H,dk,dv] fp32 is updated in place.  Returns o_t [B,H,dv]."""
-    B, H, dk = q_t.shape
-    dv = v_t.shape[-1]
-    assert state.dtype == torch.float32 and tuple(state.shape) == (B, H, dk, dv)
-    if o_t is None:
-        o_t = torch.empty_like(v_t)
-    rc = lib().hgrn2_step(B, H, dk, dv, _dt(q_t), _dt(f_t), _ptr(q_t), _ptr(f_t), _ptr(v_t), _ptr(state),
-                          _ptr(o_t), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn2_step")
-    return o_t
+    return (_host or native()).step(q_t, f_t, None, v_t, state, o_t)
 
 
 def hgrn2_step_gated(q_t, z_t, beta, v_t, state, o_t=None):
     """One decode step from the gate's pre-activations z_t [B,H,dk] and the layer's lower bounds
     beta [H,dk] fp32 (Eq. 2); `state` is updated in place.  Returns o_t [B,H,dv]."""
-    B, H, dk = q_t.shape
-    dv = v_t.shape[-1]
-    assert state.dtype == torch.float32 and tuple(state.shape) == (B, H, dk, dv)
-    assert beta.dtype == torch.float32 and tuple(beta.shape) == (H, dk)
-    if o_t is None:
-        o_t = torch.empty_like(v_t)
-    rc = lib().hgrn2_step_gated(B, H, dk, dv, _dt(q_t), _dt(z_t), _ptr(q_t), _ptr(z_t), _ptr(beta), _ptr(v_t),
-                                _ptr(state), _ptr(o_t), _stream())
-    if rc != 0:
-        raise Hgrn2Error(rc, "hgrn2_step_gated")
-    return o_t
+    return (_host or native()).step_gated(q_t, z_t, beta, v_t, state, o_t)
 
 
 def hgrn2_state_sweep(shape, mode, q, f, b_src, chunk_states, init_state=None, final_state=None):
