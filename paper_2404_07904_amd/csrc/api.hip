@@ -76,6 +76,11 @@ int check_shape_varlen(const hgrn2_shape* s, bool backward, SeqDims* d, bool fin
 
 size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Runs per sequence up to which the workgroups of the forward walk add up the contributions of the runs
+// before theirs themselves (a state of 64 KB each, out of the last-level cache) instead of a carry
+// kernel between the two walks.
+constexpr int kInlineCarryRuns = 16;
+
 // Long sequences in a small batch leave most of the chip idle in the kernels that walk a sequence
 // chunk by chunk.  Those then see every sequence cut into runs of whole chunks: a first walk per
 // run from a zero state yields what the run adds and how it decays what enters it, a carry over
@@ -120,6 +125,23 @@ size_t run_decay_bytes(const SeqDims& d, bool backward)
 {
     int rc;
     const int seg = plan_runs(d, backward, &rc);
+    return seg > 1 ? round256((size_t)d.BH * seg * d.dk * sizeof(float)) : 0;
+}
+
+// The same two for the forward pass, which has a plan of its own for bf16 storage.
+int fwd_segments(const SeqDims& d)
+{
+    int rc;
+    return fwd_fused_supported(d) ? plan_fwd_runs(d).seg : plan_runs(d, false, &rc);
+}
+size_t fwd_run_state_bytes(const SeqDims& d)
+{
+    const int seg = fwd_segments(d);
+    return seg > 1 ? round256((size_t)d.BH * seg * d.dk * d.dv * sizeof(float)) : 0;
+}
+size_t fwd_run_decay_bytes(const SeqDims& d)
+{
+    const int seg = fwd_segments(d);
     return seg > 1 ? round256((size_t)d.BH * seg * d.dk * sizeof(float)) : 0;
 }
 
@@ -303,7 +325,7 @@ size_t hgrn2_fwd_workspace_bytes(const hgrn2_shape* shape)
     return max_over_alternatives(shape, [](const hgrn2_shape* s) -> size_t {
         SeqDims d;
         if (check_shape(s, false, &d, false, true) != HGRN2_OK) return 0;
-        return round256(state_ws_bytes(d)) + run_state_bytes(d, false) + run_decay_bytes(d, false);
+        return round256(state_ws_bytes(d)) + fwd_run_state_bytes(d) + fwd_run_decay_bytes(d);
     }, true, false);
 }
 
@@ -384,7 +406,7 @@ static int fwd_one(const hgrn2_shape* shape, const void* q, const void* f, const
     d.beta = gated ? beta : nullptr;
     if (alt) { d.lay.choice = alt->choice; d.lay.path = alt->path; d.lay.alt = alt->choice2; d.lay.alt_path = alt->path2; d.domain_flag = alt->flag; }
     const size_t one = round256(state_ws_bytes(d));
-    const size_t need = one + run_state_bytes(d, false) + run_decay_bytes(d, false);
+    const size_t need = one + fwd_run_state_bytes(d) + fwd_run_decay_bytes(d);
     if (need > 0 && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255))) return HGRN2_ERR_WORKSPACE;
     if (alt && alt->validate_only) return HGRN2_OK;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
@@ -396,24 +418,36 @@ static int fwd_one(const hgrn2_shape* shape, const void* q, const void* f, const
         return !save_states || !has_tokens ||
                launch_sweep(d, kSweepStateBwd, nullptr, f, v, h0, nullptr, save_states, nullptr, stream) == hipSuccess;
     };
+    float* run_state = reinterpret_cast<float*>(static_cast<char*>(workspace) + one);
+    float* run_decay = reinterpret_cast<float*>(reinterpret_cast<char*>(run_state) + fwd_run_state_bytes(d));
+    if (fwd_fused_supported(d)) {
+        const FwdRuns fr = plan_fwd_runs(d);
+        if (fr.seg <= 1)
+            return launch_fwd_fused(d, q, f, v, h0, o, hT, save_states, stream, fr.light) == hipSuccess ? HGRN2_OK : HGRN2_ERR_HIP;
+        const SeqDims r = as_runs(d, fr.seg, fr.run_chunks);
+        if (fr.seg <= kInlineCarryRuns) {
+            // the runs' workgroups add up what the runs before theirs have left
+            return launch_run_ends(r, fr.seg - 1, q, f, v, run_state, run_decay, stream) == hipSuccess &&
+                   launch_fwd_fused(r, q, f, v, h0, o, hT, save_states, stream, 1, run_state, run_decay) == hipSuccess
+                       ? HGRN2_OK : HGRN2_ERR_HIP;
+        }
+        return launch_run_ends(r, fr.seg, q, f, v, run_state, run_decay, stream) == hipSuccess &&
+               launch_run_carry(d.BH, fr.seg, d.dk, d.dv, h0, run_state, run_decay, hT, false, stream, d.lay.choice, d.lay.path) == hipSuccess &&
+               launch_fwd_fused(r, q, f, v, run_state, o, nullptr, save_states, stream) == hipSuccess
+                   ? HGRN2_OK : HGRN2_ERR_HIP;
+    }
     int run_chunks;
     const int seg = plan_runs(d, false, &run_chunks);
     if (seg > 1) {
         const SeqDims r = as_runs(d, seg, run_chunks);
-        float* run_state = reinterpret_cast<float*>(static_cast<char*>(workspace) + one);
-        float* run_decay = reinterpret_cast<float*>(reinterpret_cast<char*>(run_state) + run_state_bytes(d, false));
         if (launch_sweep(r, kSweepStateFwd, q, f, v, nullptr, run_state, nullptr, run_decay, stream) != hipSuccess ||
             launch_run_carry(d.BH, seg, d.dk, d.dv, h0, run_state, run_decay, hT, false, stream, d.lay.choice, d.lay.path) != hipSuccess)
             return HGRN2_ERR_HIP;
-        if (fwd_fused_supported(r))
-            return launch_fwd_fused(r, q, f, v, run_state, o, nullptr, save_states, stream) == hipSuccess ? HGRN2_OK : HGRN2_ERR_HIP;
         if (launch_sweep(r, kSweepStateFwd, q, f, v, run_state, nullptr, workspace, nullptr, stream) != hipSuccess ||
             launch_fwd_out(d, q, f, v, workspace, o, stream) != hipSuccess || !save_by_sweep())
             return HGRN2_ERR_HIP;
         return HGRN2_OK;
     }
-    if (fwd_fused_supported(d))
-        return launch_fwd_fused(d, q, f, v, h0, o, hT, save_states, stream) == hipSuccess ? HGRN2_OK : HGRN2_ERR_HIP;
     if (launch_sweep(d, kSweepStateFwd, q, f, v, h0, hT, workspace, nullptr, stream) != hipSuccess) return HGRN2_ERR_HIP;
     if (launch_fwd_out(d, q, f, v, workspace, o, stream) != hipSuccess || !save_by_sweep()) return HGRN2_ERR_HIP;
     return HGRN2_OK;
@@ -765,14 +799,17 @@ static int fwd_varlen_one(const hgrn2_shape* shape, const int32_t* cu_seqlens, c
         return HGRN2_ERR_HIP;
     if (first_run) {
         // d now describes the runs: walk each from zero, carry the states over the runs of a sequence, walk again
+        d.lay.spans = 0;                     // a workgroup per run, not per span of chunks
         float* run_state = reinterpret_cast<float*>(static_cast<char*>(ws_s) + one);
         float* run_decay = reinterpret_cast<float*>(static_cast<char*>(ws_s) + one + pr.state_bytes);
-        if (launch_sweep(d, kSweepStateFwd, q, f, v, nullptr, run_state, nullptr, run_decay, stream) != hipSuccess ||
+        if ((fwd_fused_supported(d) ? launch_run_ends(d, 1, q, f, v, run_state, run_decay, stream)
+                                    : launch_sweep(d, kSweepStateFwd, q, f, v, nullptr, run_state, nullptr, run_decay, stream)) != hipSuccess ||
             launch_run_carry_packed(shape->B, shape->H, first_run, d.dk, d.dv, h0, run_state, run_decay, hT, false,
                                     stream, d.lay.alt, d.lay.alt_path) != hipSuccess)
             return HGRN2_ERR_HIP;
-        if (fwd_fused_supported(d))
+        if (fwd_fused_supported(d)) {
             return launch_fwd_fused(d, q, f, v, run_state, o, nullptr, save_states, stream) == hipSuccess ? HGRN2_OK : HGRN2_ERR_HIP;
+        }
         if (launch_sweep(d, kSweepStateFwd, q, f, v, run_state, nullptr, ws_s, nullptr, stream) != hipSuccess ||
             launch_fwd_out(d, q, f, v, ws_s, o, stream) != hipSuccess)
             return HGRN2_ERR_HIP;
@@ -781,8 +818,20 @@ static int fwd_varlen_one(const hgrn2_shape* shape, const int32_t* cu_seqlens, c
             return HGRN2_ERR_HIP;
         return HGRN2_OK;
     }
-    if (fwd_fused_supported(d))
+    if (fwd_fused_supported(d)) {
+        // Spans of two chunks and more get the state a sequence enters them with from a kernel that walks
+        // every span's last sequence from zero (its states lie where the sweeps of fp32 storage keep
+        // theirs); shorter ones take a light walk each.
+        const size_t add = round256((size_t)d.lay.spans * shape->H * d.dk * d.dv * sizeof(float));
+        if (d.N / d.lay.sub >= 2 * d.lay.spans && add + (size_t)d.lay.spans * shape->H * d.dk * sizeof(float) <= one) {
+            float* run_add = static_cast<float*>(ws_s);
+            float* run_decay = reinterpret_cast<float*>(static_cast<char*>(ws_s) + add);
+            return launch_run_ends(d, 1, q, f, v, run_add, run_decay, stream) == hipSuccess &&
+                   launch_fwd_fused(d, q, f, v, h0, o, hT, save_states, stream, 1, run_add, run_decay) == hipSuccess
+                       ? HGRN2_OK : HGRN2_ERR_HIP;
+        }
         return launch_fwd_fused(d, q, f, v, h0, o, hT, save_states, stream) == hipSuccess ? HGRN2_OK : HGRN2_ERR_HIP;
+    }
     if (launch_sweep(d, kSweepStateFwd, q, f, v, h0, hT, ws_s, nullptr, stream) != hipSuccess) return HGRN2_ERR_HIP;
     if (launch_fwd_out(d, q, f, v, ws_s, o, stream) != hipSuccess) return HGRN2_ERR_HIP;
     // (this sweep keeps the states in the read-out's orientation: the backward pass's come from one of their own)

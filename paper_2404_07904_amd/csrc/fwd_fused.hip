@@ -31,21 +31,29 @@
 //   * with fewer sequences than compute units, two workgroups share a sequence, each owning one
 //     half of the dv columns (of V, O and the state): the element-wise work on q and f and the
 //     P blocks are done twice, everything that scales with dv is halved, and the whole chip is busy.
-//   * a packed batch with a group table gives a workgroup a group of consecutive sequences of one
-//     head: the pipeline runs on across the sequence boundaries (the rows of the next sequence's
+//   * heads of 64 channels take workgroups of four waves, two on a compute unit: a wave then owns
+//     two row blocks, one per half wave, since a row has only 32 channel pairs.
+//   * few or long sequences: a workgroup owns a run of a sequence's chunks.  The state that enters
+//     the run comes from a light walk over the chunks before it (the recurrence alone: f, V and
+//     about 0.4 of a chunk's time), either its own, from the sequence's initial state (cuts
+//     placed so that all workgroups finish together), or -- for long sequences -- from walks
+//     from zero, one per run, by run_ends_kernel, whose results the workgroup adds up first.
+//   * a packed batch gives a workgroup a SPAN of a head's chunks, sequence after sequence, however
+//     they lie: the pipeline runs on across the sequence boundaries (the rows of the next sequence's
 //     first chunks are fetched while the current one ends), the state is replaced by the next
-//     sequence's initial state where it starts and written out where one ends.  Many short
-//     sequences then cost the start-up of a workgroup once per group, not once per sequence.
-// Used for bf16 storage with dk = dv = 128 when there are enough sequences to fill the chip;
-// other cases take the sweep + read-out path.
+//     sequence's initial state where it starts and written out where one ends; a span that starts
+//     inside a sequence finds its state as a run does, by a light walk or from run_ends_kernel.
+//     Every workgroup walks equally many chunks, whatever the lengths are.
+// Used for bf16 storage; fp32 storage takes the sweep + read-out path.
 #include "common.hpp"
 #include "kernels.hpp"
 #include <type_traits>
 
 namespace hgrn2 {
 
-constexpr int kFusedWaves = 8;
-constexpr int kFusedThreads = 64 * kFusedWaves;
+// Row blocks of a chunk for the element-wise work: 8 rows each.
+constexpr int kRowBlocks = 8;
+constexpr int kMaxFwdRuns = 16;
 
 struct FwdFusedParams {
     const void* q;
@@ -61,11 +69,24 @@ struct FwdFusedParams {
     TokenLayout lay;     // used when dense == 0
     int dense;           // sequence tensors are [B][H][N][d]: token strides are the compile-time dk, dv
     int* flag;           // null, or set to 1 when a gate product falls below the floor of the reciprocals
+    // Runs of a sequence.  R > 0: run r of sequence s is chunks bnd[r] .. bnd[r + 1] - 1 and the workgroup
+    // numbered s R + r takes it, after a light walk over the chunks before it.
+    int R;
+    short bnd[kMaxFwdRuns + 1];
+    // Otherwise (TokenLayout::seg > 1), with `run_add` set: the state entering run r of sequence s is
+    //   Diag(decay_{r-1}) ( ... Diag(decay_0) h0[s] + add_0 ... ) + add_{r-1},
+    // run_add [s (seg - 1) + j][dk][dv], run_decay [s (seg - 1) + j][dk], j = 0 .. seg - 2.
+    // (run_add null: h0 holds the state entering every run, one per run.)  Spans of a packed batch: entry
+    // span * H + head is what the span adds to the last of its sequences, which goes on in later spans.
+    float* run_add;
+    float* run_decay;
+    int ends_per_seq;    // run_ends_kernel: how many of a sequence's runs are walked, the first ones
 };
 
+constexpr int fused_waves(int dk) { return dk == 128 ? 8 : 4; }
 
-template <int NSPLIT> struct FwdFusedLds {
-    static constexpr int DK = 128, DV = 128, DVW = DV / NSPLIT, C = kChunk;   // DVW: dv columns of one workgroup
+template <int DK_, int DVW_> struct FwdFusedLds {
+    static constexpr int DK = DK_, DVW = DVW_, C = kChunk, NW = fused_waves(DK);   // DVW: dv columns of one workgroup
     // Row pitches in elements.  Tiles read row-major with 16-byte vectors want consecutive rows
     // 4 banks apart (+8 elements); tiles read with transpose loads (4 rows x 64 bytes per half
     // wave) want them 16 banks apart (+32 elements).
@@ -75,14 +96,52 @@ template <int NSPLIT> struct FwdFusedLds {
     static constexpr size_t vm = km + (size_t)2 * DK * PT * 2;          // V     [C][PV]
     static constexpr size_t pm = vm + (size_t)C * PV * 2;               // P   [C][PC]
     static constexpr size_t sb = pm + (size_t)C * PC * 2;               // G_m S_n, bf16, fragment order
-    static constexpr int NSB = (NSPLIT == 2) ? 2 : 1;                  // copies of the published state (see LATE_QS)
+    static constexpr bool late_qs = (C / 32) * (DVW / 32) < NW;         // see LATE_QS
+    static constexpr int NSB = late_qs ? 2 : 1;                         // copies of the published state
     static constexpr size_t ost = sb + (size_t)NSB * DK * DVW * 2;      // O   [C][PO]
     static constexpr size_t tot = ost + (size_t)C * PO * 2;             // [8][DK] fp32 block totals + one row of ones
-    static constexpr size_t ca = tot + (size_t)(kFusedWaves + 1) * DK * 4;   // [DK] fp32 state rescale
+    static constexpr size_t ca = tot + (size_t)(kRowBlocks + 1) * DK * 4;    // [DK] fp32 state rescale
     static constexpr size_t ch = ca + (size_t)DK * 4;                   // [DK] fp32 h of the chunk before (grouped walks)
     static constexpr size_t total = ch + (size_t)DK * 4;
     static_assert(total <= 160 * 1024, "LDS budget of one workgroup");
+    // light walk (the same memory, before the walk proper)
+    static constexpr size_t lk = 0;                                     // K^^T  [2][DK][PT]
+    static constexpr size_t lv = lk + (size_t)2 * DK * PT * 2;          // V     [2][C][PV]
+    static constexpr size_t lt = lv + (size_t)2 * C * PV * 2;           // [2][8][DK] fp32 block totals, then a row of ones
+    static constexpr size_t lg = lt + (size_t)(2 * kRowBlocks + 1) * DK * 4;   // [2][DK] fp32 whole-chunk gate product
+    static constexpr size_t light_total = lg + (size_t)2 * DK * 4;
+    static_assert(light_total <= total, "the light walk fits the tiles of the walk proper");
 };
+
+// RW rows of this lane's channel pair of a [token][DK] tensor.  Heads of 128 channels: rows row0 .. row0
+// + 7 for the whole wave (row0 wave-uniform); heads of 64: rows row0 .. row0 + 7 for the lower half wave
+// and the eight after them for the upper one.  Rows outside the sequence re-read a row inside it.
+template <int DK, int RW, bool IS_BF16>
+__device__ __forceinline__ void load_block_rows(RawRows<RW>& out, const char* seq_base, int row0, int last_row, int ld, int lane)
+{
+    if constexpr (DK == 128) {
+        load_rows_clamped<RW, IS_BF16>(out, seq_base, row0, last_row, ld, 2 * lane);
+    } else {
+        constexpr int ES = IS_BF16 ? 2 : 4;
+        const int half = lane >> 5, col = 2 * (lane & 31);
+        if (row0 >= 0 && row0 + 2 * RW - 1 <= last_row) {
+            const char* rp = seq_base + (size_t)row0 * (ld * ES) + (uint32_t)((half * RW * ld + col) * ES);
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp + i * ld * ES));
+                else out.r[i] = *reinterpret_cast<const f32x2*>(rp + i * ld * ES);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                const int rc = min(max(row0 + half * RW + i, 0), last_row);
+                const char* rp = seq_base + (size_t)rc * (ld * ES) + col * ES;
+                if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp));
+                else out.r[i] = *reinterpret_cast<const f32x2*>(rp);
+            }
+        }
+    }
+}
 
 // One chunk of the walk: tokens row0 .. row0 + C - 1 of a sequence of N tokens whose first token is
 // token tok0 of the packed tensors (grouped walks; 0 otherwise).  N = 0: a pass past the end.
@@ -94,30 +153,36 @@ struct FusedChunk {
     int tok0, row0, N, bh, first, last, slot, lo, hi;
 };
 
-template <bool GATE_BF16, int NSPLIT, bool DENSE, bool GROUPED>
+// GROUPED: a span of a packed batch's chunks (else: a sequence, or a run of one).  ENDS: only the state
+// that a run leaves when it starts from zero, and the product of its gates (run_ends_kernel).  RUNS: the
+// workgroup may own a run that does not start with the sequence, and an odd number of chunks ends in
+// a single pass of its own; without it the chunk loop always takes an even number of passes (a pass
+// over a chunk past the end sees gates equal to one and is an exact no-op), which costs short odd walks
+// a pass and saves long ones registers (128 sequences of 2048 tokens: 92.4 against 95.9 us).
+template <int DK, int DV, int DVW, bool GATE_BF16, bool DENSE, bool GROUPED, bool ENDS, bool RUNS = true>
 __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
 {
-    static_assert(!(DENSE && GROUPED), "groups are a feature of packed batches");
+    static_assert(!(DENSE && GROUPED), "spans are a feature of packed batches");
     typedef __bf16 T;
     typedef Mma<T> M;
     typedef typename M::frag frag;
-    typedef FwdFusedLds<NSPLIT> L;
-    constexpr int DK = L::DK, DV = L::DV, DVW = L::DVW, C = L::C, NW = kFusedWaves, RW = C / NW;
+    typedef FwdFusedLds<DK, DVW> L;
+    constexpr int NSPLIT = DV / DVW, C = L::C, NW = L::NW, NT = 64 * NW, RW = C / kRowBlocks;
     constexpr int PQ = L::PQ, PT = L::PT, PV = L::PV, PC = L::PC, PO = L::PO;
     constexpr int NBT = DVW / 32, NKS = DK / 16;
-    constexpr int NST = (DK / 32) * NBT / NW;        // state tiles per wave: 2 (whole dv) or 1 (half)
+    constexpr int NST = (DK / 32) * NBT / NW;        // state tiles per wave: 2 (128 x 128) or 1
     constexpr int NOT = (C / 32) * NBT;              // output tiles of the workgroup: waves 0 .. NOT-1 own one
     constexpr int PW0 = (NOT == NW) ? 0 : NOT;       // first of the three waves that compute the P blocks
-    // With half the dv columns per workgroup only four waves own an output tile; their read-out of
+    // With 64 dv columns per workgroup of eight waves only four own an output tile; their read-out of
     // the incoming state, Q~ (G_m S_n), is then issued one stage late, in stage A of the next pass,
     // next to the P blocks the other waves compute there (the published state is double-buffered
     // for that, and O(n) leaves in stage B of pass n+1).  This evens out the matrix work of the
     // two stages.
-    constexpr bool LATE_QS = (NSPLIT == 2);
-    // With the smaller register footprint of the split variant, every MFMA chain requests all its
+    constexpr bool LATE_QS = L::late_qs;
+    // With the smaller register footprint of the 64-column variants (and of bf16 gates), every MFMA chain requests all its
     // operand fragments first and the instruction scheduler is told not to sink those loads back
     // between the MFMAs: one LDS latency per chain instead of one per k-step pair.
-    constexpr bool BATCH_LOADS = (NSPLIT == 2);
+    constexpr bool BATCH_LOADS = (DVW == 64) && GATE_BF16;
     constexpr int KB8 = BATCH_LOADS ? DK / 16 : 2, KB4 = BATCH_LOADS ? kChunk / 16 : 1;   // k-steps per batch
     static_assert(RW == 8 && NST * NW == (DK / 32) * NBT && NOT <= NW && PW0 + 3 <= NW, "tile/wave mapping");
 
@@ -133,44 +198,83 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     float* cH = reinterpret_cast<float*>(smem + L::ch);
 
     if (not_chosen(p.lay)) return;       // one of several chunk lengths, and not the one called for
-    // workgroup -> (sequence, dv half): ids 8 apart land on the same XCD (ids are dealt to the 8
-    // XCDs round-robin), so the two halves of a sequence share an L2 for the q, f rows both read
-    int bh, split;
-    if (NSPLIT == 1) { bh = blockIdx.x; split = 0; }
-    else { const int x = blockIdx.x & 7, r = blockIdx.x >> 3; split = r % NSPLIT; bh = (r / NSPLIT) * 8 + x; }
+    // workgroup -> (sequence, run, dv half): ids 8 apart land on the same XCD (ids are dealt to the 8
+    // XCDs round-robin), so the workgroups of a sequence share an L2 for the rows several of them read
+    int bh, split, run = 0;
+    const int n_run = (GROUPED || !RUNS || p.R == 0) ? 1 : p.R;
+    if (NSPLIT == 1 && n_run == 1) { bh = blockIdx.x; split = 0; }
+    else {
+        const int x = blockIdx.x & 7, r = blockIdx.x >> 3, per = n_run * NSPLIT, sub = r % per;
+        bh = (r / per) * 8 + x;
+        split = sub % NSPLIT; run = sub / NSPLIT;
+    }
     // padding of the grid (uniform, before any barrier)
-    if (bh >= (GROUPED ? p.lay.G * p.lay.H : p.BH)) return;
-    // grouped: the sequences e0 .. e1 - 1 of head `head`, found through the table's arrays
-    int e0 = 0, e1 = 0, head = 0;
+    int ends_slot = bh;
+    if constexpr (ENDS && !GROUPED) {
+        // the first ends_per_seq of the seg runs of every sequence
+        const int whole = bh / p.ends_per_seq;
+        if (whole * p.lay.seg >= p.BH) return;
+        bh = whole * p.lay.seg + (bh - whole * p.ends_per_seq);
+    } else {
+        if (bh >= (GROUPED ? p.lay.spans * p.lay.H : p.BH)) return;
+    }
     const int* t_start = p.lay.vl;
     const int* t_len = p.lay.vl + (p.lay.B + 1);
+    const int* t_before = p.lay.vl + 2 * (p.lay.B + 1);
+    // GROUPED: the span is chunks p0 .. p1 - 1 of head `head`, counted over the sequences in order; it
+    // starts with chunk cur_n of sequence cur_e
+    int head = 0, cur_e = 0, cur_n = 0, span_id = 0;
+    SeqView sv;
+    int NC;                                  // chunks of the walk
+    int n0 = 0;                              // its first chunk, within the sequence (not GROUPED)
     if constexpr (GROUPED) {
-        const int grp = bh / p.lay.H;
-        head = bh - grp * p.lay.H;
-        e0 = table_read(p.lay.groups, grp); e1 = table_read(p.lay.groups, grp + 1);
-        bh = e0 * p.lay.H + head;            // (only for the view below, whose chunk count is replaced)
+        span_id = bh / p.lay.H;
+        head = bh - span_id * p.lay.H;
+        // addresses are formed from token numbers: the view is the head's slice of the whole tensor
+        sv.off_k = (size_t)head * p.lay.sh_k; sv.off_v = (size_t)head * p.lay.sh_v; sv.chunk0 = 0;
+        sv.N = 0; sv.NC = 0;
+        const int total = table_read(t_before, p.lay.B);
+        const int p0 = (int)((long long)span_id * total / p.lay.spans), p1 = (int)((long long)(span_id + 1) * total / p.lay.spans);
+        NC = p1 - p0;
+        if (NC > 0) {
+            // the sequence that holds chunk p0 (ENDS: the span's last chunk): the last one with at most
+            // that many chunks before it
+            const int at = ENDS ? p1 - 1 : p0;
+            int lo = 0, hi = p.lay.B;        // invariant: before[lo] <= at < before[hi]
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (table_read(t_before, mid) <= at) lo = mid; else hi = mid;
+            }
+            cur_e = lo;
+            const int before = table_read(t_before, lo);
+            cur_n = max(p0 - before, 0);
+            if constexpr (ENDS) {
+                // that sequence's chunks inside the span, if it goes on in the next one
+                if (table_read(t_before, lo + 1) == p1) return;
+                NC = p1 - before - cur_n;
+            }
+        }
     } else {
         bh = sequence_of_workgroup<DENSE>(p.lay, bh);
+        if constexpr (ENDS) { if (!DENSE && p.lay.vl) ends_slot = bh; }
+        sv = seq_view<DENSE, DK, DV, true>(p.lay, p.N, p.NC, bh);
+        NC = sv.NC;
+        if (RUNS && n_run > 1) { n0 = p.bnd[run]; NC = p.bnd[run + 1] - n0; }
+        head = bh / p.lay.seg % p.H;
     }
+    // the sequence whose entries of h0 and hT the walk starts from and ends in
+    const int whole = (RUNS && !ENDS && !GROUPED && p.run_add) ? bh / p.lay.seg : bh;
     const int dv0 = split * DVW;             // first dv column of this workgroup
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave index, in a scalar register
-    SeqView sv;
-    if constexpr (GROUPED) {
-        // addresses are formed from token numbers: the view is the head's slice of the whole tensor
-        sv.off_k = (size_t)head * p.lay.sh_k; sv.off_v = (size_t)head * p.lay.sh_v; sv.chunk0 = 0;
-        sv.N = 0;
-        sv.NC = table_read(p.lay.vl, 2 * (p.lay.B + 1) + e1) - table_read(p.lay.vl, 2 * (p.lay.B + 1) + e0);   // chunks of all the group's sequences
-    } else {
-        sv = seq_view<DENSE, DK, DV, true>(p.lay, p.N, p.NC, bh);
-    }
+    // element-wise work: this lane's row block (of 8) and channel pair
+    const int rb = (DK == 128) ? w : 2 * w + g, cl = (DK == 128) ? lane : r32;
+    const int wrow = (C / NW) * w;           // first row of the wave
     const size_t seq_k = sv.off_k, seq_v = sv.off_v;
     const int ld_k = DENSE ? DK : (int)p.lay.sn_k, ld_v = DENSE ? DV : (int)p.lay.sn_v;   // token stride, elements
     const T* qg = static_cast<const T*>(p.q);
     const T* vg = static_cast<const T*>(p.v);
     T* og = static_cast<T*>(p.o);
-    const int NC = sv.NC;                    // passes over chunks with tokens
-
     const int rt = w / NBT, bt = w % NBT;    // output tile (rt, bt) of this wave, if w < NOT
     const int at0 = NST * (w / NBT);         // its state tiles: (at0 .. at0 + NST - 1, bt)
     const bool has_o = (NOT == NW) || w < NOT;
@@ -180,58 +284,69 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     // a sequence without tokens ends in the state it starts from
     auto pass_state_on = [&](int seq) {
         if (p.hT)
-            for (int idx = tid; idx < DK * DVW; idx += kFusedThreads) {
+            for (int idx = tid; idx < DK * DVW; idx += NT) {
                 const size_t e = (size_t)seq * DK * DV + (size_t)(idx / DVW) * DV + dv0 + idx % DVW;
                 p.hT[e] = p.h0 ? p.h0[e] : 0.0f;
             }
     };
     if constexpr (GROUPED) {
-        for (int e = e0; e < e1; ++e)
+        // (such sequences lie in no span: they are dealt out by their number)
+        for (int e = ENDS ? p.lay.B : span_id; e < p.lay.B; e += p.lay.spans)
             if (table_read(t_len, e) == 0) pass_state_on(e * p.lay.H + head);
         if (NC == 0) return;                 // (uniform early exit, before any barrier)
     } else if (NC == 0) {
-        pass_state_on(bh);
+        if constexpr (!ENDS) pass_state_on(bh);
         return;
     }
 
-    // ---- the chunks of the walk, in order.  Grouped walks step through the group's sequences with
-    // a cursor that runs three chunks ahead of the pass (everything here is wave-uniform).
-    int cur_e = e0 - 1, cur_n = 0, cur_nc = 0, cur_tok = 0, cur_N = 0, cur_slot = 0;
+    // ---- the chunks of the walk, in order.  Spans step through the sequences with a cursor that runs
+    // three chunks ahead of the pass (everything here is wave-uniform).
+    int cur_nc = 0, cur_tok = 0, cur_N = 0, cur_slot = 0, left = NC;
+    auto open_sequence = [&](int e) {
+        cur_e = e;
+        cur_N = table_read(t_len, e); cur_nc = p.lay.chunks_of(cur_N); cur_tok = table_read(t_start, e);
+        // the chunks of (sequence, head) lie together, the heads of a sequence one after the other
+        cur_slot = table_read(t_before, e) * p.lay.H + head * cur_nc;
+    };
     auto next_chunk = [&]() {
         FusedChunk c;
-        if (cur_n + 1 < cur_nc) ++cur_n;
-        else {
-            int e = cur_e + 1, len = 0;
-            while (e < e1 && (len = table_read(t_len, e)) == 0) ++e;
-            if (e < e1) {
-                cur_e = e; cur_N = len; cur_nc = p.lay.chunks_of(len); cur_tok = table_read(t_start, e);
-                // the chunks of (sequence, head) lie together, the heads of a sequence one after the other
-                cur_slot = table_read(p.lay.vl, 2 * (p.lay.B + 1) + e) * p.lay.H + head * cur_nc;
-            } else { cur_e = e1; cur_N = 0; cur_nc = 0; cur_tok = 0; cur_slot = 0; }          // past the end, for good
-            cur_n = 0;
+        if (left <= 0) {                     // past the end of the span, for good
+            c.tok0 = 0; c.row0 = 0; c.lo = 0; c.hi = 0; c.N = 0; c.bh = 0; c.first = 0; c.last = 0; c.slot = 0;
+            return c;
         }
         const ChunkRows cr = chunk_rows(p.lay.sub, cur_n, cur_N);
         c.tok0 = cur_tok; c.row0 = cr.tok0; c.lo = cr.first; c.hi = cr.end; c.N = cur_N; c.bh = cur_e * p.lay.H + head;
-        c.first = cur_n == 0; c.last = cur_N > 0 && cur_n == cur_nc - 1; c.slot = cur_slot + cur_n;
+        c.first = cur_n == 0; c.last = cur_n == cur_nc - 1; c.slot = cur_slot + cur_n;
+        if (--left > 0 && ++cur_n == cur_nc) {
+            int e = cur_e + 1;
+            while (table_read(t_len, e) == 0) ++e;       // (left > 0: a later sequence has tokens)
+            open_sequence(e);
+            cur_n = 0;
+        }
         return c;
     };
     const int N_one = sv.N;
-    auto chunk_at = [&](int c) {             // one sequence per workgroup: chunk c of it (any c >= -1)
+    auto chunk_at = [&](int c) {             // chunk c of the workgroup's sequence; rows of chunks outside the walk stand for no token
         FusedChunk k;
         const ChunkRows cr = chunk_rows(p.lay.sub, c, N_one);
-        k.tok0 = 0; k.row0 = cr.tok0; k.lo = cr.first; k.hi = cr.end;
+        const bool in = !RUNS || (c >= n0 && c < n0 + NC);
+        k.tok0 = 0; k.row0 = cr.tok0; k.lo = cr.first; k.hi = in ? cr.end : cr.first;
         k.N = N_one; k.bh = bh; k.first = c == 0; k.last = c == NC - 1; k.slot = sv.chunk0 + c;
         return k;
     };
-    // window of the pass: ck[j] = chunk n - 1 + j of pass n (grouped walks only)
+    // window of the pass: ck[j] = chunk n - 1 + j of pass n (spans only)
     FusedChunk ck[5];
+    const int first_n = cur_n;               // the span starts with this chunk of its first sequence
+    int first_tok = 0, first_N = 0, first_bh = bh;
     if constexpr (GROUPED) {
-        ck[0].tok0 = 0; ck[0].row0 = 0; ck[0].N = 0; ck[0].bh = bh; ck[0].first = 1; ck[0].last = 0; ck[0].slot = 0;
+        open_sequence(cur_e);
+        first_tok = cur_tok; first_N = cur_N; first_bh = cur_e * p.lay.H + head;
+        ck[0].tok0 = 0; ck[0].row0 = 0; ck[0].N = 0; ck[0].bh = 0; ck[0].first = 0; ck[0].last = 0; ck[0].slot = 0;
         ck[0].lo = 0; ck[0].hi = 0;
 #pragma unroll
         for (int j = 1; j < 5; ++j) ck[j] = next_chunk();
     }
-    auto chunk_rel = [&](int n, int rel) { return GROUPED ? ck[rel + 1] : chunk_at(n + rel); };
+    auto chunk_rel = [&](int n, int rel) { return GROUPED ? ck[rel + 1] : chunk_at(n0 + n + rel); };
 
     // ---- state: fp32 accumulators.  Between chunks they hold S_n / h(n-1); see stage A. ----
     f32x16 accS[NST];
@@ -277,37 +392,69 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
                 for (int jj = 0; jj < 4; ++jj) *reinterpret_cast<float*>(rows + st_lane + jj * DV * 4) = accS[j][4 * c + jj];
             }
     };
-    initial_state(GROUPED ? ck[1].bh : bh);
-    float hprev0 = 1.0f, hprev1 = 1.0f;      // h of the previous chunk, channels 2*lane, 2*lane+1 (wave 0 only)
+    if constexpr (ENDS) {
+#pragma unroll
+        for (int j = 0; j < NST; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) accS[j][v] = 0.0f;
+    } else {
+        initial_state(GROUPED ? first_bh : whole);
+        if (RUNS && p.run_add) {
+            // what the runs before this one add, and how their gates decay what enters them
+            int k0 = 0, k1 = bh - whole * p.lay.seg;
+            if constexpr (GROUPED) {
+                // the spans from the one in which the span's first sequence starts
+                k1 = k0 = span_id;
+                if (first_n > 0) {
+                    const int total = table_read(t_before, p.lay.B), before = table_read(t_before, first_bh / p.lay.H);
+                    while (k0 > 0 && (int)((long long)k0 * total / p.lay.spans) > before) --k0;
+                }
+            }
+            for (int k = k0; k < k1; ++k) {
+                const int slot = GROUPED ? k * p.lay.H + head : whole * (p.lay.seg - 1) + k;
+                const float* dec = p.run_decay + (size_t)slot * DK;
+#pragma unroll
+                for (int j = 0; j < NST; ++j)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const f32x4 dm = *reinterpret_cast<const f32x4*>(dec + 32 * (at0 + j) + 8 * c + 4 * g);
+                        const char* rows = state_rows(p.run_add, slot, j, c);
+#pragma unroll
+                        for (int jj = 0; jj < 4; ++jj)
+                            accS[j][4 * c + jj] = fmaf(dm[jj], accS[j][4 * c + jj], *reinterpret_cast<const float*>(rows + st_lane + jj * DV * 4));
+                    }
+            }
+        }
+    }
+    float hprev0 = 1.0f, hprev1 = 1.0f;      // h of the previous chunk, channels 2*cl, 2*cl+1 (wave 0 only)
 
     // ---- row fetch, two chunks ahead, two register sets ----
     RawRows<RW> rawf[2], rawq[2];
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int VPR = DVW / 8;             // 16-byte vectors per V / O row
-    constexpr int NVV = VPR / 8;             // vectors per thread
+    constexpr int NVV = C * VPR / NT;        // vectors per thread
     constexpr int VRS = 64 / VPR;            // rows one wave covers per vector
     // V: two chunks ahead too, in alternating sets, where the registers allow it (fp32 gates take
     // twice the prefetch registers of bf16 ones; V is then fetched one chunk ahead)
     constexpr int VD = GATE_BF16 ? 2 : 1;
     u32x4 rawv[VD][NVV];
-    const int vrow = RW * w + lane / VPR, vcol = 8 * (lane % VPR);      // V copy: 16 bytes per lane, rows vrow (+ VRS)
+    const int vrow = wrow + lane / VPR, vcol = 8 * (lane % VPR);      // V copy: 16 bytes per lane, rows vrow (+ VRS)
     // Every load is issued unconditionally (a row past the end of the sequence re-reads the last
-    // row), and the chunk loop always runs an even number of passes, so that its body is
-    // straight-line code: the compiler can then count outstanding loads exactly and the two
-    // register sets never have to be copied.  A pass over a chunk index >= NC sees gates equal
-    // to one on every row and is an exact no-op on the state.  Row addresses are wave-uniform.
+    // row), and the chunk loop takes two chunks per turn, so that its body is straight-line code:
+    // the compiler can then count outstanding loads exactly and the two register sets never have
+    // to be copied.  Row addresses are wave-uniform.
     const char* fbase = static_cast<const char*>(p.f) + seq_k * (GATE_BF16 ? 2 : 4);
     const char* qbase = reinterpret_cast<const char*>(qg + seq_k);
     const char* vbase = reinterpret_cast<const char*>(vg + seq_v + dv0);
     auto load_f = [&](RawRows<RW>& d, const FusedChunk& c) {
-        load_rows_clamped<RW, GATE_BF16>(d, fbase + (size_t)c.tok0 * ((size_t)ld_k * (GATE_BF16 ? 2 : 4)), c.row0 + RW * w,
-                                         max(c.N - 1, 0), ld_k, 2 * lane);
+        load_block_rows<DK, RW, GATE_BF16>(d, fbase + (size_t)c.tok0 * ((size_t)ld_k * (GATE_BF16 ? 2 : 4)), c.row0 + wrow,
+                                           max(c.N - 1, 0), ld_k, lane);
     };
     auto load_q = [&](RawRows<RW>& d, const FusedChunk& c) {
-        load_rows_clamped<RW, true>(d, qbase + (size_t)c.tok0 * ((size_t)ld_k * 2), c.row0 + RW * w, max(c.N - 1, 0), ld_k, 2 * lane);
+        load_block_rows<DK, RW, true>(d, qbase + (size_t)c.tok0 * ((size_t)ld_k * 2), c.row0 + wrow, max(c.N - 1, 0), ld_k, lane);
     };
     auto load_v = [&](u32x4 (&d)[NVV], const FusedChunk& c) {
-        const int row0 = c.row0 + RW * w, last_row = max(c.N - 1, 0);
+        const int row0 = c.row0 + wrow, last_row = max(c.N - 1, 0);
         const char* vb = vbase + (size_t)c.tok0 * ((size_t)ld_v * 2);
 #pragma unroll
         for (int j = 0; j < NVV; ++j) {
@@ -337,9 +484,8 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     float below_floor = 1.0f;            // smallest product a reciprocal was taken of (reported once, at the end)
     auto prep_gates = [&](const RawRows<RW>& rf_raw, const RawRows<RW>& rq_raw, const FusedChunk& c) {
         f32x2 rf[RW];
-        convert_rows<RW>(rf, rf_raw, c.row0 + RW * w, c.hi, true, GATE_BF16, 1.0f, c.lo);
-        if (p.beta)
-            gate_rows<RW>(rf, p.beta + (size_t)(GROUPED ? head : bh / p.lay.seg % p.H) * DK, 2 * lane, true, c.row0 + RW * w, c.hi, c.lo);
+        convert_rows<RW>(rf, rf_raw, c.row0 + RW * rb, c.hi, true, GATE_BF16, 1.0f, c.lo);
+        if (p.beta) gate_rows<RW>(rf, p.beta + (size_t)head * DK, 2 * cl, true, c.row0 + RW * rb, c.hi, c.lo);
         float run0 = 1.0f, run1 = 1.0f;
 #pragma unroll
         for (int i = 0; i < RW; ++i) {
@@ -356,19 +502,19 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
             kz0[i] = run0 - n0; kz1[i] = run1 - n1;
             run0 = n0; run1 = n1;
         }
-        *reinterpret_cast<f32x2*>(tot + w * DK + 2 * lane) = f32x2{bt0, bt1};
+        *reinterpret_cast<f32x2*>(tot + rb * DK + 2 * cl) = f32x2{bt0, bt1};
     };
     // Second half: block factors from the exchanged totals, tiles to LDS.
     auto prep_tiles = [&](int c, bool starts_sequence) {      // c: only its parity matters (which tile buffer)
         // product of the (at most three) block totals between this block and the reference row;
-        // the row addresses are wave-uniform, an absent factor reads the row of ones
-        const float* ones = tot + NW * DK;
-        const float* r1 = after ? (w > 4 ? tot + 4 * DK : ones) : (w < 3 ? tot + 3 * DK : ones);
-        const float* r2 = after ? (w > 5 ? tot + 5 * DK : ones) : (w < 2 ? tot + 2 * DK : ones);
-        const float* r3 = after ? (w > 6 ? tot + 6 * DK : ones) : (w < 1 ? tot + 1 * DK : ones);
-        const f32x2 m1 = *reinterpret_cast<const f32x2*>(r1 + 2 * lane);
-        const f32x2 m2 = *reinterpret_cast<const f32x2*>(r2 + 2 * lane);
-        const f32x2 m3 = *reinterpret_cast<const f32x2*>(r3 + 2 * lane);
+        // an absent factor reads the row of ones
+        const float* ones = tot + kRowBlocks * DK;
+        const float* r1 = after ? (rb > 4 ? tot + 4 * DK : ones) : (rb < 3 ? tot + 3 * DK : ones);
+        const float* r2 = after ? (rb > 5 ? tot + 5 * DK : ones) : (rb < 2 ? tot + 2 * DK : ones);
+        const float* r3 = after ? (rb > 6 ? tot + 6 * DK : ones) : (rb < 1 ? tot + 1 * DK : ones);
+        const f32x2 m1 = *reinterpret_cast<const f32x2*>(r1 + 2 * cl);
+        const f32x2 m2 = *reinterpret_cast<const f32x2*>(r2 + 2 * cl);
+        const f32x2 m3 = *reinterpret_cast<const f32x2*>(r3 + 2 * cl);
         const float mid0 = m1.x * m2.x * m3.x, mid1 = m1.y * m2.y * m3.y;
         const float R0 = fast_rcp(fmaxf(mid0 * bt0, kTinyProduct));
         const float R1 = fast_rcp(fmaxf(mid1 * bt1, kTinyProduct));
@@ -377,9 +523,9 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         const float sz0 = after ? R0 : mid0, sz1 = after ? R1 : mid1;       // multiplies k z
         // Q~: row-major, channel pair (2l, 2l+1) at column position sigma(2l) (bits 2 and 3 swapped);
         // K~^T: this thread's 8 tokens of each of its two channels as one 16-byte vector
-        const int qcol = ((2 * lane) & ~12) | (((2 * lane) & 4) << 1) | (((2 * lane) & 8) >> 1);
-        T* Qd = Qm + (size_t)(c & 1) * C * PQ + (size_t)(RW * w) * PQ + qcol;
-        T* Kd = Km + (size_t)(c & 1) * DK * PT + (size_t)(2 * lane) * PT + RW * w;
+        const int qcol = ((2 * cl) & ~12) | (((2 * cl) & 4) << 1) | (((2 * cl) & 8) >> 1);
+        T* Qd = Qm + (size_t)(c & 1) * C * PQ + (size_t)(RW * rb) * PQ + qcol;
+        T* Kd = Km + (size_t)(c & 1) * DK * PT + (size_t)(2 * cl) * PT + RW * rb;
         float k0[RW], k1[RW];
 #pragma unroll
         for (int i = 0; i < RW; ++i) {
@@ -390,17 +536,17 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         *reinterpret_cast<frag*>(Kd + PT) = M::pack(k1);
         // state rescale of the chunk, by wave 0: h of the previous chunk times G_m of this one
         if (w == 0) {
-            f32x2 t[NW];
+            f32x2 t[kRowBlocks];
 #pragma unroll
-            for (int i = 0; i < NW; ++i) t[i] = *reinterpret_cast<const f32x2*>(tot + i * DK + 2 * lane);
+            for (int i = 0; i < kRowBlocks; ++i) t[i] = *reinterpret_cast<const f32x2*>(tot + i * DK + 2 * cl);
             const float gm0 = (t[0].x * t[1].x) * (t[2].x * t[3].x), gm1 = (t[0].y * t[1].y) * (t[2].y * t[3].y);
             if constexpr (GROUPED) {
                 // the state of a sequence's first chunk is its initial state, not what the walk carries;
                 // and h alone turns the carried accumulators into the state a sequence ends in
-                *reinterpret_cast<f32x2*>(cH + 2 * lane) = f32x2{hprev0, hprev1};
+                *reinterpret_cast<f32x2*>(cH + 2 * cl) = f32x2{hprev0, hprev1};
                 if (starts_sequence) { hprev0 = 1.0f; hprev1 = 1.0f; }
             }
-            *reinterpret_cast<f32x2*>(cA + 2 * lane) = f32x2{hprev0 * gm0, hprev1 * gm1};
+            *reinterpret_cast<f32x2*>(cA + 2 * cl) = f32x2{hprev0 * gm0, hprev1 * gm1};
             hprev0 = (t[4].x * t[5].x) * (t[6].x * t[7].x); hprev1 = (t[4].y * t[5].y) * (t[6].y * t[7].y);
         }
     };
@@ -408,11 +554,11 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     // O leaves through registers that stay reserved for the whole pass (see the end of stage B):
     // a global store reads its data registers late, and overwriting them earlier would make the
     // wave wait for the store, and with it for every prefetch issued before it, to complete.
-    u32x4 obuf[C * VPR / kFusedThreads];
+    u32x4 obuf[C * VPR / NT];
     auto store_o = [&](const FusedChunk& c) {
 #pragma unroll
-        for (int k = 0; k < C * VPR / kFusedThreads; ++k) {
-            const int idx = tid + k * kFusedThreads;
+        for (int k = 0; k < C * VPR / NT; ++k) {
+            const int idx = tid + k * NT;
             const int row = idx / VPR, cv = idx % VPR;
             const int grow = c.row0 + row;
             obuf[k] = *reinterpret_cast<const u32x4*>(Ost + (size_t)row * PO + cv * 8);
@@ -422,10 +568,121 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     };
 
 
+    // ---- light walk: the recurrence alone over chunks c0 .. c1 - 1 of one sequence (N tokens from token
+    // tok0 of the packed tensors), in place in the accumulators, which hold the true state before and
+    // after:  S <- Diag(g) S + K^^T V,  K^_j = k_j prod_{s > j in chunk} f_s  (no quotients).  One
+    // barrier per chunk: pass n writes the tiles of chunk n and the block totals of chunk n + 1, and
+    // after the barrier multiplies while the other waves go on to the next pass.  A pass takes well
+    // under a microsecond, less than half a trip to memory: rows are fetched four chunks ahead.
+    auto light_walk = [&](int tok0, int N, int c0, int c1, float* decay_out) {
+        T* Kl = reinterpret_cast<T*>(smem + L::lk);
+        T* Vl = reinterpret_cast<T*>(smem + L::lv);
+        float* tl = reinterpret_cast<float*>(smem + L::lt);
+        float* gl = reinterpret_cast<float*>(smem + L::lg);
+        const float* ones = tl + 2 * kRowBlocks * DK;
+        constexpr int AH = 4;
+        RawRows<RW> lf[AH];
+        u32x4 lv[AH][NVV];
+        float kz0[RW], kz1[RW], t0, t1, dec0 = 1.0f, dec1 = 1.0f;
+        auto at = [&](int c) {
+            FusedChunk k;
+            const ChunkRows cr = chunk_rows(p.lay.sub, c, N);
+            k.tok0 = tok0; k.row0 = cr.tok0; k.lo = cr.first; k.hi = c < c1 ? cr.end : cr.first; k.N = N;
+            k.bh = 0; k.first = 0; k.last = 0; k.slot = 0;
+            return k;
+        };
+        auto gates = [&](const RawRows<RW>& raw, const FusedChunk& c, int par) {
+            f32x2 rf[RW];
+            convert_rows<RW>(rf, raw, c.row0 + RW * rb, c.hi, true, GATE_BF16, 1.0f, c.lo);
+            if (p.beta) gate_rows<RW>(rf, p.beta + (size_t)head * DK, 2 * cl, true, c.row0 + RW * rb, c.hi, c.lo);
+            float run0 = 1.0f, run1 = 1.0f;
+#pragma unroll
+            for (int i = RW - 1; i >= 0; --i) {
+                const float n0 = run0 * rf[i].x, n1 = run1 * rf[i].y;
+                kz0[i] = run0 - n0; kz1[i] = run1 - n1;
+                run0 = n0; run1 = n1;
+            }
+            t0 = run0; t1 = run1;
+            *reinterpret_cast<f32x2*>(tl + (par * kRowBlocks + rb) * DK + 2 * cl) = f32x2{t0, t1};
+        };
+        auto pass = [&](auto SET, int n) {
+            constexpr int set = decltype(SET)::value, par = set & 1;
+            float post0 = 1.0f, post1 = 1.0f;
+#pragma unroll
+            for (int i = 1; i < kRowBlocks; ++i) {
+                const float* src = (i > rb) ? tl + (par * kRowBlocks + i) * DK : ones;
+                const f32x2 t = *reinterpret_cast<const f32x2*>(src + 2 * cl);
+                post0 *= t.x; post1 *= t.y;
+            }
+            if (rb == 0) {
+                *reinterpret_cast<f32x2*>(gl + par * DK + 2 * cl) = f32x2{post0 * t0, post1 * t1};
+                dec0 *= post0 * t0; dec1 *= post1 * t1;
+            }
+            float k0[RW], k1[RW];
+#pragma unroll
+            for (int i = 0; i < RW; ++i) { k0[i] = kz0[i] * post0; k1[i] = kz1[i] * post1; }
+            T* Kd = Kl + (size_t)par * DK * PT + (size_t)(2 * cl) * PT + RW * rb;
+            *reinterpret_cast<frag*>(Kd) = M::pack(k0);
+            *reinterpret_cast<frag*>(Kd + PT) = M::pack(k1);
+#pragma unroll
+            for (int j = 0; j < NVV; ++j)
+                *reinterpret_cast<u32x4*>(Vl + (size_t)par * C * PV + (vrow + VRS * j) * PV + vcol) = lv[set][j];
+            load_v(lv[set], at(n + AH));
+            gates(lf[(set + 1) % AH], at(n + 1), 1 - par);
+            load_f(lf[(set + 1) % AH], at(n + 1 + AH));
+            __syncthreads();
+            scale_state(gl + par * DK);
+            const T* Kc = Kl + (size_t)par * DK * PT;
+#pragma unroll
+            for (int ks = 0; ks < C / 16; ++ks) {
+                const frag vf = M::load_kmajor(Vl + (size_t)par * C * PV, PV, 16 * ks, 32 * bt, lane);
+#pragma unroll
+                for (int j = 0; j < NST; ++j) M::mma(accS[j], M::load(Kc + (32 * (at0 + j) + r32) * PT + 16 * ks + 8 * g), vf);
+            }
+        };
+        if (tid < DK) tl[2 * kRowBlocks * DK + tid] = 1.0f;
+#pragma unroll
+        for (int j = 0; j < AH; ++j) { load_f(lf[j], at(c0 + j)); load_v(lv[j], at(c0 + j)); }
+        gates(lf[0], at(c0), 0);
+        load_f(lf[0], at(c0 + AH));
+        __syncthreads();
+        int n = c0;
+        for (; n + AH <= c1; n += AH) {
+            pass(std::integral_constant<int, 0>(), n);
+            pass(std::integral_constant<int, 1>(), n + 1);
+            pass(std::integral_constant<int, 2>(), n + 2);
+            pass(std::integral_constant<int, 3>(), n + 3);
+        }
+        if (n < c1) pass(std::integral_constant<int, 0>(), n);
+        if (n + 1 < c1) pass(std::integral_constant<int, 1>(), n + 1);
+        if (n + 2 < c1) pass(std::integral_constant<int, 2>(), n + 2);
+        if (decay_out && rb == 0) *reinterpret_cast<f32x2*>(decay_out + 2 * cl) = f32x2{dec0, dec1};
+        __syncthreads();                     // the tiles make room for those of the walk proper
+    };
+    if constexpr (ENDS) {
+        light_walk(first_tok, GROUPED ? first_N : N_one, first_n, first_n + NC, split == 0 ? p.run_decay + (size_t)ends_slot * DK : nullptr);
+#pragma unroll
+        for (int j = 0; j < NST; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                char* rows = const_cast<char*>(state_rows(p.run_add, ends_slot, j, c));
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) *reinterpret_cast<float*>(rows + st_lane + jj * DV * 4) = accS[j][4 * c + jj];
+            }
+        return;
+    }
+    if (RUNS && !(GROUPED && p.run_add) && (GROUPED ? first_n > 0 : n0 > 0)) {
+        light_walk(first_tok, GROUPED ? first_N : N_one, 0, GROUPED ? first_n : n0, nullptr);
+        // Keeps the compiler from computing the chunk loop's lane-dependent values ahead of the light
+        // walk and carrying them through it in registers.
+        int opaque = lane;
+        asm volatile("" : "+v"(opaque));
+    }
+
     // ---- prologue: rows of chunks 0 and 1 in flight, element-wise work of chunk 0 ----
     // the never-written block of P (rows 0..31 x columns 32..63) must read as zero
-    for (int idx = tid; idx < 32 * 32; idx += kFusedThreads) Pm[(idx >> 5) * PC + 32 + (idx & 31)] = (T)0.0f;
-    if (tid < DK) tot[NW * DK + tid] = 1.0f;
+    for (int idx = tid; idx < 32 * 32; idx += NT) Pm[(idx >> 5) * PC + 32 + (idx & 31)] = (T)0.0f;
+    if (tid < DK) tot[kRowBlocks * DK + tid] = 1.0f;
     load_f(rawf[0], chunk_rel(0, 0)); load_q(rawq[0], chunk_rel(0, 0)); load_v(rawv[0], chunk_rel(0, 0));
     load_f(rawf[1], chunk_rel(0, 1)); load_q(rawq[1], chunk_rel(0, 1));
     if (VD == 2) load_v(rawv[VD - 1], chunk_rel(0, 1));
@@ -467,7 +724,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     };
     auto pin_obuf = [&]() {
 #pragma unroll
-        for (int k = 0; k < C * VPR / kFusedThreads; ++k) asm volatile("" :: "v"(obuf[k]));
+        for (int k = 0; k < C * VPR / NT; ++k) asm volatile("" :: "v"(obuf[k]));
     };
 
     // The published state holds, per lane, 8 channels of one dv column (the read-out contracts over
@@ -611,93 +868,195 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     };
 
     int n_end = 0;
-    for (; n_end < NC; n_end += 2) {
+    for (; RUNS ? n_end + 1 < NC : n_end < NC; n_end += 2) {
         chunk(std::integral_constant<int, 0>(), n_end);
         chunk(std::integral_constant<int, 1>(), n_end + 1);
     }
-    if (LATE_QS) {
-        // an even number of chunks leaves the last one without its state read-out (an odd number
-        // is followed by a pass over an empty chunk, which has done it)
-        if (NC % 2 == 0) {
-            if (has_o) {
-                read_out_state(Qm + (size_t)((NC - 1) & 1) * C * PQ, Sb + (size_t)((NC - 1) & 1) * DK * DVW);
-                stage_o();
-            }
-            __syncthreads();
-            store_o(chunk_rel(NC, -1));
+    if (RUNS && n_end < NC) { chunk(std::integral_constant<int, 0>(), n_end); ++n_end; }
+    if (LATE_QS && n_end == NC) {
+        // the last chunk is still without its state read-out (a pass over an empty chunk has done it)
+        if (has_o) {
+            read_out_state(Qm + (size_t)((NC - 1) & 1) * C * PQ, Sb + (size_t)((NC - 1) & 1) * DK * DVW);
+            stage_o();
         }
-    } else {
-        store_o(chunk_rel(n_end, -1));
+        __syncthreads();
     }
+    if (!LATE_QS || n_end == NC) store_o(chunk_rel(n_end, -1));
 
     if (p.flag && below_floor < kTinyProduct) *p.flag = 1;
     if (p.hT) {
-        // S_N = pending rescale * accumulators (the chunk after the last one has G_m = 1).  A
-        // grouped walk has written the state of every sequence that a further pass followed; after
-        // an even number of chunks the last sequence is still to do.
+        // S_N = pending rescale * accumulators (the chunk after the last one has G_m = 1).  A span has
+        // written the state of every sequence that a further pass followed.
         if constexpr (GROUPED) {
-            if (NC % 2 == 0) final_state(ck[0].bh, cH);
+            if (ck[0].last) final_state(ck[0].bh, cH);
         } else {
-            final_state(bh, cA);
+            if (!RUNS || (p.run_add ? bh - whole * p.lay.seg == p.lay.seg - 1 : run == n_run - 1)) final_state(whole, cA);
         }
     }
 }
 
-template <bool GATE_BF16, int NSPLIT>
-__global__ __launch_bounds__(kFusedThreads) void fwd_fused_kernel(FwdFusedParams p)
+// (a workgroup of four waves shares a compute unit with another: two waves per SIMD either way)
+template <int DK, int DV, int DVW, bool GATE_BF16, bool RUNS>
+__global__ __launch_bounds__(64 * fused_waves(DK), 2) void fwd_fused_kernel(FwdFusedParams p)
 {
-    if (p.dense) fwd_fused_body<GATE_BF16, NSPLIT, true, false>(p);
-    else         fwd_fused_body<GATE_BF16, NSPLIT, false, false>(p);
+    if (p.dense) fwd_fused_body<DK, DV, DVW, GATE_BF16, true, false, false, RUNS>(p);
+    else         fwd_fused_body<DK, DV, DVW, GATE_BF16, false, false, false, RUNS>(p);
 }
 
-// The walk over groups of a packed batch's sequences (a kernel of its own: its register needs are
-// not those of the walk over one sequence).
-template <bool GATE_BF16, int NSPLIT>
-__global__ __launch_bounds__(kFusedThreads) void fwd_fused_grouped_kernel(FwdFusedParams p)
+// The walk over spans of a packed batch's chunks (a kernel of its own: its register needs are not
+// those of the walk over one sequence).
+template <int DK, int DV, int DVW, bool GATE_BF16>
+__global__ __launch_bounds__(64 * fused_waves(DK), 2) void fwd_fused_grouped_kernel(FwdFusedParams p)
 {
-    fwd_fused_body<GATE_BF16, NSPLIT, false, true>(p);
+    fwd_fused_body<DK, DV, DVW, GATE_BF16, false, true, false>(p);
 }
 
-// Groups of a packed batch's sequences are walked by one workgroup each from two sequences per
-// group on (with fewer, a workgroup per sequence, longest first, balances uneven lengths better and
-// needs less bookkeeping).
-static bool fused_grouped(const SeqDims& d) { return d.lay.vl && d.lay.groups && d.lay.B >= 2 * d.lay.G; }
-// workgroups' worth of independent walks
-static int fused_walkers(const SeqDims& d) { return fused_grouped(d) ? d.lay.G * d.lay.H : d.BH; }
-
-bool fwd_fused_supported(const SeqDims& d)
+// What every run of a sequence (every span of a packed batch) adds to the state from zero, and the
+// product of its gates.
+template <int DK, int DV, int DVW, bool GATE_BF16>
+__global__ __launch_bounds__(64 * fused_waves(DK), 2) void run_ends_kernel(FwdFusedParams p)
 {
-    return d.io_bf16 && d.dk == 128 && d.dv == 128 && fused_walkers(d) >= 64;
+    if (p.lay.vl && p.lay.spans > 0) fwd_fused_body<DK, DV, DVW, GATE_BF16, false, true, true>(p);
+    else if (p.dense) fwd_fused_body<DK, DV, DVW, GATE_BF16, true, false, true>(p);
+    else         fwd_fused_body<DK, DV, DVW, GATE_BF16, false, false, true>(p);
 }
 
-template <int NSPLIT>
-static hipError_t launch_fused(const SeqDims& d, const FwdFusedParams& p, hipStream_t stream)
+static bool fused_grouped(const SeqDims& d) { return d.lay.vl && d.lay.spans > 0; }
+
+bool fwd_fused_supported(const SeqDims& d) { return d.io_bf16; }
+
+// Places for workgroups that run at once: one to a compute unit for heads of 128 channels, two for
+// heads of 64 (whose 128-wide dv takes two workgroups per walk).
+static int fused_slots(const SeqDims& d) { return d.dk == 128 ? 256 : d.dv == 128 ? 256 : 512; }
+
+template <int DK, int DV, int DVW>
+static hipError_t launch_fused(const SeqDims& d, const FwdFusedParams& p, int walkers, bool ends, hipStream_t stream)
 {
-    typedef FwdFusedLds<NSPLIT> L;
-    const bool grouped = fused_grouped(d);
-    auto kern = grouped ? (d.gate_bf16 ? fwd_fused_grouped_kernel<true, NSPLIT> : fwd_fused_grouped_kernel<false, NSPLIT>)
-                        : (d.gate_bf16 ? fwd_fused_kernel<true, NSPLIT> : fwd_fused_kernel<false, NSPLIT>);
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::total);
+    typedef FwdFusedLds<DK, DVW> L;
+    constexpr int NSPLIT = DV / DVW;
+    // (walks of a few, odd chunks: the pass over an empty chunk that the other variant takes would be felt)
+    const bool short_odd = d.NC < 16 && d.NC % 2 == 1;
+    auto kern = ends ? (d.gate_bf16 ? run_ends_kernel<DK, DV, DVW, true> : run_ends_kernel<DK, DV, DVW, false>)
+              : fused_grouped(d) ? (d.gate_bf16 ? fwd_fused_grouped_kernel<DK, DV, DVW, true> : fwd_fused_grouped_kernel<DK, DV, DVW, false>)
+              : (p.R > 0 || p.run_add || short_odd) ? (d.gate_bf16 ? fwd_fused_kernel<DK, DV, DVW, true, true> : fwd_fused_kernel<DK, DV, DVW, false, true>)
+                                       : (d.gate_bf16 ? fwd_fused_kernel<DK, DV, DVW, true, false> : fwd_fused_kernel<DK, DV, DVW, false, false>);
+    const int lds = (int)(ends ? L::light_total : L::total);
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
-    const int walkers = fused_walkers(d);
-    const unsigned grid = (NSPLIT == 1) ? (unsigned)walkers : (unsigned)(NSPLIT * 8 * ((walkers + 7) / 8));
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kFusedThreads), L::total, stream, p);
+    const int per = NSPLIT * (p.R > 0 ? p.R : 1);
+    const unsigned grid = per == 1 ? (unsigned)walkers : (unsigned)(per * 8 * ((walkers + 7) / 8));
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * L::NW), lds, stream, p);
     return hipGetLastError();
 }
 
-hipError_t launch_fwd_fused(const SeqDims& d, const void* q, const void* f, const void* v, const float* h0,
-                            void* o, float* hT, void* save_states, hipStream_t stream)
+static hipError_t launch_fused_dims(const SeqDims& d, const FwdFusedParams& p, int walkers, bool ends, hipStream_t stream)
 {
-    if (d.BH == 0) return hipSuccess;
+    // Two workgroups per walk (each half of the dv columns) keep twice as many compute units busy,
+    // but only as long as all of them run at once (144 sequences of 2048 tokens, 128-wide heads: 137 us
+    // halved against 84 us whole; up to 128 sequences halving wins).
+    const int all = walkers * (p.R > 0 ? p.R : 1);
+    if (d.dk == 128 && d.dv == 128)
+        return 2 * all > fused_slots(d) ? launch_fused<128, 128, 128>(d, p, walkers, ends, stream)
+                                        : launch_fused<128, 128, 64>(d, p, walkers, ends, stream);
+    if (d.dk == 64 && d.dv == 64) return launch_fused<64, 64, 64>(d, p, walkers, ends, stream);
+    if (d.dk == 128 && d.dv == 64) return launch_fused<128, 64, 64>(d, p, walkers, ends, stream);
+    if (d.dk == 64 && d.dv == 128) return launch_fused<64, 128, 64>(d, p, walkers, ends, stream);
+    return hipErrorInvalidValue;
+}
+
+static FwdFusedParams fused_params(const SeqDims& d, const void* q, const void* f, const void* v)
+{
     FwdFusedParams p;
-    p.q = q; p.f = f; p.v = v; p.h0 = h0; p.o = o; p.hT = hT; p.save = save_states;
+    p.q = q; p.f = f; p.v = v; p.h0 = nullptr; p.o = nullptr; p.hT = nullptr; p.save = nullptr;
     p.N = d.N; p.NC = d.NC; p.BH = d.BH; p.beta = d.beta; p.H = d.H; p.lay = d.lay; p.dense = d.dense() ? 1 : 0;
     p.flag = d.domain_flag;
-    // Two workgroups per sequence (each half of the dv columns) keep twice as many compute units
-    // busy, but a compute unit holds one workgroup: beyond 128 sequences the halves would no longer
-    // all run at once (the rest waits for a free unit: 137 us instead of 84 us for 144 sequences of 2048 tokens), so
-    // from there on a sequence gets one workgroup.
-    return fused_walkers(d) > 128 ? launch_fused<1>(d, p, stream) : launch_fused<2>(d, p, stream);
+    p.R = 0; p.run_add = nullptr; p.run_decay = nullptr; p.ends_per_seq = 1;
+    return p;
+}
+
+// Cost of a chunk of a light walk in chunks of the walk proper (measured: 1.0 us against 2.0 us in the
+// 128 x 64 variant, and less next to other workgroups that stream).
+constexpr double kLightCost = 0.42;
+
+// Runs with a light walk each: the cuts that let all of them finish together,
+// len_r + rho start_r = T for every run r, so that start_{r+1} = T + (1 - rho) start_r.
+static void fused_cuts(int NC, int R, short (&bnd)[kMaxFwdRuns + 1])
+{
+    const double rho = kLightCost;
+    double sum = 0.0, x = 1.0;
+    for (int r = 0; r < R; ++r) { sum += x; x *= 1.0 - rho; }
+    const double T = NC / sum;
+    double end = 0.0;
+    bnd[0] = 0;
+    for (int r = 1; r < R; ++r) {
+        end = T + (1.0 - rho) * end;
+        int b = (int)(end + 0.5);
+        if (b < bnd[r - 1] + 1) b = bnd[r - 1] + 1;
+        if (b > NC - (R - r)) b = NC - (R - r);
+        bnd[r] = (short)b;
+    }
+    bnd[R] = (short)NC;
+}
+
+FwdRuns plan_fwd_runs(const SeqDims& d)
+{
+    FwdRuns r;
+    r.run_chunks = d.NC;
+    if (!d.io_bf16 || d.packed || d.BH == 0 || d.NC < 2) return r;
+    const int slots = fused_slots(d);
+    // With light walks of their own: as many runs as find a place at once.  128 x 128 heads: up to 32
+    // sequences the two halves of dv count too (they are faster per chunk than twice the runs: 1 x 16
+    // heads of 777 tokens, 8 runs in halves 27.9 us, 13 runs whole 31 us), beyond that they do not
+    // (48 and 64 sequences of 1024 tokens: halved 31.3 and 32.2 us, whole 29.9 and 30.5 us).
+    // Heads of 64: a place means half a compute unit, so from 129 sequences on a second run only slows
+    // the first down (256 sequences of 2000 tokens: 73 us in two runs, 70 us in one).
+    int light = slots / d.BH;
+    if (d.dk == 128 && d.dv == 128 && d.BH <= 32) light /= 2;
+    if (d.dk == 64 && d.BH > slots / 4) light = 1;
+    if (light > kMaxFwdRuns) light = kMaxFwdRuns;
+    if (light > d.NC) light = d.NC;
+    if (light < 1) light = 1;
+    // With walks from zero in a kernel of their own: at least four chunks each.  A run costs 1 + rho of
+    // its chunks' time, but the second launch, the states in between and the start-up of the second
+    // walk cost as much as about six chunks more.
+    int seg = d.BH <= 16 ? 128 / d.BH : 256 / d.BH;
+    if (seg > d.NC / 4) seg = d.NC / 4;
+    if (seg >= 2) {
+        double keep = 1.0;
+        for (int i = 0; i < light; ++i) keep *= 1.0 - kLightCost;
+        const double t_light = d.NC * kLightCost / (1.0 - keep), t_ends = 6.0 + (1.0 + kLightCost) * d.NC / seg;
+        if (t_ends < t_light) {
+            r.run_chunks = (d.NC + seg - 1) / seg;
+            r.seg = (d.NC + r.run_chunks - 1) / r.run_chunks;
+            return r;
+        }
+    }
+    r.light = light;
+    return r;
+}
+
+hipError_t launch_fwd_fused(const SeqDims& d, const void* q, const void* f, const void* v, const float* h0,
+                            void* o, float* hT, void* save_states, hipStream_t stream, int light_runs, const float* run_add,
+                            const float* run_decay)
+{
+    if (d.BH == 0) return hipSuccess;
+    FwdFusedParams p = fused_params(d, q, f, v);
+    p.h0 = h0; p.o = o; p.hT = hT; p.save = save_states;
+    if (light_runs > 1) {
+        p.R = light_runs;
+        fused_cuts(d.NC, p.R, p.bnd);
+    }
+    p.run_add = const_cast<float*>(run_add); p.run_decay = const_cast<float*>(run_decay);
+    return launch_fused_dims(d, p, fused_grouped(d) ? d.lay.spans * d.lay.H : d.BH, false, stream);
+}
+
+hipError_t launch_run_ends(const SeqDims& d, int ends_per_seq, const void* q, const void* f, const void* v, float* run_add,
+                           float* run_decay, hipStream_t stream)
+{
+    if (d.BH == 0 || ends_per_seq <= 0) return hipSuccess;
+    FwdFusedParams p = fused_params(d, q, f, v);
+    p.run_add = run_add; p.run_decay = run_decay; p.ends_per_seq = ends_per_seq;
+    return launch_fused_dims(d, p, fused_grouped(d) ? d.lay.spans * d.lay.H : d.BH / d.lay.seg * ends_per_seq, true, stream);
 }
 
 }   // namespace hgrn2

@@ -163,12 +163,30 @@ hipError_t launch_fwd_out(const SeqDims& d, const void* q, const void* f, const 
                           void* o, hipStream_t stream);
 
 // Fused forward (state recurrence + read-out in one pass, states never leave the chip); only for
-// the shapes fwd_fused_supported() accepts.
+// the storage fwd_fused_supported() accepts (bf16).
 bool fwd_fused_supported(const SeqDims& d);
+// How the fused forward walk of an equal-length batch cuts its sequences.  light > 1: into that many
+// runs, each of whose workgroups finds the state it starts from by a light walk of its own over the
+// chunks before the run.  seg > 1: into runs of run_chunks chunks (TokenLayout::seg), whose entering
+// states launch_run_ends provides.
+struct FwdRuns { int light = 1, seg = 1, run_chunks = 0; };
+FwdRuns plan_fwd_runs(const SeqDims& d);
+// What every run of segmented sequences (TokenLayout::seg, or the entries of a run table) adds to the
+// state from zero, run_add [slot][dk][dv], and the product of its gates, run_decay [slot][dk]; only
+// the first ends_per_seq runs of each sequence, slot = sequence * ends_per_seq + run.  Packed batch with
+// spans (TokenLayout::spans): what every span adds to the sequence it ends in, where that goes on in
+// the next span, slot = span * H + head.
+hipError_t launch_run_ends(const SeqDims& d, int ends_per_seq, const void* q, const void* f, const void* v, float* run_add,
+                           float* run_decay, hipStream_t stream);
 // `save_states` (may be null): receives G_m S_n of every chunk in the fragment order of a
 // kSweepStateBwd sweep, state_ws_bytes() in all, for a backward pass that then needs no such sweep.
+// light_runs > 1: cut so (not with TokenLayout::seg).  run_add, run_decay (with TokenLayout::seg > 1): the
+// runs' contributions without the last run of every sequence, launch_run_ends(d, seg - 1, ...), which
+// the kernel adds up itself from h0; without them h0 holds one entering state per run and hT is null.
+// With TokenLayout::spans: the spans' contributions; without them every span takes a light walk.
 hipError_t launch_fwd_fused(const SeqDims& d, const void* q, const void* f, const void* v, const float* h0,
-                            void* o, float* hT, void* save_states, hipStream_t stream);
+                            void* o, float* hT, void* save_states, hipStream_t stream, int light_runs = 1,
+                            const float* run_add = nullptr, const float* run_decay = nullptr);
 
 // Per-chunk gradients dq, df, dv from the two state sweeps.
 // With d.beta set, grad_f receives the gradient w.r.t. the pre-activation z, and every wave of

@@ -1,0 +1,85 @@
+"""How the forward walk of bf16 batches is cut: runs with a light walk of their own, runs whose entering
+states come from walks from zero (added up by the runs' workgroups, or by the carry kernel when there
+are many), spans of a packed batch that start and end inside sequences; heads of 64 (workgroups of four
+waves).  Against the oracle, at the sizes where a cut can go wrong: one chunk per run, ragged last
+chunks, fewer chunks than runs, an initial and a final state.  Tolerance: the bf16 bound of gpu_util.
+The states kept for the backward pass are checked through its gradients."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2404_07904_amd import binding, synth
+from gpu_util import TOL, check, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+# (B, H, N, dk, dv, gate dtype): what the cut is for it
+CASES = [
+    (1, 1, 65, 64, 64, "bf16"),          # two chunks, two light runs of one chunk
+    (1, 3, 777, 128, 128, "bf16"),       # 13 chunks, ragged: light runs, halves of dv
+    (2, 20, 460, 128, 128, "f32"),       # more than 32 sequences: light runs, whole dv
+    (1, 2, 1000, 64, 64, "f32"),         # 16 chunks of 64-wide heads
+    (1, 2, 700, 128, 64, "bf16"),
+    (1, 2, 700, 64, 128, "f32"),
+    (1, 2, 2100, 64, 64, "bf16"),        # 33 chunks: walks from zero in eight runs, the last one shorter
+    (1, 3, 3001, 128, 128, "bf16"),      # the same, 47 chunks in eleven runs
+    (1, 1, 4481, 64, 128, "bf16"),       # 71 chunks: 17 runs and more, with the carry kernel
+]
+
+
+@pytest.mark.parametrize("B,H,N,dk,dv,gate", CASES)
+@pytest.mark.parametrize("token_major", [False, True])
+def test_forward_in_runs(B, H, N, dk, dv, gate, token_major):
+    print("\n[fwd runs] B=%d H=%d N=%d dk=%d dv=%d gate=%s token_major=%s" % (B, H, N, dk, dv, gate, token_major), flush=True)
+    w = synth.make_sequence(3000 + N, B, H, N, dk, dv, io_dtype="bf16", gate_dtype=gate, lb=0.9, with_h0=True, with_dO=True)
+    layout = binding.HGRN2_LAYOUT_BNHD if token_major else binding.HGRN2_LAYOUT_BHND
+    arr = (lambda t: t.permute(0, 2, 1, 3).contiguous()) if token_major else (lambda t: t)
+    q, v, dO = (arr(dev(x, "bf16")) for x in (w.q, w.v, w.dO))
+    f, h0 = arr(dev(w.f, gate)), dev(w.h0)
+    o, hT = binding.hgrn2_fwd(q, f, v, h0, layout=layout)
+    o2, hT2, saved = binding.hgrn2_fwd_saving(q, f, v, h0, layout=layout)
+    g = binding.hgrn2_bwd_saved(q, f, v, saved, dO, layout=layout)
+    torch.cuda.synchronize()
+    ro, rhT = oracle.fwd(w.q, w.f, w.v, w.h0)
+    check("o", host(arr(o)), ro, TOL["bf16"])
+    check("hT", host(hT), rhT, TOL["bf16"])
+    assert torch.equal(o, o2) and torch.equal(hT, hT2)
+    for name, x, r in zip(("dq", "df", "dv"), g, oracle.bwd(w.q, w.f, w.v, w.dO, w.h0, None)):
+        check(name, host(arr(x)), r, TOL["bf16"])
+
+
+# 64 heads: four spans per head; lengths that make spans start and end inside sequences, cross several
+# short ones, contain empty ones, and leave a sequence over three spans
+@pytest.mark.parametrize("lens", [[5, 700, 64, 0, 1], [64, 64, 64, 64, 64, 64, 64, 65], [0, 30, 200], [1, 0, 0, 63, 900, 40, 130]])
+@pytest.mark.parametrize("dk,dv", [(64, 64), (128, 128)])
+def test_packed_forward_in_spans(lens, dk, dv):
+    print("\n[fwd spans] lens=%s dk=%d dv=%d" % (lens, dk, dv), flush=True)
+    H, T, B = 64, sum(lens), len(lens)
+    w = synth.make_sequence(3100 + T, 1, H, T, dk, dv, io_dtype="bf16", lb=0.9, with_dO=True)
+    rng = np.random.default_rng(T)
+    h0 = (0.1 * rng.standard_normal((B, H, dk, dv))).astype(np.float32)
+    pk = lambda x: dev(x, "bf16")[0].permute(1, 0, 2).contiguous()
+    q, f, v, dO = (pk(x) for x in (w.q, w.f, w.v, w.dO))
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), device="cuda")
+    shape = binding.make_shape_varlen(q, v, f, B)
+    saved = torch.full((binding.hgrn2_saved_states_varlen_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    o, hT = binding.hgrn2_fwd_varlen(q, f, v, cu, dev(h0))
+    o2, hT2 = binding.hgrn2_fwd_varlen(q, f, v, cu, dev(h0), saved_states=saved)
+    g = binding.hgrn2_bwd_varlen(q, f, v, dO, cu, dev(h0), saved_states=saved)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o2) and torch.equal(hT, hT2)
+    at = 0
+    for b, n in enumerate(lens):
+        if n == 0:
+            assert np.array_equal(host(hT[b]), h0[b].astype(np.float64))
+            continue
+        s = slice(at, at + n)
+        at += n
+        cut = lambda x: x[:, :, s]
+        ro, rhT = oracle.fwd(cut(w.q), cut(w.f), cut(w.v), h0[b:b + 1])
+        check("o[%d]" % b, host(o[s].permute(1, 0, 2)[None]), ro, TOL["bf16"])
+        check("hT[%d]" % b, host(hT[b:b + 1]), rhT, TOL["bf16"])
+        for name, x, r in zip(("dq", "df", "dv"), g, oracle.bwd(cut(w.q), cut(w.f), cut(w.v), cut(w.dO), h0[b:b + 1], None)):
+            check("%s[%d]" % (name, b), host(x[s].permute(1, 0, 2)[None]), r, TOL["bf16"])
