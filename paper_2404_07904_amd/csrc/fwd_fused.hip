@@ -410,19 +410,36 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
                     while (k0 > 0 && (int)((long long)k0 * total / p.lay.spans) > before) --k0;
                 }
             }
-            for (int k = k0; k < k1; ++k) {
-                const int slot = GROUPED ? k * p.lay.H + head : whole * (p.lay.seg - 1) + k;
-                const float* dec = p.run_decay + (size_t)slot * DK;
+            // (the values come from other XCDs: what a request takes is most of what a run costs, so
+            // several runs' are requested at a time)
+            constexpr int AHEAD = NST == 1 ? 4 : 2;
+            for (int k = k0; k < k1; k += AHEAD) {
+                f32x4 dm[AHEAD][NST][4];
+                float a[AHEAD][NST][16];
 #pragma unroll
-                for (int j = 0; j < NST; ++j)
+                for (int u = 0; u < AHEAD; ++u) {
+                    const int ku = min(k + u, k1 - 1);
+                    const int slot = GROUPED ? ku * p.lay.H + head : whole * (p.lay.seg - 1) + ku;
+                    const float* dec = p.run_decay + (size_t)slot * DK;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const f32x4 dm = *reinterpret_cast<const f32x4*>(dec + 32 * (at0 + j) + 8 * c + 4 * g);
-                        const char* rows = state_rows(p.run_add, slot, j, c);
+                    for (int j = 0; j < NST; ++j)
 #pragma unroll
-                        for (int jj = 0; jj < 4; ++jj)
-                            accS[j][4 * c + jj] = fmaf(dm[jj], accS[j][4 * c + jj], *reinterpret_cast<const float*>(rows + st_lane + jj * DV * 4));
-                    }
+                        for (int c = 0; c < 4; ++c) {
+                            dm[u][j][c] = *reinterpret_cast<const f32x4*>(dec + 32 * (at0 + j) + 8 * c + 4 * g);
+                            const char* rows = state_rows(p.run_add, slot, j, c);
+#pragma unroll
+                            for (int jj = 0; jj < 4; ++jj) a[u][j][4 * c + jj] = *reinterpret_cast<const float*>(rows + st_lane + jj * DV * 4);
+                        }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+                    if (k + u >= k1) break;
+#pragma unroll
+                    for (int j = 0; j < NST; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) accS[j][v] = fmaf(dm[u][j][v >> 2][v & 3], accS[j][v], a[u][j][v]);
+                }
             }
         }
     }
@@ -572,22 +589,24 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     // tok0 of the packed tensors), in place in the accumulators, which hold the true state before and
     // after:  S <- Diag(g) S + K^^T V,  K^_j = k_j prod_{s > j in chunk} f_s  (no quotients).  One
     // barrier per chunk: pass n writes the tiles of chunk n and the block totals of chunk n + 1, and
-    // after the barrier multiplies while the other waves go on to the next pass.  A pass takes well
-    // under a microsecond, less than half a trip to memory: rows are fetched four chunks ahead.
+    // after the barrier multiplies while the other waves go on to the next pass.  The LDS pipe is what
+    // a pass waits for (about 1 us; rows fetched four chunks ahead instead of two change nothing); an
+    // odd number of chunks starts with a pass over a chunk without tokens, which keeps the code small
+    // (a short walk meets most of it cold).
     auto light_walk = [&](int tok0, int N, int c0, int c1, float* decay_out) {
         T* Kl = reinterpret_cast<T*>(smem + L::lk);
         T* Vl = reinterpret_cast<T*>(smem + L::lv);
         float* tl = reinterpret_cast<float*>(smem + L::lt);
         float* gl = reinterpret_cast<float*>(smem + L::lg);
         const float* ones = tl + 2 * kRowBlocks * DK;
-        constexpr int AH = 4;
+        constexpr int AH = 2;
         RawRows<RW> lf[AH];
         u32x4 lv[AH][NVV];
         float kz0[RW], kz1[RW], t0, t1, dec0 = 1.0f, dec1 = 1.0f;
         auto at = [&](int c) {
             FusedChunk k;
             const ChunkRows cr = chunk_rows(p.lay.sub, c, N);
-            k.tok0 = tok0; k.row0 = cr.tok0; k.lo = cr.first; k.hi = c < c1 ? cr.end : cr.first; k.N = N;
+            k.tok0 = tok0; k.row0 = cr.tok0; k.lo = cr.first; k.hi = (c >= c0 && c < c1) ? cr.end : cr.first; k.N = N;
             k.bh = 0; k.first = 0; k.last = 0; k.slot = 0;
             return k;
         };
@@ -641,21 +660,16 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
             }
         };
         if (tid < DK) tl[2 * kRowBlocks * DK + tid] = 1.0f;
-#pragma unroll
-        for (int j = 0; j < AH; ++j) { load_f(lf[j], at(c0 + j)); load_v(lv[j], at(c0 + j)); }
-        gates(lf[0], at(c0), 0);
-        load_f(lf[0], at(c0 + AH));
+        const int n0 = c1 - ((c1 - c0 + 1) & ~1);
+        load_f(lf[0], at(n0)); load_v(lv[0], at(n0));
+        load_f(lf[1], at(n0 + 1)); load_v(lv[1], at(n0 + 1));
+        gates(lf[0], at(n0), 0);
+        load_f(lf[0], at(n0 + AH));
         __syncthreads();
-        int n = c0;
-        for (; n + AH <= c1; n += AH) {
+        for (int n = n0; n < c1; n += 2) {
             pass(std::integral_constant<int, 0>(), n);
             pass(std::integral_constant<int, 1>(), n + 1);
-            pass(std::integral_constant<int, 2>(), n + 2);
-            pass(std::integral_constant<int, 3>(), n + 3);
         }
-        if (n < c1) pass(std::integral_constant<int, 0>(), n);
-        if (n + 1 < c1) pass(std::integral_constant<int, 1>(), n + 1);
-        if (n + 2 < c1) pass(std::integral_constant<int, 2>(), n + 2);
         if (decay_out && rb == 0) *reinterpret_cast<f32x2*>(decay_out + 2 * cl) = f32x2{dec0, dec1};
         __syncthreads();                     // the tiles make room for those of the walk proper
     };
@@ -925,10 +939,6 @@ static bool fused_grouped(const SeqDims& d) { return d.lay.vl && d.lay.spans > 0
 
 bool fwd_fused_supported(const SeqDims& d) { return d.io_bf16; }
 
-// Places for workgroups that run at once: one to a compute unit for heads of 128 channels, two for
-// heads of 64 (whose 128-wide dv takes two workgroups per walk).
-static int fused_slots(const SeqDims& d) { return d.dk == 128 ? 256 : d.dv == 128 ? 256 : 512; }
-
 template <int DK, int DV, int DVW>
 static hipError_t launch_fused(const SeqDims& d, const FwdFusedParams& p, int walkers, bool ends, hipStream_t stream)
 {
@@ -956,8 +966,8 @@ static hipError_t launch_fused_dims(const SeqDims& d, const FwdFusedParams& p, i
     // halved against 84 us whole; up to 128 sequences halving wins).
     const int all = walkers * (p.R > 0 ? p.R : 1);
     if (d.dk == 128 && d.dv == 128)
-        return 2 * all > fused_slots(d) ? launch_fused<128, 128, 128>(d, p, walkers, ends, stream)
-                                        : launch_fused<128, 128, 64>(d, p, walkers, ends, stream);
+        return 2 * all > 256 ? launch_fused<128, 128, 128>(d, p, walkers, ends, stream)
+                             : launch_fused<128, 128, 64>(d, p, walkers, ends, stream);
     if (d.dk == 64 && d.dv == 64) return launch_fused<64, 64, 64>(d, p, walkers, ends, stream);
     if (d.dk == 128 && d.dv == 64) return launch_fused<128, 64, 64>(d, p, walkers, ends, stream);
     if (d.dk == 64 && d.dv == 128) return launch_fused<64, 128, 64>(d, p, walkers, ends, stream);
@@ -982,7 +992,7 @@ constexpr double kLightCost = 0.42;
 // len_r + rho start_r = T for every run r, so that start_{r+1} = T + (1 - rho) start_r.
 static void fused_cuts(int NC, int R, short (&bnd)[kMaxFwdRuns + 1])
 {
-    const double rho = kLightCost;
+    const double rho = 0.33;         // (below the cost: the last run, with the longest light walk, has one chunk anyway)
     double sum = 0.0, x = 1.0;
     for (int r = 0; r < R; ++r) { sum += x; x *= 1.0 - rho; }
     const double T = NC / sum;
@@ -1003,35 +1013,44 @@ FwdRuns plan_fwd_runs(const SeqDims& d)
     FwdRuns r;
     r.run_chunks = d.NC;
     if (!d.io_bf16 || d.packed || d.BH == 0 || d.NC < 2) return r;
-    const int slots = fused_slots(d);
-    // With light walks of their own: as many runs as find a place at once.  128 x 128 heads: up to 32
-    // sequences the two halves of dv count too (they are faster per chunk than twice the runs: 1 x 16
-    // heads of 777 tokens, 8 runs in halves 27.9 us, 13 runs whole 31 us), beyond that they do not
-    // (48 and 64 sequences of 1024 tokens: halved 31.3 and 32.2 us, whole 29.9 and 30.5 us).
-    // Heads of 64: a place means half a compute unit, so from 129 sequences on a second run only slows
-    // the first down (256 sequences of 2000 tokens: 73 us in two runs, 70 us in one).
-    int light = slots / d.BH;
-    if (d.dk == 128 && d.dv == 128 && d.BH <= 32) light /= 2;
-    if (d.dk == 64 && d.BH > slots / 4) light = 1;
-    if (light > kMaxFwdRuns) light = kMaxFwdRuns;
-    if (light > d.NC) light = d.NC;
-    if (light < 1) light = 1;
-    // With walks from zero in a kernel of their own: at least four chunks each.  A run costs 1 + rho of
-    // its chunks' time, but the second launch, the states in between and the start-up of the second
-    // walk cost as much as about six chunks more.
-    int seg = d.BH <= 16 ? 128 / d.BH : 256 / d.BH;
-    if (seg > d.NC / 4) seg = d.NC / 4;
-    if (seg >= 2) {
-        double keep = 1.0;
-        for (int i = 0; i < light; ++i) keep *= 1.0 - kLightCost;
-        const double t_light = d.NC * kLightCost / (1.0 - keep), t_ends = 6.0 + (1.0 + kLightCost) * d.NC / seg;
-        if (t_ends < t_light) {
-            r.run_chunks = (d.NC + seg - 1) / seg;
-            r.seg = (d.NC + r.run_chunks - 1) / r.run_chunks;
-            return r;
+    // The candidates and what they take, in chunks of the 64-column variants (2 us each), fitted to runs of
+    // 1 to 128 heads of 128 and 64 and 2 to 256 chunks; the start-up they share is left out.  "halves": two
+    // workgroups per run, each half of dv (the only way for 64 x 128 heads, no way for dv = 64); "whole": twice
+    // the runs, whose chunks take 1.5 to 1.6 times as long.  Beyond 256 workgroups nothing gains: heads of 64
+    // find two places on a compute unit, but two runs there slow each other down as much (256 heads of 2000
+    // tokens: 70 us, in two runs each 73 us).
+    //   light walks (all runs finish together):  NC rho / (1 - (1 - rho)^R)
+    //   walks from zero: the second launch and the states in between cost as much as 5 to 9 chunks
+    // e.g. 16 heads, 13 chunks: 27.9 us with 8 light walks (halves), 31 us whole, 28.8 us from zero;
+    // 32 heads: 32 chunks 40 / 41.5 us (light / from zero), 64 chunks 65 us from zero in halves, 256 chunks
+    // 209 us in halves, 182 us whole; 64 heads whole, 16 / 32 / 64 chunks: 30.5 / 52 / 96 us light, 39 / 55 / 91 us from zero.
+    double best = d.NC;                                  // one run (128 x 128: in halves up to 128 heads)
+    if (d.dk == 128 && d.dv == 128 && d.BH > 128) return r;
+    auto consider = [&](int places, double light_factor, double ends_cost, double per_chunk) {
+        int R = places / d.BH;
+        if (R > kMaxFwdRuns) R = kMaxFwdRuns;
+        if (R > d.NC) R = d.NC;
+        if (R >= 2) {
+            double keep = 1.0;
+            for (int i = 0; i < R; ++i) keep *= 1.0 - kLightCost;
+            const double t = light_factor * d.NC * kLightCost / (1.0 - keep);
+            if (t < best) { best = t; r.light = R; r.seg = 1; r.run_chunks = d.NC; }
         }
-    }
-    r.light = light;
+        int seg = places / d.BH;
+        if (seg > d.NC / 3) seg = d.NC / 3;              // at least three chunks each
+        if (seg >= 2) {
+            const double t = ends_cost + per_chunk * d.NC / seg;
+            if (t < best) {
+                best = t;
+                r.light = 1;
+                r.run_chunks = (d.NC + seg - 1) / seg;
+                r.seg = (d.NC + r.run_chunks - 1) / r.run_chunks;
+            }
+        }
+    };
+    const bool halves = d.dv == 128;
+    consider(halves ? 128 : 256, 1.1, 5.0, 1.5);
+    if (d.dk == 128 && halves) consider(256, 1.47, 9.0, 2.2);
     return r;
 }
 

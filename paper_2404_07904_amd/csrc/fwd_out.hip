@@ -12,6 +12,13 @@
 // One workgroup handles one chunk of one (batch, head); all chunks are independent because the
 // state sweep has already written every S_n.  P is built transposed so that the accumulator
 // registers already hold 4 consecutive j per lane and go to LDS as 8-byte vectors.
+//
+// From contributions (ADD, fp32 storage, few sequences of few chunks): instead of a sweep that walks the
+// chunks in order -- one workgroup per sequence and column slab, 5 us a chunk, 20 of the 29 us of a
+// forward pass over 256 tokens of one head -- a sweep launch takes every chunk from zero at once, and
+// the workgroup of chunk n adds up the contributions of the chunks before it,
+//     S_n = Diag(g_{n-1}) ( ... Diag(g_0) h0 + A_0 ... ) + A_{n-1},
+// out of the cache; the last chunk's workgroup also forms the final state, h (G_m S_n + K~^T V).
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -29,6 +36,13 @@ struct FwdOutParams {
     TokenLayout lay;     // used when dense == 0
     int dense;           // sequence tensors are [B][H][N][d]
     int* flag;           // null, or set to 1 when a gate product falls below the floor of the reciprocals
+    // ADD: what chunk j of sequence s adds from zero is at add + (s NC + j) dk dv, the product of its gates
+    // at decay + s decay_stride + j dk (j < NC - 1); initial and final states as the C ABI's
+    const float* add;
+    const float* decay;
+    size_t decay_stride;
+    const float* h0;
+    float* hT;
 };
 
 template <typename T, int DK, int DV> struct FwdOutLds {
@@ -45,9 +59,10 @@ template <typename T, int DK, int DV> struct FwdOutLds {
     static constexpr size_t total = tot + (size_t)kWaves * DK * sizeof(float);
 };
 
-template <typename T, int DK, int DV, bool DENSE>
+template <typename T, int DK, int DV, bool DENSE, bool ADD>
 __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
 {
+    static_assert(!ADD || !is_bf16_type<T>(), "bf16 storage takes the fused walk");
     constexpr int C = kChunk, RW = C / kWaves;
     typedef FwdOutLds<T, DK, DV> L;
     constexpr int PK = L::PK, PC = L::PC, PO = L::PO;
@@ -82,10 +97,12 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
     static_assert(kWaves % NBT == 0 && (NRT * NBT) % kWaves == 0, "tile/wave mapping");
     const int bt = w % NBT;
     typename M::frag sfrag[NKS];
+    if constexpr (!ADD) {
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks)
-        sfrag[ks] = *reinterpret_cast<const typename M::frag*>(
-            wsn + state_frag_offset(ks >> 1, bt, NBT, ks & 1, lane));
+        for (int ks = 0; ks < NKS; ++ks)
+            sfrag[ks] = *reinterpret_cast<const typename M::frag*>(
+                wsn + state_frag_offset(ks >> 1, bt, NBT, ks & 1, lane));
+    }
     f32x2 rf[RW], rq[RW], rv[RW];
     {
         RawRows<RW> raw_f, raw_q, raw_v;
@@ -98,6 +115,53 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
         if (p.beta) gate_rows<RW>(rf, p.beta + (size_t)(bh % p.H) * DK, col_k, k_act, row0, cr.end, cr.first);
         convert_rows<RW>(rq, raw_q, row0, cr.end, k_act, is_bf16_type<T>(), 0.0f, cr.first);
         convert_rows<RW>(rv, raw_v, row0, cr.end, v_act, is_bf16_type<T>(), 0.0f, cr.first);
+    }
+    if constexpr (ADD) {
+        // The sum goes over the whole workgroup in 16-byte vectors, several chunks' requested at a time
+        // (what one request takes -- the values come from other XCDs -- is most of what a chunk costs:
+        // 5 us each when every lane fetched its fragments chunk after chunk), and reaches the fragments
+        // through the memory of the tiles that are written next.
+        constexpr int NV = DK * DV / 4 / kThreads, AHEAD = NV > 8 ? 2 : 8;
+        f32x4 st[NV];
+        const float* h0 = p.h0 ? p.h0 + (size_t)bh * DK * DV : nullptr;
+        const float* add = p.add + (size_t)bh * p.NC * DK * DV;
+        const float* dec = p.decay + (size_t)bh * p.decay_stride;
+        auto at = [&](int i) { return 4 * (tid + kThreads * i); };
+#pragma unroll
+        for (int i = 0; i < NV; ++i) st[i] = h0 ? *reinterpret_cast<const f32x4*>(h0 + at(i)) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int j0 = 0; j0 < n; j0 += AHEAD) {
+            f32x4 a[AHEAD][NV];
+            float dm[AHEAD][NV];
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                const int j = min(j0 + u, n - 1);
+#pragma unroll
+                for (int i = 0; i < NV; ++i) {
+                    a[u][i] = *reinterpret_cast<const f32x4*>(add + (size_t)j * DK * DV + at(i));
+                    dm[u][i] = dec[j * DK + at(i) / DV];
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                if (j0 + u >= n) break;
+#pragma unroll
+                for (int i = 0; i < NV; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) st[i][e] = fmaf(dm[u][i], st[i][e], a[u][i][e]);
+            }
+        }
+        float* sum = reinterpret_cast<float*>(smem);
+        static_assert((size_t)DK * DV * sizeof(float) <= L::tot, "the state fits the memory of the tiles");
+#pragma unroll
+        for (int i = 0; i < NV; ++i) *reinterpret_cast<f32x4*>(sum + at(i)) = st[i];
+        __syncthreads();
+        // element s of fragment ks: row 16 ks + 8 (s / 4) + 4 g + s % 4 of column 32 bt + r32
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+            for (int s = 0; s < 8; ++s) sfrag[ks].v[s] = sum[(size_t)(16 * ks + 8 * (s >> 2) + 4 * g + (s & 3)) * DV + 32 * bt + r32];
+        // (the tiles are written after the next barrier)
     }
 
     // ---------------- gate products and scaled operands ----------------
@@ -150,6 +214,39 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
         store_run<T, RW>(Vt + (2 * lane + 1) * PC + RW * w, x1);
     }
     __syncthreads();
+
+    if constexpr (ADD) {
+        // the read-out takes G_m S_n (the totals are complete since the first barrier)
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int row = 16 * ks + 8 * c + 4 * g;
+                const f32x4 t0 = *reinterpret_cast<const f32x4*>(tot + row), t1 = *reinterpret_cast<const f32x4*>(tot + DK + row);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) sfrag[ks].v[4 * c + s] *= t0[s] * t1[s];
+            }
+        // final state, by the last chunk's workgroup: tiles (at, bt), the channel tiles dealt to the waves
+        // of a dv tile.  Fragments 2 at and 2 at + 1 hold the state in accumulator order.
+        if (p.hT && n == p.NC - 1) {
+#pragma unroll
+            for (int at = 0; at < DK / 32; ++at) {
+                if (at % (kWaves / NBT) != w / NBT) continue;
+                f32x16 acc;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[v] = sfrag[2 * at + (v >> 3)].v[v & 7];
+#pragma unroll
+                for (int ks = 0; ks < C / 16; ++ks)
+                    M::mma(acc, M::load_kmajor(Km, PK, 16 * ks, 32 * at, lane), M::load(Vt + (32 * bt + r32) * PC + 16 * ks + 8 * g));
+                float* out = p.hT + (size_t)bh * DK * DV + (size_t)(32 * at) * DV + 32 * bt + r32;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = acc_row(v, lane);
+                    out[(size_t)row * DV] = acc[v] * (tot[2 * DK + 32 * at + row] * tot[3 * DK + 32 * at + row]);
+                }
+            }
+        }
+    }
 
     // ---------------- P^T blocks: (J, I) with J <= I; wave w takes block w ----------------
     {
@@ -224,43 +321,61 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
     }
 }
 
-template <typename T, int DK, int DV>
+template <typename T, int DK, int DV, bool ADD>
 __global__ __launch_bounds__(kThreads) void fwd_out_kernel(FwdOutParams p)
 {
-    if (p.dense) fwd_out_body<T, DK, DV, true>(p);
-    else         fwd_out_body<T, DK, DV, false>(p);
+    if (p.dense) fwd_out_body<T, DK, DV, true, ADD>(p);
+    else         fwd_out_body<T, DK, DV, false, ADD>(p);
 }
 
-template <typename T, int DK, int DV>
+template <typename T, int DK, int DV, bool ADD>
 static hipError_t launch_one(const SeqDims& d, const FwdOutParams& p, hipStream_t stream)
 {
     typedef FwdOutLds<T, DK, DV> L;
-    auto kern = fwd_out_kernel<T, DK, DV>;
+    auto kern = fwd_out_kernel<T, DK, DV, ADD>;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::total);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)d.total_chunks()), dim3(kThreads), L::total, stream, p);
     return hipGetLastError();
 }
 
-template <typename T>
+template <typename T, bool ADD>
 static hipError_t launch_dims(const SeqDims& d, const FwdOutParams& p, hipStream_t stream)
 {
-    if (d.dk == 128 && d.dv == 128) return launch_one<T, 128, 128>(d, p, stream);
-    if (d.dk == 64 && d.dv == 64) return launch_one<T, 64, 64>(d, p, stream);
-    if (d.dk == 128 && d.dv == 64) return launch_one<T, 128, 64>(d, p, stream);
-    if (d.dk == 64 && d.dv == 128) return launch_one<T, 64, 128>(d, p, stream);
+    if (d.dk == 128 && d.dv == 128) return launch_one<T, 128, 128, ADD>(d, p, stream);
+    if (d.dk == 64 && d.dv == 64) return launch_one<T, 64, 64, ADD>(d, p, stream);
+    if (d.dk == 128 && d.dv == 64) return launch_one<T, 128, 64, ADD>(d, p, stream);
+    if (d.dk == 64 && d.dv == 128) return launch_one<T, 64, 128, ADD>(d, p, stream);
     return hipErrorInvalidValue;
+}
+
+static FwdOutParams out_params(const SeqDims& d, const void* q, const void* f, const void* v, void* o)
+{
+    FwdOutParams p;
+    p.q = q; p.f = f; p.v = v; p.ws = nullptr; p.o = o;
+    p.BH = d.BH; p.N = d.N; p.NC = d.NC; p.gate_bf16 = d.gate_bf16 ? 1 : 0;
+    p.beta = d.beta; p.H = d.H; p.lay = d.lay; p.dense = d.dense() ? 1 : 0; p.flag = d.domain_flag;
+    p.add = nullptr; p.decay = nullptr; p.decay_stride = 0; p.h0 = nullptr; p.hT = nullptr;
+    return p;
 }
 
 hipError_t launch_fwd_out(const SeqDims& d, const void* q, const void* f, const void* v, const void* ws_state,
                           void* o, hipStream_t stream)
 {
     if (d.total_chunks() == 0) return hipSuccess;
-    FwdOutParams p;
-    p.q = q; p.f = f; p.v = v; p.ws = ws_state; p.o = o;
-    p.BH = d.BH; p.N = d.N; p.NC = d.NC; p.gate_bf16 = d.gate_bf16 ? 1 : 0;
-    p.beta = d.beta; p.H = d.H; p.lay = d.lay; p.dense = d.dense() ? 1 : 0; p.flag = d.domain_flag;
-    return d.io_bf16 ? launch_dims<__bf16>(d, p, stream) : launch_dims<float>(d, p, stream);
+    FwdOutParams p = out_params(d, q, f, v, o);
+    p.ws = ws_state;
+    return d.io_bf16 ? launch_dims<__bf16, false>(d, p, stream) : launch_dims<float, false>(d, p, stream);
+}
+
+hipError_t launch_fwd_out_add(const SeqDims& d, const void* q, const void* f, const void* v, const float* add,
+                              const float* decay, size_t decay_stride, const float* h0, void* o, float* hT, hipStream_t stream)
+{
+    if (d.total_chunks() == 0) return hipSuccess;
+    if (d.io_bf16 || d.packed) return hipErrorInvalidValue;
+    FwdOutParams p = out_params(d, q, f, v, o);
+    p.add = add; p.decay = decay; p.decay_stride = decay_stride; p.h0 = h0; p.hT = hT;
+    return launch_dims<float, true>(d, p, stream);
 }
 
 }   // namespace hgrn2

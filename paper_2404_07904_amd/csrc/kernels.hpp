@@ -132,7 +132,8 @@ enum SweepMode {
 // (`final_state`, may be null) in plain fp32 [dk][dv].  `a_src` is f (modes 0/1) or q (mode 2);
 // `b_src` is v (modes 0/1) or grad_o (mode 2).
 hipError_t launch_sweep(const SeqDims& d, SweepMode mode, const void* q, const void* f, const void* b_src,
-                        const float* init_state, float* final_state, void* ws, float* decay, hipStream_t stream);
+                        const float* init_state, float* final_state, void* ws, float* decay, hipStream_t stream,
+                        size_t decay_stride = 0);
 
 // Both sweeps of the backward pass (kSweepStateBwd into ws_state, kSweepGrad into ws_dstate) in
 // one launch.
@@ -157,6 +158,15 @@ hipError_t launch_run_carry(int n_seq, int seg, int dk, int dv, const float* car
 hipError_t launch_run_carry_packed(int B, int H, const int* first_run, int dk, int dv, const float* carried_in,
                                    float* run_state, const float* run_decay, float* carried_out, bool reverse,
                                    hipStream_t stream, const int* choice = nullptr, int path = 0);
+
+// (decay_stride != 0, on the runs of segmented sequences: the last run of each sequence is left out and the
+// products of run r of sequence s go to decay + s decay_stride + r dk)
+
+// The read-out from what every chunk adds to the state from zero (add: [sequence][NC][dk][dv], the last
+// chunk's entry unused) and the gate products of the chunks (decay + s decay_stride + chunk dk): no walk
+// over the chunks at all.  fp32 storage, equal lengths.
+hipError_t launch_fwd_out_add(const SeqDims& d, const void* q, const void* f, const void* v, const float* add,
+                              const float* decay, size_t decay_stride, const float* h0, void* o, float* hT, hipStream_t stream);
 
 // Per-chunk forward read-out  O = tril(Q~ K~^T) V + (Q G) S_n.
 hipError_t launch_fwd_out(const SeqDims& d, const void* q, const void* f, const void* v, const void* ws_state,

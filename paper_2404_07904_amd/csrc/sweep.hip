@@ -43,6 +43,9 @@ struct SweepParams {
     int H;
     TokenLayout lay;     // used when dense == 0
     int dense;           // sequence tensors are [B][H][N][d]: token strides are the compile-time dk, dv
+    // ENDS over the runs of segmented sequences, without the last run of each: the gate products of run r
+    // of sequence s go to decay + s decay_stride + r DK (0: all runs are walked, products at [run][DK])
+    size_t decay_stride;
 };
 
 
@@ -86,6 +89,7 @@ __device__ __forceinline__ void sweep_body(const SweepParams& p, int block_id)
         bh_end = table_read(p.lay.groups, grp + 1) * p.lay.H + head;
     } else {
         if (id >= p.BH) return;
+        if (ENDS && p.decay_stride && id % p.lay.seg == p.lay.seg - 1) return;
         bh_first = sequence_of_workgroup<DENSE>(p.lay, id);
         bh_step = 1;
         bh_end = bh_first + 1;
@@ -290,7 +294,8 @@ __device__ __forceinline__ void sweep_body(const SweepParams& p, int block_id)
         }
         if (it == NC - 1) {
             // the sequence ends: the slab as it stands, and the product of the gates it passed
-            if (ENDS && tile == 0 && tid < DK && p.decay) p.decay[(size_t)bh * DK + tid] = run_decay;
+            if (ENDS && tile == 0 && tid < DK && p.decay)
+                p.decay[(p.decay_stride ? (size_t)(bh / p.lay.seg) * p.decay_stride + (size_t)(bh % p.lay.seg) * DK : (size_t)bh * DK) + tid] = run_decay;
             if (p.fin) {
                 float* s1 = p.fin + (size_t)bh * DK * DV;
 #pragma unroll
@@ -409,10 +414,12 @@ static hipError_t launch_dims(const SeqDims& d, const SweepParams& p, hipStream_
 }
 
 hipError_t launch_sweep(const SeqDims& d, SweepMode mode, const void* q, const void* f, const void* b_src,
-                        const float* init_state, float* final_state, void* ws, float* decay, hipStream_t stream)
+                        const float* init_state, float* final_state, void* ws, float* decay, hipStream_t stream,
+                        size_t decay_stride)
 {
     if (d.BH == 0) return hipSuccess;
     SweepParams p;
+    p.decay_stride = decay_stride;
     p.q = q; p.f = f; p.bsrc = b_src; p.init = init_state; p.fin = final_state; p.ws = ws; p.decay = decay;
     p.BH = d.BH; p.N = d.N; p.NC = d.NC; p.n_tile = 1; p.gate_bf16 = d.gate_bf16 ? 1 : 0;
     p.beta = d.beta; p.H = d.H; p.lay = d.lay; p.dense = d.dense() ? 1 : 0;
@@ -439,7 +446,7 @@ hipError_t launch_sweep_pair(const SeqDims& d, const void* q, const void* f, con
     if (d.BH == 0) return hipSuccess;
     if (!d.io_bf16) return hipErrorInvalidValue;
     SweepParams ps, pg;
-    ps.decay = pg.decay = nullptr;
+    ps.decay = pg.decay = nullptr; ps.decay_stride = pg.decay_stride = 0;
     ps.q = nullptr; ps.f = f; ps.bsrc = v; ps.init = h0; ps.fin = nullptr; ps.ws = ws_state;
     pg.q = q; pg.f = f; pg.bsrc = grad_o; pg.init = grad_hT; pg.fin = grad_h0; pg.ws = ws_dstate;
     ps.BH = pg.BH = d.BH; ps.N = pg.N = d.N; ps.NC = pg.NC = d.NC; ps.n_tile = pg.n_tile = 1;
@@ -458,6 +465,7 @@ hipError_t launch_sweep_pair_ends(const SeqDims& d, const void* q, const void* f
     if (d.BH == 0) return hipSuccess;
     if (!d.io_bf16) return hipErrorInvalidValue;
     SweepParams ps, pg;
+    ps.decay_stride = pg.decay_stride = 0;
     ps.decay = run_decay; pg.decay = nullptr;        // both walks pass the same gates: one copy of their product
     ps.q = nullptr; ps.f = f; ps.bsrc = v; ps.init = nullptr; ps.fin = run_state; ps.ws = nullptr;
     pg.q = q; pg.f = f; pg.bsrc = grad_o; pg.init = nullptr; pg.fin = run_dstate; pg.ws = nullptr;
@@ -496,13 +504,28 @@ __global__ __launch_bounds__(256) void run_carry_kernel(const float* carried_in,
     }
     f32x4 st = {0.0f, 0.0f, 0.0f, 0.0f};
     if (carried_in) st = *reinterpret_cast<const f32x4*>(carried_in + (size_t)s * per + e4);
-    for (int j = 0; j < n_runs; ++j) {
-        const size_t r = slot0 + step * (reverse ? n_runs - 1 - j : j);
-        f32x4* slot = reinterpret_cast<f32x4*>(run_state + r * per + e4);
-        const f32x4 add = *slot;
-        const float g = run_decay[r * dk + k];
-        *slot = st;
-        st = st * g + add;
+    // Eight runs' contributions are requested at a time: taken one after the other, each run costs a trip to
+    // memory (30 us for 28 runs).
+    constexpr int AHEAD = 8;
+    for (int j0 = 0; j0 < n_runs; j0 += AHEAD) {
+        f32x4 add[AHEAD];
+        float g[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int j = min(j0 + u, n_runs - 1);
+            const size_t r = slot0 + step * (reverse ? n_runs - 1 - j : j);
+            add[u] = *reinterpret_cast<const f32x4*>(run_state + r * per + e4);
+            g[u] = run_decay[r * dk + k];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int j = j0 + u;
+            if (j >= n_runs) break;
+            const size_t r = slot0 + step * (reverse ? n_runs - 1 - j : j);
+            *reinterpret_cast<f32x4*>(run_state + r * per + e4) = st;
+            st = st * g[u] + add[u];
+        }
     }
     if (carried_out) *reinterpret_cast<f32x4*>(carried_out + (size_t)s * per + e4) = st;
 }

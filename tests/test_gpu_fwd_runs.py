@@ -83,3 +83,19 @@ def test_packed_forward_in_spans(lens, dk, dv):
         check("hT[%d]" % b, host(hT[b:b + 1]), rhT, TOL["bf16"])
         for name, x, r in zip(("dq", "df", "dv"), g, oracle.bwd(cut(w.q), cut(w.f), cut(w.v), cut(w.dO), h0[b:b + 1], None)):
             check("%s[%d]" % (name, b), host(x[s].permute(1, 0, 2)[None]), r, TOL["bf16"])
+
+
+# fp32 storage: the read-out that adds up the chunks' contributions (up to 1 MB of them: 64 chunks of 64 x 64
+# states, 16 of 128 x 128), its limits on either side, one chunk, a ragged last one
+@pytest.mark.parametrize("B,H,N,dk,dv", [(1, 1, 256, 64, 64), (2, 3, 777, 128, 64), (1, 2, 1000, 64, 128), (1, 1, 40, 128, 128),
+                                         (1, 2, 1024, 128, 128), (1, 2, 1025, 128, 128), (1, 1, 4096, 64, 64), (33, 2, 500, 64, 64)])
+@pytest.mark.parametrize("states", [False, True])
+def test_forward_fp32_from_contributions(B, H, N, dk, dv, states):
+    print("\n[fwd f32] B=%d H=%d N=%d dk=%d dv=%d states=%s" % (B, H, N, dk, dv, states), flush=True)
+    w = synth.make_sequence(3200 + N, B, H, N, dk, dv, io_dtype="f32", lb=0.9, with_h0=states)
+    o, hT = binding.hgrn2_fwd(dev(w.q), dev(w.f), dev(w.v), dev(w.h0), want_hT=states)
+    torch.cuda.synchronize()
+    ro, rhT = oracle.fwd(w.q, w.f, w.v, w.h0)
+    check("o", host(o), ro, TOL["f32"])
+    if states:
+        check("hT", host(hT), rhT, TOL["f32"])
