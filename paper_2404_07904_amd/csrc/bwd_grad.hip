@@ -45,8 +45,8 @@
 namespace hgrn2 {
 
 constexpr int kMaxLightRuns = 4;
-constexpr int kBwdWaves = 8;
-constexpr int kBwdThreads = 64 * kBwdWaves;
+constexpr int kBwdWaves = 8;         // (and rows of partial sums of the gradient of beta per chunk or run: one per row block)
+static_assert(kBwdWaves == kRowBlocks, "a row block per wave");
 
 struct BwdGradParams {
     const void* q;
@@ -84,7 +84,10 @@ struct BwdGradParams {
 };
 
 
-template <typename T, int DK, int DV> struct BwdGradLds {
+// NW: waves of the workgroup.  Four (heads of 64, bf16): a wave owns two row blocks, one per half wave, since
+// a row has only 32 channel pairs, and two workgroups share a compute unit, which covers the latencies
+// that eight half-idle waves of one workgroup do not.
+template <typename T, int DK, int DV, int NW> struct BwdGradLds {
     static constexpr int C = kChunk;
     // Tiles that are also read with LDS transpose loads (Q~, K~, dO, dS) take a pitch of D + 24
     // elements: row-major 16-byte reads stay conflict-free and the transpose reads run at twice
@@ -104,24 +107,28 @@ template <typename T, int DK, int DV> struct BwdGradLds {
     static constexpr size_t pt = dsm + (size_t)DK * PV * sizeof(T);         // P^T  [C][PC]  ([j][i])
     static constexpr size_t dpt = pt + (size_t)C * PC * sizeof(T);          // dP^T [C][PC]
     static constexpr size_t tot = dpt + (size_t)C * PC * sizeof(T);         // [8][DK] fp32 block products
-    static constexpr size_t p1_end = tot + (size_t)kBwdWaves * DK * sizeof(float);
+    static constexpr size_t p1_end = tot + (size_t)kRowBlocks * DK * sizeof(float);
     // phase 2 (aliases phase 1): fp32 staging of X, Y1, Ks and the block sums of the epilogue
     static constexpr size_t cx = 0;                                         // [C][PF] fp32
     static constexpr size_t cy = cx + (size_t)C * PF * sizeof(float);
     static constexpr size_t cks = cy + (size_t)C * PF * sizeof(float);
     static constexpr size_t blke = cks + (size_t)C * PF * sizeof(float);    // [8][DK] fp32 block sums of e'
-    static constexpr size_t blkk = blke + (size_t)kBwdWaves * DK * sizeof(float);   // [8][DK] block sums of K~ Ks
-    static constexpr size_t p2_end = blkk + (size_t)kBwdWaves * DK * sizeof(float);
+    static constexpr size_t blkk = blke + (size_t)kRowBlocks * DK * sizeof(float);  // [8][DK] block sums of K~ Ks
+    static constexpr size_t p2_end = blkk + (size_t)kRowBlocks * DK * sizeof(float);
+    // The dv staging tile [C][PVR] lies behind both phases and is written as soon as dv is formed; with two
+    // workgroups on a compute unit it lies behind the block sums and is written after the contractions.
+    static constexpr bool late_dv = NW == 4;
     // The next chunk's first stage writes the V, dO tiles and the block products while the last
     // stage of this one may still read the block sums; where those overlap, a barrier ends the chunk.
     static constexpr bool end_barrier = !(blke >= dsm && p2_end <= tot);
     // both phases
-    static constexpr size_t rp = cmax(p1_end, p2_end);                      // [DK] fp32  g * rowsum(dS * S_n)
-    static constexpr size_t dvs = rp + (size_t)DK * sizeof(float);          // dv staging [C][PVR]
-    static constexpr size_t one = dvs + (size_t)C * PVR * sizeof(T);        // [DK] fp32, all 1.0 (neutral factor)
+    static constexpr size_t dv_bytes = (size_t)C * PVR * sizeof(T);
+    static constexpr size_t rp = cmax(p1_end, p2_end + (late_dv ? dv_bytes : 0));   // [DK] fp32  g * rowsum(dS * S_n)
+    static constexpr size_t dvs = late_dv ? p2_end : rp + (size_t)DK * sizeof(float);
+    static constexpr size_t one = rp + (size_t)DK * sizeof(float) + (late_dv ? 0 : dv_bytes);   // [DK] fp32, all 1.0 (neutral factor)
     static constexpr size_t zero = one + (size_t)DK * sizeof(float);        // [DK] fp32, all 0.0 (neutral term)
     static constexpr size_t total = zero + (size_t)DK * sizeof(float);
-    static_assert(total <= 160 * 1024, "LDS budget of one workgroup");
+    static_assert(total * (8 / NW) <= 160 * 1024, "LDS budget of the workgroups of a compute unit");
 };
 
 // FUSED: the workgroup owns run `r` of sequence `bh` and walks its chunks from the last to the
@@ -138,12 +145,14 @@ template <typename T, int DK, int DV> struct BwdGradLds {
 // rows of the next chunk of the walk -- be it of the sequence before -- are always in flight during
 // the epilogue of the current one.  A span that ends inside a sequence first takes the light walk
 // over the chunks between its end and the sequence's, which yields the state gradient it starts from.
-template <typename T, int DK, int DV, bool GATE_BF16, bool DENSE, bool FUSED, bool GROUPED = false>
+template <typename T, int DK, int DV, bool GATE_BF16, bool DENSE, bool FUSED, bool GROUPED, int NW>
 __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
 {
     static_assert(!GROUPED || (FUSED && !DENSE), "groups: fused walk over a packed batch");
-    constexpr int C = kChunk, NW = kBwdWaves, RW = C / NW;
-    typedef BwdGradLds<T, DK, DV> L;
+    constexpr int C = kChunk, RW = C / kRowBlocks, NT = 64 * NW;
+    constexpr bool HALVES = NW == 4;         // a row block per half wave
+    static_assert(!HALVES || (DK == 64 && DV == 64 && FUSED), "four waves: heads of 64");
+    typedef BwdGradLds<T, DK, DV, NW> L;
     constexpr int PK = L::PK, PV = L::PV, PVR = L::PVR, PC = L::PC, PF = L::PF;
     constexpr int NRT = C / 32, NAT = DK / 32, NBT = DV / 32;
     static_assert(NRT == 2 && NRT * NAT <= NW && NRT * NBT <= NW, "one tile per wave");
@@ -219,10 +228,10 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
         return min(max(chunk_rows(p.lay.sub, c.n, c.sv.N).tok0 + vd_row, 0), c.sv.N - 1);
     };
     auto load_fq_rows = [&](RawRows<RW>& cf, RawRows<RW>& cq, const ChunkAt& c, int lane) {
-        const int col_k = (2 * lane < DK) ? 2 * lane : 0;
-        const int r0 = chunk_rows(p.lay.sub, c.n, c.sv.N).tok0 + RW * w;
-        load_rows_clamped<RW, GATE_BF16>(cf, static_cast<const char*>(p.f) + c.sv.off_k * GES, r0, c.sv.N - 1, DENSE ? DK : (int)p.lay.sn_k, col_k);
-        load_rows_clamped<RW, io_bf16>(cq, reinterpret_cast<const char*>(qg + c.sv.off_k), r0, c.sv.N - 1, DENSE ? DK : (int)p.lay.sn_k, col_k);
+        const int pair = (HALVES || 2 * lane < DK) ? lane : 0;
+        const int r0 = chunk_rows(p.lay.sub, c.n, c.sv.N).tok0 + (C / NW) * w;
+        load_block_rows<HALVES, RW, GATE_BF16>(cf, static_cast<const char*>(p.f) + c.sv.off_k * GES, r0, c.sv.N - 1, DENSE ? DK : (int)p.lay.sn_k, pair);
+        load_block_rows<HALVES, RW, io_bf16>(cq, reinterpret_cast<const char*>(qg + c.sv.off_k), r0, c.sv.N - 1, DENSE ? DK : (int)p.lay.sn_k, pair);
     };
     auto load_chunk_rows = [&](RawRows<RW>& cf, RawRows<RW>& cq, Raw16<T>& cv, Raw16<T>& cd, const ChunkAt& c, int lane) {
         load_fq_rows(cf, cq, c, lane);
@@ -283,7 +292,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
         if (p.dh0)
             for (int e = grp; e < p.lay.B; e += p.lay.spans)
                 if (table_read(p.lay.vl, p.lay.B + 1 + e) == 0)
-                    for (int i = tid; i < DK * DV; i += kBwdThreads) {
+                    for (int i = tid; i < DK * DV; i += NT) {
                         const size_t x = (size_t)(e * p.lay.H + g_head) * DK * DV + i;
                         p.dh0[x] = p.dhT ? p.dhT[x] : 0.0f;
                     }
@@ -342,15 +351,15 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     constexpr bool RUN_BETA = FUSED && !GROUPED;
     float run_b0 = 0.0f, run_b1 = 0.0f;
     auto store_run_beta = [&]() {
-        const int lane = threadIdx.x & 63;
-        if (RUN_BETA && p.beta && 2 * lane < DK)
-            *reinterpret_cast<f32x2*>(p.beta_partials + ((size_t)(f_bh * p.NC + f_run) * NW + w) * DK + 2 * lane) = f32x2{run_b0, run_b1};
+        const int lane = threadIdx.x & 63, cl = HALVES ? lane & 31 : lane, rb = HALVES ? 2 * w + (lane >> 5) : w;
+        if (RUN_BETA && p.beta && 2 * cl < DK)
+            *reinterpret_cast<f32x2*>(p.beta_partials + ((size_t)(f_bh * p.NC + f_run) * kBwdWaves + rb) * DK + 2 * cl) = f32x2{run_b0, run_b1};
     };
     if (n_iter <= 0) {                    // (FUSED) a sequence without tokens: the host routes those elsewhere
         store_run_beta();
         return;
     }
-    for (int i = tid; i < DK; i += kBwdThreads) { ones[i] = 1.0f; zeros[i] = 0.0f; }    // first read after a barrier
+    for (int i = tid; i < DK; i += NT) { ones[i] = 1.0f; zeros[i] = 0.0f; }    // first read after a barrier
     ChunkAt cur;
     bool rows_loaded = false;
     float below_floor = 1.0f;             // smallest product a reciprocal was taken of (reported once, at the end)
@@ -395,18 +404,19 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
                 int lane_opaque = threadIdx.x & 63;
                 asm volatile("" : "+v"(lane_opaque));
                 const int lane = lane_opaque, r32 = lane & 31;
-                const bool k_act = 2 * lane < DK;
+                const int cl = HALVES ? r32 : lane, rb = HALVES ? 2 * w + (lane >> 5) : w;     // channel pair, row block
+                const bool k_act = 2 * cl < DK;
                 if (vd_act) raw_d.store_swapped(dOm + (size_t)vd_row * PV + 16 * vd_grp);
                 const ChunkRows lr = chunk_rows(p.lay.sub, cur.n, cur.sv.N);
-                const int row0 = lr.tok0 + RW * w;
+                const int row0 = lr.tok0 + RW * rb;
                 f32x2 rf[RW], rq[RW];
                 convert_rows<RW>(rf, raw_f, row0, lr.end, k_act, gate_bf16, 1.0f, lr.first);
-                if (p.beta) gate_rows<RW>(rf, p.beta + (size_t)(cur.bh % p.H) * DK, k_act ? 2 * lane : 0, k_act, row0, lr.end, lr.first);
+                if (p.beta) gate_rows<RW>(rf, p.beta + (size_t)(cur.bh % p.H) * DK, k_act ? 2 * cl : 0, k_act, row0, lr.end, lr.first);
                 convert_rows<RW>(rq, raw_q, row0, lr.end, k_act, io_bf16, 0.0f, lr.first);
                 float a0[RW], a1[RW], t0 = 1.0f, t1 = 1.0f;
 #pragma unroll
                 for (int i = 0; i < RW; ++i) { t0 *= rf[i].x; t1 *= rf[i].y; a0[i] = t0; a1[i] = t1; }
-                if (k_act) *reinterpret_cast<f32x2*>(tot + w * DK + 2 * lane) = f32x2{t0, t1};
+                if (k_act) *reinterpret_cast<f32x2*>(tot + rb * DK + 2 * cl) = f32x2{t0, t1};
                 __syncthreads();
                 // rows of the next chunk of the walk (after the last light chunk: the run's own last chunk)
                 RawRows<RW> nxt_f, nxt_q;
@@ -416,22 +426,22 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
                 if (k_act) {
                     float pre0 = 1.0f, pre1 = 1.0f;
 #pragma unroll
-                    for (int i = 0; i < NW - 1; ++i) {
-                        const float* src = (i < w) ? tot + i * DK : ones;       // wave-uniform row address
-                        const f32x2 t = *reinterpret_cast<const f32x2*>(src + 2 * lane);
+                    for (int i = 0; i < kRowBlocks - 1; ++i) {
+                        const float* src = (i < rb) ? tot + i * DK : ones;
+                        const f32x2 t = *reinterpret_cast<const f32x2*>(src + 2 * cl);
                         pre0 *= t.x; pre1 *= t.y;
                     }
 #pragma unroll
                     for (int i = 0; i < RW; ++i) {
                         tx2 x;
                         x.x = (T)(rq[i].x * (pre0 * a0[i])); x.y = (T)(rq[i].y * (pre1 * a1[i]));
-                        *reinterpret_cast<tx2*>(Qm + (size_t)(RW * w + i) * PK + 2 * lane) = x;
+                        *reinterpret_cast<tx2*>(Qm + (size_t)(RW * rb + i) * PK + 2 * cl) = x;
                     }
                 }
                 float g_all = 1.0f;
                 if (has_d) {
 #pragma unroll
-                    for (int i = 0; i < NW; ++i) g_all *= tot[i * DK + 32 * at + r32];
+                    for (int i = 0; i < kRowBlocks; ++i) g_all *= tot[i * DK + 32 * at + r32];
                 }
                 __syncthreads();
                 if (has_d) {
@@ -478,7 +488,8 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     int lane_opaque = threadIdx.x & 63;
     asm volatile("" : "+v"(lane_opaque));
     const int lane = lane_opaque, r32 = lane & 31, g = lane >> 5;
-    const bool k_act = 2 * lane < DK;
+    const int cl = HALVES ? r32 : lane, rb = HALVES ? 2 * w + g : w;     // channel pair and row block of the element-wise work
+    const bool k_act = 2 * cl < DK;
     const int n = cur.n, bh = cur.bh;
     const size_t seq_k = cur.sv.off_k, seq_v = cur.sv.off_v;
     const int N = cur.sv.N;
@@ -493,10 +504,10 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     }
     // rf is re-derived from the raw rows in the epilogue (the raw bf16 pairs cost half the registers)
     const ChunkRows cr = chunk_rows(p.lay.sub, n, N);     // which tokens the chunk's rows stand for
-    const int row0 = cr.tok0 + RW * w;
+    const int row0 = cr.tok0 + RW * rb;
     f32x2 rf[RW], rq[RW];
     convert_rows<RW>(rf, raw_f, row0, cr.end, k_act, gate_bf16, 1.0f, cr.first);
-    if (p.beta) gate_rows<RW>(rf, p.beta + (size_t)(bh % p.H) * DK, k_act ? 2 * lane : 0, k_act, row0, cr.end, cr.first);
+    if (p.beta) gate_rows<RW>(rf, p.beta + (size_t)(bh % p.H) * DK, k_act ? 2 * cl : 0, k_act, row0, cr.end, cr.first);
     convert_rows<RW>(rq, raw_q, row0, cr.end, k_act, io_bf16, 0.0f, cr.first);
 
     // ---------------- gate products; scaled operand tiles ----------------
@@ -519,17 +530,17 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
         float u0 = 1.0f, u1 = 1.0f;
 #pragma unroll
         for (int i = RW - 1; i >= 0; --i) { z0[i] = u0; z1[i] = u1; u0 *= rf[i].x; u1 *= rf[i].y; }
-        if (k_act) *reinterpret_cast<f32x2*>(tot + w * DK + 2 * lane) = f32x2{t0, t1};
+        if (k_act) *reinterpret_cast<f32x2*>(tot + rb * DK + 2 * cl) = f32x2{t0, t1};
         __syncthreads();
         if (k_act) {
             // product of the (at most three) block totals between this block and the reference
-            // row; the row addresses are wave-uniform, an absent factor reads the row of ones
-            const float* r1 = after ? (w > 4 ? tot + 4 * DK : ones) : (w < 3 ? tot + 3 * DK : ones);
-            const float* r2 = after ? (w > 5 ? tot + 5 * DK : ones) : (w < 2 ? tot + 2 * DK : ones);
-            const float* r3 = after ? (w > 6 ? tot + 6 * DK : ones) : (w < 1 ? tot + 1 * DK : ones);
-            const f32x2 m1 = *reinterpret_cast<const f32x2*>(r1 + 2 * lane);
-            const f32x2 m2 = *reinterpret_cast<const f32x2*>(r2 + 2 * lane);
-            const f32x2 m3 = *reinterpret_cast<const f32x2*>(r3 + 2 * lane);
+            // row; an absent factor reads the row of ones
+            const float* r1 = after ? (rb > 4 ? tot + 4 * DK : ones) : (rb < 3 ? tot + 3 * DK : ones);
+            const float* r2 = after ? (rb > 5 ? tot + 5 * DK : ones) : (rb < 2 ? tot + 2 * DK : ones);
+            const float* r3 = after ? (rb > 6 ? tot + 6 * DK : ones) : (rb < 1 ? tot + 1 * DK : ones);
+            const f32x2 m1 = *reinterpret_cast<const f32x2*>(r1 + 2 * cl);
+            const f32x2 m2 = *reinterpret_cast<const f32x2*>(r2 + 2 * cl);
+            const f32x2 m3 = *reinterpret_cast<const f32x2*>(r3 + 2 * cl);
             const float mid0 = m1.x * m2.x * m3.x, mid1 = m1.y * m2.y * m3.y;
             const float R0 = fast_rcp(fmaxf(mid0 * t0, kTinyProduct)), R1 = fast_rcp(fmaxf(mid1 * t1, kTinyProduct));
             below_floor = fminf(below_floor, fminf(mid0 * t0, mid1 * t1));
@@ -537,11 +548,11 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
             sz0 = after ? R0 : mid0; sz1 = after ? R1 : mid1;
 #pragma unroll
             for (int i = 0; i < RW; ++i) {
-                const int row = RW * w + i;
+                const int row = RW * rb + i;
                 qb[i].x = (T)(rq[i].x * (sa0 * a0[i])); qb[i].y = (T)(rq[i].y * (sa1 * a1[i]));
                 kb[i].x = (T)((1.0f - rf[i].x) * (sz0 * z0[i])); kb[i].y = (T)((1.0f - rf[i].y) * (sz1 * z1[i]));
-                *reinterpret_cast<tx2*>(Qm + (size_t)row * PK + 2 * lane) = qb[i];
-                *reinterpret_cast<tx2*>(Km + (size_t)row * PK + 2 * lane) = kb[i];
+                *reinterpret_cast<tx2*>(Qm + (size_t)row * PK + 2 * cl) = qb[i];
+                *reinterpret_cast<tx2*>(Km + (size_t)row * PK + 2 * cl) = kb[i];
             }
         } else {
 #pragma unroll
@@ -626,12 +637,10 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     }
 
     // ---------------- P^T and dP^T blocks ----------------
-    // waves 0..2: P blocks (I,J) = (0,0), (1,0), (1,1); waves 3..5: the same for dP; waves 6, 7 zero
-    // the never-computed block (rows j >= 32, columns i < 32) so that every later contraction can
-    // run over the full chunk without reading stale data.
-    if (w < 6) {
-        const bool is_dp = w >= 3;
-        const int b = is_dp ? w - 3 : w;
+    // Eight waves: 0..2 take the P blocks (I,J) = (0,0), (1,0), (1,1), 3..5 the same for dP, 6 and 7 zero
+    // the never-computed block (rows j >= 32, columns i < 32) so that every later contraction can run
+    // over the full chunk without reading stale data.  Four waves: 0..2 take a block of both, 3 zeroes both.
+    auto p_block = [&](bool is_dp, int b) {
         const int I = (b == 0) ? 0 : 1, J = (b == 2) ? 1 : 0;
         f32x16 acc0, acc1;
 #pragma unroll
@@ -664,12 +673,19 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
             for (int ii = 0; ii < 4; ++ii) pk[ii] = (T)((j_glob <= i0 + ii) ? acc0[4 * c + ii] + acc1[4 * c + ii] : 0.0f);
             *reinterpret_cast<tx4*>(dst + (size_t)j_glob * PC + i0) = pk;
         }
-    } else {
-        T* dst = (w == 6) ? Pt : dPt;    // rows 32..63, columns 0..31: 32 x 32 values, 16 per lane
+    };
+    auto zero_block = [&](T* dst) {      // rows 32..63, columns 0..31: 32 x 32 values, 16 per lane
         const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int k = 0; k < 16 / VEC; ++k)
             *reinterpret_cast<u32x4*>(dst + (size_t)(32 + (lane >> 1)) * PC + 16 * (lane & 1) + VEC * k) = z;
+    };
+    if constexpr (HALVES) {
+        if (w < 3) { p_block(false, w); p_block(true, w); }
+        else { zero_block(Pt); zero_block(dPt); }
+    } else {
+        if (w < 6) p_block(w >= 3, w >= 3 ? w - 3 : w);
+        else zero_block((w == 6) ? Pt : dPt);
     }
     __syncthreads();
 
@@ -678,16 +694,8 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     // halves of P^T / dP^T are zero, so every contraction runs over the full chunk with no
     // branches).  It goes to its staging area at once, which frees its registers.  Its columns
     // come out in the position order of the dO and dS tiles and are put back here.
-    if (has_b) {
-        f32x16 aV, aV2;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) { aV[v] = 0.0f; aV2[v] = 0.0f; }
-#pragma unroll
-        for (int ks = 0; ks < 2 * NRT; ++ks)
-            M::mma(aV2, M::load_kmajor(dOm, PV, 16 * ks, 32 * bt, lane), M::load(Pt + (32 * rt_b + r32) * PC + 16 * ks + 8 * g));
-#pragma unroll
-        for (int ks = 0; ks < DK / 16; ++ks)
-            M::mma(aV, M::load_kmajor(dSm, PV, 16 * ks, 32 * bt, lane), M::load(Km + (32 * rt_b + r32) * PK + 16 * ks + 8 * g));
+    f32x16 aV, aV2;
+    auto stage_dv = [&]() {
         // The tile is held transposed (accumulator row = dv position 8 c + 4 g + jj, column = token), so
         // that four registers are four neighbouring dv columns of one token: position -> column swaps
         // bits 2 and 3, which sends them to columns 16 (c / 2) + 8 g + 4 (c % 2) + jj.
@@ -699,6 +707,17 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
             for (int jj = 0; jj < 4; ++jj) pk[jj] = (T)(aV[4 * c + jj] + aV2[4 * c + jj]);
             *reinterpret_cast<tx4*>(dst + 16 * (c >> 1) + 4 * (c & 1)) = pk;
         }
+    };
+    if (has_b) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { aV[v] = 0.0f; aV2[v] = 0.0f; }
+#pragma unroll
+        for (int ks = 0; ks < 2 * NRT; ++ks)
+            M::mma(aV2, M::load_kmajor(dOm, PV, 16 * ks, 32 * bt, lane), M::load(Pt + (32 * rt_b + r32) * PC + 16 * ks + 8 * g));
+#pragma unroll
+        for (int ks = 0; ks < DK / 16; ++ks)
+            M::mma(aV, M::load_kmajor(dSm, PV, 16 * ks, 32 * bt, lane), M::load(Km + (32 * rt_b + r32) * PK + 16 * ks + 8 * g));
+        if (!L::late_dv) stage_dv();
     }
     // tile (rt_a, at), transposed (channel = accumulator row):
     //   X^T = K~^T dP^T + (G_m S_n) dO^T,   Y1^T = Q~^T dP,   Ks^T = (H_m dS) V^T
@@ -759,6 +778,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     else nxt = where(chunk_of(it + 1));
     load_chunk_rows(nxt_f, nxt_q, raw_v, raw_d, nxt, lane);   // v, dO of this chunk are dead
     __syncthreads();     // every wave is done with the operand tiles
+    if (L::late_dv && has_b) stage_dv();
 
     // ---------------- staging: X, Y1, Ks as [row][channel] fp32, 16 bytes per store ----------------
     if (has_a) {
@@ -795,14 +815,14 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     // rows of this wave's block to global memory: one address and constant offsets when the
     // whole block lies inside the sequence, row by row otherwise
     auto store_block = [&](T* dst, const float (&x0)[RW], const float (&x1)[RW]) {
-        T* bp = dst + seq_k + (ptrdiff_t)row0 * (ptrdiff_t)ld_k + 2 * lane;
+        T* bp = dst + seq_k + (ptrdiff_t)row0 * (ptrdiff_t)ld_k + 2 * cl;
         if (row0 >= cr.first && row0 + RW <= cr.end) {
 #pragma unroll
             for (int i = 0; i < RW; ++i) store_pair_t<T>(bp, (size_t)i * ld_k, x0[i], x1[i]);
         } else {
 #pragma unroll
             for (int i = 0; i < RW; ++i)
-                if (cr.holds(RW * w + i)) store_pair_t<T>(bp, (size_t)i * ld_k, x0[i], x1[i]);
+                if (cr.holds(RW * rb + i)) store_pair_t<T>(bp, (size_t)i * ld_k, x0[i], x1[i]);
         }
     };
     if (k_act) {
@@ -810,10 +830,10 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
         float se0 = 0.0f, se1 = 0.0f;
 #pragma unroll
         for (int i = RW - 1; i >= 0; --i) {
-            const int row = RW * w + i;
-            const f32x2 xq = *reinterpret_cast<const f32x2*>(cX + (size_t)row * PF + 2 * lane);
-            const f32x2 xy = *reinterpret_cast<const f32x2*>(cY + (size_t)row * PF + 2 * lane);
-            const f32x2 xs = *reinterpret_cast<const f32x2*>(cKs + (size_t)row * PF + 2 * lane);
+            const int row = RW * rb + i;
+            const f32x2 xq = *reinterpret_cast<const f32x2*>(cX + (size_t)row * PF + 2 * cl);
+            const f32x2 xy = *reinterpret_cast<const f32x2*>(cY + (size_t)row * PF + 2 * cl);
+            const f32x2 xs = *reinterpret_cast<const f32x2*>(cKs + (size_t)row * PF + 2 * cl);
             const float qb0 = (float)qb[i].x, qb1 = (float)qb[i].y, kb0 = (float)kb[i].x, kb1 = (float)kb[i].y;
             dk0[i] = (sz0 * z0[i]) * (xy.x + xs.x); dk1[i] = (sz1 * z1[i]) * (xy.y + xs.y);
             se0 = fmaf(qb0, xq.x, se0); se0 = fmaf(-kb0, xy.x, se0);
@@ -826,14 +846,14 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
         float pk0 = 0.0f, pk1 = 0.0f;
 #pragma unroll
         for (int i = 0; i < RW; ++i) { gs0[i] += pk0; gs1[i] += pk1; pk0 += kk0[i]; pk1 += kk1[i]; }   // exclusive prefix inside the block
-        *reinterpret_cast<f32x2*>(blkE + w * DK + 2 * lane) = f32x2{se0, se1};
-        *reinterpret_cast<f32x2*>(blkK + w * DK + 2 * lane) = f32x2{pk0, pk1};
+        *reinterpret_cast<f32x2*>(blkE + rb * DK + 2 * cl) = f32x2{se0, se1};
+        *reinterpret_cast<f32x2*>(blkK + rb * DK + 2 * cl) = f32x2{pk0, pk1};
     }
     // coalesced store of dv
     {
         constexpr int VPR = DV / VEC;
         T* dvg = static_cast<T*>(p.dv);
-        for (int idx = tid; idx < C * VPR; idx += kBwdThreads) {
+        for (int idx = tid; idx < C * VPR; idx += NT) {
             const int row = idx / VPR, cv = idx % VPR;
             const int grow = cr.tok0 + row;
             if (cr.holds(row))
@@ -843,13 +863,13 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     }
     __syncthreads();
     if (k_act) {
-        // R + block sums of e' of the later blocks + block sums of K~ Ks of the earlier ones (row
-        // addresses are wave-uniform; this block's own slot reads the row of zeros)
-        f32x2 add = *reinterpret_cast<const f32x2*>(Rp + 2 * lane);
+        // R + block sums of e' of the later blocks + block sums of K~ Ks of the earlier ones (this
+        // block's own slot reads the row of zeros)
+        f32x2 add = *reinterpret_cast<const f32x2*>(Rp + 2 * cl);
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) {
-            const float* src = (ww > w) ? blkE + ww * DK : (ww < w) ? blkK + ww * DK : zeros;
-            const f32x2 b = *reinterpret_cast<const f32x2*>(src + 2 * lane);
+        for (int ww = 0; ww < kRowBlocks; ++ww) {
+            const float* src = (ww > rb) ? blkE + ww * DK : (ww < rb) ? blkK + ww * DK : zeros;
+            const f32x2 b = *reinterpret_cast<const f32x2*>(src + 2 * cl);
             add.x += b.x; add.y += b.y;
         }
 #pragma unroll
@@ -861,7 +881,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
             // gate formed from its pre-activation z (paper Eq. 2): with g = sigmoid(z) = (f - beta)/(1 - beta),
             //   dL/dz = df (1 - beta) g (1 - g) = df (f - beta)(1 - f)/(1 - beta),   dL/dbeta = sum df (1 - g)
             // (rows past the end of the sequence have f = 1 and drop out of the sum by themselves)
-            const f32x2 b = *reinterpret_cast<const f32x2*>(p.beta + (size_t)(bh % p.H) * DK + 2 * lane);
+            const f32x2 b = *reinterpret_cast<const f32x2*>(p.beta + (size_t)(bh % p.H) * DK + 2 * cl);
             const float inv0 = fast_rcp(1.0f - b.x), inv1 = fast_rcp(1.0f - b.y);
             float sb0 = 0.0f, sb1 = 0.0f;
 #pragma unroll
@@ -871,7 +891,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
                 gs0[i] = u0 * (rf[i].x - b.x); gs1[i] = u1 * (rf[i].y - b.y);
             }
             if constexpr (RUN_BETA) { run_b0 += sb0; run_b1 += sb1; }
-            else *reinterpret_cast<f32x2*>(p.beta_partials + ((size_t)chunk * NW + w) * DK + 2 * lane) = f32x2{sb0, sb1};
+            else *reinterpret_cast<f32x2*>(p.beta_partials + ((size_t)chunk * kBwdWaves + rb) * DK + 2 * cl) = f32x2{sb0, sb1};
         }
         store_block(dfg, gs0, gs1);
     }
@@ -899,37 +919,40 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
 }
 
 template <typename T, int DK, int DV, bool GATE_BF16>
-__global__ __launch_bounds__(kBwdThreads) void bwd_grad_kernel(BwdGradParams p)
+__global__ __launch_bounds__(64 * kBwdWaves) void bwd_grad_kernel(BwdGradParams p)
 {
-    if (p.dense) bwd_grad_body<T, DK, DV, GATE_BF16, true, false>(p);
-    else         bwd_grad_body<T, DK, DV, GATE_BF16, false, false>(p);
+    if (p.dense) bwd_grad_body<T, DK, DV, GATE_BF16, true, false, false, kBwdWaves>(p);
+    else         bwd_grad_body<T, DK, DV, GATE_BF16, false, false, false, kBwdWaves>(p);
 }
 
-template <typename T, int DK, int DV, bool GATE_BF16>
-__global__ __launch_bounds__(kBwdThreads) void bwd_fused_kernel(BwdGradParams p)
+// Waves of the reverse walk over runs: heads of 64 (bf16) take workgroups of four, two on a compute unit.
+constexpr int fused_waves(int dk, int dv, bool bf16) { return dk == 64 && dv == 64 && bf16 ? 4 : kBwdWaves; }
+
+template <typename T, int DK, int DV, bool GATE_BF16, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void bwd_fused_kernel(BwdGradParams p)
 {
-    if (p.dense) bwd_grad_body<T, DK, DV, GATE_BF16, true, true>(p);
-    else         bwd_grad_body<T, DK, DV, GATE_BF16, false, true>(p);
+    if (p.dense) bwd_grad_body<T, DK, DV, GATE_BF16, true, true, false, NW>(p);
+    else         bwd_grad_body<T, DK, DV, GATE_BF16, false, true, false, NW>(p);
 }
 
 // The fused reverse walk over groups of a packed batch's sequences (a kernel of its own).
 template <typename T, int DK, int DV, bool GATE_BF16>
-__global__ __launch_bounds__(kBwdThreads) void bwd_fused_grouped_kernel(BwdGradParams p)
+__global__ __launch_bounds__(64 * kBwdWaves) void bwd_fused_grouped_kernel(BwdGradParams p)
 {
-    bwd_grad_body<T, DK, DV, GATE_BF16, false, true, true>(p);
+    bwd_grad_body<T, DK, DV, GATE_BF16, false, true, true, kBwdWaves>(p);
 }
 
 template <typename T, int DK, int DV>
 static hipError_t launch_one(const SeqDims& d, const BwdGradParams& p, hipStream_t stream)
 {
-    typedef BwdGradLds<T, DK, DV> L;
+    typedef BwdGradLds<T, DK, DV, kBwdWaves> L;
     auto kern = d.gate_bf16 ? bwd_grad_kernel<T, DK, DV, true> : bwd_grad_kernel<T, DK, DV, false>;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::total);
     if (e != hipSuccess) return e;
     // one persistent workgroup per CU (the LDS footprint admits no more), each walking its share of chunks
     const size_t n_chunks = d.total_chunks();
     const unsigned grid = (unsigned)(n_chunks < 256 ? n_chunks : 256);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBwdThreads), L::total, stream, p);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kBwdWaves), L::total, stream, p);
     return hipGetLastError();
 }
 
@@ -959,23 +982,25 @@ hipError_t launch_bwd_grad(const SeqDims& d, const void* q, const void* f, const
 template <typename T, int DK, int DV>
 static hipError_t launch_fused_one(const SeqDims& d, const BwdGradParams& p, hipStream_t stream)
 {
-    typedef BwdGradLds<T, DK, DV> L;
-    auto kern = d.gate_bf16 ? bwd_fused_kernel<T, DK, DV, true> : bwd_fused_kernel<T, DK, DV, false>;
+    constexpr int NW = fused_waves(DK, DV, is_bf16_type<T>());
+    typedef BwdGradLds<T, DK, DV, NW> L;
+    auto kern = d.gate_bf16 ? bwd_fused_kernel<T, DK, DV, true, NW> : bwd_fused_kernel<T, DK, DV, false, NW>;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::total);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(d.BH * p.R)), dim3(kBwdThreads), L::total, stream, p);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(d.BH * p.R)), dim3(64 * NW), L::total, stream, p);
     return hipGetLastError();
 }
 
 BwdFusedPlan plan_bwd_fused(const SeqDims& d)
 {
-    // One workgroup per run and one run per compute unit at a time: as many runs per sequence as it
-    // takes to fill the chip, but at least four chunks each.  The zero-start sweep that supplies the
+    // One workgroup per run and one run per compute unit (heads of 64: two) at a time: as many runs per
+    // sequence as it takes to fill the chip, but at least four chunks each.  The zero-start sweep that supplies the
     // state gradient at the run boundaries walks sub-runs of about eight chunks.
     BwdFusedPlan pl;
     pl.light = 0;
     for (int i = 0; i <= kMaxLightRuns; ++i) pl.bnd[i] = 0;
-    int R = d.BH > 0 ? 256 / d.BH : 1;
+    const int places = fused_waves(d.dk, d.dv, d.io_bf16) == 4 ? 512 : 256;      // workgroups that run at once
+    int R = d.BH > 0 ? places / d.BH : 1;
     if (R > d.NC / 4) R = d.NC / 4;
     if (R < 1) R = 1;
     if (R >= 2 && R <= kMaxLightRuns) {
@@ -1050,11 +1075,11 @@ hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void
 template <int DK, int DV>
 static hipError_t launch_grouped_one(const SeqDims& d, const BwdGradParams& p, hipStream_t stream)
 {
-    typedef BwdGradLds<__bf16, DK, DV> L;
+    typedef BwdGradLds<__bf16, DK, DV, kBwdWaves> L;
     auto kern = d.gate_bf16 ? bwd_fused_grouped_kernel<__bf16, DK, DV, true> : bwd_fused_grouped_kernel<__bf16, DK, DV, false>;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::total);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(d.lay.spans * d.lay.H)), dim3(kBwdThreads), L::total, stream, p);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(d.lay.spans * d.lay.H)), dim3(64 * kBwdWaves), L::total, stream, p);
     return hipGetLastError();
 }
 

@@ -31,6 +31,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 constexpr int kWaves = 4;
+constexpr int kRowBlocks = 8;              // row blocks of a chunk for the element-wise work of the fused kernels, 8 rows each
 constexpr float kTinyProduct = 7.888609052210118e-31f;   // 2^-100: floor under a reciprocal
 
 // LDS row padding (in elements) that keeps rows 16-byte aligned and staggers banks.
@@ -290,6 +291,36 @@ __device__ __forceinline__ void load_rows_clamped(RawRows<RW>& out, const char* 
             const char* rp = seq_base + (size_t)min(max(row0 + i, 0), last_row) * (row_elems * ES);
             if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp + lane_col * ES));
             else out.r[i] = *reinterpret_cast<const f32x2*>(rp + lane_col * ES);
+        }
+    }
+}
+
+// RW rows of this lane's channel pair, row0 wave-uniform: rows row0 .. row0 + RW - 1 of pair `lane` for the
+// whole wave, or (HALVES: heads of 64, whose rows have only 32 pairs) of pair lane % 32, the upper half
+// wave taking the RW rows after those of the lower one.  Rows outside the sequence re-read a row inside it.
+template <bool HALVES, int RW, bool IS_BF16>
+__device__ __forceinline__ void load_block_rows(RawRows<RW>& out, const char* seq_base, int row0, int last_row, int ld, int lane)
+{
+    if constexpr (!HALVES) {
+        load_rows_clamped<RW, IS_BF16>(out, seq_base, row0, last_row, ld, 2 * lane);
+    } else {
+        constexpr int ES = IS_BF16 ? 2 : 4;
+        const int half = lane >> 5, col = 2 * (lane & 31);
+        if (row0 >= 0 && row0 + 2 * RW - 1 <= last_row) {
+            const char* rp = seq_base + (size_t)row0 * (ld * ES) + (uint32_t)((half * RW * ld + col) * ES);
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp + i * ld * ES));
+                else out.r[i] = *reinterpret_cast<const f32x2*>(rp + i * ld * ES);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                const int rc = min(max(row0 + half * RW + i, 0), last_row);
+                const char* rp = seq_base + (size_t)rc * (ld * ES) + col * ES;
+                if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp));
+                else out.r[i] = *reinterpret_cast<const f32x2*>(rp);
+            }
         }
     }
 }

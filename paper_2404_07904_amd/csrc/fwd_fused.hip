@@ -51,8 +51,6 @@
 
 namespace hgrn2 {
 
-// Row blocks of a chunk for the element-wise work: 8 rows each.
-constexpr int kRowBlocks = 8;
 constexpr int kMaxFwdRuns = 16;
 
 struct FwdFusedParams {
@@ -112,36 +110,6 @@ template <int DK_, int DVW_> struct FwdFusedLds {
     static constexpr size_t light_total = lg + (size_t)2 * DK * 4;
     static_assert(light_total <= total, "the light walk fits the tiles of the walk proper");
 };
-
-// RW rows of this lane's channel pair of a [token][DK] tensor.  Heads of 128 channels: rows row0 .. row0
-// + 7 for the whole wave (row0 wave-uniform); heads of 64: rows row0 .. row0 + 7 for the lower half wave
-// and the eight after them for the upper one.  Rows outside the sequence re-read a row inside it.
-template <int DK, int RW, bool IS_BF16>
-__device__ __forceinline__ void load_block_rows(RawRows<RW>& out, const char* seq_base, int row0, int last_row, int ld, int lane)
-{
-    if constexpr (DK == 128) {
-        load_rows_clamped<RW, IS_BF16>(out, seq_base, row0, last_row, ld, 2 * lane);
-    } else {
-        constexpr int ES = IS_BF16 ? 2 : 4;
-        const int half = lane >> 5, col = 2 * (lane & 31);
-        if (row0 >= 0 && row0 + 2 * RW - 1 <= last_row) {
-            const char* rp = seq_base + (size_t)row0 * (ld * ES) + (uint32_t)((half * RW * ld + col) * ES);
-#pragma unroll
-            for (int i = 0; i < RW; ++i) {
-                if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp + i * ld * ES));
-                else out.r[i] = *reinterpret_cast<const f32x2*>(rp + i * ld * ES);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < RW; ++i) {
-                const int rc = min(max(row0 + half * RW + i, 0), last_row);
-                const char* rp = seq_base + (size_t)rc * (ld * ES) + col * ES;
-                if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp));
-                else out.r[i] = *reinterpret_cast<const f32x2*>(rp);
-            }
-        }
-    }
-}
 
 // One chunk of the walk: tokens row0 .. row0 + C - 1 of a sequence of N tokens whose first token is
 // token tok0 of the packed tensors (grouped walks; 0 otherwise).  N = 0: a pass past the end.
@@ -464,11 +432,11 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     const char* qbase = reinterpret_cast<const char*>(qg + seq_k);
     const char* vbase = reinterpret_cast<const char*>(vg + seq_v + dv0);
     auto load_f = [&](RawRows<RW>& d, const FusedChunk& c) {
-        load_block_rows<DK, RW, GATE_BF16>(d, fbase + (size_t)c.tok0 * ((size_t)ld_k * (GATE_BF16 ? 2 : 4)), c.row0 + wrow,
+        load_block_rows<DK == 64, RW, GATE_BF16>(d, fbase + (size_t)c.tok0 * ((size_t)ld_k * (GATE_BF16 ? 2 : 4)), c.row0 + wrow,
                                            max(c.N - 1, 0), ld_k, lane);
     };
     auto load_q = [&](RawRows<RW>& d, const FusedChunk& c) {
-        load_block_rows<DK, RW, true>(d, qbase + (size_t)c.tok0 * ((size_t)ld_k * 2), c.row0 + wrow, max(c.N - 1, 0), ld_k, lane);
+        load_block_rows<DK == 64, RW, true>(d, qbase + (size_t)c.tok0 * ((size_t)ld_k * 2), c.row0 + wrow, max(c.N - 1, 0), ld_k, lane);
     };
     auto load_v = [&](u32x4 (&d)[NVV], const FusedChunk& c) {
         const int row0 = c.row0 + wrow, last_row = max(c.N - 1, 0);
