@@ -325,6 +325,7 @@ struct Alternative {
     int path2 = 0;
     int* flag = nullptr;
     bool validate_only = false;           // stop after the argument checks
+    BetaRows* beta_rows = nullptr;        // set: where to say what the reduction of the gradient of beta has to add up, instead of doing it
 };
 
 }   // namespace
@@ -537,7 +538,16 @@ static int bwd_impl(const hgrn2_shape* shape, const void* q, const void* f, cons
                                    : nullptr;
     if (!saved_states && launch_zero_floats(reinterpret_cast<float*>(flags), 4, stream) != hipSuccess) return HGRN2_ERR_HIP;
     a.validate_only = false;
+    // the gradient of beta: one reduction for whichever alternative runs, where their rows are few enough
+    BetaRows rows[kAlternatives];
+    SeqDims dims[kAlternatives];
+    bool one_reduction = gated && (size_t)shape->B * shape->H * shape->N > 0;
     for (int i = 0; i < kAlternatives; ++i) {
+        if (check_shape(&alt[i], true, &dims[i], false, true) != HGRN2_OK) one_reduction = false;
+        else one_reduction = one_reduction && reduce_beta_once(BetaRows{nullptr, shape->B, plan_bwd_fused(dims[i]).R});
+    }
+    for (int i = 0; i < kAlternatives; ++i) {
+        a.beta_rows = one_reduction ? &rows[i] : nullptr;
         a.choice2 = nullptr; a.path2 = 0;
         if (saved_states) {
             a.choice = i == 2 ? kept + 1 : kept; a.path = i == 0 ? 0 : 1;
@@ -551,6 +561,8 @@ static int bwd_impl(const hgrn2_shape* shape, const void* q, const void* f, cons
                                rest, rest_bytes, hip_stream, saved_states, &a);
         if (rc != HGRN2_OK) return rc;
     }
+    if (one_reduction && launch_reduce_beta(dims[0], rows, kAlternatives, saved_states ? kept : flags, grad_beta, stream) != hipSuccess)
+        return HGRN2_ERR_HIP;
     return HGRN2_OK;
 }
 
@@ -625,7 +637,11 @@ static int bwd_one(const hgrn2_shape* shape, const void* q, const void* f, const
             return HGRN2_ERR_HIP;
     }
     // an empty batch or sequence has NC = 0 or B = 0: the reduction then writes zeros
-    if (gated && reduce_beta_partials(d, ws_part, grad_beta, stream, has_tokens ? l.plan.R : 0) != hipSuccess) return HGRN2_ERR_HIP;
+    if (gated && has_tokens && alt && alt->beta_rows) {
+        *alt->beta_rows = BetaRows{ws_part, shape->B, l.plan.R};       // the caller adds up the alternatives' rows
+        return HGRN2_OK;
+    }
+    if (gated && reduce_beta_partials(d, ws_part, grad_beta, stream, l.plan.R) != hipSuccess) return HGRN2_ERR_HIP;
     return HGRN2_OK;
 }
 
@@ -1041,7 +1057,7 @@ static int bwd_varlen_one(const hgrn2_shape* shape, const int32_t* cu_seqlens, c
             if (launch_bwd_fused_grouped(d, q, f, v, grad_o, ws_s, grad_hT, grad_h0, grad_q, grad_f, grad_v, ws_part,
                                          stream) != hipSuccess)
                 return HGRN2_ERR_HIP;
-            if (beta && reduce_beta_partials(d, ws_part, grad_beta, stream) != hipSuccess) return HGRN2_ERR_HIP;
+            if (beta && reduce_beta_partials(d, ws_part, grad_beta, stream, beta_spans(d)) != hipSuccess) return HGRN2_ERR_HIP;
             return HGRN2_OK;
         }
         SeqDims walk = d, split = d;
@@ -1059,8 +1075,13 @@ static int bwd_varlen_one(const hgrn2_shape* shape, const int32_t* cu_seqlens, c
             (has_tokens &&
              launch_bwd_grad(split, q, f, v, grad_o, ws_s, ws_ds, grad_q, grad_f, grad_v, ws_part, stream) != hipSuccess))
             return HGRN2_ERR_HIP;
+        // (each way leaves rows of its own; the reduction of the other way's returns at once)
+        if (beta && has_tokens && (reduce_beta_partials(walk, ws_part, grad_beta, stream, beta_spans(d)) != hipSuccess ||
+                                   reduce_beta_partials(split, ws_part, grad_beta, stream, 0) != hipSuccess))
+            return HGRN2_ERR_HIP;
+        if (beta && has_tokens) return HGRN2_OK;
     }
-    if (beta && reduce_beta_partials(d, ws_part, grad_beta, stream) != hipSuccess) return HGRN2_ERR_HIP;
+    if (beta && reduce_beta_partials(d, ws_part, grad_beta, stream, beta_spans(d)) != hipSuccess) return HGRN2_ERR_HIP;
     return HGRN2_OK;
 }
 

@@ -81,6 +81,7 @@ struct BwdGradParams {
     int light;
     int bnd[kMaxLightRuns + 1];
     int* flag;               // null, or set to 1 when a gate product falls below the floor of the reciprocals
+    int beta_spans;          // row sets of partial sums per head (packed batches)
 };
 
 
@@ -278,7 +279,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     frag sS[2 * NBT], sD[2 * NBT];
     // chunks of this workgroup: every gridDim.x-th one, or (FUSED) those of its run, last to first
     int n_iter, f_bh = 0, f_run = 0, f_first = 0, f_last = 0;
-    int span_end = 0;                     // GROUPED: one past the last chunk of the span, counted over the head's chunks
+    int span_first = 0, span_end = 0, span_total = 0;    // GROUPED: the span's chunks and the number of all, counted over the head's chunks
     if constexpr (GROUPED) {
         if ((int)blockIdx.x >= p.lay.spans * p.lay.H) return;
         const int grp = (int)blockIdx.x / p.lay.H;
@@ -286,6 +287,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
         const int total = table_read(p.lay.vl, 2 * (p.lay.B + 1) + p.lay.B);       // chunks of one head
         const int span_start = (int)((long long)grp * total / p.lay.spans);
         span_end = (int)((long long)(grp + 1) * total / p.lay.spans);
+        span_first = span_start; span_total = total;
         n_iter = span_end - span_start;
         // a sequence without tokens hands the gradient of its final state on to its initial state
         // (such sequences lie in no span: they are dealt out by their number)
@@ -346,14 +348,25 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
                 accD[j][v] = (init && has_d) ? init[(size_t)(32 * at + r32i) * DV + 32 * btj + 8 * (v >> 2) + 4 * gi + (v & 3)] : 0.0f;
         }
     }
-    // FUSED walks over one run add up their partial sums of the gradient w.r.t. beta chunk after chunk
-    // (a fixed order) and leave one row per wave and run, in the slot of chunk `run` of the sequence.
-    constexpr bool RUN_BETA = FUSED && !GROUPED;
+    // FUSED walks add up their partial sums of the gradient w.r.t. beta chunk after chunk (a fixed order; a
+    // span's chunks are all of one head) and leave one row per row block and run, or span.
+    constexpr bool RUN_BETA = FUSED;
     float run_b0 = 0.0f, run_b1 = 0.0f;
     auto store_run_beta = [&]() {
         const int lane = threadIdx.x & 63, cl = HALVES ? lane & 31 : lane, rb = HALVES ? 2 * w + (lane >> 5) : w;
+        // (rows of a packed batch: beta_spans() per head.  More spans than that leave at most one chunk to a
+        // span: those with a chunk take the place of its number, those without fill the places behind.)
+        int slot = f_bh * p.R + f_run;
+        if constexpr (GROUPED) {
+            const int grp = (int)blockIdx.x / p.lay.H;
+            int grp_slot;
+            if (p.lay.spans > p.beta_spans) grp_slot = span_end > span_first ? span_first : span_total + grp - span_first;
+            else grp_slot = grp;
+            if (grp_slot >= p.beta_spans) return;
+            slot = g_head * p.beta_spans + grp_slot;
+        }
         if (RUN_BETA && p.beta && 2 * cl < DK)
-            *reinterpret_cast<f32x2*>(p.beta_partials + ((size_t)(f_bh * p.NC + f_run) * kBwdWaves + rb) * DK + 2 * cl) = f32x2{run_b0, run_b1};
+            *reinterpret_cast<f32x2*>(p.beta_partials + ((size_t)slot * kBwdWaves + rb) * DK + 2 * cl) = f32x2{run_b0, run_b1};
     };
     if (n_iter <= 0) {                    // (FUSED) a sequence without tokens: the host routes those elsewhere
         store_run_beta();
@@ -968,7 +981,7 @@ hipError_t launch_bwd_grad(const SeqDims& d, const void* q, const void* f, const
     p.BH = d.BH; p.N = d.N; p.NC = d.NC;
     p.beta = d.beta; p.beta_partials = beta_partials; p.H = d.H; p.lay = d.lay; p.dense = d.dense() ? 1 : 0;
     p.dhT = nullptr; p.dh0 = nullptr; p.bound0 = nullptr; p.run_state = nullptr; p.R = 1; p.rc = d.NC; p.s_sub = 1; p.seg_tail = 0;
-    p.light = 0;
+    p.light = 0; p.beta_spans = 0;
     for (int i = 0; i <= kMaxLightRuns; ++i) p.bnd[i] = 0;
     p.flag = d.domain_flag;
     if (d.beta && !beta_partials) return hipErrorInvalidValue;
@@ -1061,7 +1074,7 @@ hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void
     p.beta = d.beta; p.beta_partials = beta_partials; p.H = d.H; p.lay = d.lay; p.dense = d.dense() ? 1 : 0;
     p.dhT = grad_hT; p.dh0 = grad_h0; p.bound0 = bound0; p.run_state = run_state;
     p.R = pl.R; p.rc = pl.rc; p.s_sub = pl.s_sub; p.seg_tail = pl.seg_tail;
-    p.light = pl.light;
+    p.light = pl.light; p.beta_spans = 0;
     for (int i = 0; i <= kMaxLightRuns; ++i) p.bnd[i] = pl.bnd[i];
     p.flag = d.domain_flag;
     if (!d.io_bf16) return launch_fused_one<float, 64, 64>(d, p, stream);
@@ -1071,6 +1084,8 @@ hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void
     if (d.dk == 64 && d.dv == 128) return launch_fused_one<__bf16, 64, 128>(d, p, stream);
     return hipErrorInvalidValue;
 }
+
+int beta_spans(const SeqDims& d) { return d.lay.spans < d.NC ? d.lay.spans : d.NC; }
 
 template <int DK, int DV>
 static hipError_t launch_grouped_one(const SeqDims& d, const BwdGradParams& p, hipStream_t stream)
@@ -1097,6 +1112,7 @@ hipError_t launch_bwd_fused_grouped(const SeqDims& d, const void* q, const void*
     p.beta = d.beta; p.beta_partials = beta_partials; p.H = d.H; p.lay = d.lay; p.dense = 0;
     p.dhT = grad_hT; p.dh0 = grad_h0; p.bound0 = nullptr; p.run_state = nullptr;
     p.R = 1; p.rc = d.NC; p.s_sub = 1; p.seg_tail = 0; p.light = 0;
+    p.beta_spans = beta_spans(d);
     for (int i = 0; i <= kMaxLightRuns; ++i) p.bnd[i] = 0;
     p.flag = d.domain_flag;
     if (d.dk == 128 && d.dv == 128) return launch_grouped_one<128, 128>(d, p, stream);
@@ -1116,28 +1132,79 @@ size_t beta_partials_bytes(const SeqDims& d)
     return (d.total_chunks() * kBwdWaves + (size_t)kRedSlices * d.H) * d.dk * sizeof(float);
 }
 
-// grad_beta[h][a] = sum over batch, chunks and waves of the partial sums, in a fixed order.  First
-// pass: workgroup (head, 64 channels, slice) adds its share of the partial rows (the groups of 16
-// consecutive rows numbered slice, slice + 8, ... of every sequence; 16 groups of 64 threads take a
-// row each, coalesced across the channels, and the 16 group sums are added in order).  Second
-// pass: the slice sums are added in order.
-__global__ __launch_bounds__(64 * kRedGroups) void reduce_beta_kernel(const float* partials, float* slice_sums, int B,
-                                                                      int H, int NC, int used, int dk, const int* vl,
-                                                                      const int* choice, int path, int sub)
+// grad_beta[h][a] = sum of the partial sums, in a fixed order.  The rows of sequence b and head h lie
+// together.  Up to kRedOnce rows per head one workgroup per (head, 64 channels) adds them all: 16 groups of
+// 64 threads take every 16th row, coalesced across the channels, and the 16 group sums are added in
+// order.  With chunk = HGRN2_CHUNK_AUTO the rows of three passes are candidates, of which the flags name the
+// one that ran.
+constexpr int kRedOnce = 2048;
+
+struct BetaRowsParams {
+    BetaRows c[kBetaCandidates];
+    const int* flags;         // null, or {first pass left the gate domain, second pass left it}
+    TokenLayout lay;          // (for its conditions only)
+    float* grad_beta;
+    int H, dk;
+};
+
+__global__ __launch_bounds__(64 * kRedGroups) void reduce_beta_once_kernel(BetaRowsParams p)
 {
-    if (choice && table_read(choice, 0) != path) return;        // one of several alternatives, and not the one called for
+    if (not_chosen(p.lay)) return;        // one of several alternatives, and not the one called for
+    __shared__ float part[kRedGroups][64];
+    int pick = 0;
+    if (p.flags) pick = table_read(p.flags, 0) == 0 ? 0 : table_read(p.flags, 1) == 0 ? 1 : 2;
+    const float* src = pick == 0 ? p.c[0].rows : pick == 1 ? p.c[1].rows : p.c[2].rows;
+    const int B = pick == 0 ? p.c[0].B : pick == 1 ? p.c[1].B : p.c[2].B;
+    const int per = kBwdWaves * (pick == 0 ? p.c[0].runs : pick == 1 ? p.c[1].runs : p.c[2].runs);      // rows of a sequence and head
+    const int h = blockIdx.x / (p.dk / 64), a = 64 * (blockIdx.x % (p.dk / 64)) + (threadIdx.x & 63), grp = threadIdx.x >> 6;
+    float s = 0.0f;
+    // (per is a multiple of 8: a sequence's rows are taken by 8 or 16 of the groups, step by step)
+    const int total = B * per;
+#pragma unroll 8
+    for (int i = grp; i < total; i += kRedGroups) {
+        const int b = i / per;
+        s += src[(((size_t)b * p.H + h) * per + (i - b * per)) * p.dk + a];
+    }
+    part[grp][threadIdx.x & 63] = s;
+    __syncthreads();
+    if (grp == 0) {
+        float t = 0.0f;
+#pragma unroll
+        for (int j = 0; j < kRedGroups; ++j) t += part[j][threadIdx.x];
+        p.grad_beta[(size_t)h * p.dk + a] = t;
+    }
+}
+
+bool reduce_beta_once(const BetaRows& c) { return (size_t)c.B * c.runs * kBwdWaves <= kRedOnce; }
+
+hipError_t launch_reduce_beta(const SeqDims& d, const BetaRows* cand, int n, const int* flags, float* grad_beta, hipStream_t stream)
+{
+    if (d.H * d.dk == 0) return hipSuccess;
+    BetaRowsParams p;
+    for (int i = 0; i < kBetaCandidates; ++i) p.c[i] = cand[i < n ? i : 0];
+    p.flags = flags; p.lay = d.lay; p.grad_beta = grad_beta; p.H = d.H; p.dk = d.dk;
+    hipLaunchKernelGGL(reduce_beta_once_kernel, dim3(d.H * (d.dk / 64)), dim3(64 * kRedGroups), 0, stream, p);
+    return hipGetLastError();
+}
+
+// More rows, or one per chunk (the per-chunk gradient kernel's), in two passes.  First pass: workgroup
+// (head, 64 channels, slice) adds its share of the rows (the groups of 16 consecutive rows numbered slice,
+// slice + 8, ... of every sequence).  Second pass: the slice sums are added in order.  `per_seq`: runs of
+// a sequence; 0: one row set per chunk.
+__global__ __launch_bounds__(64 * kRedGroups) void reduce_beta_kernel(const float* partials, float* slice_sums, int B,
+                                                                      int H, int per_seq, int dk, TokenLayout lay)
+{
+    if (not_chosen(lay)) return;
     __shared__ float part[kRedGroups][64];
     const int h = blockIdx.x / (dk / 64), a = 64 * (blockIdx.x % (dk / 64)) + (threadIdx.x & 63);
     const int grp = threadIdx.x >> 6, slice = blockIdx.y;
     float s = 0.0f;
     for (int b = 0; b < B; ++b) {
-        // partial rows of (batch, head): kBwdWaves per chunk, the chunks of a sequence and head together
-        // (of which the first `used` hold rows: one per chunk, or one per run of a reverse walk)
-        size_t first = (size_t)(b * H + h) * NC;
-        int nc = used;
-        if (vl) {
-            nc = (vl[B + 1 + b] + sub - 1) >> (31 - __builtin_clz((unsigned)sub));
-            first = (size_t)vl[2 * (B + 1) + b] * H + (size_t)h * nc;
+        size_t first = (size_t)(b * H + h) * per_seq;
+        int nc = per_seq;
+        if (per_seq == 0) {                // chunk slots of a packed batch
+            nc = lay.chunks_of(lay.vl[lay.B + 1 + b]);
+            first = (size_t)lay.vl[2 * (lay.B + 1) + b] * H + (size_t)h * nc;
         }
         const int rows = nc * kBwdWaves;
         const float* pp = partials + first * kBwdWaves * dk + a;
@@ -1154,9 +1221,9 @@ __global__ __launch_bounds__(64 * kRedGroups) void reduce_beta_kernel(const floa
     }
 }
 
-__global__ void reduce_beta_slices_kernel(const float* slice_sums, float* grad_beta, int n, const int* choice, int path)
+__global__ void reduce_beta_slices_kernel(const float* slice_sums, float* grad_beta, int n, TokenLayout lay)
 {
-    if (choice && table_read(choice, 0) != path) return;
+    if (not_chosen(lay)) return;
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= n) return;
     float t = 0.0f;
@@ -1165,17 +1232,17 @@ __global__ void reduce_beta_slices_kernel(const float* slice_sums, float* grad_b
     grad_beta[c] = t;
 }
 
-hipError_t reduce_beta_partials(const SeqDims& d, float* beta_partials, float* grad_beta, hipStream_t stream, int runs)
+hipError_t reduce_beta_partials(const SeqDims& d, float* beta_partials, float* grad_beta, hipStream_t stream, int per_seq)
 {
     if (d.H * d.dk == 0) return hipSuccess;
-    const int B = d.BH / d.H, n = d.H * d.dk;
+    const int n = d.H * d.dk, B = (per_seq > 0 && d.lay.vl) ? 1 : d.BH / d.H;       // (spans belong to no sequence)
     if (d.total_chunks() == 0) return launch_zero_floats(grad_beta, (size_t)n, stream);      // nothing contributes
+    const BetaRows rows{beta_partials, B, per_seq};
+    if (per_seq > 0 && reduce_beta_once(rows)) return launch_reduce_beta(d, &rows, 1, nullptr, grad_beta, stream);
     float* slice_sums = beta_partials + d.total_chunks() * kBwdWaves * d.dk;
     hipLaunchKernelGGL(reduce_beta_kernel, dim3(d.H * (d.dk / 64), kRedSlices), dim3(64 * kRedGroups), 0, stream,
-                       beta_partials, slice_sums, B, d.H, d.NC, runs > 0 ? runs : d.NC, d.dk, d.lay.vl,
-                       d.packed ? d.lay.alt : d.lay.choice, d.packed ? d.lay.alt_path : d.lay.path, d.lay.sub);
-    hipLaunchKernelGGL(reduce_beta_slices_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, slice_sums, grad_beta, n,
-                       d.packed ? d.lay.alt : d.lay.choice, d.packed ? d.lay.alt_path : d.lay.path);
+                       beta_partials, slice_sums, B, d.H, per_seq, d.dk, d.lay);
+    hipLaunchKernelGGL(reduce_beta_slices_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, slice_sums, grad_beta, n, d.lay);
     return hipGetLastError();
 }
 

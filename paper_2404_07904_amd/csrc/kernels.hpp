@@ -199,10 +199,11 @@ hipError_t launch_fwd_fused(const SeqDims& d, const void* q, const void* f, cons
                             const float* run_add = nullptr, const float* run_decay = nullptr);
 
 // Per-chunk gradients dq, df, dv from the two state sweeps.
-// With d.beta set, grad_f receives the gradient w.r.t. the pre-activation z, and every wave of
-// every chunk (launch_bwd_fused: of every run) leaves its partial sum of the gradient w.r.t. beta in `beta_partials`
-// ([B*H*NC][8][dk] fp32, followed by room for the sums of the reduction's first pass:
-// beta_partials_bytes() in all), which reduce_beta_partials() adds up in a fixed order.
+// With d.beta set, grad_f receives the gradient w.r.t. the pre-activation z, and every row block of every
+// chunk (launch_bwd_fused: of every run, rows [sequence][run][8][dk]; launch_bwd_fused_grouped: of every
+// span, rows [head][beta_spans(d)][8][dk]) leaves its partial sum of the gradient w.r.t. beta in `beta_partials`
+// (beta_partials_bytes(): room for one per chunk, followed by room for the sums of the reduction's first
+// pass), which reduce_beta_partials() adds up in a fixed order.
 hipError_t launch_bwd_grad(const SeqDims& d, const void* q, const void* f, const void* v, const void* grad_o,
                            const void* ws_state, const void* ws_dstate, void* grad_q, void* grad_f,
                            void* grad_v, float* beta_partials, hipStream_t stream);
@@ -229,9 +230,18 @@ hipError_t launch_bwd_fused_grouped(const SeqDims& d, const void* q, const void*
                                     const void* ws_state, const float* grad_hT, float* grad_h0, void* grad_q,
                                     void* grad_f, void* grad_v, float* beta_partials, hipStream_t stream);
 size_t beta_partials_bytes(const SeqDims& d);
-// runs > 0: the partial sums come from launch_bwd_fused with a plan of that many runs, which leaves one
-// row per wave and RUN (in the first `runs` chunk slots of every sequence) instead of one per chunk.
-hipError_t reduce_beta_partials(const SeqDims& d, float* beta_partials, float* grad_beta, hipStream_t stream, int runs = 0);
+// Row sets per head that the walk over spans leaves: one per span, but never more than there is room for,
+// one per chunk of the host's bound (a small batch has fewer chunks than spans).
+int beta_spans(const SeqDims& d);
+// per_seq: row sets per sequence and head (runs; the spans of a packed batch count as those of one sequence),
+// or 0: one per chunk of a packed batch (launch_bwd_grad).
+hipError_t reduce_beta_partials(const SeqDims& d, float* beta_partials, float* grad_beta, hipStream_t stream, int per_seq);
+// The same from one of several passes' rows, the one the flags name (flags[0] clear: the first; flags[1] clear:
+// the second; else the third), in one launch; only where reduce_beta_once() holds for all of them.
+struct BetaRows { const float* rows = nullptr; int B = 0, runs = 0; };
+constexpr int kBetaCandidates = 3;
+bool reduce_beta_once(const BetaRows& c);
+hipError_t launch_reduce_beta(const SeqDims& d, const BetaRows* cand, int n, const int* flags, float* grad_beta, hipStream_t stream);
 
 // Lower bounds of all layers from Gamma [L][d] (paper Section 2): cumulative softmax over the
 // layer axis minus its first row.
