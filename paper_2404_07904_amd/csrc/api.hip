@@ -278,6 +278,20 @@ hipError_t build_packed_tables(const hgrn2_shape* s, const PackedRuns& p, const 
     return e;
 }
 
+// Spans of a packed batch: whether the state (state gradient) a span enters a sequence with comes from a
+// kernel that walks every span's part of the sequence from zero (run_ends, bwd_ends), rather than from a
+// light walk by every span over all of the sequence outside it.  The lengths are on the device; the host
+// knows the mean: with sequences of a quarter of a span on average some are likely to reach over spans.
+// (the contributions lie where a set of chunk states of another path lies: `room` bytes)
+size_t span_add_bytes(const hgrn2_shape* s, const SeqDims& d) { return round256((size_t)d.lay.spans * s->H * d.dk * d.dv * sizeof(float)); }
+bool spans_from_ends(const hgrn2_shape* s, const SeqDims& d, size_t room)
+{
+    if (d.lay.spans <= 0 || s->B <= 0) return false;
+    const long long chunks = d.N / d.lay.sub;
+    return chunks >= 2LL * d.lay.spans && 4 * (chunks / s->B) >= chunks / d.lay.spans &&
+           span_add_bytes(s, d) + (size_t)d.lay.spans * s->H * d.dk * sizeof(float) <= room;
+}
+
 // ---- small-gate modes -----------------------------------------------------------------------------
 bool fine_mode(const hgrn2_shape* s) { return s && (s->chunk == kFineChunk || s->chunk == 2 * kFineChunk || s->chunk == kFineChunk / 2); }
 
@@ -627,8 +641,9 @@ static int bwd_one(const hgrn2_shape* shape, const void* q, const void* f, const
             const char* q_t = static_cast<const char*>(q) + (size_t)skip * d.lay.sn_k * io;
             const char* f_t = static_cast<const char*>(f) + (size_t)skip * d.lay.sn_k * ge;
             const char* g_t = static_cast<const char*>(grad_o) + (size_t)skip * d.lay.sn_v * io;
-            if (launch_sweep(r, kSweepGrad, q_t, f_t, g_t, nullptr, tail_state, nullptr, tail_decay, stream) != hipSuccess ||
-                launch_run_carry(d.BH, pl.seg_tail, d.dk, d.dv, grad_hT, tail_state, tail_decay, bound0, true, stream, d.lay.choice, d.lay.path) != hipSuccess)
+            if ((d.io_bf16 ? launch_bwd_ends(r, q_t, f_t, g_t, tail_state, tail_decay, stream)
+                           : launch_sweep(r, kSweepGrad, q_t, f_t, g_t, nullptr, tail_state, nullptr, tail_decay, stream)) != hipSuccess ||
+                launch_run_carry(d.BH, pl.seg_tail, d.dk, d.dv, grad_hT, tail_state, tail_decay, bound0, true, stream, d.lay.choice, d.lay.path, pl.s_sub) != hipSuccess)
                 return HGRN2_ERR_HIP;
         }
         // 3. the reverse walk: dq, df, dv of every chunk, grad_h0
@@ -857,11 +872,8 @@ static int fwd_varlen_one(const hgrn2_shape* shape, const int32_t* cu_seqlens, c
         return HGRN2_OK;
     }
     if (fwd_fused_supported(d)) {
-        // Spans of two chunks and more get the state a sequence enters them with from a kernel that walks
-        // every span's last sequence from zero (its states lie where the sweeps of fp32 storage keep
-        // theirs); shorter ones take a light walk each.
-        const size_t add = round256((size_t)d.lay.spans * shape->H * d.dk * d.dv * sizeof(float));
-        if (d.N / d.lay.sub >= 2 * d.lay.spans && add + (size_t)d.lay.spans * shape->H * d.dk * sizeof(float) <= one) {
+        const size_t add = span_add_bytes(shape, d);
+        if (spans_from_ends(shape, d, one)) {
             float* run_add = static_cast<float*>(ws_s);
             float* run_decay = reinterpret_cast<float*>(static_cast<char*>(ws_s) + add);
             return launch_run_ends(d, 1, q, f, v, run_add, run_decay, stream) == hipSuccess &&
@@ -1032,7 +1044,9 @@ static int bwd_varlen_one(const hgrn2_shape* shape, const int32_t* cu_seqlens, c
         // chunks, for which a run is a sequence whose grad_hT is the state gradient the carry left
         // at its end (the carry has written the sequences' grad_h0).
         if (saved_states) {
-            if (launch_sweep(d, kSweepGrad, q, f, grad_o, nullptr, run_ds, nullptr, run_decay, stream) != hipSuccess)
+            SeqDims by_run = d;
+            by_run.lay.spans = 0;            // a workgroup per run, not per span of chunks
+            if (launch_bwd_ends(by_run, q, f, grad_o, run_ds, run_decay, stream) != hipSuccess)
                 return HGRN2_ERR_HIP;
         } else if (launch_sweep_pair_ends(d, q, f, v, grad_o, run_s, run_ds, run_decay, stream) != hipSuccess ||
                    launch_run_carry_packed(shape->B, shape->H, first_run, d.dk, d.dv, h0, run_s, run_decay, nullptr, false,
@@ -1053,9 +1067,13 @@ static int bwd_varlen_one(const hgrn2_shape* shape, const int32_t* cu_seqlens, c
         // kernels of both are enqueued and those of the other way return at once.  With the states
         // left by the forward pass the walk is the faster one for any lengths (measured also with one
         // document of half or all of the tokens): it alone is enqueued then.
+        const bool from_ends = spans_from_ends(shape, d, one);
+        float* span_add = from_ends ? static_cast<float*>(ws_ds) : nullptr;        // (the place of the two-sweep way's state gradients)
+        float* span_decay = from_ends ? reinterpret_cast<float*>(static_cast<char*>(ws_ds) + span_add_bytes(shape, d)) : nullptr;
         if (saved_states) {
-            if (launch_bwd_fused_grouped(d, q, f, v, grad_o, ws_s, grad_hT, grad_h0, grad_q, grad_f, grad_v, ws_part,
-                                         stream) != hipSuccess)
+            if ((from_ends && launch_bwd_ends(d, q, f, grad_o, span_add, span_decay, stream) != hipSuccess) ||
+                launch_bwd_fused_grouped(d, q, f, v, grad_o, ws_s, grad_hT, grad_h0, grad_q, grad_f, grad_v, ws_part,
+                                         stream, span_add, span_decay) != hipSuccess)
                 return HGRN2_ERR_HIP;
             if (beta && reduce_beta_partials(d, ws_part, grad_beta, stream, beta_spans(d)) != hipSuccess) return HGRN2_ERR_HIP;
             return HGRN2_OK;
@@ -1069,8 +1087,9 @@ static int bwd_varlen_one(const hgrn2_shape* shape, const int32_t* cu_seqlens, c
             split.lay.G = 0;                 // groups that only has to return is the cheaper one)
         }
         if (launch_sweep(walk, kSweepStateBwd, nullptr, f, v, h0, nullptr, ws_s, nullptr, stream) != hipSuccess ||
+            (from_ends && launch_bwd_ends(walk, q, f, grad_o, span_add, span_decay, stream) != hipSuccess) ||
             launch_bwd_fused_grouped(walk, q, f, v, grad_o, ws_s, grad_hT, grad_h0, grad_q, grad_f, grad_v, ws_part,
-                                     stream) != hipSuccess ||
+                                     stream, span_add, span_decay) != hipSuccess ||
             launch_sweep_pair(split, q, f, v, grad_o, h0, grad_hT, grad_h0, ws_s, ws_ds, stream) != hipSuccess ||
             (has_tokens &&
              launch_bwd_grad(split, q, f, v, grad_o, ws_s, ws_ds, grad_q, grad_f, grad_v, ws_part, stream) != hipSuccess))

@@ -82,6 +82,11 @@ struct BwdGradParams {
     int bnd[kMaxLightRuns + 1];
     int* flag;               // null, or set to 1 when a gate product falls below the floor of the reciprocals
     int beta_spans;          // row sets of partial sums per head (packed batches)
+    // What bwd_ends_kernel leaves: per slot a state gradient [dk][dv] and the gate products [dk].  Spans of a
+    // packed batch: slot span * H + head, read by the walk over spans (null: every span takes a light walk);
+    // runs of segmented sequences: slot = run.
+    float* span_add;
+    float* span_decay;
 };
 
 
@@ -130,7 +135,128 @@ template <typename T, int DK, int DV, int NW> struct BwdGradLds {
     static constexpr size_t zero = one + (size_t)DK * sizeof(float);        // [DK] fp32, all 0.0 (neutral term)
     static constexpr size_t total = zero + (size_t)DK * sizeof(float);
     static_assert(total * (8 / NW) <= 160 * 1024, "LDS budget of the workgroups of a compute unit");
+    // the light walk alone (bwd_ends_kernel)
+    static constexpr size_t lq = 0;
+    static constexpr size_t ld = lq + (size_t)C * PK * sizeof(T);
+    static constexpr size_t lt = ld + (size_t)C * PV * sizeof(T);
+    static constexpr size_t lo = lt + (size_t)kRowBlocks * DK * sizeof(float);
+    static constexpr size_t light_total = lo + (size_t)DK * sizeof(float);
 };
+
+// A chunk of a walk: sequence and chunk within it.
+struct ChunkAt { SeqView sv; int bh, n; };
+
+// The token whose V / dO row goes to row `row` of the tiles (a row that stands for no token re-reads a
+// neighbouring one: what it holds drops out of every stored result).
+__device__ __forceinline__ int tile_row_token(int sub, const ChunkAt& c, int row)
+{
+    return min(max(chunk_rows(sub, c.n, c.sv.N).tok0 + row, 0), c.sv.N - 1);
+}
+
+// The raw rows of f and q of this thread's row block.
+template <typename T, int DK, bool GATE_BF16, bool DENSE, int NW>
+__device__ __forceinline__ void load_fq(const BwdGradParams& p, RawRows<8>& cf, RawRows<8>& cq, const ChunkAt& c, int w, int lane)
+{
+    constexpr bool HALVES = NW == 4;
+    const int pair = (HALVES || 2 * lane < DK) ? lane : 0;
+    const int r0 = chunk_rows(p.lay.sub, c.n, c.sv.N).tok0 + (kChunk / NW) * w, ld = DENSE ? DK : (int)p.lay.sn_k;
+    load_block_rows<HALVES, 8, GATE_BF16>(cf, static_cast<const char*>(p.f) + c.sv.off_k * (GATE_BF16 ? 2 : 4), r0, c.sv.N - 1, ld, pair);
+    load_block_rows<HALVES, 8, is_bf16_type<T>()>(cq, reinterpret_cast<const char*>(static_cast<const T*>(p.q) + c.sv.off_k), r0, c.sv.N - 1, ld, pair);
+}
+
+// ---- light walk, last chunk to first, over `count` chunks of one sequence from chunk `cur` on:
+// dS_n = Diag(g_n) dS_{n+1} + Q^_n^T dO_n with Q^ = q G (G the gate product from the chunk start: no
+// quotient), the true state gradient in the accumulators (tiles as in bwd_grad_body).  Three barriers
+// per chunk.  Returns the chunk before the last one walked, whose f, q and dO rows are then loaded.
+// decay (null: not wanted): receives the product of the gates passed, channel 32 at + lane % 32.
+template <typename T, int DK, int DV, bool GATE_BF16, bool DENSE, int NW, int TPW>
+__device__ __forceinline__ ChunkAt light_walk(const BwdGradParams& p, T* Qm, T* dOm, float* tot, const float* ones, ChunkAt cur,
+                                              int count, f32x16 (&accD)[TPW], float* decay, RawRows<8>& raw_f, RawRows<8>& raw_q,
+                                              Raw16<T>& raw_d)
+{
+    typedef BwdGradLds<T, DK, DV, NW> L;
+    typedef Mma<T> M;
+    typedef typename M::frag frag;
+    typedef T tx2 __attribute__((ext_vector_type(2)));
+    constexpr int C = kChunk, RW = 8, NAT = DK / 32, NBT = DV / 32, GPR = DV / 16, PK = L::PK, PV = L::PV;
+    constexpr bool HALVES = NW == 4;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), at = w % NAT;
+    const bool has_d = (NAT * NBT) % NW == 0 || w < NAT * NBT, vd_act = tid < C * GPR;
+    const int vd_row = vd_act ? tid / GPR : 0, vd_grp = tid % GPR;
+    const T* dog = static_cast<const T*>(p.dO);
+    auto load = [&](RawRows<RW>& cf, RawRows<RW>& cq, const ChunkAt& c, int lane) {
+        load_fq<T, DK, GATE_BF16, DENSE, NW>(p, cf, cq, c, w, lane);
+        raw_d.load(dog + c.sv.off_v + (size_t)tile_row_token(p.lay.sub, c, vd_row) * (DENSE ? (size_t)DV : (size_t)p.lay.sn_v) + 16 * vd_grp);
+    };
+    load(raw_f, raw_q, cur, tid & 63);
+    float g_run = 1.0f;
+    const int head = cur.bh / p.lay.seg % p.H;
+    for (int li = 0; li < count; ++li) {
+        int lane_opaque = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane_opaque));
+        const int lane = lane_opaque, r32 = lane & 31;
+        const int cl = HALVES ? r32 : lane, rb = HALVES ? 2 * w + (lane >> 5) : w;     // channel pair, row block
+        const bool k_act = 2 * cl < DK;
+        if (vd_act) raw_d.store_swapped(dOm + (size_t)vd_row * PV + 16 * vd_grp);
+        const ChunkRows lr = chunk_rows(p.lay.sub, cur.n, cur.sv.N);
+        const int row0 = lr.tok0 + RW * rb;
+        f32x2 rf[RW], rq[RW];
+        convert_rows<RW>(rf, raw_f, row0, lr.end, k_act, GATE_BF16, 1.0f, lr.first);
+        if (p.beta) gate_rows<RW>(rf, p.beta + (size_t)head * DK, k_act ? 2 * cl : 0, k_act, row0, lr.end, lr.first);
+        convert_rows<RW>(rq, raw_q, row0, lr.end, k_act, is_bf16_type<T>(), 0.0f, lr.first);
+        float a0[RW], a1[RW], t0 = 1.0f, t1 = 1.0f;
+#pragma unroll
+        for (int i = 0; i < RW; ++i) { t0 *= rf[i].x; t1 *= rf[i].y; a0[i] = t0; a1[i] = t1; }
+        if (k_act) *reinterpret_cast<f32x2*>(tot + rb * DK + 2 * cl) = f32x2{t0, t1};
+        __syncthreads();
+        // rows of the next chunk of the walk
+        RawRows<RW> nxt_f, nxt_q;
+        ChunkAt nxt = cur;            // the chunk before, in the same sequence
+        nxt.n = cur.n - 1;
+        load(nxt_f, nxt_q, nxt, lane);
+        if (k_act) {
+            float pre0 = 1.0f, pre1 = 1.0f;
+#pragma unroll
+            for (int i = 0; i < kRowBlocks - 1; ++i) {
+                const float* src = (i < rb) ? tot + i * DK : ones;
+                const f32x2 t = *reinterpret_cast<const f32x2*>(src + 2 * cl);
+                pre0 *= t.x; pre1 *= t.y;
+            }
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                tx2 x;
+                x.x = (T)(rq[i].x * (pre0 * a0[i])); x.y = (T)(rq[i].y * (pre1 * a1[i]));
+                *reinterpret_cast<tx2*>(Qm + (size_t)(RW * rb + i) * PK + 2 * cl) = x;
+            }
+        }
+        float g_all = 1.0f;
+        if (has_d) {
+#pragma unroll
+            for (int i = 0; i < kRowBlocks; ++i) g_all *= tot[i * DK + 32 * at + r32];
+            g_run *= g_all;
+        }
+        __syncthreads();
+        if (has_d) {
+#pragma unroll
+            for (int j = 0; j < TPW; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) accD[j][v] *= g_all;
+#pragma unroll
+            for (int ks = 0; ks < C / 16; ++ks) {
+                const frag qf = M::load_kmajor(Qm, PK, 16 * ks, 32 * at, lane);
+#pragma unroll
+                for (int j = 0; j < TPW; ++j)
+                    M::mma(accD[j], M::load_kmajor_swapped(dOm, PV, 16 * ks, 32 * ((w + NW * j) / NAT), lane), qf);
+            }
+        }
+        raw_f = nxt_f;
+        raw_q = nxt_q;
+        cur = nxt;
+        __syncthreads();          // the tiles and totals are free for the next chunk
+    }
+    if (decay && w < NAT && (tid & 63) < 32) decay[32 * at + (tid & 31)] = g_run;
+    return cur;
+}
 
 // FUSED: the workgroup owns run `r` of sequence `bh` and walks its chunks from the last to the
 // first with the state gradient in fp32 MFMA accumulators, oriented [dv][channel]:
@@ -145,7 +271,9 @@ template <typename T, int DK, int DV, int NW> struct BwdGradLds {
 // sequence's grad_hT (or zero) at its last chunk and leaves as its grad_h0 after its first, and the
 // rows of the next chunk of the walk -- be it of the sequence before -- are always in flight during
 // the epilogue of the current one.  A span that ends inside a sequence first takes the light walk
-// over the chunks between its end and the sequence's, which yields the state gradient it starts from.
+// over the chunks between its end and the sequence's, which yields the state gradient it starts from; or,
+// with `span_add`, adds up what bwd_ends_kernel found for the later spans of that sequence:
+//     dS = Diag(decay_{s+1}) ( ... Diag(decay_last) grad_hT + add_last ... ) + add_{s+1}.
 template <typename T, int DK, int DV, bool GATE_BF16, bool DENSE, bool FUSED, bool GROUPED, int NW>
 __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
 {
@@ -215,7 +343,6 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     // chunk index -> sequence and chunk within it (every chunk index handed in is a valid one)
     // chunk index -> sequence and chunk within it (every chunk index handed in is a valid one);
     // found once per chunk, when its rows are requested, and kept for the chunk's own pass
-    struct ChunkAt { SeqView sv; int bh, n; };
     int seq_hint = 0;         // the workgroup asks for chunk indices in non-decreasing order
     auto where = [&](int chunk) {
         ChunkAt c;
@@ -223,16 +350,9 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
         c.sv = seq_view<DENSE, DK, DV>(p.lay, p.N, p.NC, c.bh);
         return c;
     };
-    // the token whose V / dO row this thread copies into row vd_row of the tiles (a row that stands for
-    // no token re-reads a neighbouring one: what it holds drops out of every stored result)
-    auto tile_token = [&](const ChunkAt& c) {
-        return min(max(chunk_rows(p.lay.sub, c.n, c.sv.N).tok0 + vd_row, 0), c.sv.N - 1);
-    };
+    auto tile_token = [&](const ChunkAt& c) { return tile_row_token(p.lay.sub, c, vd_row); };
     auto load_fq_rows = [&](RawRows<RW>& cf, RawRows<RW>& cq, const ChunkAt& c, int lane) {
-        const int pair = (HALVES || 2 * lane < DK) ? lane : 0;
-        const int r0 = chunk_rows(p.lay.sub, c.n, c.sv.N).tok0 + (C / NW) * w;
-        load_block_rows<HALVES, RW, GATE_BF16>(cf, static_cast<const char*>(p.f) + c.sv.off_k * GES, r0, c.sv.N - 1, DENSE ? DK : (int)p.lay.sn_k, pair);
-        load_block_rows<HALVES, RW, io_bf16>(cq, reinterpret_cast<const char*>(qg + c.sv.off_k), r0, c.sv.N - 1, DENSE ? DK : (int)p.lay.sn_k, pair);
+        load_fq<T, DK, GATE_BF16, DENSE, NW>(p, cf, cq, c, w, lane);
     };
     auto load_chunk_rows = [&](RawRows<RW>& cf, RawRows<RW>& cq, Raw16<T>& cv, Raw16<T>& cd, const ChunkAt& c, int lane) {
         load_fq_rows(cf, cq, c, lane);
@@ -386,6 +506,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
             const int nc_e = table_read(before, lo + 1) - table_read(before, lo);
             cur = chunk_en(lo, nc_e - 1);                          // that sequence's last chunk
             n_light = table_read(before, lo + 1) - span_end;       // its chunks after the span
+            const int seq_end = table_read(before, lo + 1);
             if (n_light > 0) {
                 // the light walk starts from the sequence's grad_hT (the chunk loop does that itself
                 // for every sequence whose last chunk lies in the span)
@@ -399,82 +520,44 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
                             accD[j][4 * c + e] = (p.dhT && has_d) ? *reinterpret_cast<const float*>(cols + st_lane + 4 * e) : 0.0f;
                     }
             }
+            if (n_light > 0 && p.span_add) {
+                // the spans from the one in which the sequence ends down to the next one, two requested at a time
+                const int span = (int)blockIdx.x / p.lay.H;
+                int k = span + 1;
+                while (k + 1 < p.lay.spans && (int)((long long)(k + 1) * span_total / p.lay.spans) < seq_end) ++k;
+                constexpr int AHEAD = 2;
+                if (has_d)
+                    for (; k > span; k -= AHEAD) {
+                        float dm[AHEAD];
+                        f32x4 add[AHEAD][TPW][4];
+#pragma unroll
+                        for (int u = 0; u < AHEAD; ++u) {
+                            const int slot = max(k - u, span + 1) * p.lay.H + g_head;
+                            dm[u] = p.span_decay[(size_t)slot * DK + 32 * at + (tid & 31)];
+#pragma unroll
+                            for (int j = 0; j < TPW; ++j)
+#pragma unroll
+                                for (int c = 0; c < 4; ++c) add[u][j][c] = *reinterpret_cast<const f32x4*>(state_cols(p.span_add, slot, j, c) + st_lane);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int u = 0; u < AHEAD; ++u) {
+                            if (k - u <= span) break;
+#pragma unroll
+                            for (int j = 0; j < TPW; ++j)
+#pragma unroll
+                                for (int v = 0; v < 16; ++v) accD[j][v] = fmaf(dm[u], accD[j][v], add[u][j][v >> 2][v & 3]);
+                        }
+                    }
+                cur.n -= n_light;                                  // the span's last chunk
+                n_light = 0;
+            }
         } else {
             n_light = p.light ? p.NC - 1 - f_last : 0;
             if (n_light > 0) cur = where(f_bh * p.NC + p.NC - 1);
         }
         if (n_light > 0) {
-            // ---- light walk over the chunks after this run: dS_n = Diag(g_n) dS_{n+1} + Q^_n^T dO_n with
-            // Q^ = q G (G the gate product from the chunk start: no quotient), true state gradient in
-            // the accumulators.  Three barriers per chunk; the Q~ and dO tiles and the block totals are reused.
-            auto load_light = [&](RawRows<RW>& cf, RawRows<RW>& cq, Raw16<T>& cd, const ChunkAt& c, int lane) {
-                load_fq_rows(cf, cq, c, lane);
-                const size_t vo = c.sv.off_v + (size_t)tile_token(c) * (DENSE ? (size_t)DV : (size_t)p.lay.sn_v) + 16 * vd_grp;
-                cd.load(dog + vo);
-            };
-            load_light(raw_f, raw_q, raw_d, cur, tid & 63);
-            for (int li = 0; li < n_light; ++li) {
-                int lane_opaque = threadIdx.x & 63;
-                asm volatile("" : "+v"(lane_opaque));
-                const int lane = lane_opaque, r32 = lane & 31;
-                const int cl = HALVES ? r32 : lane, rb = HALVES ? 2 * w + (lane >> 5) : w;     // channel pair, row block
-                const bool k_act = 2 * cl < DK;
-                if (vd_act) raw_d.store_swapped(dOm + (size_t)vd_row * PV + 16 * vd_grp);
-                const ChunkRows lr = chunk_rows(p.lay.sub, cur.n, cur.sv.N);
-                const int row0 = lr.tok0 + RW * rb;
-                f32x2 rf[RW], rq[RW];
-                convert_rows<RW>(rf, raw_f, row0, lr.end, k_act, gate_bf16, 1.0f, lr.first);
-                if (p.beta) gate_rows<RW>(rf, p.beta + (size_t)(cur.bh % p.H) * DK, k_act ? 2 * cl : 0, k_act, row0, lr.end, lr.first);
-                convert_rows<RW>(rq, raw_q, row0, lr.end, k_act, io_bf16, 0.0f, lr.first);
-                float a0[RW], a1[RW], t0 = 1.0f, t1 = 1.0f;
-#pragma unroll
-                for (int i = 0; i < RW; ++i) { t0 *= rf[i].x; t1 *= rf[i].y; a0[i] = t0; a1[i] = t1; }
-                if (k_act) *reinterpret_cast<f32x2*>(tot + rb * DK + 2 * cl) = f32x2{t0, t1};
-                __syncthreads();
-                // rows of the next chunk of the walk (after the last light chunk: the run's own last chunk)
-                RawRows<RW> nxt_f, nxt_q;
-                ChunkAt nxt = cur;            // the chunk before, in the same sequence
-                nxt.n = cur.n - 1;
-                load_light(nxt_f, nxt_q, raw_d, nxt, lane);
-                if (k_act) {
-                    float pre0 = 1.0f, pre1 = 1.0f;
-#pragma unroll
-                    for (int i = 0; i < kRowBlocks - 1; ++i) {
-                        const float* src = (i < rb) ? tot + i * DK : ones;
-                        const f32x2 t = *reinterpret_cast<const f32x2*>(src + 2 * cl);
-                        pre0 *= t.x; pre1 *= t.y;
-                    }
-#pragma unroll
-                    for (int i = 0; i < RW; ++i) {
-                        tx2 x;
-                        x.x = (T)(rq[i].x * (pre0 * a0[i])); x.y = (T)(rq[i].y * (pre1 * a1[i]));
-                        *reinterpret_cast<tx2*>(Qm + (size_t)(RW * rb + i) * PK + 2 * cl) = x;
-                    }
-                }
-                float g_all = 1.0f;
-                if (has_d) {
-#pragma unroll
-                    for (int i = 0; i < kRowBlocks; ++i) g_all *= tot[i * DK + 32 * at + r32];
-                }
-                __syncthreads();
-                if (has_d) {
-#pragma unroll
-                    for (int j = 0; j < TPW; ++j)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) accD[j][v] *= g_all;
-#pragma unroll
-                    for (int ks = 0; ks < 2 * NRT; ++ks) {
-                        const frag qf = M::load_kmajor(Qm, PK, 16 * ks, 32 * at, lane);
-#pragma unroll
-                        for (int j = 0; j < TPW; ++j)
-                            M::mma(accD[j], M::load_kmajor_swapped(dOm, PV, 16 * ks, 32 * ((w + NW * j) / NAT), lane), qf);
-                    }
-                }
-                raw_f = nxt_f;
-                raw_q = nxt_q;
-                cur = nxt;
-                __syncthreads();          // the tiles and totals are free for the next chunk
-            }
+            cur = light_walk<T, DK, DV, GATE_BF16, DENSE, NW>(p, Qm, dOm, tot, ones, cur, n_light, accD, nullptr, raw_f, raw_q, raw_d);
             // what the full pass over the run's last chunk needs on top: its V rows
             const size_t vo = cur.sv.off_v + (size_t)tile_token(cur) * (DENSE ? (size_t)DV : (size_t)p.lay.sn_v) + 16 * vd_grp;
             raw_v.load(vg + vo);
@@ -938,6 +1021,76 @@ __global__ __launch_bounds__(64 * kBwdWaves) void bwd_grad_kernel(BwdGradParams 
     else         bwd_grad_body<T, DK, DV, GATE_BF16, false, false, false, kBwdWaves>(p);
 }
 
+// What a run of chunks adds to the state gradient from zero (the light walk alone), and the product of its
+// gates: for every run of segmented sequences, or for every span of a packed batch whose first sequence has
+// begun in an earlier span, over that sequence's chunks in the span.  Three workgroups to a compute unit
+// by their LDS: bound by what they read (q, f, dO), which the sweep with its four waves was not (2 x 16
+// heads of 16384 tokens in 28 runs each, fp32 gates, 537 MB: 137 us).
+template <typename T, int DK, int DV, bool GATE_BF16, bool DENSE, bool GROUPED, int NW>
+__device__ __forceinline__ void bwd_ends_body(const BwdGradParams& p)
+{
+    typedef BwdGradLds<T, DK, DV, NW> L;
+    constexpr int NAT = DK / 32, NBT = DV / 32, NDT = NAT * NBT, TPW = (NDT + NW - 1) / NW, NT = 64 * NW;
+    extern __shared__ __align__(16) char smem[];
+    T* Qm = reinterpret_cast<T*>(smem + L::lq);
+    T* dOm = reinterpret_cast<T*>(smem + L::ld);
+    float* tot = reinterpret_cast<float*>(smem + L::lt);
+    float* ones = reinterpret_cast<float*>(smem + L::lo);
+    if (not_chosen(p.lay)) return;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), at = w % NAT, slot = blockIdx.x;
+    ChunkAt cur;
+    int count;
+    if constexpr (GROUPED) {
+        const int span = slot / p.lay.H, head = slot - span * p.lay.H;
+        if (span >= p.lay.spans) return;
+        const int* before = p.lay.vl + 2 * (p.lay.B + 1);
+        const int total = table_read(before, p.lay.B);
+        const int p0 = (int)((long long)span * total / p.lay.spans), p1 = (int)((long long)(span + 1) * total / p.lay.spans);
+        if (span == 0 || p1 <= p0) return;
+        // the sequence that holds chunk p0 is the one the span before ends in, unless it starts here
+        const int e = min(max(table_read(p.lay.span_seq, span - 1), 0), p.lay.B - 1);
+        const int b0 = table_read(before, e), b1 = min(table_read(before, e + 1), p1);
+        if (b0 >= p0 || b1 <= p0) return;
+        cur.bh = e * p.lay.H + head;
+        cur.sv = seq_view<DENSE, DK, DV>(p.lay, p.N, p.NC, cur.bh);
+        cur.n = b1 - 1 - b0;
+        count = b1 - p0;
+    } else {
+        if (slot >= p.BH) return;
+        cur.bh = slot;
+        cur.sv = seq_view<DENSE, DK, DV, true>(p.lay, p.N, p.NC, slot);
+        count = cur.sv.NC;
+        cur.n = count - 1;
+        if (count <= 0) return;
+    }
+    for (int i = tid; i < DK; i += NT) ones[i] = 1.0f;          // first read after a barrier
+    f32x16 accD[TPW];
+#pragma unroll
+    for (int j = 0; j < TPW; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) accD[j][v] = 0.0f;
+    RawRows<8> raw_f, raw_q;
+    Raw16<T> raw_d;
+    light_walk<T, DK, DV, GATE_BF16, DENSE, NW>(p, Qm, dOm, tot, ones, cur, count, accD, p.span_decay + (size_t)slot * DK, raw_f, raw_q, raw_d);
+    if (NDT % NW == 0 || w < NDT) {
+        float* out = p.span_add + (size_t)slot * DK * DV + (size_t)(32 * at + (tid & 31)) * DV + 4 * ((tid >> 5) & 1);
+#pragma unroll
+        for (int j = 0; j < TPW; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                *reinterpret_cast<f32x4*>(out + 32 * ((w + NW * j) / NAT) + 8 * c) =
+                    f32x4{accD[j][4 * c], accD[j][4 * c + 1], accD[j][4 * c + 2], accD[j][4 * c + 3]};
+    }
+}
+
+template <typename T, int DK, int DV, bool GATE_BF16, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 3) void bwd_ends_kernel(BwdGradParams p)
+{
+    if (p.lay.vl && p.lay.spans > 0) bwd_ends_body<T, DK, DV, GATE_BF16, false, true, NW>(p);
+    else if (p.dense) bwd_ends_body<T, DK, DV, GATE_BF16, true, false, NW>(p);
+    else bwd_ends_body<T, DK, DV, GATE_BF16, false, false, NW>(p);
+}
+
 // Waves of the reverse walk over runs: heads of 64 (bf16) take workgroups of four, two on a compute unit.
 constexpr int fused_waves(int dk, int dv, bool bf16) { return dk == 64 && dv == 64 && bf16 ? 4 : kBwdWaves; }
 
@@ -981,7 +1134,7 @@ hipError_t launch_bwd_grad(const SeqDims& d, const void* q, const void* f, const
     p.BH = d.BH; p.N = d.N; p.NC = d.NC;
     p.beta = d.beta; p.beta_partials = beta_partials; p.H = d.H; p.lay = d.lay; p.dense = d.dense() ? 1 : 0;
     p.dhT = nullptr; p.dh0 = nullptr; p.bound0 = nullptr; p.run_state = nullptr; p.R = 1; p.rc = d.NC; p.s_sub = 1; p.seg_tail = 0;
-    p.light = 0; p.beta_spans = 0;
+    p.light = 0; p.beta_spans = 0; p.span_add = nullptr; p.span_decay = nullptr;
     for (int i = 0; i <= kMaxLightRuns; ++i) p.bnd[i] = 0;
     p.flag = d.domain_flag;
     if (d.beta && !beta_partials) return hipErrorInvalidValue;
@@ -1074,7 +1227,7 @@ hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void
     p.beta = d.beta; p.beta_partials = beta_partials; p.H = d.H; p.lay = d.lay; p.dense = d.dense() ? 1 : 0;
     p.dhT = grad_hT; p.dh0 = grad_h0; p.bound0 = bound0; p.run_state = run_state;
     p.R = pl.R; p.rc = pl.rc; p.s_sub = pl.s_sub; p.seg_tail = pl.seg_tail;
-    p.light = pl.light; p.beta_spans = 0;
+    p.light = pl.light; p.beta_spans = 0; p.span_add = nullptr; p.span_decay = nullptr;
     for (int i = 0; i <= kMaxLightRuns; ++i) p.bnd[i] = pl.bnd[i];
     p.flag = d.domain_flag;
     if (!d.io_bf16) return launch_fused_one<float, 64, 64>(d, p, stream);
@@ -1082,6 +1235,39 @@ hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void
     if (d.dk == 64 && d.dv == 64) return launch_fused_one<__bf16, 64, 64>(d, p, stream);
     if (d.dk == 128 && d.dv == 64) return launch_fused_one<__bf16, 128, 64>(d, p, stream);
     if (d.dk == 64 && d.dv == 128) return launch_fused_one<__bf16, 64, 128>(d, p, stream);
+    return hipErrorInvalidValue;
+}
+
+template <int DK, int DV>
+static hipError_t launch_ends_one(const SeqDims& d, const BwdGradParams& p, unsigned grid, hipStream_t stream)
+{
+    constexpr int NW = fused_waves(DK, DV, true);
+    typedef BwdGradLds<__bf16, DK, DV, NW> L;
+    auto kern = d.gate_bf16 ? bwd_ends_kernel<__bf16, DK, DV, true, NW> : bwd_ends_kernel<__bf16, DK, DV, false, NW>;
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::light_total);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NW), L::light_total, stream, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_bwd_ends(const SeqDims& d, const void* q, const void* f, const void* grad_o, float* add, float* decay, hipStream_t stream)
+{
+    const bool spans = d.lay.vl && d.lay.spans > 0;
+    const unsigned grid = spans ? (unsigned)(d.lay.spans * d.lay.H) : (unsigned)d.BH;
+    if (grid == 0 || d.total_chunks() == 0) return hipSuccess;
+    if (!d.io_bf16 || (spans && !d.lay.span_seq)) return hipErrorInvalidValue;
+    BwdGradParams p;
+    p.q = q; p.f = f; p.v = nullptr; p.dO = grad_o; p.ws_s = nullptr; p.ws_ds = nullptr; p.dq = nullptr; p.df = nullptr; p.dv = nullptr;
+    p.BH = d.BH; p.N = d.N; p.NC = d.NC;
+    p.beta = d.beta; p.beta_partials = nullptr; p.H = d.H; p.lay = d.lay; p.dense = d.dense() ? 1 : 0;
+    p.dhT = nullptr; p.dh0 = nullptr; p.bound0 = nullptr; p.run_state = nullptr; p.R = 1; p.rc = d.NC; p.s_sub = 1; p.seg_tail = 0;
+    p.light = 0; p.beta_spans = 0; p.flag = nullptr;
+    for (int i = 0; i <= kMaxLightRuns; ++i) p.bnd[i] = 0;
+    p.span_add = add; p.span_decay = decay;
+    if (d.dk == 128 && d.dv == 128) return launch_ends_one<128, 128>(d, p, grid, stream);
+    if (d.dk == 64 && d.dv == 64) return launch_ends_one<64, 64>(d, p, grid, stream);
+    if (d.dk == 128 && d.dv == 64) return launch_ends_one<128, 64>(d, p, grid, stream);
+    if (d.dk == 64 && d.dv == 128) return launch_ends_one<64, 128>(d, p, grid, stream);
     return hipErrorInvalidValue;
 }
 
@@ -1100,7 +1286,8 @@ static hipError_t launch_grouped_one(const SeqDims& d, const BwdGradParams& p, h
 
 hipError_t launch_bwd_fused_grouped(const SeqDims& d, const void* q, const void* f, const void* v, const void* grad_o,
                                     const void* ws_state, const float* grad_hT, float* grad_h0, void* grad_q,
-                                    void* grad_f, void* grad_v, float* beta_partials, hipStream_t stream)
+                                    void* grad_f, void* grad_v, float* beta_partials, hipStream_t stream, const float* span_add,
+                                    const float* span_decay)
 {
     if (d.total_chunks() == 0) return hipSuccess;
     if (!d.lay.vl || d.lay.spans <= 0 || !d.lay.span_seq || !d.io_bf16) return hipErrorInvalidValue;
@@ -1113,6 +1300,7 @@ hipError_t launch_bwd_fused_grouped(const SeqDims& d, const void* q, const void*
     p.dhT = grad_hT; p.dh0 = grad_h0; p.bound0 = nullptr; p.run_state = nullptr;
     p.R = 1; p.rc = d.NC; p.s_sub = 1; p.seg_tail = 0; p.light = 0;
     p.beta_spans = beta_spans(d);
+    p.span_add = const_cast<float*>(span_add); p.span_decay = const_cast<float*>(span_decay);
     for (int i = 0; i <= kMaxLightRuns; ++i) p.bnd[i] = 0;
     p.flag = d.domain_flag;
     if (d.dk == 128 && d.dv == 128) return launch_grouped_one<128, 128>(d, p, stream);

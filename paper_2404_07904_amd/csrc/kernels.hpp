@@ -149,10 +149,12 @@ hipError_t launch_sweep_pair(const SeqDims& d, const void* q, const void* f, con
 // state entering each run, from which the ordinary sweeps then start run by run.
 hipError_t launch_sweep_pair_ends(const SeqDims& d, const void* q, const void* f, const void* v, const void* grad_o,
                                   float* run_state, float* run_dstate, float* run_decay, hipStream_t stream);
-// (choice, path: as TokenLayout's; the kernel returns at once when *choice != path)
+// (choice, path: as TokenLayout's; the kernel returns at once when *choice != path.  keep > 1: of the states
+// entering the runs only those of every keep-th run are wanted, runs 0, keep, 2 keep, ... or, reverse, those
+// that end at a multiple of keep runs; the other slots are left as they are)
 hipError_t launch_run_carry(int n_seq, int seg, int dk, int dv, const float* carried_in, float* run_state,
                             const float* run_decay, float* carried_out, bool reverse, hipStream_t stream,
-                            const int* choice = nullptr, int path = 0);
+                            const int* choice = nullptr, int path = 0, int keep = 1);
 // The same for a packed batch cut by launch_varlen_run_table: sequence b of head h owns the runs
 // first_run[b] .. first_run[b + 1] - 1, whose states sit at [run * H + h].
 hipError_t launch_run_carry_packed(int B, int H, const int* first_run, int dk, int dv, const float* carried_in,
@@ -228,7 +230,14 @@ hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void
 // of a kSweepStateBwd sweep over the same table.
 hipError_t launch_bwd_fused_grouped(const SeqDims& d, const void* q, const void* f, const void* v, const void* grad_o,
                                     const void* ws_state, const float* grad_hT, float* grad_h0, void* grad_q,
-                                    void* grad_f, void* grad_v, float* beta_partials, hipStream_t stream);
+                                    void* grad_f, void* grad_v, float* beta_partials, hipStream_t stream,
+                                    const float* span_add = nullptr, const float* span_decay = nullptr);
+// What every run of segmented sequences adds to the state gradient from zero, add [run][dk][dv], and the
+// product of its gates, decay [run][dk] (a reverse counterpart of launch_run_ends; bf16 storage); or, for a
+// packed batch with spans, what every span adds to the state gradient of its first sequence where that has
+// begun in an earlier span, slot = span * H + head: launch_bwd_fused_grouped then adds these up (span_add,
+// span_decay) instead of giving every span a light walk.
+hipError_t launch_bwd_ends(const SeqDims& d, const void* q, const void* f, const void* grad_o, float* add, float* decay, hipStream_t stream);
 size_t beta_partials_bytes(const SeqDims& d);
 // Row sets per head that the walk over spans leaves: one per span, but never more than there is room for,
 // one per chunk of the host's bound (a small batch has fewer chunks than spans).

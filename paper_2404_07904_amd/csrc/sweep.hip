@@ -486,7 +486,7 @@ hipError_t launch_sweep_pair_ends(const SeqDims& d, const void* q, const void* f
 // entering each run, which replaces add_r in place, and the state leaving the sequence.
 __global__ __launch_bounds__(256) void run_carry_kernel(const float* carried_in, float* run_state, const float* run_decay,
                                                         float* carried_out, int seg, const int* first_run, int H,
-                                                        int dk, int dv, int reverse, const int* choice, int path)
+                                                        int dk, int dv, int reverse, const int* choice, int path, int keep)
 {
     if (choice && table_read(choice, 0) != path) return;        // one of several alternatives, and not the one called for
     const size_t per = (size_t)dk * dv;
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(256) void run_carry_kernel(const float* carried_in,
             const int j = j0 + u;
             if (j >= n_runs) break;
             const size_t r = slot0 + step * (reverse ? n_runs - 1 - j : j);
-            *reinterpret_cast<f32x4*>(run_state + r * per + e4) = st;
+            if (keep <= 1 || (reverse ? n_runs - j : j) % keep == 0) *reinterpret_cast<f32x4*>(run_state + r * per + e4) = st;
             st = st * g[u] + add[u];
         }
     }
@@ -532,12 +532,12 @@ __global__ __launch_bounds__(256) void run_carry_kernel(const float* carried_in,
 
 hipError_t launch_run_carry(int n_seq, int seg, int dk, int dv, const float* carried_in, float* run_state,
                             const float* run_decay, float* carried_out, bool reverse, hipStream_t stream,
-                            const int* choice, int path)
+                            const int* choice, int path, int keep)
 {
     if (n_seq == 0) return hipSuccess;
     const unsigned blocks = (unsigned)(((size_t)dk * dv / 4 + 255) / 256);
     hipLaunchKernelGGL(run_carry_kernel, dim3(blocks, n_seq), dim3(256), 0, stream, carried_in, run_state, run_decay,
-                       carried_out, seg, static_cast<const int*>(nullptr), 1, dk, dv, reverse ? 1 : 0, choice, path);
+                       carried_out, seg, static_cast<const int*>(nullptr), 1, dk, dv, reverse ? 1 : 0, choice, path, keep);
     return hipGetLastError();
 }
 
@@ -548,7 +548,7 @@ hipError_t launch_run_carry_packed(int B, int H, const int* first_run, int dk, i
     if (B * H == 0) return hipSuccess;
     const unsigned blocks = (unsigned)(((size_t)dk * dv / 4 + 255) / 256);
     hipLaunchKernelGGL(run_carry_kernel, dim3(blocks, B * H), dim3(256), 0, stream, carried_in, run_state, run_decay,
-                       carried_out, 0, first_run, H, dk, dv, reverse ? 1 : 0, choice, path);
+                       carried_out, 0, first_run, H, dk, dv, reverse ? 1 : 0, choice, path, 1);
     return hipGetLastError();
 }
 
