@@ -68,6 +68,34 @@ def test_proj_without_av_and_empty():
     assert err.value.status == 3
 
 
+# The element-wise pass takes 16-byte vectors of aligned arrays and pairs of others: rows of a part, of a
+# batch of loads and of a block of 128, one less and one more.  dx and dW3 follow from the same bf16 values,
+# so they agree bit for bit; the bias gradients are fp32 sums of M terms in another order (M 2^-24 of their sum of moduli).
+@pytest.mark.parametrize("M,d", [(1, 256), (15, 256), (17, 512), (63, 256), (65, 256), (127, 256), (129, 256), (300, 768)])
+def test_proj_bwd_of_unaligned_arrays(M, d):
+    print("\n[proj unaligned] M=%d d=%d" % (M, d), flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(9400 + M)
+    rnd = lambda *n: torch.randn(n, generator=gen, device="cuda").to(torch.bfloat16)
+    x, w3 = rnd(M, d), rnd(3 * d, d)
+    args = [torch.sigmoid(rnd(M, d))] + [rnd(M, d) for _ in range(4)]           # q, av, grad_z, grad_v, grad_q
+    moved = []
+    for t in args:
+        m = torch.empty(M * d + 2, dtype=torch.bfloat16, device="cuda")[2:].view(M, d)
+        m.copy_(t)
+        assert m.data_ptr() % 16 == 4 and t.data_ptr() % 16 == 0
+        moved.append(m)
+    dx, dw, db = binding.hgru2_proj_bwd(x, w3, *args)
+    dx2, dw2, db2 = binding.hgru2_proj_bwd(x, w3, *moved)
+    torch.cuda.synchronize()
+    assert torch.equal(dx, dx2) and torch.equal(dw, dw2)
+    q, av, gz, gv, gq = (t.double() for t in args)
+    sg = torch.sigmoid(av)
+    ref = torch.cat([gz, gv * sg * (1.0 + av * (1.0 - sg)), gq * q * (1.0 - q)], dim=1)
+    bound = (M * 2.0 ** -24 + 2.0 ** -8 + 2.0 ** -18) * ref.abs().sum(0) + 1e-30       # sums; bf16 terms; sigmoid in fp32
+    assert bool(((db.double() - ref.sum(0)).abs() <= bound).all())
+    assert bool(((db.double() - db2.double()).abs() <= 2 * M * 2.0 ** -24 * 1.01 * ref.abs().sum(0) + 1e-30).all())
+
+
 @pytest.mark.parametrize("B,N,d,H", [(2, 200, 256, 2), (1, 333, 512, 4)])
 def test_layer_projection_recurrence_and_reverse_mode(B, N, d, H):
     """Eq. 1 -> Eq. 2 -> Eq. 3: projection, then hgrn2_fwd_gated on its token-major outputs (no copy in
