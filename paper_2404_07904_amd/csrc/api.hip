@@ -168,10 +168,13 @@ struct BwdLayout {
     size_t total() const { return states + fwd_run_state + fwd_run_decay + tail_state + tail_decay + bound0 + partials; }
 };
 
-BwdLayout bwd_layout(const SeqDims& d, bool gated, bool states_given = false)
+constexpr size_t kScratchBytes = (size_t)32 << 20;      // the array inside the library that hgrn2_bwd_noalloc works in
+constexpr size_t kAutoHead = 256;         // chunk length chosen on the device: the flags, at the head of the workspace (ints: flag of 64, flag of 32)
+
+BwdLayout bwd_layout(const SeqDims& d, bool gated, bool states_given = false, bool one_per_unit = false)
 {
     BwdLayout l;
-    l.plan = plan_bwd_fused(d);
+    l.plan = plan_bwd_fused(d, one_per_unit);
     if (!states_given) {
         l.states = round256(state_ws_bytes(d));
         l.fwd_run_state = run_state_bytes(d, false);
@@ -184,6 +187,12 @@ BwdLayout bwd_layout(const SeqDims& d, bool gated, bool states_given = false)
         l.bound0 = round256((size_t)d.BH * d.dk * d.dv * sizeof(float));
     }
     l.partials = gated ? round256(beta_partials_bytes(d)) : 0;
+    // The states of twice as many run boundaries must not push a call out of the array that
+    // hgrn2_bwd_noalloc works in (80 heads of 64, 2552 tokens each: 34 MB against 26 MB).
+    if (!gated && !states_given && !one_per_unit && l.total() > kScratchBytes - kAutoHead) {
+        const BwdLayout fewer = bwd_layout(d, gated, states_given, true);
+        if (fewer.total() <= kScratchBytes) return fewer;
+    }
     return l;
 }
 
@@ -301,7 +310,6 @@ bool fine_mode(const hgrn2_shape* s) { return s && (s->chunk == kFineChunk || s-
 // raise a second flag, on which the third depends: the results are those of the longest chunk the
 // gates allow, at the cost of two launches that do nothing when the gates are ordinary.
 bool auto_mode(const hgrn2_shape* s) { return s && s->chunk == HGRN2_CHUNK_AUTO; }
-constexpr size_t kAutoHead = 256;         // the flags, at the head of the workspace (ints: flag of 64, flag of 32)
 constexpr int kAlternatives = 3;
 
 // the shapes the pass is run on: the caller's, or its three alternatives
@@ -672,7 +680,6 @@ int hgrn2_bwd(const hgrn2_shape* shape, const void* q, const void* f, const void
 // The workspace is a fixed array in device memory that belongs to the library's code object: every
 // GPU the library runs on holds its own copy, at its own address, until the process ends.
 namespace {
-constexpr size_t kScratchBytes = (size_t)32 << 20;
 constexpr int kMaxDevices = 64;
 }
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];

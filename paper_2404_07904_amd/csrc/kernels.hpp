@@ -219,7 +219,9 @@ hipError_t launch_bwd_grad(const SeqDims& d, const void* q, const void* f, const
 // With few runs (light != 0) nothing of that is needed: every workgroup first walks the chunks after
 // its own run from grad_hT, carrying only the state gradient, and the runs are cut at bnd[0..R].
 struct BwdFusedPlan { int R, rc, s_sub, sub_chunks, seg_tail, light, bnd[5]; };
-BwdFusedPlan plan_bwd_fused(const SeqDims& d);
+// one_per_unit: half as many runs for the heads that find two places on a compute unit (fewer run boundaries
+// to keep).
+BwdFusedPlan plan_bwd_fused(const SeqDims& d, bool one_per_unit = false);
 hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void* q, const void* f, const void* v,
                             const void* grad_o, const void* ws_state, const float* grad_hT, float* grad_h0,
                             const float* bound0, const float* run_state, void* grad_q, void* grad_f, void* grad_v,

@@ -236,6 +236,15 @@ def test_gated_workspace_and_error_codes():
     assert lib.hgrn2_cumax(0, 4, None, None, None) == OK
 
 
+@pytest.mark.parametrize("B,H,N,chunk,layout", [(80, 1, 2552, 0, 1), (40, 2, 2552, 0, 0), (1, 29, 1666, -1, 1),
+                                                (96, 1, 612, 16, 0), (66, 1, 380, 8, 0), (2, 8, 11988, 0, 1)])
+def test_heads_of_64_that_the_built_in_workspace_holds(B, H, N, chunk, layout):
+    """The states (8 KB a chunk) and the run boundaries of one run per compute unit fit in 32 MiB; the finer cut
+    that heads of 64 otherwise take would not."""
+    s = shape(B=B, H=H, N=N, dk=64, dv=64, chunk=chunk, layout=layout)
+    assert 0 < binding.hgrn2_bwd_workspace_bytes(s) <= binding.hgrn2_noalloc_workspace_limit()
+
+
 def test_layout_field():
     assert call_fwd(shape(layout=1), ws_bytes=16) == E_WS          # a valid layout gets as far as the workspace check
     assert call_fwd(shape(layout=2)) == E_SHAPE

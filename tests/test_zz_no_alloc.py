@@ -53,6 +53,15 @@ def test_chunk_length_chosen_on_the_device_in_the_built_in_workspace():
         run_pair(910 + k, 2, 3, 200 - 30 * k, 128, 128, chunk=-1, small_gates=small)
 
 
+def test_heads_of_64_whose_finest_cut_would_not_fit():
+    """Two runs per compute unit would keep 38 and 36 MB of states here (the limit is 32 MiB): half as many are
+    walked; N = 2552 and 1666 are no multiples of the chunk."""
+    for seed, B, H, N, layout, chunk in ((920, 40, 2, 2552, binding.HGRN2_LAYOUT_BNHD, 0),
+                                         (921, 1, 29, 1666, binding.HGRN2_LAYOUT_BHND, -1)):
+        print("\n  B=%d H=%d N=%d heads of 64, chunk %d" % (B, H, N, chunk), flush=True)
+        run_pair(seed, B, H, N, 64, 64, layout=layout, chunk=chunk)
+
+
 def test_limit_is_enforced_before_any_launch():
     limit = binding.hgrn2_noalloc_workspace_limit()
     assert limit == 32 << 20
