@@ -208,10 +208,15 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
             // the sequence that holds chunk p0 (ENDS: the span's last chunk): the last one with at most
             // that many chunks before it
             const int at = ENDS ? p1 - 1 : p0;
+            // (64 table entries a step, one per lane: every step waits for memory before the first chunk is
+            // requested; against a bisection, 32 sequences of 512 tokens 75.8 -> 74.5 us, 256 of 64 96.7 -> 95.0)
             int lo = 0, hi = p.lay.B;        // invariant: before[lo] <= at < before[hi]
             while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (table_read(t_before, mid) <= at) lo = mid; else hi = mid;
+                const int stride = (hi - lo + 63) >> 6, i = lo + ((int)(threadIdx.x & 63) + 1) * stride;
+                const bool below = i < hi && t_before[i] <= at;
+                const int c = __builtin_amdgcn_readfirstlane(__popcll(__ballot(below)));
+                hi = min(hi, lo + (c + 1) * stride);
+                lo += c * stride;
             }
             cur_e = lo;
             const int before = table_read(t_before, lo);
