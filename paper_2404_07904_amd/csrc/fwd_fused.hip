@@ -51,8 +51,6 @@
 
 namespace hgrn2 {
 
-constexpr int kMaxFwdRuns = 16;
-
 struct FwdFusedParams {
     const void* q;
     const void* f;
@@ -67,10 +65,10 @@ struct FwdFusedParams {
     TokenLayout lay;     // used when dense == 0
     int dense;           // sequence tensors are [B][H][N][d]: token strides are the compile-time dk, dv
     int* flag;           // null, or set to 1 when a gate product falls below the floor of the reciprocals
-    // Runs of a sequence.  R > 0: run r of sequence s is chunks bnd[r] .. bnd[r + 1] - 1 and the workgroup
+    // Runs of a sequence.  R > 0: run r of sequence s is chunks cuts.bnd[r] .. bnd[r + 1] - 1 and the workgroup
     // numbered s R + r takes it, after a light walk over the chunks before it.
     int R;
-    short bnd[kMaxFwdRuns + 1];
+    FwdCuts cuts;
     // Otherwise (TokenLayout::seg > 1), with `run_add` set: the state entering run r of sequence s is
     //   Diag(decay_{r-1}) ( ... Diag(decay_0) h0[s] + add_0 ... ) + add_{r-1},
     // run_add [s (seg - 1) + j][dk][dv], run_decay [s (seg - 1) + j][dk], j = 0 .. seg - 2.
@@ -232,7 +230,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         if constexpr (ENDS) { if (!DENSE && p.lay.vl) ends_slot = bh; }
         sv = seq_view<DENSE, DK, DV, true>(p.lay, p.N, p.NC, bh);
         NC = sv.NC;
-        if (RUNS && n_run > 1) { n0 = p.bnd[run]; NC = p.bnd[run + 1] - n0; }
+        if (RUNS && n_run > 1) { n0 = p.cuts.bnd[run]; NC = p.cuts.bnd[run + 1] - n0; }
         head = bh / p.lay.seg % p.H;
     }
     // the sequence whose entries of h0 and hT the walk starts from and ends in
@@ -957,74 +955,10 @@ static FwdFusedParams fused_params(const SeqDims& d, const void* q, const void* 
     return p;
 }
 
-// Cost of a chunk of a light walk in chunks of the walk proper (measured: 1.0 us against 2.0 us in the
-// 128 x 64 variant, and less next to other workgroups that stream).
-constexpr double kLightCost = 0.42;
-
-// Runs with a light walk each: the cuts that let all of them finish together,
-// len_r + rho start_r = T for every run r, so that start_{r+1} = T + (1 - rho) start_r.
-static void fused_cuts(int NC, int R, short (&bnd)[kMaxFwdRuns + 1])
-{
-    const double rho = 0.33;         // (below the cost: the last run, with the longest light walk, has one chunk anyway)
-    double sum = 0.0, x = 1.0;
-    for (int r = 0; r < R; ++r) { sum += x; x *= 1.0 - rho; }
-    const double T = NC / sum;
-    double end = 0.0;
-    bnd[0] = 0;
-    for (int r = 1; r < R; ++r) {
-        end = T + (1.0 - rho) * end;
-        int b = (int)(end + 0.5);
-        if (b < bnd[r - 1] + 1) b = bnd[r - 1] + 1;
-        if (b > NC - (R - r)) b = NC - (R - r);
-        bnd[r] = (short)b;
-    }
-    bnd[R] = (short)NC;
-}
-
 FwdRuns plan_fwd_runs(const SeqDims& d)
 {
-    FwdRuns r;
-    r.run_chunks = d.NC;
-    if (!d.io_bf16 || d.packed || d.BH == 0 || d.NC < 2) return r;
-    // The candidates and what they take, in chunks of the 64-column variants (2 us each), fitted to runs of
-    // 1 to 128 heads of 128 and 64 and 2 to 256 chunks; the start-up they share is left out.  "halves": two
-    // workgroups per run, each half of dv (the only way for 64 x 128 heads, no way for dv = 64); "whole": twice
-    // the runs, whose chunks take 1.5 to 1.6 times as long.  Beyond 256 workgroups nothing gains: heads of 64
-    // find two places on a compute unit, but two runs there slow each other down as much (256 heads of 2000
-    // tokens: 70 us, in two runs each 73 us).
-    //   light walks (all runs finish together):  NC rho / (1 - (1 - rho)^R)
-    //   walks from zero: the second launch and the states in between cost as much as 5 to 9 chunks
-    // e.g. 16 heads, 13 chunks: 27.9 us with 8 light walks (halves), 31 us whole, 28.8 us from zero;
-    // 32 heads: 32 chunks 40 / 41.5 us (light / from zero), 64 chunks 65 us from zero in halves, 256 chunks
-    // 209 us in halves, 182 us whole; 64 heads whole, 16 / 32 / 64 chunks: 30.5 / 52 / 96 us light, 39 / 55 / 91 us from zero.
-    double best = d.NC;                                  // one run (128 x 128: in halves up to 128 heads)
-    if (d.dk == 128 && d.dv == 128 && d.BH > 128) return r;
-    auto consider = [&](int places, double light_factor, double ends_cost, double per_chunk) {
-        int R = places / d.BH;
-        if (R > kMaxFwdRuns) R = kMaxFwdRuns;
-        if (R > d.NC) R = d.NC;
-        if (R >= 2) {
-            double keep = 1.0;
-            for (int i = 0; i < R; ++i) keep *= 1.0 - kLightCost;
-            const double t = light_factor * d.NC * kLightCost / (1.0 - keep);
-            if (t < best) { best = t; r.light = R; r.seg = 1; r.run_chunks = d.NC; }
-        }
-        int seg = places / d.BH;
-        if (seg > d.NC / 3) seg = d.NC / 3;              // at least three chunks each
-        if (seg >= 2) {
-            const double t = ends_cost + per_chunk * d.NC / seg;
-            if (t < best) {
-                best = t;
-                r.light = 1;
-                r.run_chunks = (d.NC + seg - 1) / seg;
-                r.seg = (d.NC + r.run_chunks - 1) / r.run_chunks;
-            }
-        }
-    };
-    const bool halves = d.dv == 128;
-    consider(halves ? 128 : 256, 1.1, 5.0, 1.5);
-    if (d.dk == 128 && halves) consider(256, 1.47, 9.0, 2.2);
-    return r;
+    if (!d.io_bf16 || d.packed) { FwdRuns r; r.run_chunks = d.NC; return r; }
+    return plan_fwd_runs(d.BH, d.NC, d.dk, d.dv);
 }
 
 hipError_t launch_fwd_fused(const SeqDims& d, const void* q, const void* f, const void* v, const float* h0,
@@ -1036,7 +970,7 @@ hipError_t launch_fwd_fused(const SeqDims& d, const void* q, const void* f, cons
     p.h0 = h0; p.o = o; p.hT = hT; p.save = save_states;
     if (light_runs > 1) {
         p.R = light_runs;
-        fused_cuts(d.NC, p.R, p.bnd);
+        fused_cuts(d.NC, p.R, &p.cuts);
     }
     p.run_add = const_cast<float*>(run_add); p.run_decay = const_cast<float*>(run_decay);
     return launch_fused_dims(d, p, fused_grouped(d) ? d.lay.spans * d.lay.H : d.BH, false, stream);

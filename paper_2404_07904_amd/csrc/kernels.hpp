@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "fwd_plan.hpp"
+
 namespace hgrn2 {
 
 // Compile-time chunk length of the chunkwise kernels.
@@ -177,11 +179,7 @@ hipError_t launch_fwd_out(const SeqDims& d, const void* q, const void* f, const 
 // Fused forward (state recurrence + read-out in one pass, states never leave the chip); only for
 // the storage fwd_fused_supported() accepts (bf16).
 bool fwd_fused_supported(const SeqDims& d);
-// How the fused forward walk of an equal-length batch cuts its sequences.  light > 1: into that many
-// runs, each of whose workgroups finds the state it starts from by a light walk of its own over the
-// chunks before the run.  seg > 1: into runs of run_chunks chunks (TokenLayout::seg), whose entering
-// states launch_run_ends provides.
-struct FwdRuns { int light = 1, seg = 1, run_chunks = 0; };
+// (fwd_plan.hpp; a packed batch and fp32 storage are not cut this way)
 FwdRuns plan_fwd_runs(const SeqDims& d);
 // What every run of segmented sequences (TokenLayout::seg, or the entries of a run table) adds to the
 // state from zero, run_add [slot][dk][dv], and the product of its gates, run_decay [slot][dk]; only
