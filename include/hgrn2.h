@@ -116,7 +116,10 @@ size_t hgrn2_bwd_workspace_bytes(const hgrn2_shape* shape);
  *   q, f, v   in   device, read-only
  *   h0        in   device fp32 [B][H][dk][dv], or NULL for a zero initial state
  *   o         out  device [B][H][N][dv], io_dtype
- *   hT        out  device fp32 [B][H][dk][dv] final state S_N, or NULL if not wanted
+ *   hT        out  device fp32 [B][H][dk][dv] final state S_N, or NULL if not wanted.  May be h0 itself (a
+ *                  state continued in place) unless chunk = HGRN2_CHUNK_AUTO, whose later alternatives start
+ *                  from h0 again; the forward calls must not be given buffers that overlap otherwise.
+ *                  In place, few sequences are spread over fewer compute units
  *   workspace      device scratch of at least hgrn2_fwd_workspace_bytes(shape) bytes, 256-byte
  *                  aligned; contents on entry are ignored, contents on return are unspecified
  */
@@ -132,7 +135,8 @@ int hgrn2_fwd(const hgrn2_shape* shape, const void* q, const void* f, const void
  *   grad_hT   in   device fp32 [B][H][dk][dv], or NULL for zero
  *   grad_q, grad_f, grad_v   out  device, io_dtype.  grad_f is the gradient w.r.t. the gate f
  *             INCLUDING the tied path k = 1 - f, so callers never see k or its gradient.
- *   grad_h0   out  device fp32 [B][H][dk][dv], or NULL if not wanted
+ *   grad_h0   out  device fp32 [B][H][dk][dv], or NULL if not wanted.  May be grad_hT itself (equal-length
+ *             batches, chunk other than HGRN2_CHUNK_AUTO): a sequence is then walked by one workgroup
  *   workspace as for hgrn2_fwd, sized by hgrn2_bwd_workspace_bytes(shape)
  */
 int hgrn2_bwd(const hgrn2_shape* shape, const void* q, const void* f, const void* v,

@@ -171,10 +171,10 @@ struct BwdLayout {
 constexpr size_t kScratchBytes = (size_t)32 << 20;      // the array inside the library that hgrn2_bwd_noalloc works in
 constexpr size_t kAutoHead = 256;         // chunk length chosen on the device: the flags, at the head of the workspace (ints: flag of 64, flag of 32)
 
-BwdLayout bwd_layout(const SeqDims& d, bool gated, bool states_given = false, bool one_per_unit = false)
+BwdLayout bwd_layout(const SeqDims& d, bool gated, bool states_given = false, int places = 0)
 {
     BwdLayout l;
-    l.plan = plan_bwd_fused(d, one_per_unit);
+    l.plan = plan_bwd_fused(d, places);
     if (!states_given) {
         l.states = round256(state_ws_bytes(d));
         l.fwd_run_state = run_state_bytes(d, false);
@@ -189,12 +189,17 @@ BwdLayout bwd_layout(const SeqDims& d, bool gated, bool states_given = false, bo
     l.partials = gated ? round256(beta_partials_bytes(d)) : 0;
     // The states of twice as many run boundaries must not push a call out of the array that
     // hgrn2_bwd_noalloc works in (80 heads of 64, 2552 tokens each: 34 MB against 26 MB).
-    if (!gated && !states_given && !one_per_unit && l.total() > kScratchBytes - kAutoHead) {
-        const BwdLayout fewer = bwd_layout(d, gated, states_given, true);
+    if (!gated && !states_given && places == 0 && l.total() > kScratchBytes - kAutoHead) {
+        const BwdLayout fewer = bwd_layout(d, gated, states_given, kOnePerUnit);
         if (fewer.total() <= kScratchBytes) return fewer;
     }
     return l;
 }
+
+// A state gradient continued in place (grad_h0 is grad_hT): the runs of a sequence all start from grad_hT,
+// directly or through the carry, and the first run writes grad_h0, at no fixed time.  A sequence is one run
+// then (whose workgroup reads every element before it writes it), and the plan needs less room than the usual one.
+int bwd_places(const float* grad_hT, const float* grad_h0) { return grad_h0 && grad_h0 == grad_hT ? 1 : 0; }
 
 // A packed batch is cut the way an equal-length batch of its mean sequence length would be (the
 // host does not know the lengths): runs of `run_chunks` chunks (0: not cut), at most `R` of them.
@@ -452,14 +457,24 @@ static int fwd_one(const hgrn2_shape* shape, const void* q, const void* f, const
         return !save_states || !has_tokens ||
                launch_sweep(d, kSweepStateBwd, nullptr, f, v, h0, nullptr, save_states, nullptr, stream) == hipSuccess;
     };
+    // A state continued in place (hT is h0): whoever reads an element of h0 has to be who writes it, or to be
+    // done before.  That holds for a sequence walked by one workgroup (or one per slab of columns) and for the
+    // carry kernel, not where several workgroups of a sequence start from h0: such calls are cut another way.
+    const bool in_place = h0 && h0 == hT;
     float* run_state = reinterpret_cast<float*>(static_cast<char*>(workspace) + one);
     float* run_decay = reinterpret_cast<float*>(reinterpret_cast<char*>(run_state) + fwd_run_state_bytes(d));
     if (fwd_fused_supported(d)) {
-        const FwdRuns fr = plan_fwd_runs(d);
+        const FwdRuns fr = plan_fwd_runs(d, !in_place);
+        if (in_place && fr.seg > 1) {
+            // (the runs need not be the ones the workspace is sized for; their states, 4 dk dv bytes for three
+            // chunks or more, take the place of the chunk states, 2 dk dv bytes each, which this pass does not write)
+            run_state = static_cast<float*>(workspace);
+            run_decay = run_state + (size_t)d.BH * fr.seg * d.dk * d.dv;
+        }
         if (fr.seg <= 1)
             return launch_fwd_fused(d, q, f, v, h0, o, hT, save_states, stream, fr.light) == hipSuccess ? HGRN2_OK : HGRN2_ERR_HIP;
         const SeqDims r = as_runs(d, fr.seg, fr.run_chunks);
-        if (fr.seg <= kInlineCarryRuns) {
+        if (fr.seg <= kInlineCarryRuns && !in_place) {
             // the runs' workgroups add up what the runs before theirs have left
             return launch_run_ends(r, fr.seg - 1, q, f, v, run_state, run_decay, stream) == hipSuccess &&
                    launch_fwd_fused(r, q, f, v, h0, o, hT, save_states, stream, 1, run_state, run_decay) == hipSuccess
@@ -470,7 +485,9 @@ static int fwd_one(const hgrn2_shape* shape, const void* q, const void* f, const
                launch_fwd_fused(r, q, f, v, run_state, o, nullptr, save_states, stream) == hipSuccess
                    ? HGRN2_OK : HGRN2_ERR_HIP;
     }
-    if (has_tokens && out_from_contributions(d)) {
+    // (before the state they start from may be replaced)
+    if (!save_by_sweep()) return HGRN2_ERR_HIP;
+    if (has_tokens && out_from_contributions(d) && !in_place) {
         // every chunk from zero at once; the place of the last chunk's contribution, which nobody adds,
         // holds the gate products of the others
         float* add = static_cast<float*>(workspace);
@@ -478,7 +495,7 @@ static int fwd_one(const hgrn2_shape* shape, const void* q, const void* f, const
         float* decay = add + (size_t)(d.NC - 1) * d.dk * d.dv;
         const SeqDims r = as_runs(d, d.NC, 1);
         return (d.NC == 1 || launch_sweep(r, kSweepStateFwd, q, f, v, nullptr, add, nullptr, decay, stream, stride) == hipSuccess) &&
-               launch_fwd_out_add(d, q, f, v, add, decay, stride, h0, o, hT, stream) == hipSuccess && save_by_sweep()
+               launch_fwd_out_add(d, q, f, v, add, decay, stride, h0, o, hT, stream) == hipSuccess
                    ? HGRN2_OK : HGRN2_ERR_HIP;
     }
     int run_chunks;
@@ -489,12 +506,12 @@ static int fwd_one(const hgrn2_shape* shape, const void* q, const void* f, const
             launch_run_carry(d.BH, seg, d.dk, d.dv, h0, run_state, run_decay, hT, false, stream, d.lay.choice, d.lay.path) != hipSuccess)
             return HGRN2_ERR_HIP;
         if (launch_sweep(r, kSweepStateFwd, q, f, v, run_state, nullptr, workspace, nullptr, stream) != hipSuccess ||
-            launch_fwd_out(d, q, f, v, workspace, o, stream) != hipSuccess || !save_by_sweep())
+            launch_fwd_out(d, q, f, v, workspace, o, stream) != hipSuccess)
             return HGRN2_ERR_HIP;
         return HGRN2_OK;
     }
     if (launch_sweep(d, kSweepStateFwd, q, f, v, h0, hT, workspace, nullptr, stream) != hipSuccess) return HGRN2_ERR_HIP;
-    if (launch_fwd_out(d, q, f, v, workspace, o, stream) != hipSuccess || !save_by_sweep()) return HGRN2_ERR_HIP;
+    if (launch_fwd_out(d, q, f, v, workspace, o, stream) != hipSuccess) return HGRN2_ERR_HIP;
     return HGRN2_OK;
 }
 
@@ -566,7 +583,7 @@ static int bwd_impl(const hgrn2_shape* shape, const void* q, const void* f, cons
     bool one_reduction = gated && (size_t)shape->B * shape->H * shape->N > 0;
     for (int i = 0; i < kAlternatives; ++i) {
         if (check_shape(&alt[i], true, &dims[i], false, true) != HGRN2_OK) one_reduction = false;
-        else one_reduction = one_reduction && reduce_beta_once(BetaRows{nullptr, shape->B, plan_bwd_fused(dims[i]).R});
+        else one_reduction = one_reduction && reduce_beta_once(BetaRows{nullptr, shape->B, plan_bwd_fused(dims[i], bwd_places(grad_hT, grad_h0)).R});
     }
     for (int i = 0; i < kAlternatives; ++i) {
         a.beta_rows = one_reduction ? &rows[i] : nullptr;
@@ -601,7 +618,7 @@ static int bwd_one(const hgrn2_shape* shape, const void* q, const void* f, const
     if (gated && (size_t)shape->H * d.dk > 0 && (!grad_beta || (has_tokens && !beta))) return HGRN2_ERR_NULL;
     d.beta = gated ? beta : nullptr;
     if (alt) { d.lay.choice = alt->choice; d.lay.path = alt->path; d.lay.alt = alt->choice2; d.lay.alt_path = alt->path2; d.domain_flag = alt->flag; }
-    const BwdLayout l = bwd_layout(d, gated, saved_states != nullptr);
+    const BwdLayout l = bwd_layout(d, gated, saved_states != nullptr, bwd_places(grad_hT, grad_h0));
     const size_t need = l.total();
     if (need > 0 && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255))) return HGRN2_ERR_WORKSPACE;
     if (alt && alt->validate_only) return HGRN2_OK;
@@ -878,6 +895,8 @@ static int fwd_varlen_one(const hgrn2_shape* shape, const int32_t* cu_seqlens, c
             return HGRN2_ERR_HIP;
         return HGRN2_OK;
     }
+    // (spans that start inside a sequence all read its h0: a state continued in place takes a workgroup per sequence)
+    if (h0 && h0 == hT) d.lay.spans = 0;
     if (fwd_fused_supported(d)) {
         const size_t add = span_add_bytes(shape, d);
         if (spans_from_ends(shape, d, one)) {

@@ -1157,7 +1157,7 @@ static hipError_t launch_fused_one(const SeqDims& d, const BwdGradParams& p, hip
     return hipGetLastError();
 }
 
-BwdFusedPlan plan_bwd_fused(const SeqDims& d, bool one_per_unit)
+BwdFusedPlan plan_bwd_fused(const SeqDims& d, int places)
 {
     // One workgroup per run and one run per compute unit (heads of 64: two) at a time: as many runs per
     // sequence as it takes to fill the chip, but at least four chunks each.  The zero-start sweep that supplies the
@@ -1165,7 +1165,7 @@ BwdFusedPlan plan_bwd_fused(const SeqDims& d, bool one_per_unit)
     BwdFusedPlan pl;
     pl.light = 0;
     for (int i = 0; i <= kMaxLightRuns; ++i) pl.bnd[i] = 0;
-    const int places = fused_waves(d.dk, d.dv, d.io_bf16) == 4 && !one_per_unit ? 512 : 256;      // workgroups that run at once
+    if (places == 0) places = fused_waves(d.dk, d.dv, d.io_bf16) == 4 ? 512 : kOnePerUnit;      // workgroups that run at once
     int R = d.BH > 0 ? places / d.BH : 1;
     if (R > d.NC / 4) R = d.NC / 4;
     if (R < 1) R = 1;

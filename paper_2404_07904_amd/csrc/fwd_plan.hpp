@@ -40,7 +40,9 @@ inline void fused_cuts(int NC, int R, FwdCuts* cuts)
     bnd[R] = NC;
 }
 
-inline FwdRuns plan_fwd_runs(int BH, int NC, int dk, int dv)
+// light_walks = false: no light walks (whose workgroups all read the sequence's initial state, while one of
+// them writes the final one: not for a state that is continued in place).
+inline FwdRuns plan_fwd_runs(int BH, int NC, int dk, int dv, bool light_walks = true)
 {
     FwdRuns r;
     r.run_chunks = NC;
@@ -56,20 +58,20 @@ inline FwdRuns plan_fwd_runs(int BH, int NC, int dk, int dv)
     // e.g. 16 heads, 13 chunks: 27.9 us with 8 light walks (halves), 31 us whole, 28.8 us from zero;
     // 32 heads: 32 chunks 40 / 41.5 us (light / from zero), 64 chunks 65 us from zero in halves, 256 chunks
     // 209 us in halves, 182 us whole; 64 heads whole, 16 / 32 / 64 chunks: 30.5 / 52 / 96 us light, 39 / 55 / 91 us from zero.
-    double best = NC;                                  // one run (128 x 128: in halves up to 128 heads)
+    double best = NC;                                    // one run (128 x 128: in halves up to 128 heads)
     if (dk == 128 && dv == 128 && BH > 128) return r;
     auto consider = [&](int places, double light_factor, double ends_cost, double per_chunk) {
         int R = places / BH;
         if (R > kMaxFwdRuns) R = kMaxFwdRuns;
         if (R > NC) R = NC;
-        if (R >= 2) {
+        if (light_walks && R >= 2) {
             double keep = 1.0;
             for (int i = 0; i < R; ++i) keep *= 1.0 - kLightCost;
             const double t = light_factor * NC * kLightCost / (1.0 - keep);
             if (t < best) { best = t; r.light = R; r.seg = 1; r.run_chunks = NC; }
         }
         int seg = places / BH;
-        if (seg > NC / 3) seg = NC / 3;              // at least three chunks each
+        if (seg > NC / 3) seg = NC / 3;                  // at least three chunks each
         if (seg >= 2) {
             const double t = ends_cost + per_chunk * NC / seg;
             if (t < best) {

@@ -180,7 +180,7 @@ hipError_t launch_fwd_out(const SeqDims& d, const void* q, const void* f, const 
 // the storage fwd_fused_supported() accepts (bf16).
 bool fwd_fused_supported(const SeqDims& d);
 // (fwd_plan.hpp; a packed batch and fp32 storage are not cut this way)
-FwdRuns plan_fwd_runs(const SeqDims& d);
+FwdRuns plan_fwd_runs(const SeqDims& d, bool light_walks = true);
 // What every run of segmented sequences (TokenLayout::seg, or the entries of a run table) adds to the
 // state from zero, run_add [slot][dk][dv], and the product of its gates, run_decay [slot][dk]; only
 // the first ends_per_seq runs of each sequence, slot = sequence * ends_per_seq + run.  Packed batch with
@@ -217,9 +217,10 @@ hipError_t launch_bwd_grad(const SeqDims& d, const void* q, const void* f, const
 // With few runs (light != 0) nothing of that is needed: every workgroup first walks the chunks after
 // its own run from grad_hT, carrying only the state gradient, and the runs are cut at bnd[0..R].
 struct BwdFusedPlan { int R, rc, s_sub, sub_chunks, seg_tail, light, bnd[5]; };
-// one_per_unit: half as many runs for the heads that find two places on a compute unit (fewer run boundaries
-// to keep).
-BwdFusedPlan plan_bwd_fused(const SeqDims& d, bool one_per_unit = false);
+// places: the workgroups the runs are to fill (0: as many as run at once; kOnePerUnit: half as many for the
+// heads that find two places on a compute unit, fewer run boundaries to keep; 1: sequences are not cut).
+constexpr int kOnePerUnit = 256;
+BwdFusedPlan plan_bwd_fused(const SeqDims& d, int places = 0);
 hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void* q, const void* f, const void* v,
                             const void* grad_o, const void* ws_state, const float* grad_hT, float* grad_h0,
                             const float* bound0, const float* run_state, void* grad_q, void* grad_f, void* grad_v,

@@ -13,9 +13,9 @@ SHIM = """
 using namespace hgrn2;
 extern "C" int max_runs() { return kMaxFwdRuns; }
 // out: light, seg, run_chunks, then the light runs' cuts
-extern "C" void plan(int BH, int NC, int dk, int dv, int* out)
+extern "C" void plan(int BH, int NC, int dk, int dv, int light_walks, int* out)
 {
-    const FwdRuns r = plan_fwd_runs(BH, NC, dk, dv);
+    const FwdRuns r = plan_fwd_runs(BH, NC, dk, dv, light_walks != 0);
     out[0] = r.light; out[1] = r.seg; out[2] = r.run_chunks;
     FwdCuts c = {};
     if (r.light > 1) fused_cuts(NC, r.light, &c);
@@ -42,7 +42,7 @@ def test_cuts_rise_and_cover_every_chunk(lib, dk, dv):
         for NC in [*range(1, 70), 127, 256, 511, 4095, 32766, 32767, 32768, 40000, 65535, 65536, 65540, 70000, 1 << 20, most - 1, most]:
             if NC > most:
                 continue
-            lib.plan(BH, NC, dk, dv, out)
+            lib.plan(BH, NC, dk, dv, 1, out)
             light, seg, run_chunks, bnd = out[0], out[1], out[2], list(out)[3:]
             case = (BH, NC, dk, dv, light, seg, run_chunks, bnd)
             assert 1 <= light <= runs and 1 <= seg <= max(1, NC) and (light == 1 or seg == 1), case
@@ -51,3 +51,10 @@ def test_cuts_rise_and_cover_every_chunk(lib, dk, dv):
                 assert cuts[0] == 0 and cuts[-1] == NC and all(a < b for a, b in zip(cuts, cuts[1:])), case
             if seg > 1:
                 assert (seg - 1) * run_chunks < NC <= seg * run_chunks, case
+            # a state continued in place: no light walks, and the runs' states (fp32, with their gate products)
+            # fit the room of the chunk states (bf16)
+            lib.plan(BH, NC, dk, dv, 0, out)
+            light, seg, run_chunks = out[0], out[1], out[2]
+            case = (BH, NC, dk, dv, light, seg, run_chunks)
+            assert light == 1 and seg >= 1 and (seg - 1) * run_chunks < NC <= seg * run_chunks, case
+            assert seg == 1 or seg * (4 * dk * dv + 4 * dk) <= NC * 2 * dk * dv, case
