@@ -98,8 +98,9 @@ template <int DK_, int DVW_> struct FwdFusedLds {
     static constexpr size_t tot = ost + (size_t)C * PO * 2;             // [8][DK] fp32 block totals + one row of ones
     static constexpr size_t ca = tot + (size_t)(kRowBlocks + 1) * DK * 4;    // [DK] fp32 state rescale
     static constexpr size_t ch = ca + (size_t)DK * 4;                   // [DK] fp32 h of the chunk before (grouped walks)
-    static constexpr size_t total = ch + (size_t)DK * 4;
-    static_assert(total <= 160 * 1024, "LDS budget of one workgroup");
+    static constexpr size_t cr = ch + (size_t)DK * 4;                   // [DK] fp32 r of a chunk that ends its sequence
+    static constexpr size_t total = cr + (size_t)DK * 4;
+    static_assert(total * (8 / NW) <= 160 * 1024, "LDS budget of the workgroups of a compute unit");
     // light walk (the same memory, before the walk proper)
     static constexpr size_t lk = 0;                                     // K^^T  [2][DK][PT]
     static constexpr size_t lv = lk + (size_t)2 * DK * PT * 2;          // V     [2][C][PV]
@@ -125,7 +126,13 @@ struct FusedChunk {
 // a single pass of its own; without it the chunk loop always takes an even number of passes (a pass
 // over a chunk past the end sees gates equal to one and is an exact no-op), which costs short odd walks
 // a pass and saves long ones registers (128 sequences of 2048 tokens: 92.4 against 95.9 us).
-template <int DK, int DV, int DVW, bool GATE_BF16, bool DENSE, bool GROUPED, bool ENDS, bool RUNS = true>
+// EXACT_END: the state a sequence ends in is wanted.  It is used on (decoding starts from it), and most of it is
+// what the last few tokens add, whose 1 - f is exact in bf16 for bf16 gates of 0.5 and more, but K~ = (1 - f) G_m / G
+// is not.  The products of a sequence's last chunk are therefore factored around G_m r instead of G_m, with
+// r = h 2^-e in [1, 2): Q~ / r, K~ r, r G_m S_n, and 2^e for h.  K~ r is the product of the later gates times a power of
+// two, so that it rounds as K^ = k prod_{s > j} f_s does (error of the final state against 64 bits, 32 heads of 1024
+// tokens, gates from 0.5 to 1: 1.66e-3 -> 1.27e-3; 0.5 us a call, which calls without hT do not pay).
+template <int DK, int DV, int DVW, bool GATE_BF16, bool DENSE, bool GROUPED, bool ENDS, bool RUNS = true, bool EXACT_END = false>
 __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
 {
     static_assert(!(DENSE && GROUPED), "spans are a feature of packed batches");
@@ -162,6 +169,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     float* tot = reinterpret_cast<float*>(smem + L::tot);
     float* cA = reinterpret_cast<float*>(smem + L::ca);
     float* cH = reinterpret_cast<float*>(smem + L::ch);
+    float* cR = reinterpret_cast<float*>(smem + L::cr);
 
     if (not_chosen(p.lay)) return;       // one of several chunk lengths, and not the one called for
     // workgroup -> (sequence, run, dv half): ids 8 apart land on the same XCD (ids are dealt to the 8
@@ -492,8 +500,11 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         }
         *reinterpret_cast<f32x2*>(tot + rb * DK + 2 * cl) = f32x2{bt0, bt1};
     };
+    // x = significand(x) power_of_two(x) for normal numbers (h is 2^-100 to 1 in the gate domain)
+    auto significand = [](float x) { return __uint_as_float((__float_as_uint(x) & 0x7fffffu) | 0x3f800000u); };
+    auto power_of_two = [](float x) { return __uint_as_float(__float_as_uint(x) & 0xff800000u); };
     // Second half: block factors from the exchanged totals, tiles to LDS.
-    auto prep_tiles = [&](int c, bool starts_sequence) {      // c: only its parity matters (which tile buffer)
+    auto prep_tiles = [&](int c, bool starts_sequence, bool ends) {      // c: only its parity matters (which tile buffer)
         // product of the (at most three) block totals between this block and the reference row;
         // an absent factor reads the row of ones
         const float* ones = tot + kRowBlocks * DK;
@@ -507,8 +518,20 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         const float R0 = fast_rcp(fmaxf(mid0 * bt0, kTinyProduct));
         const float R1 = fast_rcp(fmaxf(mid1 * bt1, kTinyProduct));
         below_floor = fminf(below_floor, fminf(mid0 * bt0, mid1 * bt1));
-        const float sa0 = after ? mid0 : R0, sa1 = after ? mid1 : R1;       // multiplies q a
-        const float sz0 = after ? R0 : mid0, sz1 = after ? R1 : mid1;       // multiplies k z
+        float sa0 = after ? mid0 : R0, sa1 = after ? mid1 : R1;             // multiplies q a
+        float sz0 = after ? R0 : mid0, sz1 = after ? R1 : mid1;             // multiplies k z
+        if (EXACT_END && ends) {
+            f32x2 h = {1.0f, 1.0f};
+#pragma unroll
+            for (int i = kRowBlocks / 2; i < kRowBlocks; ++i) {
+                const f32x2 t = *reinterpret_cast<const f32x2*>(tot + i * DK + 2 * cl);
+                h.x *= t.x; h.y *= t.y;
+            }
+            const float e0 = significand(h.x), e1 = significand(h.y);
+            sz0 *= e0; sz1 *= e1;
+            sa0 *= fast_rcp(e0); sa1 *= fast_rcp(e1);
+            if (rb == 0) *reinterpret_cast<f32x2*>(cR + 2 * cl) = f32x2{e0, e1};
+        }
         // Q~: row-major, channel pair (2l, 2l+1) at column position sigma(2l) (bits 2 and 3 swapped);
         // K~^T: this thread's 8 tokens of each of its two channels as one 16-byte vector
         const int qcol = ((2 * cl) & ~12) | (((2 * cl) & 4) << 1) | (((2 * cl) & 8) >> 1);
@@ -536,6 +559,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
             }
             *reinterpret_cast<f32x2*>(cA + 2 * cl) = f32x2{hprev0 * gm0, hprev1 * gm1};
             hprev0 = (t[4].x * t[5].x) * (t[6].x * t[7].x); hprev1 = (t[4].y * t[5].y) * (t[6].y * t[7].y);
+            if (EXACT_END && ends) { hprev0 = power_of_two(hprev0); hprev1 = power_of_two(hprev1); }
         }
     };
 
@@ -674,7 +698,10 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     prep_gates(rawf[0], rawq[0], chunk_rel(0, 0));
     load_f(rawf[0], chunk_rel(0, 2)); load_q(rawq[0], chunk_rel(0, 2));
     __syncthreads();
-    prep_tiles(0, true);
+    // whether chunk n + rel of the walk ends its sequence and the state is wanted
+    const bool ends_here = EXACT_END && !GROUPED && (!RUNS || (p.run_add ? bh - whole * p.lay.seg == p.lay.seg - 1 : run == n_run - 1));
+    auto ends = [&](int n, int rel) { return GROUPED ? ck[rel + 1].last != 0 : (ends_here && n + rel == NC - 1); };
+    prep_tiles(0, true, ends(0, 0));
     __syncthreads();
 
     // output tile accumulator, transposed: accO[v] = O[token 32 rt + r32][channel 32 bt + 8 (v/4) + 4 g + v%4]
@@ -752,17 +779,21 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
             if (ck[1].first && n > 0 && ck[1].N > 0) initial_state(ck[1].bh);
         }
         // G_m(n) S_n = c(n) * accumulators, published as the bf16 operand of the read-out
-        scale_state(cA);
+        auto publish = [&]() {
 #pragma unroll
-        for (int j = 0; j < NST; ++j) {
+            for (int j = 0; j < NST; ++j) {
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                float x[8];
+                for (int half = 0; half < 2; ++half) {
+                    float x[8];
 #pragma unroll
-                for (int s = 0; s < 8; ++s) x[s] = accS[j][8 * half + s];
-                *reinterpret_cast<frag*>(Sp + state_frag_offset(at0 + j, bt, NBT, half, lane)) = M::pack(x);
+                    for (int s = 0; s < 8; ++s) x[s] = accS[j][8 * half + s];
+                    *reinterpret_cast<frag*>(Sp + state_frag_offset(at0 + j, bt, NBT, half, lane)) = M::pack(x);
+                }
             }
-        }
+        };
+        scale_state(cA);
+        if (EXACT_END && ends(n, 0) && !p.save) scale_state(cR);
+        publish();
         prep_gates(rawf[1 - par], rawq[1 - par], chunk_rel(n, 1));
         load_f(rawf[1 - par], chunk_rel(n, 3)); load_q(rawq[1 - par], chunk_rel(n, 3));
         if (LATE_QS) {
@@ -816,7 +847,15 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         // ======================= stage B =======================
         // O^T tile (bt, rt) = V^T P^T + (G_m S)^T Q~^T   and   accumulators += K~^T V
         if (LATE_QS) store_o(chunk_rel(n, -1));
-        if (p.save && n < NC) save_state(Sp, chunk_rel(n, 0).slot);
+        if (p.save && n < NC) {
+            save_state(Sp, chunk_rel(n, 0).slot);
+            if (EXACT_END && ends(n, 0)) {       // (kept states are G_m S_n whatever the chunk: r comes once they are out)
+                __syncthreads();
+                scale_state(cR);
+                publish();
+                __syncthreads();
+            }
+        }
 #pragma unroll
         for (int v = 0; v < 16; ++v) accO[v] = 0.0f;
 #pragma unroll
@@ -839,7 +878,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
             }
         }
         if (!LATE_QS) read_out_state(Qc, Sp);
-        prep_tiles(n + 1, chunk_rel(n, 1).first != 0);
+        prep_tiles(n + 1, chunk_rel(n, 1).first != 0, ends(n, 1));
         if (!LATE_QS) {
             if (has_o) stage_o();
             pin_obuf();
@@ -881,19 +920,19 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
 }
 
 // (a workgroup of four waves shares a compute unit with another: two waves per SIMD either way)
-template <int DK, int DV, int DVW, bool GATE_BF16, bool RUNS>
+template <int DK, int DV, int DVW, bool GATE_BF16, bool RUNS, bool EXACT_END>
 __global__ __launch_bounds__(64 * fused_waves(DK), 2) void fwd_fused_kernel(FwdFusedParams p)
 {
-    if (p.dense) fwd_fused_body<DK, DV, DVW, GATE_BF16, true, false, false, RUNS>(p);
-    else         fwd_fused_body<DK, DV, DVW, GATE_BF16, false, false, false, RUNS>(p);
+    if (p.dense) fwd_fused_body<DK, DV, DVW, GATE_BF16, true, false, false, RUNS, EXACT_END>(p);
+    else         fwd_fused_body<DK, DV, DVW, GATE_BF16, false, false, false, RUNS, EXACT_END>(p);
 }
 
 // The walk over spans of a packed batch's chunks (a kernel of its own: its register needs are not
 // those of the walk over one sequence).
-template <int DK, int DV, int DVW, bool GATE_BF16>
+template <int DK, int DV, int DVW, bool GATE_BF16, bool EXACT_END>
 __global__ __launch_bounds__(64 * fused_waves(DK), 2) void fwd_fused_grouped_kernel(FwdFusedParams p)
 {
-    fwd_fused_body<DK, DV, DVW, GATE_BF16, false, true, false>(p);
+    fwd_fused_body<DK, DV, DVW, GATE_BF16, false, true, false, true, EXACT_END>(p);
 }
 
 // What every run of a sequence (every span of a packed batch) adds to the state from zero, and the
@@ -910,17 +949,28 @@ static bool fused_grouped(const SeqDims& d) { return d.lay.vl && d.lay.spans > 0
 
 bool fwd_fused_supported(const SeqDims& d) { return d.io_bf16; }
 
+typedef void (*FusedKernel)(FwdFusedParams);
+
+template <int DK, int DV, int DVW, bool GATE_BF16>
+static FusedKernel fused_kernel(bool ends, bool grouped, bool runs, bool exact_end)
+{
+    if (ends) return run_ends_kernel<DK, DV, DVW, GATE_BF16>;
+    if (grouped) return exact_end ? fwd_fused_grouped_kernel<DK, DV, DVW, GATE_BF16, true> : fwd_fused_grouped_kernel<DK, DV, DVW, GATE_BF16, false>;
+    if (runs) return exact_end ? fwd_fused_kernel<DK, DV, DVW, GATE_BF16, true, true> : fwd_fused_kernel<DK, DV, DVW, GATE_BF16, true, false>;
+    // (the walk that takes many 128 x 128 sequences whole is bound by its registers and never had the exact end)
+    constexpr bool EXACT = DK != 128 || DV != 128;
+    return exact_end ? fwd_fused_kernel<DK, DV, DVW, GATE_BF16, false, EXACT> : fwd_fused_kernel<DK, DV, DVW, GATE_BF16, false, false>;
+}
+
 template <int DK, int DV, int DVW>
 static hipError_t launch_fused(const SeqDims& d, const FwdFusedParams& p, int walkers, bool ends, hipStream_t stream)
 {
     typedef FwdFusedLds<DK, DVW> L;
     constexpr int NSPLIT = DV / DVW;
     // (walks of a few, odd chunks: the pass over an empty chunk that the other variant takes would be felt)
-    const bool short_odd = d.NC < 16 && d.NC % 2 == 1;
-    auto kern = ends ? (d.gate_bf16 ? run_ends_kernel<DK, DV, DVW, true> : run_ends_kernel<DK, DV, DVW, false>)
-              : fused_grouped(d) ? (d.gate_bf16 ? fwd_fused_grouped_kernel<DK, DV, DVW, true> : fwd_fused_grouped_kernel<DK, DV, DVW, false>)
-              : (p.R > 0 || p.run_add || short_odd) ? (d.gate_bf16 ? fwd_fused_kernel<DK, DV, DVW, true, true> : fwd_fused_kernel<DK, DV, DVW, false, true>)
-                                       : (d.gate_bf16 ? fwd_fused_kernel<DK, DV, DVW, true, false> : fwd_fused_kernel<DK, DV, DVW, false, false>);
+    const bool runs = p.R > 0 || p.run_add || (d.NC < 16 && d.NC % 2 == 1), grouped = fused_grouped(d), exact_end = p.hT != nullptr;
+    const FusedKernel kern = d.gate_bf16 ? fused_kernel<DK, DV, DVW, true>(ends, grouped, runs, exact_end)
+                                         : fused_kernel<DK, DV, DVW, false>(ends, grouped, runs, exact_end);
     const int lds = (int)(ends ? L::light_total : L::total);
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
