@@ -18,7 +18,7 @@
 // forward pass over 256 tokens of one head -- a sweep launch takes every chunk from zero at once, and
 // the workgroup of chunk n adds up the contributions of the chunks before it,
 //     S_n = Diag(g_{n-1}) ( ... Diag(g_0) h0 + A_0 ... ) + A_{n-1},
-// out of the cache; the last chunk's workgroup also forms the final state, h (G_m S_n + K~^T V).
+// out of the cache; the last chunk's workgroup also forms the final state, h (G_m S_n) + K^^T V.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -174,6 +174,11 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
 #pragma unroll
         for (int i = RW - 1; i >= 0; --i) { z0[i] = run0; z1[i] = run1; run0 *= rf[i].x; run1 *= rf[i].y; }
     }
+    float kz0[ADD ? RW : 1], kz1[ADD ? RW : 1];          // k z, for the final state
+    if constexpr (ADD) {
+#pragma unroll
+        for (int i = 0; i < RW; ++i) { kz0[i] = (1.0f - rf[i].x) * z0[i]; kz1[i] = (1.0f - rf[i].y) * z1[i]; }
+    }
     if (k_act) {
         tot[w * DK + 2 * lane] = a0[RW - 1];
         tot[w * DK + 2 * lane + 1] = a1[RW - 1];
@@ -226,26 +231,6 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
 #pragma unroll
                 for (int s = 0; s < 4; ++s) sfrag[ks].v[4 * c + s] *= t0[s] * t1[s];
             }
-        // final state, by the last chunk's workgroup: tiles (at, bt), the channel tiles dealt to the waves
-        // of a dv tile.  Fragments 2 at and 2 at + 1 hold the state in accumulator order.
-        if (p.hT && n == p.NC - 1) {
-#pragma unroll
-            for (int at = 0; at < DK / 32; ++at) {
-                if (at % (kWaves / NBT) != w / NBT) continue;
-                f32x16 acc;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[v] = sfrag[2 * at + (v >> 3)].v[v & 7];
-#pragma unroll
-                for (int ks = 0; ks < C / 16; ++ks)
-                    M::mma(acc, M::load_kmajor(Km, PK, 16 * ks, 32 * at, lane), M::load(Vt + (32 * bt + r32) * PC + 16 * ks + 8 * g));
-                float* out = p.hT + (size_t)bh * DK * DV + (size_t)(32 * at) * DV + 32 * bt + r32;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = acc_row(v, lane);
-                    out[(size_t)row * DV] = acc[v] * (tot[2 * DK + 32 * at + row] * tot[3 * DK + 32 * at + row]);
-                }
-            }
-        }
     }
 
     // ---------------- P^T blocks: (J, I) with J <= I; wave w takes block w ----------------
@@ -278,6 +263,38 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
         }
     }
     __syncthreads();
+
+    if constexpr (ADD) {
+        // Final state, by the last chunk's workgroup: h (G_m S_n) + K^^T V with K^_j = k_j prod_{s > j} f_s, as the sweep
+        // forms it (K~ has a reciprocal in it, whose error the state would keep), in the tile the P blocks have
+        // read K~ from.  Tiles (at, bt), the channel tiles dealt to the waves of a dv tile; fragments 2 at and
+        // 2 at + 1 hold the state in accumulator order.
+        if (p.hT && n == p.NC - 1) {
+            if (k_act) {
+                const float p0 = block_decay(tot, DK, w, 2 * lane).post, p1 = block_decay(tot, DK, w, 2 * lane + 1).post;
+#pragma unroll
+                for (int i = 0; i < RW; ++i) store_pair_t<T>(Km, (size_t)(RW * w + i) * PK + 2 * lane, kz0[i] * p0, kz1[i] * p1);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int at = 0; at < DK / 32; ++at) {
+                if (at % (kWaves / NBT) != w / NBT) continue;
+                f32x16 acc;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int ch = 32 * at + acc_row(v, lane);
+                    acc[v] = sfrag[2 * at + (v >> 3)].v[v & 7] * (tot[2 * DK + ch] * tot[3 * DK + ch]);
+                }
+#pragma unroll
+                for (int ks = 0; ks < C / 16; ++ks)
+                    M::mma(acc, M::load_kmajor(Km, PK, 16 * ks, 32 * at, lane), M::load(Vt + (32 * bt + r32) * PC + 16 * ks + 8 * g));
+                float* out = p.hT + (size_t)bh * DK * DV + (size_t)(32 * at) * DV + 32 * bt + r32;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) out[(size_t)acc_row(v, lane) * DV] = acc[v];
+            }
+            __syncthreads();                 // (the O tiles take this memory)
+        }
+    }
 
     // ---------------- O tiles: P V + (q G) S_n ----------------
     // (NRT * NBT is a multiple of the wave count and NBT divides it, so every tile of a wave

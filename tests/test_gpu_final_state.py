@@ -53,3 +53,15 @@ def test_final_states_of_a_packed_batch(lens, H, dk, dv):
     for i, p in enumerate(parts):
         want = p[3][0] if p else torch.zeros(H, dk, dv, device="cuda")
         assert torch.equal(hT[i], want) and torch.equal(hT2[i], want), i
+
+
+# fp32 storage: the same inputs, the share exact in fp32; the read-out from contributions, on either side of its
+# limits, and the sweep
+@pytest.mark.parametrize("B,H,N,dk,dv", [(1, 1, 256, 64, 64), (1, 1, 40, 128, 128), (2, 3, 800, 128, 64), (1, 2, 1000, 64, 128),
+                                         (1, 1, 64, 64, 64), (1, 2, 1025, 128, 128), (33, 2, 500, 64, 64)])
+def test_final_state_in_fp32(B, H, N, dk, dv):
+    print("\n[final state, fp32] B=%d H=%d N=%d dk=%d dv=%d" % (B, H, N, dk, dv), flush=True)
+    q, f, v, want = inputs(6200 + N, B, H, N, dk, dv, torch.float32)
+    _, hT = binding.hgrn2_fwd(q, f, v)
+    torch.cuda.synchronize()
+    assert torch.equal(hT, want)
