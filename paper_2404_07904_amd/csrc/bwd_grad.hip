@@ -520,7 +520,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
                             accD[j][4 * c + e] = (p.dhT && has_d) ? *reinterpret_cast<const float*>(cols + st_lane + 4 * e) : 0.0f;
                     }
             }
-            if (n_light > 0 && p.span_add) {
+            if (n_light > 0 && p.span_add && span_total >= p.lay.spans) {      // (fewer chunks than spans: spans without one have left nothing)
                 // the spans from the one in which the sequence ends down to the next one, two requested at a time
                 const int span = (int)blockIdx.x / p.lay.H;
                 int k = span + 1;

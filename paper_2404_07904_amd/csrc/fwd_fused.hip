@@ -198,6 +198,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     // GROUPED: the span is chunks p0 .. p1 - 1 of head `head`, counted over the sequences in order; it
     // starts with chunk cur_n of sequence cur_e
     int head = 0, cur_e = 0, cur_n = 0, span_id = 0;
+    bool span_ends = false;                  // the spans' contributions are there
     SeqView sv;
     int NC;                                  // chunks of the walk
     int n0 = 0;                              // its first chunk, within the sequence (not GROUPED)
@@ -210,6 +211,9 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         const int total = table_read(t_before, p.lay.B);
         const int p0 = (int)((long long)span_id * total / p.lay.spans), p1 = (int)((long long)(span_id + 1) * total / p.lay.spans);
         NC = p1 - p0;
+        // (with fewer chunks than spans -- cu_seqlens names a small part of the tokens -- the spans without a
+        // chunk, which leave nothing, would have to be told apart: a light walk is short then)
+        span_ends = !ENDS && p.run_add && total >= p.lay.spans;
         if (NC > 0) {
             // the sequence that holds chunk p0 (ENDS: the span's last chunk): the last one with at most
             // that many chunks before it
@@ -378,7 +382,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
             for (int v = 0; v < 16; ++v) accS[j][v] = 0.0f;
     } else {
         initial_state(GROUPED ? first_bh : whole);
-        if (RUNS && p.run_add) {
+        if (RUNS && (GROUPED ? span_ends : p.run_add != nullptr)) {
             // what the runs before this one add, and how their gates decay what enters them
             int k0 = 0, k1 = bh - whole * p.lay.seg;
             if constexpr (GROUPED) {
@@ -680,7 +684,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
             }
         return;
     }
-    if (RUNS && !(GROUPED && p.run_add) && (GROUPED ? first_n > 0 : n0 > 0)) {
+    if (RUNS && !(GROUPED && span_ends) && (GROUPED ? first_n > 0 : n0 > 0)) {
         light_walk(first_tok, GROUPED ? first_N : N_one, 0, GROUPED ? first_n : n0, nullptr);
         // Keeps the compiler from computing the chunk loop's lane-dependent values ahead of the light
         // walk and carrying them through it in registers.

@@ -245,3 +245,42 @@ def test_varlen_with_gate_formed_in_the_kernels(H, dk, dv, nseq):
     check("dz (pair)", unpacked(gz_s), rz, tol)
     check("dbeta (pair)", host(gb_s), rb, tol)
     check("dh0 (pair)", host(gh0_s), rh0, tol)
+
+
+# cu_seqlens that names fewer chunks than there are spans (16 for 16 heads), the rest of the tokens belonging to no
+# sequence, in a workspace whose bytes read as NaN: what a span without a chunk leaves must not be read
+@pytest.mark.parametrize("lens", [[300, 276], [0, 500, 1], [64, 64, 130]])
+@pytest.mark.parametrize("dk,dv", [(64, 64), (128, 128)])
+def test_tokens_that_belong_to_no_sequence(lens, dk, dv):
+    print("\n[varlen, tokens left over] lens=%s dk=%d dv=%d" % (lens, dk, dv), flush=True)
+    H, T, B, used = 16, 8192, len(lens), sum(lens)
+    w = synth.make_sequence(1700 + used, 1, H, used, dk, dv, io_dtype="bf16", lb=0.9, with_dO=True)
+    rng = np.random.default_rng(used)
+    h0, dhT = ((0.1 * rng.standard_normal((B, H, dk, dv))).astype(np.float32) for _ in range(2))
+    wide = lambda x: torch.cat([packed(x, "bf16"), torch.ones(T - used, H, x.shape[-1], dtype=torch.bfloat16, device="cuda")])
+    q, f, v, dO = (wide(x) for x in (w.q, w.f, w.v, w.dO))
+    cu = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).cuda()
+    shape, saved = binding.make_shape_varlen(q, v, f, B), states_buffer(q, v, f, B)
+    room = lambda n: torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+    fws, bws = binding.hgrn2_fwd_varlen_workspace_bytes(shape), binding.hgrn2_bwd_varlen_workspace_bytes(shape)
+    o, hT = binding.hgrn2_fwd_varlen(q, f, v, cu, dev(h0), workspace=room(fws))
+    o2, hT2 = binding.hgrn2_fwd_varlen(q, f, v, cu, dev(h0), saved_states=saved, workspace=room(fws))
+    ga = binding.hgrn2_bwd_varlen(q, f, v, dO, cu, dev(h0), dev(dhT), want_grad_h0=True, workspace=room(bws))
+    gb = binding.hgrn2_bwd_varlen(q, f, v, dO, cu, dev(h0), dev(dhT), want_grad_h0=True, saved_states=saved, workspace=room(bws))
+    torch.cuda.synchronize()
+    at = 0
+    for b, n in enumerate(lens):
+        if n == 0:
+            continue
+        s = slice(at, at + n)
+        at += n
+        cut = lambda x: x[:, :, s]
+        ro, rhT = oracle.fwd(cut(w.q), cut(w.f), cut(w.v), h0[b:b + 1])
+        r = oracle.bwd(cut(w.q), cut(w.f), cut(w.v), cut(w.dO), h0[b:b + 1], dhT[b:b + 1])
+        for oo, hh in ((o, hT), (o2, hT2)):
+            check("o[%d]" % b, host(oo[s].permute(1, 0, 2)[None]), ro, TOL["bf16"])
+            check("hT[%d]" % b, host(hh[b:b + 1]), rhT, TOL["bf16"])
+        for g in (ga, gb):
+            for name, x, y in zip(("dq", "df", "dv"), g, r):
+                check("%s[%d]" % (name, b), host(x[s].permute(1, 0, 2)[None]), y, TOL["bf16"])
+            check("dh0[%d]" % b, host(g[3][b:b + 1]), r[3], TOL["bf16"])
