@@ -76,6 +76,7 @@ struct FwdFusedParams {
     // span * H + head is what the span adds to the last of its sequences, which goes on in later spans.
     float* run_add;
     float* run_decay;
+    int walkers;         // sequences (runs of segmented ones, spans x heads) that get a workgroup, or R of them, each for NSPLIT slabs of dv
     int ends_per_seq;    // run_ends_kernel: how many of a sequence's runs are walked, the first ones
 };
 
@@ -173,14 +174,14 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
 
     if (not_chosen(p.lay)) return;       // one of several chunk lengths, and not the one called for
     // workgroup -> (sequence, run, dv half): ids 8 apart land on the same XCD (ids are dealt to the 8
-    // XCDs round-robin), so the workgroups of a sequence share an L2 for the rows several of them read
+    // XCDs round-robin), so the workgroups of a sequence share an L2 for the rows several of them read (run_item())
     int bh, split, run = 0;
     const int n_run = (GROUPED || !RUNS || p.R == 0) ? 1 : p.R;
     if (NSPLIT == 1 && n_run == 1) { bh = blockIdx.x; split = 0; }
     else {
-        const int x = blockIdx.x & 7, r = blockIdx.x >> 3, per = n_run * NSPLIT, sub = r % per;
-        bh = (r / per) * 8 + x;
-        split = sub % NSPLIT; run = sub / NSPLIT;
+        const RunItem item = run_item(blockIdx.x, p.walkers, n_run * NSPLIT);
+        bh = item.seq;
+        split = item.sub % NSPLIT; run = item.sub / NSPLIT;
     }
     // padding of the grid (uniform, before any barrier)
     int ends_slot = bh;
@@ -967,7 +968,7 @@ static FusedKernel fused_kernel(bool ends, bool grouped, bool runs, bool exact_e
 }
 
 template <int DK, int DV, int DVW>
-static hipError_t launch_fused(const SeqDims& d, const FwdFusedParams& p, int walkers, bool ends, hipStream_t stream)
+static hipError_t launch_fused(const SeqDims& d, const FwdFusedParams& p, bool ends, hipStream_t stream)
 {
     typedef FwdFusedLds<DK, DVW> L;
     constexpr int NSPLIT = DV / DVW;
@@ -979,23 +980,24 @@ static hipError_t launch_fused(const SeqDims& d, const FwdFusedParams& p, int wa
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
     const int per = NSPLIT * (p.R > 0 ? p.R : 1);
-    const unsigned grid = per == 1 ? (unsigned)walkers : (unsigned)(per * 8 * ((walkers + 7) / 8));
+    const unsigned grid = per == 1 ? (unsigned)p.walkers : (unsigned)run_grid(p.walkers, per);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * L::NW), lds, stream, p);
     return hipGetLastError();
 }
 
-static hipError_t launch_fused_dims(const SeqDims& d, const FwdFusedParams& p, int walkers, bool ends, hipStream_t stream)
+static hipError_t launch_fused_dims(const SeqDims& d, FwdFusedParams& p, int walkers, bool ends, hipStream_t stream)
 {
+    p.walkers = walkers;
     // Two workgroups per walk (each half of the dv columns) keep twice as many compute units busy,
     // but only as long as all of them run at once (144 sequences of 2048 tokens, 128-wide heads: 137 us
     // halved against 84 us whole; up to 128 sequences halving wins).
     const int all = walkers * (p.R > 0 ? p.R : 1);
     if (d.dk == 128 && d.dv == 128)
-        return 2 * all > 256 ? launch_fused<128, 128, 128>(d, p, walkers, ends, stream)
-                             : launch_fused<128, 128, 64>(d, p, walkers, ends, stream);
-    if (d.dk == 64 && d.dv == 64) return launch_fused<64, 64, 64>(d, p, walkers, ends, stream);
-    if (d.dk == 128 && d.dv == 64) return launch_fused<128, 64, 64>(d, p, walkers, ends, stream);
-    if (d.dk == 64 && d.dv == 128) return launch_fused<64, 128, 64>(d, p, walkers, ends, stream);
+        return 2 * all > 256 ? launch_fused<128, 128, 128>(d, p, ends, stream)
+                             : launch_fused<128, 128, 64>(d, p, ends, stream);
+    if (d.dk == 64 && d.dv == 64) return launch_fused<64, 64, 64>(d, p, ends, stream);
+    if (d.dk == 128 && d.dv == 64) return launch_fused<128, 64, 64>(d, p, ends, stream);
+    if (d.dk == 64 && d.dv == 128) return launch_fused<64, 128, 64>(d, p, ends, stream);
     return hipErrorInvalidValue;
 }
 
@@ -1005,7 +1007,7 @@ static FwdFusedParams fused_params(const SeqDims& d, const void* q, const void* 
     p.q = q; p.f = f; p.v = v; p.h0 = nullptr; p.o = nullptr; p.hT = nullptr; p.save = nullptr;
     p.N = d.N; p.NC = d.NC; p.BH = d.BH; p.beta = d.beta; p.H = d.H; p.lay = d.lay; p.dense = d.dense() ? 1 : 0;
     p.flag = d.domain_flag;
-    p.R = 0; p.run_add = nullptr; p.run_decay = nullptr; p.ends_per_seq = 1;
+    p.R = 0; p.run_add = nullptr; p.run_decay = nullptr; p.walkers = 0; p.ends_per_seq = 1;
     return p;
 }
 

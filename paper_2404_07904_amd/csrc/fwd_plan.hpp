@@ -40,6 +40,22 @@ inline void fused_cuts(int NC, int R, FwdCuts* cuts)
     bnd[R] = NC;
 }
 
+// Workgroup -> sequence and item of the sequence (light run and half of dv, `per` of them).
+// Workgroups are dealt to the 8 XCDs round-robin; the items of a sequence go to one XCD, so that they
+// share an L2 for the rows several of them read, sequence s to XCD s % 8 -- but for the last BH % 8 sequences, whose
+// items are dealt out one by one: with those whole, 11 of 85 sequences in three runs made 33 workgroups on some
+// XCDs, for 32 compute units, and the pass took two rounds (85 heads of 2048 tokens: 92 us, uncut 70.6, so 55).
+// (a workgroup past the last item gets seq >= BH)
+constexpr int kXcds = 8;
+struct RunItem { int seq, sub; };
+constexpr int run_grid(int BH, int per) { return kXcds * ((BH * per + kXcds - 1) / kXcds); }
+constexpr RunItem run_item(int block, int BH, int per)
+{
+    const int x = block % kXcds, r = block / kXcds, whole = BH / kXcds, at = r - whole * per;
+    const int i = at < 0 ? r : at * kXcds + x, q = i / per;
+    return RunItem{at < 0 ? q * kXcds + x : whole * kXcds + q, i - q * per};
+}
+
 // light_walks = false: no light walks (whose workgroups all read the sequence's initial state, while one of
 // them writes the final one: not for a state that is continued in place).
 inline FwdRuns plan_fwd_runs(int BH, int NC, int dk, int dv, bool light_walks = true)

@@ -21,6 +21,8 @@ extern "C" void plan(int BH, int NC, int dk, int dv, int light_walks, int* out)
     if (r.light > 1) fused_cuts(NC, r.light, &c);
     for (int i = 0; i <= kMaxFwdRuns; ++i) out[3 + i] = c.bnd[i];
 }
+extern "C" int grid_of(int BH, int per) { return run_grid(BH, per); }
+extern "C" int item_of(int block, int BH, int per) { const RunItem r = run_item(block, BH, per); return r.seq * per + r.sub; }
 """
 INT_MAX = 2 ** 31 - 1
 
@@ -58,3 +60,23 @@ def test_cuts_rise_and_cover_every_chunk(lib, dk, dv):
             case = (BH, NC, dk, dv, light, seg, run_chunks)
             assert light == 1 and seg >= 1 and (seg - 1) * run_chunks < NC <= seg * run_chunks, case
             assert seg == 1 or seg * (4 * dk * dv + 4 * dk) <= NC * 2 * dk * dv, case
+
+
+def test_light_runs_are_dealt_evenly_to_the_xcds(lib):
+    """Every (sequence, run, half) is somebody's, and the workgroups of an XCD (every eighth one) are an eighth of all:
+    32 at most, one per compute unit, for the 256 a plan fills."""
+    for BH in [*range(1, 130), 1000]:
+        for per in range(1, 33):
+            items, grid = BH * per, lib.grid_of(BH, per)
+            if items > 1100:
+                continue
+            got = [lib.item_of(b, BH, per) for b in range(grid)]
+            assert items <= grid < items + 8 and sorted(got) == list(range(grid)), (BH, per)
+            for x in range(8):
+                assert sum(i < items for i in got[x::8]) <= (items + 7) // 8, (BH, per, x)
+    out = (ctypes.c_int * (4 + lib.max_runs()))()
+    for dk, dv in ((64, 64), (128, 64), (64, 128), (128, 128)):
+        for BH in range(1, 257):
+            for NC in (8, 16, 32, 64, 300):
+                lib.plan(BH, NC, dk, dv, 1, out)
+                assert out[0] == 1 or out[0] * BH <= 256, (BH, NC, dk, dv, out[0])

@@ -26,6 +26,9 @@ CASES = [
     (1, 2, 2100, 64, 64, "bf16"),        # 33 chunks: walks from zero in eight runs, the last one shorter
     (1, 3, 3001, 128, 128, "bf16"),      # the same, 47 chunks in eleven runs
     (1, 1, 4481, 64, 128, "bf16"),       # 71 chunks: 17 runs and more, with the carry kernel
+    (5, 17, 460, 128, 128, "bf16"),      # 85 sequences in three light runs: no whole number of sequences to an XCD
+    (1, 25, 700, 64, 128, "bf16"),       # the same in halves of dv
+    (3, 29, 300, 64, 64, "f32"),
 ]
 
 
