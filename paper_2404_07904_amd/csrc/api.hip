@@ -464,7 +464,7 @@ static int fwd_one(const hgrn2_shape* shape, const void* q, const void* f, const
     float* run_state = reinterpret_cast<float*>(static_cast<char*>(workspace) + one);
     float* run_decay = reinterpret_cast<float*>(reinterpret_cast<char*>(run_state) + fwd_run_state_bytes(d));
     if (fwd_fused_supported(d)) {
-        const FwdRuns fr = plan_fwd_runs(d, !in_place);
+        const FwdRuns fr = plan_fwd_runs(d, !in_place, save_states != nullptr);
         if (in_place && fr.seg > 1) {
             // (the runs need not be the ones the workspace is sized for; their states, 4 dk dv bytes for three
             // chunks or more, take the place of the chunk states, 2 dk dv bytes each, which this pass does not write)

@@ -1011,10 +1011,10 @@ static FwdFusedParams fused_params(const SeqDims& d, const void* q, const void* 
     return p;
 }
 
-FwdRuns plan_fwd_runs(const SeqDims& d, bool light_walks)
+FwdRuns plan_fwd_runs(const SeqDims& d, bool light_walks, bool kept)
 {
     if (!d.io_bf16 || d.packed) { FwdRuns r; r.run_chunks = d.NC; return r; }
-    return plan_fwd_runs(d.BH, d.NC, d.dk, d.dv, light_walks);
+    return plan_fwd_runs(d.BH, d.NC, d.dk, d.dv, light_walks, kept);
 }
 
 hipError_t launch_fwd_fused(const SeqDims& d, const void* q, const void* f, const void* v, const float* h0,

@@ -58,7 +58,8 @@ constexpr RunItem run_item(int block, int BH, int per)
 
 // light_walks = false: no light walks (whose workgroups all read the sequence's initial state, while one of
 // them writes the final one: not for a state that is continued in place).
-inline FwdRuns plan_fwd_runs(int BH, int NC, int dk, int dv, bool light_walks = true)
+// kept: the walk keeps the chunk states for a backward pass.
+inline FwdRuns plan_fwd_runs(int BH, int NC, int dk, int dv, bool light_walks = true, bool kept = false)
 {
     FwdRuns r;
     r.run_chunks = NC;
@@ -76,6 +77,10 @@ inline FwdRuns plan_fwd_runs(int BH, int NC, int dk, int dv, bool light_walks = 
     // 209 us in halves, 182 us whole; 64 heads whole, 16 / 32 / 64 chunks: 30.5 / 52 / 96 us light, 39 / 55 / 91 us from zero.
     double best = NC;                                    // one run (128 x 128: in halves up to 128 heads)
     if (dk == 128 && dv == 128 && BH > 128) return r;
+    // Two light runs that nearly fill the chip pay only while the walk is not bound by memory, to which kept states
+    // add 2 dk dv bytes a chunk: 128 heads with kept states, us uncut / in two runs: 32 chunks 79.2 / 76.0, 48 chunks 131 / 123,
+    // 64 chunks 169 / 177, 128 chunks 335 / 365; 112 heads: 64 chunks 157.8 / 156.6, 128 chunks 309 / 311.
+    if (kept && dk == 128 && dv == 128 && BH > 112 && NC >= 56) return r;
     auto consider = [&](int places, double light_factor, double ends_cost, double per_chunk) {
         int R = places / BH;
         if (R > kMaxFwdRuns) R = kMaxFwdRuns;

@@ -180,7 +180,7 @@ hipError_t launch_fwd_out(const SeqDims& d, const void* q, const void* f, const 
 // the storage fwd_fused_supported() accepts (bf16).
 bool fwd_fused_supported(const SeqDims& d);
 // (fwd_plan.hpp; a packed batch and fp32 storage are not cut this way)
-FwdRuns plan_fwd_runs(const SeqDims& d, bool light_walks = true);
+FwdRuns plan_fwd_runs(const SeqDims& d, bool light_walks = true, bool kept = false);
 // What every run of segmented sequences (TokenLayout::seg, or the entries of a run table) adds to the
 // state from zero, run_add [slot][dk][dv], and the product of its gates, run_decay [slot][dk]; only
 // the first ends_per_seq runs of each sequence, slot = sequence * ends_per_seq + run.  Packed batch with

@@ -13,9 +13,9 @@ SHIM = """
 using namespace hgrn2;
 extern "C" int max_runs() { return kMaxFwdRuns; }
 // out: light, seg, run_chunks, then the light runs' cuts
-extern "C" void plan(int BH, int NC, int dk, int dv, int light_walks, int* out)
+extern "C" void plan(int BH, int NC, int dk, int dv, int light_walks, int kept, int* out)
 {
-    const FwdRuns r = plan_fwd_runs(BH, NC, dk, dv, light_walks != 0);
+    const FwdRuns r = plan_fwd_runs(BH, NC, dk, dv, light_walks != 0, kept != 0);
     out[0] = r.light; out[1] = r.seg; out[2] = r.run_chunks;
     FwdCuts c = {};
     if (r.light > 1) fused_cuts(NC, r.light, &c);
@@ -44,7 +44,7 @@ def test_cuts_rise_and_cover_every_chunk(lib, dk, dv):
         for NC in [*range(1, 70), 127, 256, 511, 4095, 32766, 32767, 32768, 40000, 65535, 65536, 65540, 70000, 1 << 20, most - 1, most]:
             if NC > most:
                 continue
-            lib.plan(BH, NC, dk, dv, 1, out)
+            lib.plan(BH, NC, dk, dv, 1, 0, out)
             light, seg, run_chunks, bnd = out[0], out[1], out[2], list(out)[3:]
             case = (BH, NC, dk, dv, light, seg, run_chunks, bnd)
             assert 1 <= light <= runs and 1 <= seg <= max(1, NC) and (light == 1 or seg == 1), case
@@ -55,7 +55,7 @@ def test_cuts_rise_and_cover_every_chunk(lib, dk, dv):
                 assert (seg - 1) * run_chunks < NC <= seg * run_chunks, case
             # a state continued in place: no light walks, and the runs' states (fp32, with their gate products)
             # fit the room of the chunk states (bf16)
-            lib.plan(BH, NC, dk, dv, 0, out)
+            lib.plan(BH, NC, dk, dv, 0, 0, out)
             light, seg, run_chunks = out[0], out[1], out[2]
             case = (BH, NC, dk, dv, light, seg, run_chunks)
             assert light == 1 and seg >= 1 and (seg - 1) * run_chunks < NC <= seg * run_chunks, case
@@ -78,5 +78,19 @@ def test_light_runs_are_dealt_evenly_to_the_xcds(lib):
     for dk, dv in ((64, 64), (128, 64), (64, 128), (128, 128)):
         for BH in range(1, 257):
             for NC in (8, 16, 32, 64, 300):
-                lib.plan(BH, NC, dk, dv, 1, out)
+                lib.plan(BH, NC, dk, dv, 1, 0, out)
                 assert out[0] == 1 or out[0] * BH <= 256, (BH, NC, dk, dv, out[0])
+
+
+def test_kept_states_never_change_what_the_workspace_is_sized_for(lib):
+    """The workspace depends on the shape alone: a walk that keeps states is cut into the same runs of equal length, or
+    not at all."""
+    a, b = ((ctypes.c_int * (4 + lib.max_runs()))() for _ in range(2))
+    for dk, dv in ((64, 64), (128, 64), (64, 128), (128, 128)):
+        for BH in range(1, 140):
+            for NC in (2, 13, 32, 55, 56, 64, 300, 4000):
+                for light in (0, 1):
+                    lib.plan(BH, NC, dk, dv, light, 0, a)
+                    lib.plan(BH, NC, dk, dv, light, 1, b)
+                    assert list(a) == list(b) or (b[0] == 1 and b[1] == 1), (BH, NC, dk, dv, light)
+                    assert list(a) == list(b) or (dk == dv == 128 and BH > 112 and NC >= 56), (BH, NC, dk, dv, light)
