@@ -120,6 +120,11 @@ template <int DK_, int DVW_> struct FwdFusedLds {
 struct FusedChunk {
     int tok0, row0, N, bh, first, last, slot, lo, hi;
 };
+// What a walk over spans keeps of a chunk while it is in the window of its passes (scalar registers, of which it
+// has too few): the rest of FusedChunk is computed from it.  n: chunk of sequence e.
+struct SpanChunk {
+    int tok0, N, n, e, slot;
+};
 
 // GROUPED: a span of a packed batch's chunks (else: a sequence, or a run of one).  ENDS: only the state
 // that a run leaves when it starts from zero, and the product of its gates (run_ends_kernel).  RUNS: the
@@ -293,14 +298,12 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         cur_slot = table_read(t_before, e) * p.lay.H + head * cur_nc;
     };
     auto next_chunk = [&]() {
-        FusedChunk c;
+        SpanChunk c;
         if (left <= 0) {                     // past the end of the span, for good
-            c.tok0 = 0; c.row0 = 0; c.lo = 0; c.hi = 0; c.N = 0; c.bh = 0; c.first = 0; c.last = 0; c.slot = 0;
+            c.tok0 = 0; c.N = 0; c.n = 0; c.e = 0; c.slot = 0;
             return c;
         }
-        const ChunkRows cr = chunk_rows(p.lay.sub, cur_n, cur_N);
-        c.tok0 = cur_tok; c.row0 = cr.tok0; c.lo = cr.first; c.hi = cr.end; c.N = cur_N; c.bh = cur_e * p.lay.H + head;
-        c.first = cur_n == 0; c.last = cur_n == cur_nc - 1; c.slot = cur_slot + cur_n;
+        c.tok0 = cur_tok; c.N = cur_N; c.n = cur_n; c.e = cur_e; c.slot = cur_slot + cur_n;
         if (--left > 0 && ++cur_n == cur_nc) {
             int e = cur_e + 1;
             while (table_read(t_len, e) == 0) ++e;       // (left > 0: a later sequence has tokens)
@@ -319,18 +322,24 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         return k;
     };
     // window of the pass: ck[j] = chunk n - 1 + j of pass n (spans only)
-    FusedChunk ck[5];
+    SpanChunk ck[5];
     const int first_n = cur_n;               // the span starts with this chunk of its first sequence
     int first_tok = 0, first_N = 0, first_bh = bh;
     if constexpr (GROUPED) {
         open_sequence(cur_e);
         first_tok = cur_tok; first_N = cur_N; first_bh = cur_e * p.lay.H + head;
-        ck[0].tok0 = 0; ck[0].row0 = 0; ck[0].N = 0; ck[0].bh = 0; ck[0].first = 0; ck[0].last = 0; ck[0].slot = 0;
-        ck[0].lo = 0; ck[0].hi = 0;
+        ck[0].tok0 = 0; ck[0].N = 0; ck[0].n = 0; ck[0].e = 0; ck[0].slot = 0;
 #pragma unroll
         for (int j = 1; j < 5; ++j) ck[j] = next_chunk();
     }
-    auto chunk_rel = [&](int n, int rel) { return GROUPED ? ck[rel + 1] : chunk_at(n0 + n + rel); };
+    auto span_chunk = [&](const SpanChunk& s) {
+        FusedChunk k;
+        const ChunkRows cr = chunk_rows(p.lay.sub, s.n, s.N);
+        k.tok0 = s.tok0; k.row0 = cr.tok0; k.lo = cr.first; k.hi = cr.end; k.N = s.N; k.bh = s.e * p.lay.H + head;
+        k.first = s.n == 0 && s.N > 0; k.last = s.n == p.lay.chunks_of(s.N) - 1; k.slot = s.slot;
+        return k;
+    };
+    auto chunk_rel = [&](int n, int rel) { return GROUPED ? span_chunk(ck[rel + 1]) : chunk_at(n0 + n + rel); };
 
     // ---- state: fp32 accumulators.  Between chunks they hold S_n / h(n-1); see stage A. ----
     f32x16 accS[NST];
@@ -705,7 +714,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     __syncthreads();
     // whether chunk n + rel of the walk ends its sequence and the state is wanted
     const bool ends_here = EXACT_END && !GROUPED && (!RUNS || (p.run_add ? bh - whole * p.lay.seg == p.lay.seg - 1 : run == n_run - 1));
-    auto ends = [&](int n, int rel) { return GROUPED ? ck[rel + 1].last != 0 : (ends_here && n + rel == NC - 1); };
+    auto ends = [&](int n, int rel) { return GROUPED ? span_chunk(ck[rel + 1]).last != 0 : (ends_here && n + rel == NC - 1); };
     prep_tiles(0, true, ends(0, 0));
     __syncthreads();
 
@@ -780,8 +789,9 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         if constexpr (GROUPED) {
             // sequence boundary: the walk's accumulators, times h of the chunk before, are the state
             // the sequence before ends in; this chunk starts from its own sequence's initial state
-            if (ck[0].last && p.hT) final_state(ck[0].bh, cH);
-            if (ck[1].first && n > 0 && ck[1].N > 0) initial_state(ck[1].bh);
+            const FusedChunk before = chunk_rel(n, -1), here = chunk_rel(n, 0);
+            if (before.last && p.hT) final_state(before.bh, cH);
+            if (here.first && n > 0) initial_state(here.bh);
         }
         // G_m(n) S_n = c(n) * accumulators, published as the bf16 operand of the read-out
         auto publish = [&]() {
@@ -917,7 +927,8 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         // S_N = pending rescale * accumulators (the chunk after the last one has G_m = 1).  A span has
         // written the state of every sequence that a further pass followed.
         if constexpr (GROUPED) {
-            if (ck[0].last) final_state(ck[0].bh, cH);
+            const FusedChunk before = span_chunk(ck[0]);
+            if (before.last) final_state(before.bh, cH);
         } else {
             if (!RUNS || (p.run_add ? bh - whole * p.lay.seg == p.lay.seg - 1 : run == n_run - 1)) final_state(whole, cA);
         }
