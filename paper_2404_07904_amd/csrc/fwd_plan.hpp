@@ -46,7 +46,7 @@ inline void fused_cuts(int NC, int R, FwdCuts* cuts)
 // items are dealt out one by one: with those whole, 11 of 85 sequences in three runs made 33 workgroups on some
 // XCDs, for 32 compute units, and the pass took two rounds (85 heads of 2048 tokens: 92 us, uncut 70.6, so 55).
 // (a workgroup past the last item gets seq >= BH)
-constexpr int kXcds = 8;
+constexpr int kXcds = 8;         // accelerator dies; consecutive workgroup ids land on consecutive dies
 struct RunItem { int seq, sub; };
 constexpr int run_grid(int BH, int per) { return kXcds * ((BH * per + kXcds - 1) / kXcds); }
 constexpr RunItem run_item(int block, int BH, int per)
