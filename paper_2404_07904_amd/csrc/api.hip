@@ -265,7 +265,8 @@ hipError_t build_packed_tables(const hgrn2_shape* s, const PackedRuns& p, const 
     d->lay.vl = seq_table;
     // (a batch that is not cut gets its group array, over the sequence table, in the same launch)
     int* groups_here = (p.G > 0 && p.run_chunks == 0) ? reinterpret_cast<int*>(static_cast<char*>(workspace) + p.groups_at) : nullptr;
-    hipError_t e = launch ? launch_varlen_table(cu_seqlens, s->B, d->N, seq_table, stream, p.G, groups_here, d->lay.sub,
+    const bool heads64 = d->dk == 64 && d->dv == 64;
+    hipError_t e = launch ? launch_varlen_table(cu_seqlens, s->B, d->N, seq_table, stream, p.G, groups_here, heads64, d->lay.sub,
                                                 d->lay.alt, d->lay.alt_path) : hipSuccess;
     if (e != hipSuccess) return e;
     if (p.run_chunks != 0) {
@@ -281,28 +282,31 @@ hipError_t build_packed_tables(const hgrn2_shape* s, const PackedRuns& p, const 
     }
     if (p.G > 0) {
         int* groups = reinterpret_cast<int*>(static_cast<char*>(workspace) + p.groups_at);
-        if (launch && !groups_here) e = launch_varlen_groups(d->lay.vl, d->lay.B, p.G, groups, stream, d->lay.alt, d->lay.alt_path);
+        if (launch && !groups_here) e = launch_varlen_groups(d->lay.vl, d->lay.B, p.G, groups, heads64, stream, d->lay.alt, d->lay.alt_path);
         if (p.by_groups) {
             d->lay.groups = groups;
             d->lay.G = p.G;
         }
         d->lay.spans = p.G;
         d->lay.span_seq = groups + p.G + 2;
+        d->lay.span_walks = groups + 2 * p.G + 2;
     }
     return e;
 }
 
 // Spans of a packed batch: whether the state (state gradient) a span enters a sequence with comes from a
 // kernel that walks every span's part of the sequence from zero (run_ends, bwd_ends), rather than from a
-// light walk by every span over all of the sequence outside it.  The lengths are on the device; the host
-// knows the mean: with sequences of a quarter of a span on average some are likely to reach over spans.
+// light walk by every span over all of the sequence outside it.  The lengths are on the device, where the table
+// kernel decides (TokenLayout::span_walks); the host knows the mean and saves the launch where sequences are short:
+// with more than a quarter of a span on average some are likely to reach over spans (lognormal lengths, spans of
+// 16: 100 documents of 5.1 chunks forward 154 -> 130 us, 80 of 3.2 no difference); a launch that returns at once costs 3 us.
 // (the contributions lie where a set of chunk states of another path lies: `room` bytes)
 size_t span_add_bytes(const hgrn2_shape* s, const SeqDims& d) { return round256((size_t)d.lay.spans * s->H * d.dk * d.dv * sizeof(float)); }
 bool spans_from_ends(const hgrn2_shape* s, const SeqDims& d, size_t room)
 {
     if (d.lay.spans <= 0 || s->B <= 0) return false;
     const long long chunks = d.N / d.lay.sub;
-    return chunks >= 2LL * d.lay.spans && 4 * (chunks / s->B) >= chunks / d.lay.spans &&
+    return chunks >= 2LL * d.lay.spans && 4LL * d.lay.spans > s->B &&
            span_add_bytes(s, d) + (size_t)d.lay.spans * s->H * d.dk * sizeof(float) <= room;
 }
 

@@ -520,7 +520,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
                             accD[j][4 * c + e] = (p.dhT && has_d) ? *reinterpret_cast<const float*>(cols + st_lane + 4 * e) : 0.0f;
                     }
             }
-            if (n_light > 0 && p.span_add && span_total >= p.lay.spans) {      // (fewer chunks than spans: spans without one have left nothing)
+            if (n_light > 0 && p.span_add && table_read(p.lay.span_walks, 1) != 0) {
                 // the spans from the one in which the sequence ends down to the next one, two requested at a time
                 const int span = (int)blockIdx.x / p.lay.H;
                 int k = span + 1;
@@ -1042,7 +1042,7 @@ __device__ __forceinline__ void bwd_ends_body(const BwdGradParams& p)
     int count;
     if constexpr (GROUPED) {
         const int span = slot / p.lay.H, head = slot - span * p.lay.H;
-        if (span >= p.lay.spans) return;
+        if (span >= p.lay.spans || table_read(p.lay.span_walks, 1) == 0) return;
         const int* before = p.lay.vl + 2 * (p.lay.B + 1);
         const int total = table_read(before, p.lay.B);
         const int p0 = (int)((long long)span * total / p.lay.spans), p1 = (int)((long long)(span + 1) * total / p.lay.spans);

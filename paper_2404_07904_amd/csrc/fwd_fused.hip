@@ -217,9 +217,8 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         const int total = table_read(t_before, p.lay.B);
         const int p0 = (int)((long long)span_id * total / p.lay.spans), p1 = (int)((long long)(span_id + 1) * total / p.lay.spans);
         NC = p1 - p0;
-        // (with fewer chunks than spans -- cu_seqlens names a small part of the tokens -- the spans without a
-        // chunk, which leave nothing, would have to be told apart: a light walk is short then)
-        span_ends = !ENDS && p.run_add && total >= p.lay.spans;
+        span_ends = p.run_add && table_read(p.lay.span_walks, 0) != 0;
+        if (ENDS && !span_ends) return;
         if (NC > 0) {
             // the sequence that holds chunk p0 (ENDS: the span's last chunk): the last one with at most
             // that many chunks before it

@@ -53,6 +53,10 @@ struct TokenLayout {
     // launch_varlen_groups() writes it behind the choice).
     int spans = 0;
     const int* span_seq = nullptr;
+    // Behind them, two ints: 1 where walks from zero provide the state a span enters a sequence with (forward), the
+    // state gradient it enters it with (backward): run_ends and bwd_ends return at once where it is 0, and the
+    // spans find it by a light walk.  The table kernel knows the lengths, the host only whether to enqueue such a walk.
+    const int* span_walks = nullptr;
     // Segmented sweeps: each of the sequences the strides describe is cut into `seg` runs of whole
     // chunks that the sequential kernels treat as sequences of their own, `seg` per original one,
     // numbered run-fastest.  The kernels' N and NC are then those of a full run; `n_tokens` keeps
@@ -298,9 +302,11 @@ hipError_t launch_varlen_run_table(const int* seq_table, int B, int T, int run_c
 // = entries [groups[g], groups[g + 1]), cut where the chunk count reaches g / G of the total, so that
 // groups hold about equally many chunks (a group is never finer than one entry); and one more int,
 // the choice of backward pass (TokenLayout::path): the reverse walk over groups takes as long as its
-// largest group, the per-chunk pass as long as all chunks shared among the compute units.
+// largest group, the per-chunk pass as long as all chunks shared among the compute units.  Behind it what
+// TokenLayout::span_seq and span_walks point to.
 size_t varlen_groups_bytes(int G);
-hipError_t launch_varlen_groups(const int* table, int n_entries, int G, int* groups, hipStream_t stream,
+// (heads64: heads of 64 x 64, whose walks from zero cost less, for span_walks)
+hipError_t launch_varlen_groups(const int* table, int n_entries, int G, int* groups, bool heads64, hipStream_t stream,
                                 const int* choice = nullptr, int path = 0);
 // dst[0 .. n) = 0, as a kernel (safe under graph capture)
 hipError_t launch_zero_floats(float* dst, size_t n, hipStream_t stream);
@@ -308,6 +314,6 @@ hipError_t launch_zero_floats(float* dst, size_t n, hipStream_t stream);
 hipError_t launch_sum_ints(const int* src, int n, int* out, hipStream_t stream);
 // (groups != null: the group array over the table's G groups, launch_varlen_groups(), in the same launch)
 hipError_t launch_varlen_table(const int* cu_seqlens, int B, int T, int* table, hipStream_t stream, int G = 0,
-                               int* groups = nullptr, int sub = kChunk, const int* choice = nullptr, int path = 0);
+                               int* groups = nullptr, bool heads64 = false, int sub = kChunk, const int* choice = nullptr, int path = 0);
 
 }   // namespace hgrn2

@@ -26,10 +26,11 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 // Group g of G starts at the first entry e whose chunks-before count reaches g / G of all chunks
 // (bisection over the table's non-decreasing third array); the last group ends at the last entry,
 // so that empty entries at the end belong to a group too.  Behind the G + 1 group starts: the choice
-// between the two backward passes, then, for each of the G equal spans of chunks the reverse walk
-// takes, the entry the span ends in.
+// between the two backward passes, then, for each of the G equal spans of chunks the walks over spans
+// take, the entry the span ends in, then two ints: whether the forward walk's spans, the reverse walk's spans
+// carry the state over spans by walks from zero (TokenLayout::span_walks).
 // (Called by all threads of a one-workgroup kernel, after a barrier that follows the table's writes.)
-__device__ __forceinline__ void build_groups(const int* tab, int n_entries, int G, int* groups)
+__device__ __forceinline__ void build_groups(const int* tab, int n_entries, int G, int* groups, int heads64)
 {
     const int* before = tab + 2 * (n_entries + 1);
     const long long total = before[n_entries];
@@ -53,8 +54,7 @@ __device__ __forceinline__ void build_groups(const int* tab, int n_entries, int 
     // as long as the longest sequence at about 4.6 us a chunk, then the per-chunk kernel at 11 us per
     // chunk of a compute unit's share) wins only when one sequence is several times longer than a
     // span: the walk is chosen while the longest such tail is at most four spans long.
-    __shared__ int longest[kTabThreads];
-    int mine = 0;
+    int tail = 0, head = 0;
     for (int s = threadIdx.x; s < G; s += kTabThreads) {
         const long long p0 = (long long)s * total / G, p1 = (long long)(s + 1) * total / G;
         if (p1 <= p0) { groups[G + 2 + s] = 0; continue; }
@@ -64,23 +64,37 @@ __device__ __forceinline__ void build_groups(const int* tab, int n_entries, int 
             if (before[mid] <= p1 - 1) lo = mid; else hi = mid;
         }
         groups[G + 2 + s] = lo;                          // the sequence span s ends in
-        mine = max(mine, (int)(before[lo + 1] - p1));    // chunks of sequence `lo` after the span's last one
+        const int after = (int)(before[lo + 1] - p1);    // chunks of sequence `lo` after the span's last one
+        tail = max(tail, after);
+        if (after > 0) head = max(head, (int)(p1 - before[lo]));          // and before the next span's first one
     }
-    longest[threadIdx.x] = mine;
+    // The longest of all, over the waves' longest.
+    __shared__ int longest[2][kTabThreads / 64];
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) { tail = max(tail, __shfl_xor(tail, d, 64)); head = max(head, __shfl_xor(head, d, 64)); }
+    if ((threadIdx.x & 63) == 0) { longest[0][threadIdx.x >> 6] = tail; longest[1][threadIdx.x >> 6] = head; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        int m = 0;
-        for (int j = 0; j < kTabThreads; ++j) m = max(m, longest[j]);
+        for (int j = 1; j < kTabThreads / 64; ++j) { tail = max(tail, longest[0][j]); head = max(head, longest[1][j]); }
         const long long share = (total + G - 1) / G;
-        groups[G + 1] = (m <= 4 * share) ? 1 : 0;
+        groups[G + 1] = (tail <= 4 * share) ? 1 : 0;
+        // Walks from zero take a span's chunks, and some more for the states they leave; light walks the chunks of a
+        // sequence outside a span.  us, walks from zero / light, 16384 tokens, spans of 16: 16 heads of 128, 22 chunks
+        // outside forward 106 / 96, backward 222 / 215; 37 outside 101 / 113, 217 / 239; spans of 33, 32 heads of 64 x 128: 33
+        // outside 158 / 144, 339 / 329; 46 outside 158 / 148, 344 / 354; gate formed in the kernels, spans of 18, 30 outside
+        // forward 127 / 141.  Backward, heads of 64 x 64 (a light chunk takes 2.7 us, a chunk of
+        // a walk from zero with its four waves 0.9): spans of 33, 16 outside 259 / 265, of 17, 16 outside 137 / 142.
+        // (Fewer chunks than spans: spans without one leave nothing.)
+        groups[2 * G + 2] = (total >= G && head > share + 9) ? 1 : 0;
+        groups[2 * G + 3] = (total >= G && tail > (heads64 ? share / 3 + 2 : share + 8)) ? 1 : 0;
     }
 }
 
 __global__ __launch_bounds__(kTabThreads) void varlen_groups_kernel(const int* tab, int n_entries, int G, int* groups,
-                                                                    const int* choice, int path)
+                                                                    int heads64, const int* choice, int path)
 {
     if (choice && table_read(choice, 0) != path) return;        // one of several alternatives, and not the one called for
-    build_groups(tab, n_entries, G, groups);
+    build_groups(tab, n_entries, G, groups, heads64);
 }
 
 // Exclusive prefix (sum, or running maximum of non-negative values) of one value per thread over the
@@ -106,8 +120,8 @@ __device__ __forceinline__ int block_prefix(int v, int* wave_tot)
 }
 
 // With `groups` (null: none) the group array of the table is built in the same launch.
-__global__ __launch_bounds__(kTabThreads) void varlen_table_kernel(const int* cu, int B, int T, int* tab, int G, int* groups, int sub,
-                                                                   const int* choice, int path)
+__global__ __launch_bounds__(kTabThreads) void varlen_table_kernel(const int* cu, int B, int T, int* tab, int G, int* groups, int heads64,
+                                                                   int sub, const int* choice, int path)
 {
     if (choice && table_read(choice, 0) != path) return;        // one of several alternatives, and not the one called for
     const int shift = 31 - __builtin_clz((unsigned)sub);         // sub is a power of two
@@ -168,7 +182,7 @@ __global__ __launch_bounds__(kTabThreads) void varlen_table_kernel(const int* cu
     }
     if (groups) {
         __syncthreads();
-        build_groups(tab, B, G, groups);
+        build_groups(tab, B, G, groups, heads64);
     }
 }
 
@@ -255,18 +269,19 @@ hipError_t launch_sum_ints(const int* src, int n, int* out, hipStream_t stream)
 
 size_t varlen_table_bytes(int B) { return 4 * ((size_t)B + 1) * sizeof(int); }
 
-hipError_t launch_varlen_table(const int* cu_seqlens, int B, int T, int* table, hipStream_t stream, int G, int* groups, int sub,
-                               const int* choice, int path)
+hipError_t launch_varlen_table(const int* cu_seqlens, int B, int T, int* table, hipStream_t stream, int G, int* groups, bool heads64,
+                               int sub, const int* choice, int path)
 {
-    hipLaunchKernelGGL(varlen_table_kernel, dim3(1), dim3(kTabThreads), 0, stream, cu_seqlens, B, T, table, G, groups, sub, choice, path);
+    hipLaunchKernelGGL(varlen_table_kernel, dim3(1), dim3(kTabThreads), 0, stream, cu_seqlens, B, T, table, G, groups, heads64 ? 1 : 0, sub,
+                       choice, path);
     return hipGetLastError();
 }
 
-size_t varlen_groups_bytes(int G) { return (2 * (size_t)G + 2) * sizeof(int); }
+size_t varlen_groups_bytes(int G) { return (2 * (size_t)G + 4) * sizeof(int); }
 
-hipError_t launch_varlen_groups(const int* table, int n_entries, int G, int* groups, hipStream_t stream, const int* choice, int path)
+hipError_t launch_varlen_groups(const int* table, int n_entries, int G, int* groups, bool heads64, hipStream_t stream, const int* choice, int path)
 {
-    hipLaunchKernelGGL(varlen_groups_kernel, dim3(1), dim3(kTabThreads), 0, stream, table, n_entries, G, groups, choice, path);
+    hipLaunchKernelGGL(varlen_groups_kernel, dim3(1), dim3(kTabThreads), 0, stream, table, n_entries, G, groups, heads64 ? 1 : 0, choice, path);
     return hipGetLastError();
 }
 

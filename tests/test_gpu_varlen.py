@@ -284,3 +284,15 @@ def test_tokens_that_belong_to_no_sequence(lens, dk, dv):
             for name, x, y in zip(("dq", "df", "dv"), g, r):
                 check("%s[%d]" % (name, b), host(x[s].permute(1, 0, 2)[None]), y, TOL["bf16"])
             check("dh0[%d]" % b, host(g[3][b:b + 1]), r[3], TOL["bf16"])
+
+
+# 40 chunks in four spans (64 heads): walks from zero carry the state over spans where a sequence has more than 10 + 9
+# chunks before the start of a span (forward), the state gradient where it has more than 10 + 8 (heads of 64: 10 / 3 + 2)
+# after the end of one (backward).  Chunks before and after, in this order: 19 and 11, 20 and 11, 12 and 18, 22 and 21,
+# 3 and 5, 3 and 6
+@pytest.mark.parametrize("chunks", [[11, 20, 9], [10, 21, 9], [8, 20, 12], [8, 23, 9], [7, 8, 5, 10, 10], [7, 9, 4, 10, 10]])
+@pytest.mark.parametrize("dk,dv", [(64, 64), (128, 128)])
+def test_sequences_that_reach_over_spans(chunks, dk, dv):
+    lens = [64 * c - 5 * i for i, c in enumerate(chunks)]
+    print("\n[varlen, over spans] lens=%s dk=%d dv=%d" % (lens, dk, dv), flush=True)
+    run(1800 + sum(lens), lens, 64, dk, dv, lb=0.9)
