@@ -89,10 +89,11 @@ constexpr int kInlineCarryRuns = 16;
 int plan_runs(const SeqDims& d, bool backward, int* run_chunks)
 {
     *run_chunks = d.NC;
-    // Measured with 64- and 128-wide heads: the forward gains from 16 chunks on, up to 64 sequences
-    // and with about 256 runs in all, down to runs of 4 chunks; the backward pass of a packed batch
-    // (the only one planned here: equal lengths have a plan of their own) cuts the same way, but
-    // only from 32 chunks on and up to 32 sequences.
+    // What is planned here: the forward pass of fp32 storage and of packed batches and the sweep for the states of
+    // the stateless backward pass (bf16 forward passes of equal lengths have fwd_plan.hpp) from 16 chunks on, up to
+    // 64 sequences and with about 256 runs in all, down to runs of 4 chunks; the backward pass of a
+    // packed batch (equal lengths have plan_bwd_fused()) cuts the same way, but only from 32 chunks
+    // on and up to 32 sequences.  Measured with 64- and 128-wide heads.
     if (d.packed || d.NC < (backward ? 32 : 16) || d.BH == 0 || d.BH > (backward ? 32 : 64)) return 1;
     const int fill = 256 / d.BH;                         // rounded down: a walk more than there are units has to wait for a free one
     const int by_length = d.NC / 4;

@@ -340,7 +340,6 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     // element-wise stage is over.  Rows past the end of a sequence re-read its last row: their
     // gates are replaced by one and their q by zero, which makes whatever finite values stand in
     // for V and dO there drop out of every stored result.
-    // chunk index -> sequence and chunk within it (every chunk index handed in is a valid one)
     // chunk index -> sequence and chunk within it (every chunk index handed in is a valid one);
     // found once per chunk, when its rows are requested, and kept for the chunk's own pass
     int seq_hint = 0;         // the workgroup asks for chunk indices in non-decreasing order
@@ -1023,8 +1022,8 @@ __global__ __launch_bounds__(64 * kBwdWaves) void bwd_grad_kernel(BwdGradParams 
 
 // What a run of chunks adds to the state gradient from zero (the light walk alone), and the product of its
 // gates: for every run of segmented sequences, or for every span of a packed batch whose first sequence has
-// begun in an earlier span, over that sequence's chunks in the span.  Three workgroups to a compute unit
-// by their LDS: bound by what they read (q, f, dO), which the sweep with its four waves was not (2 x 16
+// begun in an earlier span, over that sequence's chunks in the span.  Two workgroups of eight waves to a
+// compute unit (heads of 64: three of four): bound by what they read (q, f, dO), which the sweep with its four waves was not (2 x 16
 // heads of 16384 tokens in 28 runs each, fp32 gates, 537 MB: 137 us).
 template <typename T, int DK, int DV, bool GATE_BF16, bool DENSE, bool GROUPED, int NW>
 __device__ __forceinline__ void bwd_ends_body(const BwdGradParams& p)

@@ -7,9 +7,9 @@
 // with Q~ = q G/G_m, K~ = k G_m/G (k = 1 - f, G the cumulative gate product inside the chunk, G_m
 // its value after the first half of the chunk, h the product over the second half), so that the
 // per-chunk states never travel through HBM (the two-kernel path writes and re-reads 2*dk*dv
-// bytes per chunk, as much again as the chunk's own q, f, v, o).  One workgroup of eight wave64s
-// owns a whole (batch, head) and walks its chunks in order, software-pipelined in two stages
-// per chunk with one barrier after each:
+// bytes per chunk, as much again as the chunk's own q, f, v, o).  One workgroup (eight wave64s; heads
+// of 64: four) walks the chunks of a (batch, head), or of a run or span of them (below), in order,
+// software-pipelined in two stages per chunk with one barrier after each:
 //
 //   stage A(n):  store O(n-1) from its LDS staging tile; copy V(n) into LDS; rescale the state
 //                to G_m(n) S_n and publish it (bf16, MFMA-fragment order) to LDS; first half of

@@ -19,12 +19,15 @@ pytestmark = pytest.mark.gpu
 CASES = [
     (1, 1, 65, 64, 64, "bf16"),          # two chunks, two light runs of one chunk
     (1, 3, 777, 128, 128, "bf16"),       # 13 chunks, ragged: light runs, halves of dv
-    (2, 20, 460, 128, 128, "f32"),       # more than 32 sequences: light runs, whole dv
+    (2, 20, 460, 128, 128, "f32"),       # three light runs of each of 40 sequences, halves of dv
+    (5, 13, 460, 128, 128, "f32"),       # the same of 65 sequences, whole dv
     (1, 2, 1000, 64, 64, "f32"),         # 16 chunks of 64-wide heads
     (1, 2, 700, 128, 64, "bf16"),
     (1, 2, 700, 64, 128, "f32"),
-    (1, 2, 2100, 64, 64, "bf16"),        # 33 chunks: walks from zero in eight runs, the last one shorter
-    (1, 3, 3001, 128, 128, "bf16"),      # the same, 47 chunks in eleven runs
+    (1, 2, 2100, 64, 64, "bf16"),        # 33 chunks: walks from zero in eleven runs of three
+    (1, 6, 2700, 64, 64, "bf16"),        # 43 chunks in eleven runs of four, the last one of three
+    (1, 3, 3001, 128, 128, "bf16"),      # 47 chunks in twelve runs, the last one shorter
+    (1, 64, 4100, 128, 128, "bf16"),     # 65 chunks in four runs, whole dv
     (1, 1, 4481, 64, 128, "bf16"),       # 71 chunks: 17 runs and more, with the carry kernel
     (5, 17, 460, 128, 128, "bf16"),      # 85 sequences in three light runs: no whole number of sequences to an XCD
     (1, 25, 700, 64, 128, "bf16"),       # the same in halves of dv
@@ -102,3 +105,25 @@ def test_forward_fp32_from_contributions(B, H, N, dk, dv, states):
     check("o", host(o), ro, TOL["f32"])
     if states:
         check("hT", host(hT), rhT, TOL["f32"])
+
+
+# Two light runs of 96 and 100 sequences with the gate formed in the kernels, token-major, continued from a state, the
+# chunk length chosen on the device: ordinary gates (64 tokens) and gates for which shorter chunks are taken
+@pytest.mark.parametrize("small", [False, True])
+@pytest.mark.parametrize("B,H,N,d", [(2, 48, 330, 128), (2, 50, 330, 64)])
+def test_light_runs_with_the_chunk_length_chosen_on_the_device(B, H, N, d, small):
+    print("\n[fwd runs, auto] B=%d H=%d N=%d d=%d small=%d" % (B, H, N, d, small), flush=True)
+    rng = np.random.default_rng(3300 + N + d)
+    q, v, z = (torch.from_numpy(rng.standard_normal((B, N, H, d)).astype(np.float32)).to(torch.bfloat16) for _ in range(3))
+    beta = torch.full((H, d), 0.0 if small else 0.5)
+    if small:
+        z = z - 5.0                      # gates near 0.007: products of 32 below 2^-100, of 8 above
+    h0 = (0.1 * rng.standard_normal((B, H, d, d))).astype(np.float32)
+    o, hT = binding.hgrn2_fwd_gated(q.cuda(), z.cuda(), beta.cuda(), v.cuda(), dev(h0), layout=binding.HGRN2_LAYOUT_BNHD,
+                                    chunk=-1)
+    torch.cuda.synchronize()
+    heads = lambda x: x.permute(0, 2, 1, 3).double().numpy()
+    f = heads(beta.double()[None, None] + (1.0 - beta.double()[None, None]) * torch.sigmoid(z.double()))
+    ro, rhT = oracle.fwd(heads(q), f, heads(v), h0)
+    check("o", host(o.permute(0, 2, 1, 3)), ro, TOL["bf16"])
+    check("hT", host(hT), rhT, TOL["bf16"])
