@@ -44,7 +44,6 @@
 
 namespace hgrn2 {
 
-constexpr int kMaxLightRuns = 4;
 constexpr int kBwdWaves = 8;         // (and rows of partial sums of the gradient of beta per chunk or run: one per row block)
 static_assert(kBwdWaves == kRowBlocks, "a row block per wave");
 
@@ -69,7 +68,7 @@ struct BwdGradParams {
     // workgroup each; a run starts from grad_hT (the last one), from bound0[bh] (run 0) or from
     // run_state[bh * seg_tail + r * s_sub - 1] (the state gradient at the end of run r, which a
     // zero-start sweep over the later tokens and its carry have left there); run 0 leaves grad_h0.
-    // With few runs (`light`), no boundary states are needed: a workgroup first walks the chunks
+    // With light walks (`light`), no boundary states are needed: a workgroup first walks the chunks
     // after its run, from grad_hT, doing nothing but the state-gradient recurrence (a fraction of a
     // chunk's full work), and the runs are cut at bnd[0] = 0 < bnd[1] < ... < bnd[R] = NC so that
     // all workgroups finish together.
@@ -1156,59 +1155,7 @@ static hipError_t launch_fused_one(const SeqDims& d, const BwdGradParams& p, hip
     return hipGetLastError();
 }
 
-BwdFusedPlan plan_bwd_fused(const SeqDims& d, int places)
-{
-    // One workgroup per run and one run per compute unit (heads of 64: two) at a time: as many runs per
-    // sequence as it takes to fill the chip, but at least four chunks each.  The zero-start sweep that supplies the
-    // state gradient at the run boundaries walks sub-runs of about eight chunks.
-    BwdFusedPlan pl;
-    pl.light = 0;
-    for (int i = 0; i <= kMaxLightRuns; ++i) pl.bnd[i] = 0;
-    if (places == 0) places = fused_waves(d.dk, d.dv, d.io_bf16) == 4 ? 512 : kOnePerUnit;      // workgroups that run at once
-    int R = d.BH > 0 ? places / d.BH : 1;
-    if (R > d.NC / 4) R = d.NC / 4;
-    if (R < 1) R = 1;
-    if (R >= 2 && R <= kMaxLightRuns) {
-        // Few runs: each workgroup walks the chunks after its run itself, at `rho` of a chunk's full
-        // cost, and the cuts are placed so that all runs take the same time T:
-        // len_r = T - rho (NC - end_r), from the last run (len = T) backwards; T by bisection.
-        // rho is set by the balance that measures best (128 sequences of 32 chunks in two runs: 14 + 18
-        // chunks 180 us, 15 + 17 185 us, 13 + 19 187 us; a light chunk alone costs 0.16 of a full one,
-        // but the light walks run while the memory system is busiest).
-        const double rho = 0.24;
-        double lo = 0.0, hi = (double)d.NC;
-        for (int iter = 0; iter < 50; ++iter) {
-            const double T = 0.5 * (lo + hi);
-            double end = (double)d.NC;
-            for (int r = R - 1; r >= 0; --r) end -= T - rho * ((double)d.NC - end);
-            if (end > 0.0) lo = T; else hi = T;        // runs too short: raise T
-        }
-        double end = (double)d.NC;
-        pl.bnd[R] = d.NC;
-        for (int r = R - 1; r >= 1; --r) {
-            end -= hi - rho * ((double)d.NC - end);
-            int b = (int)(end + 0.5);
-            if (b < r) b = r;                          // every run keeps at least one chunk
-            if (b > pl.bnd[r + 1] - 1) b = pl.bnd[r + 1] - 1;
-            pl.bnd[r] = b;
-        }
-        pl.bnd[0] = 0;
-        pl.light = 1;
-        pl.R = R; pl.rc = 0; pl.s_sub = 1; pl.sub_chunks = 0; pl.seg_tail = 0;
-        return pl;
-    }
-    int rc = (d.NC + R - 1) / R;
-    int s = rc / 8;                               // sub-runs of about eight chunks: fewer, longer walks and fewer states to carry
-    if (s < 1) s = 1;
-    if (R > 1) rc = (rc + s - 1) / s * s;         // whole sub-runs per run
-    pl.rc = rc;
-    pl.R = rc > 0 ? (d.NC + rc - 1) / rc : 1;
-    if (pl.R < 1) pl.R = 1;
-    pl.s_sub = s;
-    pl.sub_chunks = rc / s;
-    pl.seg_tail = pl.R > 1 ? (d.NC - rc + pl.sub_chunks - 1) / pl.sub_chunks : 0;
-    return pl;
-}
+BwdFusedPlan plan_bwd_fused(const SeqDims& d, int places) { return plan_bwd_runs(d.BH, d.NC, d.dk, d.dv, d.io_bf16, places); }
 
 hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void* q, const void* f, const void* v,
                             const void* grad_o, const void* ws_state, const float* grad_hT, float* grad_h0,

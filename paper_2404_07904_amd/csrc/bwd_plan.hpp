@@ -1,0 +1,115 @@
+// The cut of the fused reverse walk of an equal-length batch: plain host arithmetic on a few sizes, in a header
+// of its own so that it can be compiled and checked without a GPU.
+#pragma once
+
+namespace hgrn2 {
+
+constexpr int kMaxLightRuns = 16;
+
+// How the reverse walk cuts every sequence: into R runs.  light: run r is chunks bnd[r] .. bnd[r + 1] - 1, and its
+// workgroup first takes a light walk over the chunks after it (the state gradient alone).  Otherwise runs of rc
+// chunks, and the state gradients at their ends come from walks from zero over the tokens after run 0, seg_tail
+// sub-runs of sub_chunks chunks (s_sub to a run), and a carry over them.
+struct BwdFusedPlan { int R, rc, s_sub, sub_chunks, seg_tail, light, bnd[kMaxLightRuns + 1]; };
+
+// places: the workgroups the runs are to fill.  0: as many as run at once; kOnePerUnit: one per compute unit and at
+// least four chunks to a run (fewer run boundaries to keep); 1: sequences are not cut.
+constexpr int kOnePerUnit = 256;
+
+inline BwdFusedPlan uncut_bwd(int NC)
+{
+    BwdFusedPlan pl = {};
+    pl.R = 1; pl.rc = NC; pl.s_sub = 1; pl.sub_chunks = NC;
+    return pl;
+}
+
+// R runs with a light walk each, which costs `rho` of a chunk's full work per chunk; the cuts let all runs
+// take the same time T: len_r = T - rho (NC - end_r) from the last run (len = T) backwards, so T sum_{i<R} (1 - rho)^i = NC.
+// rho is set by the balance that measures best (128 sequences of 32 chunks in two runs: 14 + 18 chunks 180 us,
+// 15 + 17 185 us, 13 + 19 187 us; a light chunk alone costs 0.16 to 0.25 of a full one, but with many sequences the light
+// walks run while the memory system is busiest).
+constexpr double kBwdLightCost = 0.24;
+
+inline BwdFusedPlan light_bwd(int NC, int R, double* longest)
+{
+    BwdFusedPlan pl = {};
+    double sum = 0.0, x = 1.0;
+    for (int r = 0; r < R; ++r) { sum += x; x *= 1.0 - kBwdLightCost; }
+    const double T = NC / sum;
+    double end = NC;
+    pl.bnd[R] = NC;
+    for (int r = R - 1; r >= 1; --r) {
+        end -= T - kBwdLightCost * (NC - end);
+        int b = (int)(end + 0.5);
+        if (b < r) b = r;                              // every run keeps at least one chunk
+        if (b > pl.bnd[r + 1] - 1) b = pl.bnd[r + 1] - 1;
+        pl.bnd[r] = b;
+    }
+    *longest = 0.0;
+    for (int r = 0; r < R; ++r) {
+        const double t = pl.bnd[r + 1] - pl.bnd[r] + kBwdLightCost * (NC - pl.bnd[r + 1]);
+        if (t > *longest) *longest = t;
+    }
+    pl.light = 1; pl.R = R; pl.s_sub = 1;
+    return pl;
+}
+
+// Runs of equal length whose boundaries are walked to from zero, in sub-runs of about eight chunks: fewer, longer
+// walks and fewer states to carry.
+inline BwdFusedPlan ends_bwd(int NC, int R)
+{
+    BwdFusedPlan pl = {};
+    int rc = (NC + R - 1) / R;
+    int s = rc / 8;
+    if (s < 1) s = 1;
+    if (R > 1) rc = (rc + s - 1) / s * s;              // whole sub-runs per run
+    pl.rc = rc;
+    pl.R = rc > 0 ? (NC + rc - 1) / rc : 1;
+    if (pl.R < 1) pl.R = 1;
+    pl.s_sub = s;
+    pl.sub_chunks = rc / s;
+    pl.seg_tail = pl.R > 1 ? (NC - rc + pl.sub_chunks - 1) / pl.sub_chunks : 0;
+    return pl;
+}
+
+inline BwdFusedPlan plan_bwd_runs(int BH, int NC, int dk, int dv, bool io_bf16, int places)
+{
+    if (places == 1 || BH <= 0 || NC <= 1) return uncut_bwd(NC);
+    const bool pairs = dk == 64 && dv == 64 && io_bf16;        // workgroups of four waves, two on a compute unit
+    if (places == kOnePerUnit || !io_bf16) {
+        int R = kOnePerUnit / BH;
+        if (R > NC / 4) R = NC / 4;
+        double longest;
+        if (R >= 2 && R <= 4) return light_bwd(NC, R, &longest);
+        return R < 2 ? uncut_bwd(NC) : ends_bwd(NC, R);
+    }
+    // As many runs as find a place, however short: a run of one chunk costs little more than that chunk.  Light walks
+    // or walks from zero by what they take, in chunks of the full walk (128 x 128: 7.5 us a chunk, 64 x 64: 5 us, each
+    // on a compute unit of its own; two on one: 1.45 times as long).  The walks from zero and their carry are two more launches,
+    // 2.1 to 2.4 chunks, and states that are written and read twice.  1, 16 and 64 heads; us with runs of at
+    // least four chunks -> now:
+    //   128 x 128:  4 chunks 34 -> 16.4, 34.8 -> 17.0, 36 -> 19.5 (light)     16 chunks 48.9 -> 29.7 (from zero), 51.1 -> 36.3 (light), 56
+    //              32 chunks 55.3 -> 33.3, 60.9 -> 47.9 (from zero), 115       64 chunks 57.0 -> 40.3, 68.2 (from zero)
+    //   64 x 64:    4 chunks 23.2 -> 12.2, 23.7 -> 12.5, 24.3 -> 13.1 (light)  16 chunks 34.2 -> 19.8, 34.8 -> 22.6, 35.9 -> 34.4 (from zero)
+    BwdFusedPlan best = uncut_bwd(NC);
+    double least = NC;
+    for (int at_once = kOnePerUnit; at_once <= (pairs ? 2 : 1) * kOnePerUnit; at_once += kOnePerUnit) {
+        int R = at_once / BH;
+        if (R > NC) R = NC;
+        if (R < 2) continue;
+        const double crowd = R * BH > kOnePerUnit ? 1.45 : 1.0;
+        double t;
+        const BwdFusedPlan light = light_bwd(NC, R < kMaxLightRuns ? R : kMaxLightRuns, &t);
+        if (crowd * t < least) { least = crowd * t; best = light; }
+        // (two or three runs per sequence: the walks from zero read most of q, f and grad_o once more while the
+        // memory system is busy already; 128 x 128, 85 heads of 128 chunks 513 us light, 537 us from zero, but 64 heads, four runs each, 424 and 400)
+        if (R < 4) continue;
+        const BwdFusedPlan ends = ends_bwd(NC, R);
+        const double mb = 4e-6 * dk * dv * (double)BH * ends.seg_tail;
+        t = crowd * ends.rc + 2.2 + 0.22 * ends.sub_chunks + 0.02 * ends.seg_tail + (dk == 128 && dv == 128 ? 0.045 : 0.07) * mb;
+        if (ends.R > 1 && t < least) { least = t; best = ends; }
+    }
+    return best;
+}
+
+}   // namespace hgrn2

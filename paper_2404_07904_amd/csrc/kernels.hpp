@@ -6,6 +6,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "bwd_plan.hpp"
 #include "fwd_plan.hpp"
 
 namespace hgrn2 {
@@ -213,17 +214,13 @@ hipError_t launch_bwd_grad(const SeqDims& d, const void* q, const void* f, const
                            void* grad_v, float* beta_partials, hipStream_t stream);
 // The same gradients from the forward states alone: one workgroup per run of a sequence walks the
 // run's chunks from the last to the first with the state gradient in registers (bwd_grad.hip).
-// plan_bwd_fused() cuts the sequences into R runs of rc chunks; for R > 1 the caller provides the
+// plan_bwd_fused() (bwd_plan.hpp) cuts the sequences into R runs of rc chunks; for R > 1 the caller provides the
 // state gradient at the run boundaries: a zero-start gradient sweep over the tokens after run 0, cut
 // into seg_tail sub-runs of sub_chunks chunks, and its reverse carry from grad_hT leave it in
 // run_state ([BH][seg_tail][dk][dv], entry t = at the end of sub-run t) and bound0 ([BH][dk][dv], at
 // the end of run 0).  grad_h0 may be null.  Equal-length batches only.
-// With few runs (light != 0) nothing of that is needed: every workgroup first walks the chunks after
+// With light walks (light != 0) nothing of that is needed: every workgroup first walks the chunks after
 // its own run from grad_hT, carrying only the state gradient, and the runs are cut at bnd[0..R].
-struct BwdFusedPlan { int R, rc, s_sub, sub_chunks, seg_tail, light, bnd[5]; };
-// places: the workgroups the runs are to fill (0: as many as run at once; kOnePerUnit: half as many for the
-// heads that find two places on a compute unit, fewer run boundaries to keep; 1: sequences are not cut).
-constexpr int kOnePerUnit = 256;
 BwdFusedPlan plan_bwd_fused(const SeqDims& d, int places = 0);
 hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void* q, const void* f, const void* v,
                             const void* grad_o, const void* ws_state, const float* grad_hT, float* grad_h0,
