@@ -25,6 +25,10 @@
 // The backward first runs steps 1-2 over the whole sequence to record the state entering every
 // segment (a few MB), then walks the blocks from the last to the first with the same scheme for
 // the reverse recurrence  r_t = dy_t o_t + c_t,  c_{t-1} = f_t r_t.
+// Few channels and long sequences would leave most of the chip idle: every sequence is then cut into runs of
+// whole blocks, a workgroup each (h1_runs()).  hgrn1_ends_kernel first finds (A, H) of every run from a zero state, all runs at
+// once, and a run's workgroup chains those of the runs before it (in the reverse recurrence: after it) into
+// the state it starts from.
 // Tensors are [B][N][d] (token-major, d a multiple of 64), states [B][d] fp32.
 //
 // The "act" forms take the three pre-activations of Eq. 1 instead (the outputs of the layer's
@@ -61,8 +65,10 @@ struct H1Params {
     float* hN;
     float* dh0;
     float* carry;         // [B][NBLK * kH1Segs][d]: state entering every segment (backward)
-    float* dbeta_part;    // [B][d]: every sequence's share of the gradient of beta (act backward)
+    float* dbeta_part;    // [B * R][d]: every run's share of the gradient of beta (act backward)
+    float* ends;          // R > 1: [B][R][2][d], A and H of every run, forward; those of the reverse recurrence behind them
     int B, N, d, NBLK, NCB;
+    int R, rb;            // runs of a sequence, blocks of a run
     int NBLK16;           // blocks of 16-token segments: the granularity at which the forward pass leaves the states in `carry`
 };
 
@@ -176,6 +182,115 @@ __device__ __forceinline__ f32x2 h1_gate(RAW& raw, const f32x2& kept, bool again
     }
 }
 
+// Workgroup -> sequence b, 64 channels cb, run r.
+struct H1Item { int b, cb, r; };
+__device__ __forceinline__ H1Item h1_item(const H1Params& p)
+{
+    const int id = (int)blockIdx.x, r = id % p.R, s = id / p.R;
+    return H1Item{s / p.NCB, s % p.NCB, r};
+}
+
+// The value with which run `it.r` starts, given the one the whole sequence starts with: the runs before it
+// (REVERSE: after it) applied in order, eight requested at a time (one at a time, each costs a trip to memory).
+template <bool REVERSE>
+__device__ __forceinline__ f32x2 h1_enter(const H1Params& p, const H1Item& it, size_t c0, f32x2 c)
+{
+    const int n = REVERSE ? p.R - 1 - it.r : it.r;
+    const float* ends = p.ends + (REVERSE ? (size_t)p.B * p.R * 2 * p.d : 0) + (size_t)it.b * p.R * 2 * p.d + c0;
+    constexpr int AHEAD = 8;
+    for (int k = 0; k < n; k += AHEAD) {
+        f32x2 A[AHEAD], X[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int j = min(k + u, n - 1);
+            const float* e = ends + (size_t)(REVERSE ? p.R - 1 - j : j) * 2 * p.d;
+            A[u] = *reinterpret_cast<const f32x2*>(e);
+            X[u] = *reinterpret_cast<const f32x2*>(e + p.d);
+        }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+            if (k + u < n) c = f32x2{fmaf(A[u].x, c.x, X[u].x), fmaf(A[u].y, c.y, X[u].y)};
+    }
+    return c;
+}
+
+// ---- what every run adds from zero, and the product of its gates --------------------------------
+// Forward (f and i; the last run's is not needed) or REVERSE (f, o and dy; the first run's is not needed).  Bound by the
+// latency of a block, as the walks are where it runs.  Forward / backward, us, uncut -> in runs: 8 sequences of 4328 tokens and 128
+// channels 91 / 135 -> 23 / 33, 1 of 8192 and 128 channels 157 / 247 -> 21 / 23, 1 of 1024 and 64 channels 21 / 34 -> 13 / 18.
+template <bool GATE_BF16, bool ACT, bool REVERSE>
+__global__ __launch_bounds__(kH1Threads) void hgrn1_ends_kernel(H1Params p)
+{
+    constexpr int TS = kH1SegShort, BLOCK = kH1Segs * TS;
+    constexpr int GS = GATE_BF16 ? 1 : 2;
+    __shared__ f32x2 sA[2][kH1Segs][32], sX[2][kH1Segs][32];
+    const H1Item it = h1_item(p);
+    if (it.r == (REVERSE ? 0 : p.R - 1)) return;
+    const int cp = threadIdx.x & 31, vs = threadIdx.x >> 5;
+    const size_t c0 = (size_t)it.cb * kH1Chan + 2 * cp;
+    const size_t seq = (size_t)it.b * p.N * p.d;
+    const unsigned lane_b = 2u * (unsigned)c0;
+    const f32x2 beta = ACT ? *reinterpret_cast<const f32x2*>(p.beta + c0) : f32x2{0.0f, 0.0f};
+    const int N = min(p.N, (it.r + 1) * p.rb * BLOCK);           // where the run ends
+    const int blk0 = it.r * p.rb, nblk = min(p.rb, p.NBLK - blk0);
+    typename H1Raw<GATE_BF16>::type fr[TS];
+    uint32_t xr[TS], gr[REVERSE ? TS : 1];
+    const void* xsrc = REVERSE ? p.o : p.i;
+    auto block_of = [&](int k) { return blk0 + (REVERSE ? nblk - 1 - k : k); };
+    auto load = [&](int k) {
+        const int t0 = k < nblk ? block_of(k) * BLOCK : N;       // past the last block of the run: an empty range
+        const H1Rsrc rf = h1_rows_from(p.f, seq, t0, N, p.d, 2 * GS), rx = h1_rows_from(xsrc, seq, t0, N, p.d, 2),
+                     rg = h1_rows_from(p.dy, seq, t0, REVERSE ? N : t0, p.d, 2);
+        const unsigned pitch = h1_pitch(p.d);
+#pragma unroll
+        for (int t = 0; t < TS; ++t) {
+            const unsigned off = lane_b + (unsigned)(vs * TS + t) * pitch;
+            fr[t] = h1_ld<GATE_BF16>(rf, off * GS);
+            xr[t] = h1_ld<true>(rx, off);
+            if constexpr (REVERSE) gr[t] = h1_ld<true>(rg, off);
+        }
+    };
+    load(0);
+    f32x2 A = {1.0f, 1.0f}, X = {0.0f, 0.0f};
+    for (int k = 0; k < nblk; ++k) {
+        const int t0 = block_of(k) * BLOCK + vs * TS, par = k & 1;
+        f32x2 a = {1.0f, 1.0f}, h = {0.0f, 0.0f};
+#pragma unroll
+        for (int u = 0; u < TS; ++u) {
+            const int t = REVERSE ? TS - 1 - u : u;
+            const f32x2 f = h1_first_gate<GATE_BF16, ACT>(fr[t], beta, t0 + t < N);
+            f32x2 x = h1_cvt(xr[t]);
+            a = f32x2{a.x * f.x, a.y * f.y};
+            if constexpr (REVERSE) {
+                if constexpr (ACT) x = h1_sigmoid(x);
+                const f32x2 g = h1_cvt(gr[t]);
+                h = f32x2{f.x * fmaf(g.x, x.x, h.x), f.y * fmaf(g.y, x.y, h.y)};
+            } else {
+                if constexpr (ACT) x = h1_silu(x);
+                h = f32x2{fmaf(f.x, h.x - x.x, x.x), fmaf(f.y, h.y - x.y, x.y)};
+            }
+        }
+        sA[par][vs][cp] = a;
+        sX[par][vs][cp] = h;
+        if (k + 1 < nblk) load(k + 1);
+        __syncthreads();
+        if (vs == 0) {
+#pragma unroll
+            for (int j = 0; j < kH1Segs; ++j) {
+                const int sg = REVERSE ? kH1Segs - 1 - j : j;
+                const f32x2 aj = sA[par][sg][cp], xj = sX[par][sg][cp];
+                A = f32x2{A.x * aj.x, A.y * aj.y};
+                X = f32x2{fmaf(aj.x, X.x, xj.x), fmaf(aj.y, X.y, xj.y)};
+            }
+        }
+    }
+    if (vs == 0) {
+        float* e = p.ends + (REVERSE ? (size_t)p.B * p.R * 2 * p.d : 0) + ((size_t)it.b * p.R + it.r) * 2 * p.d + c0;
+        *reinterpret_cast<f32x2*>(e) = A;
+        *reinterpret_cast<f32x2*>(e + p.d) = X;
+    }
+}
+
 // ---- forward -------------------------------------------------------------------------------------
 // Two register sets: while one block is worked on out of one set, the loads of the next block,
 // issued in one burst before that work starts, fill the other.  (A wave can wait for "all but the
@@ -188,8 +303,11 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_fwd_kernel(H1Params p)
     __shared__ f32x2 sA[2][kH1Segs][32], sH[2][kH1Segs][32];
     const int cp = threadIdx.x & 31;                             // channel pair of the workgroup's 64 channels
     const int vs = threadIdx.x >> 5;                             // segment of the block: each half-wave walks its own
-    const int b = blockIdx.x / p.NCB, cb = blockIdx.x % p.NCB;
-    const size_t c0 = (size_t)cb * kH1Chan + 2 * cp;
+    const H1Item item = h1_item(p);
+    const int b = item.b;
+    const size_t c0 = (size_t)item.cb * kH1Chan + 2 * cp;
+    // the run's blocks and the token it ends before (the whole sequence, if that is not cut)
+    const int blk0 = item.r * p.rb, blk1 = min(p.NBLK, blk0 + p.rb), N = min(p.N, blk1 * BLOCK);
     const size_t seq = (size_t)b * p.N * p.d;
     const unsigned lane_b = 2u * (unsigned)c0;                   // byte offset of this lane's pair in a bf16 row
     const f32x2 beta = ACT ? *reinterpret_cast<const f32x2*>(p.beta + c0) : f32x2{0.0f, 0.0f};
@@ -199,10 +317,10 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_fwd_kernel(H1Params p)
         uint32_t xr[TS], orw[TS];
     };
     f32x2 fa[TS];
-    // all rows of a block; a block past the end of the sequence is an empty range and moves no data
+    // all rows of a block; a block past the end of the run is an empty range and moves no data
     auto load_block = [&](Rows& s, int blk) {
-        const H1Rsrc rf = h1_rows_from(p.f, seq, blk * BLOCK, p.N, p.d, 2 * GS),
-                     ri = h1_rows_from(p.i, seq, blk * BLOCK, p.N, p.d, 2), ro = h1_rows_from(p.o, seq, blk * BLOCK, p.N, p.d, 2);
+        const H1Rsrc rf = h1_rows_from(p.f, seq, blk * BLOCK, N, p.d, 2 * GS),
+                     ri = h1_rows_from(p.i, seq, blk * BLOCK, N, p.d, 2), ro = h1_rows_from(p.o, seq, blk * BLOCK, N, p.d, 2);
         const unsigned pitch = h1_pitch(p.d);
 #pragma unroll
         for (int t = 0; t < TS; ++t) {
@@ -214,6 +332,7 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_fwd_kernel(H1Params p)
         }
     };
     f32x2 carry = p.h0 ? *reinterpret_cast<const f32x2*>(p.h0 + (size_t)b * p.d + c0) : f32x2{0.0f, 0.0f};
+    if (p.R > 1) carry = h1_enter<false>(p, item, c0, carry);
     // one block out of one register set (a block past the end: every row neutral, every store dropped)
     auto work = [&](Rows& s, int blk) {
         const int t0 = blk * BLOCK + vs * TS;
@@ -222,7 +341,7 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_fwd_kernel(H1Params p)
         f32x2 a = {1.0f, 1.0f}, h = {0.0f, 0.0f};
 #pragma unroll
         for (int t = 0; t < TS; ++t) {
-            h1_touch_gate<GATE_BF16, ACT>(s.fr[t], fa[t], beta, t0 + t < p.N);
+            h1_touch_gate<GATE_BF16, ACT>(s.fr[t], fa[t], beta, t0 + t < N);
             if constexpr (ACT) { const f32x2 x = h1_silu(h1_cvt(s.xr[t])); s.xr[t] = h1_pack(x.x, x.y); }
             const f32x2 f = h1_gate<GATE_BF16, ACT>(s.fr[t], fa[t], false), x = h1_cvt(s.xr[t]);
             a = f32x2{a.x * f.x, a.y * f.y};
@@ -236,10 +355,10 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_fwd_kernel(H1Params p)
         f32x2 mine;
         carry = h1_chain<true>(sA[par], sH[par], vs, cp, carry, mine);
         // kept for a backward pass of the same step (hgrn1_bwd_saved): 8 bytes per lane and block
-        if (p.carry && blk < p.NBLK)
+        if (p.carry && blk < blk1)
             *reinterpret_cast<f32x2*>(p.carry + ((size_t)b * p.NBLK * kH1Segs + (size_t)blk * kH1Segs + vs) * p.d + c0) = mine;
         // 3. outputs
-        const H1Rsrc ry = h1_rows_from(p.y, seq, blk * BLOCK, p.N, p.d, 2);
+        const H1Rsrc ry = h1_rows_from(p.y, seq, blk * BLOCK, N, p.d, 2);
         const unsigned pitch = h1_pitch(p.d);
         h = mine;
 #pragma unroll
@@ -255,14 +374,16 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_fwd_kernel(H1Params p)
     };
 
     Rows even, odd;
-    load_block(even, 0);
-    for (int blk = 0; blk < p.NBLK; blk += 2) {      // always whole pairs: the pass after the last block works on an empty one
+    load_block(even, blk0);
+    for (int blk = blk0;; blk += 2) {
         load_block(odd, blk + 1);
         work(even, blk);
+        if (blk + 1 >= blk1) break;
         load_block(even, blk + 2);
         work(odd, blk + 1);
+        if (blk + 2 >= blk1) break;
     }
-    if (p.hN && vs == 0) *reinterpret_cast<f32x2*>(p.hN + (size_t)b * p.d + c0) = carry;
+    if (p.hN && vs == 0 && item.r == p.R - 1) *reinterpret_cast<f32x2*>(p.hN + (size_t)b * p.d + c0) = carry;
 }
 
 // ---- backward ------------------------------------------------------------------------------------
@@ -281,11 +402,14 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
     __shared__ f32x2 sA[2][kH1Segs][32], sX[2][kH1Segs][32];      // sX: forward H, later the reverse summary
     const int cp = threadIdx.x & 31;
     const int vs = threadIdx.x >> 5;
-    const int b = blockIdx.x / p.NCB, cb = blockIdx.x % p.NCB;
-    const size_t c0 = (size_t)cb * kH1Chan + 2 * cp;
+    const H1Item item = h1_item(p);
+    const int b = item.b;
+    const size_t c0 = (size_t)item.cb * kH1Chan + 2 * cp;
+    // the run's blocks and the token it ends before (the whole sequence, if that is not cut)
+    const int blk0 = item.r * p.rb, blk1 = min(p.NBLK, blk0 + p.rb), N = min(p.N, blk1 * BLOCK);
     const size_t seq = (size_t)b * p.N * p.d;
     const unsigned lane_b = 2u * (unsigned)c0;
-    const int last_blk = p.NBLK - 1;
+    const int last_blk = blk1 - 1;
     const f32x2 beta = ACT ? *reinterpret_cast<const f32x2*>(p.beta + c0) : f32x2{0.0f, 0.0f};
     const f32x2 inv1mb = {1.0f / (1.0f - beta.x), 1.0f / (1.0f - beta.y)};
     // this thread's own slots of the saved states: written in the forward phase, read back in the reverse one
@@ -304,8 +428,8 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
     };
     {
         // first rows: of block 0 for the forward phase, of the last block when the states are given
-        const int first_tok = SAVED ? last_blk * BLOCK : 0;
-        const H1Rsrc rf = h1_rows_from(p.f, seq, first_tok, p.N, p.d, 2 * GS), ri = h1_rows_from(p.i, seq, first_tok, p.N, p.d, 2);
+        const int first_tok = (SAVED ? last_blk : blk0) * BLOCK;
+        const H1Rsrc rf = h1_rows_from(p.f, seq, first_tok, N, p.d, 2 * GS), ri = h1_rows_from(p.i, seq, first_tok, N, p.d, 2);
         const unsigned pitch = h1_pitch(p.d);
 #pragma unroll
         for (int t = 0; t < TS; ++t) {
@@ -321,17 +445,18 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
     // The last block is not followed by a refill: its gates and inputs stay in their registers,
     // which is where the reverse phase starts.
     f32x2 carry = p.h0 ? *reinterpret_cast<const f32x2*>(p.h0 + (size_t)b * p.d + c0) : f32x2{0.0f, 0.0f};
+    if (!SAVED && p.R > 1) carry = h1_enter<false>(p, item, c0, carry);
     auto forward_block = [&](int blk, auto refill_tag) {
         constexpr bool REFILL = decltype(refill_tag)::value;
         const int t0 = blk * BLOCK + vs * TS;
         const int par = it & 1;
-        const H1Rsrc rf = h1_rows_from(p.f, seq, (blk + 1) * BLOCK, p.N, p.d, 2 * GS),
-                     ri = h1_rows_from(p.i, seq, (blk + 1) * BLOCK, p.N, p.d, 2);
+        const H1Rsrc rf = h1_rows_from(p.f, seq, (blk + 1) * BLOCK, N, p.d, 2 * GS),
+                     ri = h1_rows_from(p.i, seq, (blk + 1) * BLOCK, N, p.d, 2);
         const unsigned pitch = h1_pitch(p.d);
         f32x2 a = {1.0f, 1.0f}, h = {0.0f, 0.0f};
 #pragma unroll
         for (int t = 0; t < TS; ++t) {
-            const f32x2 f = h1_first_gate<GATE_BF16, ACT>(fr[t], beta, t0 + t < p.N), x = input_of(xr[t]);
+            const f32x2 f = h1_first_gate<GATE_BF16, ACT>(fr[t], beta, t0 + t < N), x = input_of(xr[t]);
             a = f32x2{a.x * f.x, a.y * f.y};
             h = f32x2{fmaf(f.x, h.x - x.x, x.x), fmaf(f.y, h.y - x.y, x.y)};
             if constexpr (REFILL) {
@@ -350,15 +475,15 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
         ++it;
     };
     if constexpr (!SAVED) {
-        for (int blk = 0; blk < last_blk; ++blk) forward_block(blk, std::true_type{});
+        for (int blk = blk0; blk < last_blk; ++blk) forward_block(blk, std::true_type{});
         forward_block(last_blk, std::false_type{});
     }
 
     // ---- reverse phase ----
     {
         // o and dy of the last block; f and i of it are in place
-        const H1Rsrc rg = h1_rows_from(p.dy, seq, last_blk * BLOCK, p.N, p.d, 2),
-                     ro = h1_rows_from(p.o, seq, last_blk * BLOCK, p.N, p.d, 2);
+        const H1Rsrc rg = h1_rows_from(p.dy, seq, last_blk * BLOCK, N, p.d, 2),
+                     ro = h1_rows_from(p.o, seq, last_blk * BLOCK, N, p.d, 2);
         const unsigned pitch = h1_pitch(p.d);
 #pragma unroll
         for (int t = TS - 1; t >= 0; --t) {
@@ -369,8 +494,9 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
         }
     }
     f32x2 cr = p.dhN ? *reinterpret_cast<const f32x2*>(p.dhN + (size_t)b * p.d + c0) : f32x2{0.0f, 0.0f};
+    if (p.R > 1) cr = h1_enter<true>(p, item, c0, cr);
     f32x2 dbeta = {0.0f, 0.0f};
-    for (int blk = last_blk; blk >= 0; --blk, ++it) {
+    for (int blk = last_blk; blk >= blk0; --blk, ++it) {
         const int t0 = blk * BLOCK + vs * TS;
         const int par = it & 1;
         f32x2 h_in;
@@ -386,7 +512,7 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
         f32x2 a = {1.0f, 1.0f}, q = {0.0f, 0.0f};
 #pragma unroll
         for (int t = TS - 1; t >= 0; --t) {
-            h1_touch_gate<GATE_BF16, ACT>(fr[t], fa[t], beta, t0 + t < p.N);
+            h1_touch_gate<GATE_BF16, ACT>(fr[t], fa[t], beta, t0 + t < N);
             if constexpr (ACT) { const f32x2 s = h1_sigmoid(h1_cvt(orw[t])); orw[t] = h1_pack(s.x, s.y); }
             const f32x2 f = h1_gate<GATE_BF16, ACT>(fr[t], fa[t], false), g = h1_cvt(gr[t]), og = h1_cvt(orw[t]);
             a = f32x2{a.x * f.x, a.y * f.y};
@@ -414,10 +540,10 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
         // gradients, last token first; every row is refilled with the previous block's token once consumed
         // block 0 has nothing before it: a negative first token makes its refills address an empty range
         const int pb = (blk - 1) * BLOCK, cb0 = blk * BLOCK;
-        const H1Rsrc rdo = h1_rows_from(p.dout, seq, cb0, p.N, p.d, 2), rdf = h1_rows_from(p.df, seq, cb0, p.N, p.d, 2),
-                     rdi = h1_rows_from(p.di, seq, cb0, p.N, p.d, 2);
-        const H1Rsrc rf = h1_rows_from(p.f, seq, pb, p.N, p.d, 2 * GS), ri = h1_rows_from(p.i, seq, pb, p.N, p.d, 2),
-                     rg = h1_rows_from(p.dy, seq, pb, p.N, p.d, 2), ro = h1_rows_from(p.o, seq, pb, p.N, p.d, 2);
+        const H1Rsrc rdo = h1_rows_from(p.dout, seq, cb0, N, p.d, 2), rdf = h1_rows_from(p.df, seq, cb0, N, p.d, 2),
+                     rdi = h1_rows_from(p.di, seq, cb0, N, p.d, 2);
+        const H1Rsrc rf = h1_rows_from(p.f, seq, pb, N, p.d, 2 * GS), ri = h1_rows_from(p.i, seq, pb, N, p.d, 2),
+                     rg = h1_rows_from(p.dy, seq, pb, N, p.d, 2), ro = h1_rows_from(p.o, seq, pb, N, p.d, 2);
         const unsigned pitch = h1_pitch(p.d);
 #pragma unroll
         for (int t = TS - 1; t >= 0; --t) {
@@ -451,9 +577,9 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    if (p.dh0 && vs == 0) *reinterpret_cast<f32x2*>(p.dh0 + (size_t)b * p.d + c0) = cr;
+    if (p.dh0 && vs == 0 && item.r == 0) *reinterpret_cast<f32x2*>(p.dh0 + (size_t)b * p.d + c0) = cr;
     if constexpr (ACT) {
-        // this sequence's share of the gradient of beta: the sixteen segments' sums, added in order
+        // this run's share of the gradient of beta: the sixteen segments' sums, added in order
         __syncthreads();
         sX[0][vs][cp] = dbeta;
         __syncthreads();
@@ -461,18 +587,19 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
             f32x2 t = {0.0f, 0.0f};
 #pragma unroll
             for (int j = 0; j < kH1Segs; ++j) { const f32x2 u = sX[0][j][cp]; t = f32x2{t.x + u.x, t.y + u.y}; }
-            *reinterpret_cast<f32x2*>(p.dbeta_part + (size_t)b * p.d + c0) = t;
+            *reinterpret_cast<f32x2*>(p.dbeta_part + ((size_t)b * p.R + item.r) * p.d + c0) = t;
         }
     }
 }
 
-// grad_beta[c] = sum over the batch of the sequences' shares, in index order
-__global__ void hgrn1_reduce_beta_kernel(const float* part, float* grad_beta, int B, int d)
+// grad_beta[c] = sum of the shares of all sequences' runs, in index order
+__global__ void hgrn1_reduce_beta_kernel(const float* part, float* grad_beta, int rows, int d)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= d) return;
     float s = 0.0f;
-    for (int b = 0; b < B; ++b) s += part[(size_t)b * d + c];
+#pragma unroll 8
+    for (int b = 0; b < rows; ++b) s += part[(size_t)b * d + c];
     grad_beta[c] = s;
 }
 
@@ -486,21 +613,62 @@ __global__ void hgrn1_copy_state_kernel(const float* src, float* dst, size_t n)
 // ---- host side -----------------------------------------------------------------------------------
 static int h1_blocks(int N, int seg) { return (N + kH1Segs * seg - 1) / (kH1Segs * seg); }
 
-// saved segment states of the backward (sized for its shorter segments) and the per-sequence shares of grad_beta
+// Runs of a sequence of NBLK blocks.  While the channels give fewer workgroups than the chip takes, as many as find a place; a
+// run costs the launch and the walk of hgrn1_ends_kernel on top, as much as 0.8 and 0.6 blocks (5 us each), so three and fewer
+// blocks stay together, and so do sequences that would only be halved.
+constexpr int kH1Places = 256, kH1MaxRuns = 64;
+static int h1_runs(int B, int d, int NBLK, int* blocks_per_run)
+{
+    *blocks_per_run = NBLK;
+    const long long groups = (long long)B * (d / kH1Chan);
+    if (groups <= 0 || NBLK < 4) return 1;
+    long long R = kH1Places / groups;
+    if (R > NBLK) R = NBLK;
+    if (R > kH1MaxRuns) R = kH1MaxRuns;
+    if (R < 3) return 1;
+    const int rb = (int)((NBLK + R - 1) / R);
+    if (0.8 + 1.6 * rb >= NBLK) return 1;
+    *blocks_per_run = rb;
+    return (NBLK + rb - 1) / rb;
+}
+
+// saved segment states of the backward (sized for its shorter segments), the per-sequence shares of grad_beta, and, where
+// sequences are cut into runs, the runs' (A, H) in both directions and their shares of grad_beta
 static size_t h1_carry_floats(int B, int N, int d) { return (size_t)B * h1_blocks(N, kH1SegShort) * kH1Segs * d; }
 size_t hgrn1_ws_bytes(int B, int N, int d)
 {
-    return (h1_carry_floats(B, N, d) + (size_t)B * d) * sizeof(float);
+    int rb;
+    const int r16 = h1_runs(B, d, h1_blocks(N, kH1SegShort), &rb), r32 = h1_runs(B, d, h1_blocks(N, kH1SegLong), &rb);
+    const int R = r16 > r32 ? r16 : r32;
+    return (h1_carry_floats(B, N, d) + (size_t)B * d + (R > 1 ? (size_t)B * R * 5 * d : 0)) * sizeof(float);
 }
 
-static H1Params h1_params(int B, int N, int d, int seg, void* ws)
+// in_place: the state a sequence ends in replaces the one it starts from, which every run reads: a workgroup takes the whole sequence
+static H1Params h1_params(int B, int N, int d, int seg, void* ws, bool in_place)
 {
     H1Params p = {};
     p.B = B; p.N = N; p.d = d; p.NBLK = h1_blocks(N, seg); p.NCB = d / kH1Chan;
     p.NBLK16 = h1_blocks(N, kH1SegShort);
     p.carry = static_cast<float*>(ws);
     p.dbeta_part = p.carry + h1_carry_floats(B, N, d);
+    p.R = h1_runs(B, d, p.NBLK, &p.rb);
+    if (in_place) { p.R = 1; p.rb = p.NBLK; }
+    if (p.R > 1) {
+        p.ends = p.dbeta_part + (size_t)B * d;
+        p.dbeta_part = p.ends + (size_t)B * p.R * 4 * d;
+    }
     return p;
+}
+
+// (A, H) of every run, in segments of 16 tokens whatever the walk takes
+template <bool REVERSE>
+static void launch_h1_ends(H1Params p, int seg, bool gate_bf16, hipStream_t stream)
+{
+    p.rb *= seg / kH1SegShort;
+    p.NBLK = p.NBLK16;
+    auto kern = p.beta ? (gate_bf16 ? hgrn1_ends_kernel<true, true, REVERSE> : hgrn1_ends_kernel<false, true, REVERSE>)
+                       : (gate_bf16 ? hgrn1_ends_kernel<true, false, REVERSE> : hgrn1_ends_kernel<false, false, REVERSE>);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.B * p.NCB * p.R)), dim3(kH1Threads), 0, stream, p);
 }
 
 hipError_t launch_hgrn1_fwd(int B, int N, int d, bool gate_bf16, const void* f, const void* i, const void* o,
@@ -512,9 +680,10 @@ hipError_t launch_hgrn1_fwd(int B, int N, int d, bool gate_bf16, const void* f, 
                                    stream, h0, hN, (size_t)B * d);
         return hipGetLastError();
     }
-    H1Params p = h1_params(B, N, d, kH1SegShort, ws);
+    H1Params p = h1_params(B, N, d, kH1SegShort, ws, h0 && h0 == hN);
     p.f = f; p.i = i; p.o = o; p.beta = beta; p.h0 = h0; p.y = y; p.hN = hN;
-    const dim3 grid((unsigned)(B * p.NCB));
+    if (p.R > 1) launch_h1_ends<false>(p, kH1SegShort, gate_bf16, stream);
+    const dim3 grid((unsigned)(B * p.NCB * p.R));
     auto kern = beta ? (gate_bf16 ? hgrn1_fwd_kernel<true, true> : hgrn1_fwd_kernel<false, true>)
                      : (gate_bf16 ? hgrn1_fwd_kernel<true, false> : hgrn1_fwd_kernel<false, false>);
     hipLaunchKernelGGL(kern, grid, dim3(kH1Threads), 0, stream, p);
@@ -533,9 +702,14 @@ hipError_t launch_hgrn1_bwd(int B, int N, int d, bool gate_bf16, const void* f, 
                                               static_cast<const float*>(nullptr), dbeta, 0, d);
         return hipGetLastError();
     }
-    H1Params p = h1_params(B, N, d, beta ? kH1SegShort : kH1SegLong, ws);
+    const int seg = beta ? kH1SegShort : kH1SegLong;
+    H1Params p = h1_params(B, N, d, seg, ws, dhN && dhN == dh0);
     p.f = f; p.i = i; p.o = o; p.beta = beta; p.dy = dy; p.h0 = h0; p.dhN = dhN; p.df = df; p.di = di; p.dout = dout; p.dh0 = dh0;
-    const dim3 grid((unsigned)(B * p.NCB));
+    if (p.R > 1) {
+        if (!states_saved) launch_h1_ends<false>(p, seg, gate_bf16, stream);
+        launch_h1_ends<true>(p, seg, gate_bf16, stream);
+    }
+    const dim3 grid((unsigned)(B * p.NCB * p.R));
     auto kern = states_saved
                     ? (beta ? (gate_bf16 ? hgrn1_bwd_kernel<true, true, true> : hgrn1_bwd_kernel<false, true, true>)
                             : (gate_bf16 ? hgrn1_bwd_kernel<true, false, true> : hgrn1_bwd_kernel<false, false, true>))
@@ -543,7 +717,7 @@ hipError_t launch_hgrn1_bwd(int B, int N, int d, bool gate_bf16, const void* f, 
                             : (gate_bf16 ? hgrn1_bwd_kernel<true, false, false> : hgrn1_bwd_kernel<false, false, false>));
     hipLaunchKernelGGL(kern, grid, dim3(kH1Threads), 0, stream, p);
     if (beta && dbeta)
-        hipLaunchKernelGGL(hgrn1_reduce_beta_kernel, dim3((d + 255) / 256), dim3(256), 0, stream, p.dbeta_part, dbeta, B, d);
+        hipLaunchKernelGGL(hgrn1_reduce_beta_kernel, dim3((d + 255) / 256), dim3(256), 0, stream, p.dbeta_part, dbeta, B * p.R, d);
     return hipGetLastError();
 }
 

@@ -1,0 +1,51 @@
+"""HGRN1 sequences cut into runs (few channels, four blocks of 256 tokens or more): the runs' contributions from zero, chained
+into the state every run starts from, forwards and in reverse; lengths around the edges of blocks and runs, both gate types,
+with and without states, activations formed inside, and the final state in the place of the initial one (not cut then).
+Against the fp64 oracle, tolerances as for the uncut walk."""
+import pytest
+import torch
+
+import oracle
+from paper_2404_07904_amd import binding
+from gpu_util import TOL, check, dev, host
+from test_gpu_hgrn1 import make, make_act, run, run_act
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 769, 64), (1, 1024, 320), (2, 1025, 128), (3, 2047, 64), (1, 2100, 1280), (8, 4328, 128), (1, 8192, 64)]
+
+
+@pytest.mark.parametrize("B,N,d", SHAPES)
+def test_hgrn1_in_runs(B, N, d):
+    print("\n[hgrn1 runs] B=%d N=%d d=%d" % (B, N, d), flush=True)
+    gate = "f32" if N % 2 else "bf16"
+    f, i, o, dy, h0, dhN = make(7000 + N, B, N, d, lb=0.9, gate_dtype=gate)
+    if d == 320:
+        h0 = dhN = None
+    run(f, i, o, dy, h0, dhN, gate_dtype=gate)
+
+
+@pytest.mark.parametrize("B,N,d", SHAPES)
+def test_hgrn1_act_in_runs(B, N, d):
+    print("\n[hgrn1 act runs] B=%d N=%d d=%d" % (B, N, d), flush=True)
+    gate = "bf16" if N % 2 else "f32"
+    run_act(*make_act(7100 + N, B, N, d, gate_dtype=gate), gate_dtype=gate)
+
+
+def test_states_continued_in_place():
+    f, i, o, dy, h0, dhN = make(7200, 2, 1300, 128)
+    fd, idv, od, dyd, s, g = dev(f, "bf16"), dev(i, "bf16"), dev(o, "bf16"), dev(dy, "bf16"), dev(h0), dev(dhN)
+    start = s.clone()
+    y, hN = binding.hgrn1_fwd(fd, idv, od, s, hN=s)
+    gf, gi, go = (torch.empty_like(t) for t in (fd, idv, od))
+    need = binding.hgrn1_workspace_bytes(2, 1300, 128)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    p = binding._ptr
+    rc = binding.lib().hgrn1_bwd(2, 1300, 128, binding.HGRN2_BF16, binding.HGRN2_BF16, p(fd), p(idv), p(od), p(start), p(dyd), p(g),
+                                 p(gf), p(gi), p(go), p(g), p(ws), need, binding._stream())
+    assert rc == 0
+    torch.cuda.synchronize()
+    ry, rh = oracle.hgrn1_fwd(f, i, o, h0)
+    rf, ri, ro, rh0 = oracle.hgrn1_bwd(f, i, o, dy, h0, dhN)
+    check("y", host(y), ry, TOL["bf16"]); check("hN", host(s), rh, 3e-5)
+    check("df", host(gf), rf, TOL["bf16"]); check("dh0", host(g), rh0, 3e-5)
