@@ -222,6 +222,23 @@ template <> __device__ __forceinline__ void store_pair_t<float>(float* base, siz
     *reinterpret_cast<f32x2*>(base + idx) = h;
 }
 
+// the same with non-temporal stores
+template <typename T> __device__ __forceinline__ void stream_pair_t(T* base, size_t idx, float a, float b);
+template <> __device__ __forceinline__ void stream_pair_t<__bf16>(__bf16* base, size_t idx, float a, float b)
+{
+    bf16x2 h;
+    h.x = (__bf16)a;
+    h.y = (__bf16)b;
+    __builtin_nontemporal_store(__builtin_bit_cast(uint32_t, h), reinterpret_cast<uint32_t*>(base + idx));
+}
+template <> __device__ __forceinline__ void stream_pair_t<float>(float* base, size_t idx, float a, float b)
+{
+    f32x2 h;
+    h.x = a;
+    h.y = b;
+    __builtin_nontemporal_store(h, reinterpret_cast<f32x2*>(base + idx));
+}
+
 // ---- batched row loads ---------------------------------------------------------------------------
 // RW consecutive rows of one channel pair, kept RAW (bf16 pairs as a 32-bit pattern in .x) so
 // that all loads of a batch are issued back to back and converted only when first used.  Row
