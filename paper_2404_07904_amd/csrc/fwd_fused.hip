@@ -576,7 +576,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         }
     };
 
-    // O leaves through registers that stay reserved for the whole pass (see the end of stage B):
+    // O leaves with non-temporal stores (nothing here reads it; 32 x 16 heads of 128, 2048 tokens: 232 -> 224 us) through registers that stay reserved for the whole pass (see the end of stage B):
     // a global store reads its data registers late, and overwriting them earlier would make the
     // wave wait for the store, and with it for every prefetch issued before it, to complete.
     u32x4 obuf[C * VPR / NT];
@@ -588,7 +588,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
             const int grow = c.row0 + row;
             obuf[k] = *reinterpret_cast<const u32x4*>(Ost + (size_t)row * PO + cv * 8);
             if (grow >= c.lo && grow < c.hi)       // also false for the chunk "-1" of the first pass
-                *reinterpret_cast<u32x4*>(og + seq_v + ((size_t)c.tok0 + grow) * ld_v + dv0 + cv * 8) = obuf[k];
+                __builtin_nontemporal_store(obuf[k], reinterpret_cast<u32x4*>(og + seq_v + ((size_t)c.tok0 + grow) * ld_v + dv0 + cv * 8));
         }
     };
 
