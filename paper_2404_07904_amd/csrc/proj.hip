@@ -9,20 +9,12 @@
 // as ONE bf16 matrix product [M, d] x [d, 3d] on the matrix cores with bias and activation applied
 // to the fp32 accumulators, written token-major ([B][N][H][dh] = [M][d]), which is the layout the
 // recurrence takes with HGRN2_LAYOUT_BNHD: neither the pre-activations of q nor the gate ever
-// reach memory.  The reverse mode is two more products, dx = dA W3 and dW3 = dA^T x, on the same
-// kernel, after one element-wise pass that forms dA = (dz, dv SiLU'(a_v), dq q (1 - q)) and the
-// bias gradients.
+// reach memory.  The reverse mode is two more products, dx = dA W3 and dW3 = dA^T x, after one element-wise pass that
+// forms dA = (dz, dv SiLU'(a_v), dq q (1 - q)) and the bias gradients.
 //
-// Two matrix kernels, both with a 256 x 256 tile of the result per workgroup and the accumulators
-// kept transposed (result column in the register index), so that four consecutive result columns of
-// a row leave a lane together:
-//   gemm_dl_kernel  both operands k-contiguous (x W3^T; dA W3 with W3 transposed beforehand): four
-//                   waves of 128 x 128 or eight of 128 x 64, LDS stages filled by direct
-//                   global -> LDS loads (see there);
-//   gemm_kernel     an operand whose contraction index is the slow axis of its array (both operands
-//                   of dW3 = dA^T x) keeps its natural orientation in LDS and is read with LDS
-//                   transpose loads: eight waves (2 x 4, each 128 x 64), K in steps of 64 through
-//                   double-buffered LDS tiles filled from registers loaded two steps ahead.
+// One matrix kernel (gemm_nt_kernel) for all three: both operands with the contraction index contiguous, which x W3^T has as it
+// is; W3 and x are transposed first, and the element-wise pass writes dA in both orders (dW3 straight from dA and x,
+// with LDS transpose reads, took 516 us at 16384 tokens and width 2048, this way 324 + 50).
 #include "../../include/hgrn2.h"
 #include "common.hpp"
 #include "kernels.hpp"
@@ -30,24 +22,18 @@
 
 namespace hgrn2 {
 
-constexpr int kGemmThreads = 512;
-constexpr int BM = 256, BN = 256, BK = 64;
-constexpr int PKT = BK + 8;        // pitch of a tile kept [row][k]
-constexpr int PXT = 256 + 32;      // pitch of a tile kept [k][row]: a transpose read takes 4 rows x 64 bytes per half wave, so rows 16 banks apart
-constexpr int kTileElems = (BM * PKT > BK * PXT) ? BM * PKT : BK * PXT;
 constexpr int kBandRows = 4;     // row blocks per band of the workgroup -> tile order
-constexpr int PST = BN + 8;        // pitch of the bf16 staging tile of the epilogue
 
 enum GemmEpilogue { kEpiProj = 0, kEpiPlain = 1, kEpiFloat = 2 };
 
 struct GemmParams {
-    const __bf16* A;      // [M][K] (lda = K stride) or, A_KM, [K][M]
-    const __bf16* B;      // [N][K] or, B_KM, [K][N]
+    const __bf16* A;      // [M][K], row stride lda
+    const __bf16* B;      // [N][K], row stride ldb
     long long lda, ldb;
-    int M, N, K;
+    int M, N, K;          // K a multiple of 64, N of the tile width
     // outputs
     __bf16* C;            // kEpiPlain: [M][N] bf16, row stride ldc
-    float* Cf;            // kEpiFloat: [M][N] fp32, row stride ldc
+    float* Cf;            // kEpiFloat: [splits][M][N] fp32, row stride ldc: the splits' shares of the contraction
     long long ldc;
     // kEpiProj: N = 3 d; columns [0, d) -> z, [d, 2d) -> v (and a_v), [2d, 3d) -> q, each [M][d]
     const float* bias;
@@ -55,187 +41,265 @@ struct GemmParams {
     int d;
 };
 
-template <bool KM, int TR = 256>
-__device__ __forceinline__ void tile_load(u32x4 (&r)[4], const __bf16* src, long long ld, int row0, int k0, int n_rows, int n_k, int tid)
-{
-    // TR x 64 elements = TR * 8 vectors of 16 bytes: four per thread (TR = 256) or three (192)
-#pragma unroll
-    for (int j = 0; j < TR / 64; ++j) {
-        const int vi = tid + kGemmThreads * j;
-        if constexpr (!KM) {
-            const int row = vi >> 3, kc = (vi & 7) * 8;
-            const int rc = min(row0 + row, n_rows - 1);          // rows past the end re-read the last one (never stored)
-            r[j] = *reinterpret_cast<const u32x4*>(src + (size_t)rc * ld + k0 + kc);
-        } else {
-            const int kr = vi / (TR / 8), xc = (vi % (TR / 8)) * 8;
-            const int kk = min(k0 + kr, n_k - 1);
-            const int xr = min(row0 + xc, n_rows - 8);           // whole vectors stay inside the row (n_rows is a multiple of 8)
-            u32x4 x = *reinterpret_cast<const u32x4*>(src + (size_t)kk * ld + xr);
-            if (k0 + kr >= n_k) x = u32x4{0u, 0u, 0u, 0u};     // a contraction index past the end contributes nothing
-            r[j] = x;
-        }
-    }
-}
+// s_waitcnt: all but the youngest n vector loads have landed, and all LDS reads
+constexpr int vm_lgkm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; }
 
-template <bool KM, int TR = 256>
-__device__ __forceinline__ void tile_store(__bf16* tile, const u32x4 (&r)[4], int tid)
+// ---- the products: C = A B^T, both operands k-contiguous ------------------------------------------------------------
+// A workgroup computes a TM x TN tile, WM x WN waves side by side (KG groups of them share the steps' four k-quarters between
+// them and add up at the end: small tiles of long contractions).  K advances in steps of 64, whole 128-byte lines of every row,
+// through a ring of NS tiles in LDS (A and B in turn) that `global_load_lds` fills, 16 bytes per lane, no registers in
+// between.  Such a load writes the 64 lanes' vectors to consecutive LDS addresses, so a tile row is 128 bytes with no padding; the
+// 16-byte piece c of row r is kept at position c ^ ((r >> 1) & 7), which the loading lane realises by fetching the piece that
+// belongs at its position, and 16 consecutive rows then cover all 64 banks for any piece.
+//   One barrier per step, before its last quarter: by then every wave has the last fragments of the step in registers, so the
+// barrier retires the step's two tiles, which are refilled, and publishes those of the next step (each wave has waited for its
+// own loads of them; loads are counted by hand, the compiler does not track them).  With NS = 5 the tile of A is requested 1 3/4 steps
+// ahead, that of B 3/4.  Fragments are requested right after the first MFMAs of the quarter before (the compiler waits for
+// all outstanding LDS reads before an MFMA that needs one), and the refill goes out one load at a time between the MFMAs.
+//   16384 x 2048 x 6144 with bias, activations and four outputs: 350-363 us = 1.14-1.18 PFLOP/s (an earlier kernel with steps of 32, half
+// lines, 372-400); dx 315 us = 1.31 PFLOP/s (369), dW3 324 (516).  What bounds the 256 x 256 tile (builds that leave work out): 217 us are MFMAs and LDS reads
+// (1.9 PFLOP/s), 85 us the loads' way into LDS next to 192 KB of LDS reads a step (loads that never miss L2 save 14 us, no wait for them nothing), 38 us
+// the epilogue.  Four waves of 128 x 128, with a third fewer LDS reads but one wave per SIMD: 365 us.
+template <int EPI, int TM, int TN, int WM, int WN, int KG, int NS>
+__global__ __launch_bounds__(64 * WM * WN * KG, WM * WN * KG == 4 ? 1 : 2) void gemm_nt_kernel(GemmParams p)
 {
-#pragma unroll
-    for (int j = 0; j < TR / 64; ++j) {
-        const int vi = tid + kGemmThreads * j;
-        if constexpr (!KM) *reinterpret_cast<u32x4*>(tile + (size_t)(vi >> 3) * PKT + (vi & 7) * 8) = r[j];
-        else               *reinterpret_cast<u32x4*>(tile + (size_t)(vi / (TR / 8)) * PXT + (vi % (TR / 8)) * 8) = r[j];
-    }
-}
-
-template <bool KM>
-__device__ __forceinline__ bf16x8 tile_frag(const __bf16* tile, int x0, int ks, int lane)
-{
-    if constexpr (!KM) return Mma<__bf16>::load(tile + (size_t)(x0 + (lane & 31)) * PKT + 16 * ks + 8 * (lane >> 5));
-    else               return Mma<__bf16>::load_kmajor(tile, PXT, 16 * ks, x0, lane);
-}
-
-// TBM: rows of the tile, 256 or 192 (wave tiles of 128 or 96 rows).  The narrower tile is for
-// products whose tile count would otherwise leave compute units idle (dW3 at width 2048: 24 x 8
-// tiles of 256 rows on 256 units, but 32 x 8 of 192 rows).
-template <bool A_KM, bool B_KM, int EPI, int TBM = 256>
-__global__ __launch_bounds__(kGemmThreads) void gemm_kernel(GemmParams p)
-{
-    static_assert(TBM == 256 || (TBM == 192 && EPI == kEpiFloat), "the staged epilogues assume 256 rows");
-    constexpr int NI = TBM / 64;                                    // 32-row MFMA tiles per wave
+    constexpr int NWV = WM * WN * KG, THREADS = 64 * NWV;
+    static_assert((NWV == 8 || NWV == 4) && 4 % KG == 0 && NS >= 5, "four or eight waves");
+    constexpr int SLOT = (TM > TN ? TM : TN) * 128;               // bytes of a slot of the ring
+    constexpr int LA = TM / 8 / NWV, LB = TN / 8 / NWV;           // load instructions per wave for a tile of A, of B
+    constexpr int NI = TM / WM / 32, NJ = TN / WN / 32, KPW = 4 / KG;
     typedef Mma<__bf16> M;
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    typedef const __attribute__((address_space(1))) void* global_ptr;
     extern __shared__ __align__(16) char smem[];
-    __bf16* At = reinterpret_cast<__bf16*>(smem);                   // [2][tile]
-    __bf16* Bt = At + 2 * kTileElems;                               // [2][tile]
-
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = w >> 2, wn = w & 3;                              // wave tile: rows (TBM / 2) wm .., columns 64 wn ..
-    // Workgroup -> tile.  Workgroup ids go round the eight XCDs (id % 8), each with an L2 of its
-    // own, so the ids are first renumbered so that an XCD holds a contiguous range, and the range is
-    // laid over the tile grid in bands of kBandRows row blocks walked column by column: the 32
-    // workgroups an XCD runs together then cover about 4 x 8 tiles and share their operand panels
-    // in that XCD's L2 instead of each XCD streaming whole panels of its own.
-    const int n_bn = p.N / BN, n_bm = (p.M + TBM - 1) / TBM;
+    const int wn = w % WN, wm = w / WN % WM, kg = w / (WN * WM);
+    const int n_bn = p.N / TN, n_bm = (p.M + TM - 1) / TM;
     int bm, bn;
     {
         const int grid = (int)gridDim.x, id = (int)blockIdx.x;
         const int per = grid / kXcds, rem = grid - per * kXcds, x = id % kXcds;
-        const int t = x * per + min(x, rem) + id / kXcds;             // position in the XCD-contiguous order
+        const int t = x * per + min(x, rem) + id / kXcds;
         const int band_tiles = kBandRows * n_bn, band = t / band_tiles, in_band = t - band * band_tiles;
-        const int rows = min(kBandRows, n_bm - band * kBandRows);     // the last band may be shorter
+        const int rows = min(kBandRows, n_bm - band * kBandRows);
         bn = in_band / rows;
         bm = band * kBandRows + in_band - bn * rows;
     }
-    const int m0 = bm * TBM, n0 = bn * BN;
-
-    // accumulators, transposed: acc[i][j][v] = C[m0 + (TBM / 2) wm + 32 i + lane % 32][n0 + 64 wn + 32 j + 8 (v/4) + 4 g + v%4]
-    f32x16 acc[NI][2];
+    const int m0 = bm * TM, n0 = bn * TN;
+    f32x16 acc[NI][NJ];
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    // Load instruction j of a wave: eight rows, of A from row a0(j) on.  A row of dW3's operands is 2 bytes per token and may be long, so
+    // the rows before are part of the scalar address; rows past the end of A re-read its last one (never stored).
+    const bool whole = m0 + TM <= p.M;
+    const char* abase = reinterpret_cast<const char*>(p.A) + (size_t)m0 * p.lda * 2;
+    const char* bbase = reinterpret_cast<const char*>(p.B) + (size_t)n0 * p.ldb * 2;
+    auto a0 = [&](int j) { return whole ? 8 * (LA * w + j) : 0; };
+    uint32_t ao[LA], bo[LB];
+#pragma unroll
+    for (int j = 0; j < LA; ++j) {
+        const int row = 8 * (LA * w + j) + (lane >> 3);
+        ao[j] = (uint32_t)(min(row, p.M - 1 - m0) - a0(j)) * (uint32_t)(p.lda * 2) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+    }
+#pragma unroll
+    for (int j = 0; j < LB; ++j) {
+        const int row = 8 * (LB * w + j) + (lane >> 3);
+        bo[j] = (uint32_t)(lane >> 3) * (uint32_t)(p.ldb * 2) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+    }
+    // the steps of 64 of this workgroup's share of the contraction
+    const int steps = p.K / 64, first = (int)((long long)blockIdx.y * steps / gridDim.y);
+    const int nk = (int)((long long)(blockIdx.y + 1) * steps / gridDim.y) - first;
+    // load instruction j of this wave for the A (B) tile of k-step ks into `slot`
+    auto load_a = [&](int slot, int ks, int j) {
+        const char* s = abase + (size_t)a0(j) * p.lda * 2 + (size_t)(first + min(ks, nk - 1)) * 128;
+        __builtin_amdgcn_global_load_lds((global_ptr)(s + ao[j]), (lds_ptr)(smem + slot * SLOT + 8 * (LA * w + j) * 128), 16, 0, 0);
+    };
+    auto load_b = [&](int slot, int ks, int j) {
+        const char* s = bbase + (size_t)(8 * (LB * w + j)) * p.ldb * 2 + (size_t)(first + min(ks, nk - 1)) * 128;
+        __builtin_amdgcn_global_load_lds((global_ptr)(s + bo[j]), (lds_ptr)(smem + slot * SLOT + 8 * (LB * w + j) * 128), 16, 0, 0);
+    };
+    const int sw = (r32 >> 1) & 7;
+    auto read_frags = [&](bf16x8 (&fa)[NI], bf16x8 (&fb)[NJ], int sa, int sb, int kk) {
+        const int off = r32 * 128 + (((2 * kk + g) ^ sw) << 4);
+        const char* a = smem + sa * SLOT + (TM / WM) * wm * 128 + off;
+        const char* b = smem + sb * SLOT + (TN / WN) * wn * 128 + off;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(b + 32 * j * 128);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(a + 32 * i * 128);
+    };
+    constexpr int NM = NI * NJ, HEAD = NM > 2 ? 2 : 1;
+    bf16x8 fa[2][NI], fb[2][NJ];
+    auto multiply = [&](int par, int from, int to) {
+#pragma unroll
+        for (int t = 0; t < NM; ++t)
+            if (t >= from && t < to) M::mma(acc[t / NJ][t % NJ], fb[par][t % NJ], fa[par][t / NJ]);
+    };
+        // halves 0 .. NS - 2 (A of step 0, B of step 0, A of step 1, ...)
+#pragma unroll
+    for (int h = 0; h < NS - 1; ++h)
+#pragma unroll
+        for (int j = 0; j < ((h & 1) ? LB : LA); ++j) { if (h & 1) load_b(h, h >> 1, j); else load_a(h, h >> 1, j); }
+    constexpr int FIRST = (NS - 3) / 2 * (LA + LB) + ((NS - 3) % 2 ? LA : 0);
+    __builtin_amdgcn_s_waitcnt(vm_lgkm(FIRST));
+    __builtin_amdgcn_s_barrier();
+    auto wrap = [](int s) { return s >= NS ? s - NS : s; };
+    int s0 = 0;                                   // slot of A of the step, B behind it
+    read_frags(fa[0], fb[0], 0, 1, KPW * kg);
+    // the loads that refill the two slots a step has freed: tile 2 k + NS, then 2 k + NS + 1 (even tiles are A's)
+    constexpr int L1 = (NS & 1) ? LB : LA, L2 = (NS & 1) ? LA : LB;
+    auto refill = [&](int slot, int k, int j) {   // j = 0 .. L1 + L2 - 1
+        const int sl = j < L1 ? slot : wrap(slot + 1), h = NS + (j < L1 ? 0 : 1);
+        if (h & 1) load_b(sl, k + (h >> 1), j < L1 ? j : j - L1); else load_a(sl, k + (h >> 1), j < L1 ? j : j - L1);
+    };
+    // a step: phases 0 .. KPW - 1; the loads behind the barrier of step k go out in its last phase and the first phases of the next
+    constexpr int NL = L1 + L2, LAST = L1;
+    for (int k = 0; k < nk; ++k) {
+        const int sn = wrap(s0 + 2), sp = wrap(s0 + NS - 2);       // slots of the next and of the previous step
+#pragma unroll
+        for (int ph = 0; ph < KPW; ++ph) {
+            const int par = KPW == 1 ? 0 : (ph & 1), nx = KPW == 1 ? 1 : par ^ 1;
+            const bool last = ph == KPW - 1;
+            if (last) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (KPW == 1) {
+#pragma unroll
+                    for (int j = LAST; j < NL; ++j) refill(sp, k - 1, j);
+                }
+                __builtin_amdgcn_s_waitcnt(vm_lgkm((NS & 1) ? (NS - 5) / 2 * (LA + LB) + L2 : (NS - 4) / 2 * (LA + LB)));
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            multiply(par, 0, HEAD);
+            __builtin_amdgcn_sched_barrier(0);
+            if (last) read_frags(fa[nx], fb[nx], sn, wrap(sn + 1), KPW * kg);
+            else read_frags(fa[nx], fb[nx], s0, wrap(s0 + 1), KPW * kg + ph + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (last) {
+#pragma unroll
+                for (int j = 0; j < LAST; ++j) {
+                    multiply(par, HEAD + (NM - HEAD) * j / LAST, HEAD + (NM - HEAD) * (j + 1) / LAST);
+                    __builtin_amdgcn_sched_barrier(0);
+                    refill(s0, k, j);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else if (ph == 0) {
+                constexpr int REST = NL - LAST;
+#pragma unroll
+                for (int j = 0; j < REST; ++j) {
+                    multiply(par, HEAD + (NM - HEAD) * j / REST, HEAD + (NM - HEAD) * (j + 1) / REST);
+                    __builtin_amdgcn_sched_barrier(0);
+                    refill(sp, k - 1, LAST + j);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                multiply(par, HEAD, NM);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if constexpr (KPW == 1) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) fa[0][i] = fa[1][i];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) fb[0][j] = fb[1][j];
+        }
+        s0 = sn;
+    }
+    __builtin_amdgcn_s_waitcnt(vm_lgkm(0));
+    __builtin_amdgcn_s_barrier();
 
-    // Tiles travel global memory -> registers -> LDS.  The registers are loaded TWO steps ahead (two
-    // register sets, the loop unrolled by two so that each set is a fixed group of registers): one
-    // step of matrix work is shorter than a trip to memory.  Loads are unconditional (steps past
-    // the end fetch the last one again and are never stored).
-    u32x4 ra[2][4], rb[2][4];
-    const int nk = (p.K + BK - 1) / BK;
-    auto fetch = [&](int set, int kb) {
-        const int k0 = min(kb, nk - 1) * BK;
-        tile_load<A_KM, TBM>(ra[set], p.A, p.lda, m0, k0, p.M, p.K, tid);
-        tile_load<B_KM>(rb[set], p.B, p.ldb, n0, k0, p.N, p.K, tid);
-    };
-    auto stash = [&](int set, int buf) {
-        tile_store<A_KM, TBM>(At + (size_t)buf * kTileElems, ra[set], tid);
-        tile_store<B_KM>(Bt + (size_t)buf * kTileElems, rb[set], tid);
-    };
-    auto multiply = [&](int buf) {
-        const __bf16* Ac = At + (size_t)buf * kTileElems;
-        const __bf16* Bc = Bt + (size_t)buf * kTileElems;
-#pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            bf16x8 fa[NI], fb[2];
-#pragma unroll
-            for (int i = 0; i < NI; ++i) fa[i] = tile_frag<A_KM>(Ac, (TBM / 2) * wm + 32 * i, ks, lane);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) fb[j] = tile_frag<B_KM>(Bc, 64 * wn + 32 * j, ks, lane);
+    // the groups' shares of the sum, added in order
+    if constexpr (KG > 1) {
+        float* red = reinterpret_cast<float*>(smem);
+        constexpr int TILE = NI * NJ * 16 * 64;
+        if (kg > 0) {
+            float* d = red + (size_t)((kg - 1) * WM * WN + w % (WM * WN)) * TILE + lane * 4;
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) M::mma(acc[i][j], fb[j], fa[i]);       // rows = result columns
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        *reinterpret_cast<f32x4*>(d + ((i * NJ + j) * 4 + c) * 256) = f32x4{acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
         }
-    };
-    fetch(0, 0);
-    stash(0, 0);
-    fetch(0, 1);
-    fetch(1, 2);
-    __syncthreads();
-    for (int kb = 0; kb < nk; kb += 2) {
-        multiply(0);                      // step kb
-        stash(0, 1);                      // step kb + 1 (fetched two steps ago)
-        fetch(0, kb + 3);
         __syncthreads();
-        if (kb + 1 < nk) multiply(1);     // step kb + 1
-        stash(1, 0);                      // step kb + 2
-        fetch(1, kb + 4);
-        __syncthreads();
+        if (kg == 0) {
+#pragma unroll
+            for (int k = 0; k < KG - 1; ++k) {
+                const float* d = red + (size_t)(k * WM * WN + w) * TILE + lane * 4;
+#pragma unroll
+                for (int i = 0; i < NI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const f32x4 t = *reinterpret_cast<const f32x4*>(d + ((i * NJ + j) * 4 + c) * 256);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[i][j][4 * c + e] += t[e];
+                        }
+            }
+        }
     }
-
-    // ---------------- epilogue ----------------
+    // acc[i][j][v] = C[m0 + (TM / WM) wm + 32 i + lane % 32][n0 + (TN / WN) wn + 32 j + 8 (v/4) + 4 g + v%4]
     if constexpr (EPI == kEpiFloat) {
-        // fp32 result: four consecutive columns of a row per store
+        if (kg == 0) {
 #pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const int row = m0 + (TBM / 2) * wm + 32 * i + r32;
+            for (int i = 0; i < NI; ++i) {
+                const int row = m0 + (TM / WM) * wm + 32 * i + r32;
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int col = n0 + 64 * wn + 32 * j + 8 * c + 4 * g;
-                    if (row < p.M)
-                        *reinterpret_cast<f32x4*>(p.Cf + (size_t)row * p.ldc + col) =
-                            f32x4{acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
-                }
+                    for (int c = 0; c < 4; ++c)
+                        if (row < p.M)
+                            *reinterpret_cast<f32x4*>(p.Cf + ((size_t)blockIdx.y * p.M + row) * p.ldc + n0 + (TN / WN) * wn + 32 * j + 8 * c + 4 * g) =
+                                f32x4{acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
+            }
         }
-        return;
     } else {
-        // bf16 result(s): bias and activation on the accumulators, then through an LDS tile [256][256]
-        // so that rows leave as whole 16-byte vectors.  A column block lies inside one of z, v, q.
-        // A second pass does the same for the pre-activation of v when the caller keeps it.
-        __bf16* St = reinterpret_cast<__bf16*>(smem);               // the operand tiles are free now (barrier above)
+        constexpr int PS = TN + 8, VPR = TN / 8;
+        __bf16* St = reinterpret_cast<__bf16*>(smem + (KG > 1 ? (KG - 1) * TM * TN * 4 : 0));
         int which = 0;
         if constexpr (EPI == kEpiProj) which = n0 / p.d;
         const int n_pass = (EPI == kEpiProj && which == 1 && p.av != nullptr) ? 2 : 1;
         for (int pass = 0; pass < n_pass; ++pass) {
+            // 0: the sum itself (plus bias in the projections); 1: SiLU; 2: sigmoid
+            const int mode = (EPI != kEpiProj || pass == 1 || which == 0) ? 0 : which;
+            auto stage_tile = [&](auto MODE) {
+                constexpr int md = decltype(MODE)::value;
 #pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                const int row = 128 * wm + 32 * i + r32;
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < NJ; ++j)
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        const int col = 64 * wn + 32 * j + 8 * c + 4 * g;
-                        float x[4];
+                        const int col = (TN / WN) * wn + 32 * j + 8 * c + 4 * g;
+                        f32x4 b = {0.0f, 0.0f, 0.0f, 0.0f};
+                        if constexpr (EPI == kEpiProj) b = *reinterpret_cast<const f32x4*>(p.bias + n0 + col);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) x[e] = acc[i][j][4 * c + e];
-                        if constexpr (EPI == kEpiProj) {
-                            const f32x4 b = *reinterpret_cast<const f32x4*>(p.bias + n0 + col);
+                        for (int i = 0; i < NI; ++i) {
+                            const int row = (TM / WM) * wm + 32 * i + r32;
+                            bf16x4 pk;
 #pragma unroll
                             for (int e = 0; e < 4; ++e) {
-                                const float a = x[e] + b[e];
-                                const float sg = fast_rcp(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * a));
-                                x[e] = (pass == 1 || which == 0) ? a : (which == 1) ? a * sg : sg;
+                                const float a = acc[i][j][4 * c + e] + b[e];
+                                float y = a;
+                                if constexpr (md != 0) {
+                                    const float sg = fast_rcp(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * a));
+                                    y = (md == 1) ? a * sg : sg;
+                                }
+                                pk[e] = (__bf16)y;
                             }
+                            *reinterpret_cast<bf16x4*>(St + (size_t)row * PS + col) = pk;
                         }
-                        bf16x4 pk;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) pk[e] = (__bf16)x[e];
-                        *reinterpret_cast<bf16x4*>(St + (size_t)row * PST + col) = pk;
                     }
+            };
+            if (kg == 0) {
+                if (mode == 0)      stage_tile(std::integral_constant<int, 0>());
+                else if (mode == 1) stage_tile(std::integral_constant<int, 1>());
+                else                stage_tile(std::integral_constant<int, 2>());
             }
             __syncthreads();
             __bf16* out;
@@ -248,325 +312,151 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(GemmParams p)
             } else {
                 out = p.C; ld = p.ldc; c0 = n0;
             }
-            for (int vi = tid; vi < BM * (BN / 8); vi += kGemmThreads) {       // 256 rows x 32 vectors
-                const int row = vi >> 5, vc = (vi & 31) * 8;
-                if (m0 + row < p.M)
-                    *reinterpret_cast<u32x4*>(out + (size_t)(m0 + row) * ld + c0 + vc) =
-                        *reinterpret_cast<const u32x4*>(St + (size_t)row * PST + vc);
+            constexpr int VECS = TM * VPR / THREADS, BATCH = VECS < 8 ? VECS : 8;
+#pragma unroll
+            for (int v0 = 0; v0 < VECS; v0 += BATCH) {
+                u32x4 buf[BATCH];
+#pragma unroll
+                for (int k = 0; k < BATCH; ++k) {
+                    const int vi = tid + (v0 + k) * THREADS;
+                    buf[k] = *reinterpret_cast<const u32x4*>(St + (size_t)(vi / VPR) * PS + (vi % VPR) * 8);
+                }
+#pragma unroll
+                for (int k = 0; k < BATCH; ++k) {
+                    const int vi = tid + (v0 + k) * THREADS, row = vi / VPR;
+                    if (m0 + row < p.M) *reinterpret_cast<u32x4*>(out + (size_t)(m0 + row) * ld + c0 + (vi % VPR) * 8) = buf[k];
+                }
             }
             __syncthreads();
         }
     }
 }
 
-constexpr size_t kGemmLds = (size_t)4 * kTileElems * sizeof(__bf16);
-static_assert(kGemmLds <= 160 * 1024, "LDS budget");
-static_assert((size_t)BM * PST * sizeof(__bf16) <= kGemmLds, "the staging tile of the epilogue aliases the operand tiles");
-
-template <bool A_KM, bool B_KM, int EPI, int TBM = 256>
-static hipError_t launch_gemm(const GemmParams& p, hipStream_t stream)
+template <int EPI, int TM, int TN, int WM, int WN, int KG, int NS>
+static hipError_t launch_nt(const GemmParams& p, int splits, hipStream_t stream)
 {
-    auto kern = gemm_kernel<A_KM, B_KM, EPI, TBM>;
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)kGemmLds);
+    constexpr size_t ring = (size_t)NS * (TM > TN ? TM : TN) * 128;
+    constexpr size_t tail = (size_t)(KG - 1) * TM * TN * 4 + (EPI == kEpiFloat ? 0 : (size_t)TM * (TN + 8) * 2);
+    constexpr size_t lds = ring > tail ? ring : tail;
+    static_assert(lds <= 160 * 1024, "LDS budget");
+    auto kern = gemm_nt_kernel<EPI, TM, TN, WM, WN, KG, NS>;
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds);
     if (e != hipSuccess) return e;
-    const unsigned grid = (unsigned)(((p.M + TBM - 1) / TBM) * (p.N / BN));
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kGemmThreads), kGemmLds, stream, p);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(((p.M + TM - 1) / TM) * (p.N / TN)), splits), dim3(64 * WM * WN * KG), lds, stream, p);
     return hipGetLastError();
 }
 
-// ---- the same product for operands that are both k-contiguous, fed by direct global -> LDS loads ----
-// (x W3^T of the forward pass; dA W3 of the reverse pass once W3 has been transposed.)  Four waves
-// (2 x 2), each owning 128 x 128 of the 256 x 256 tile as 4 x 4 MFMA tiles (an operand fragment read
-// from LDS feeds four MFMAs; the accumulators fill the 256 accumulation registers, the wave is
-// alone on its SIMD and overlaps its own LDS reads, loads and MFMAs), or eight waves (2 x 4) of
-// 128 x 64, two per SIMD (half again as many fragment reads, but a wave's waits and its epilogue
-// are covered by its neighbour: the projection with its activation epilogue is 5% faster this way,
-// the plain product 4% slower).  K advances in steps of 32
-// through FIVE LDS stages that are filled by `global_load_lds` (16 bytes per lane, no registers in
-// between) four steps ahead.  Such a load writes the 64 lanes' vectors to consecutive LDS
-// addresses, so a tile row is 64 bytes with no padding; bank conflicts are avoided by a swizzle
-// instead: the 16-byte piece c of row r is kept at position c ^ ((r >> 2) & 3), which the loading
-// lane realises by fetching the piece that belongs at its position, and 16 consecutive rows then
-// cover all 64 banks for any piece.  One barrier per step: it ends the reads of the stage that
-// is refilled next and publishes the stage that is read next (each wave has waited for its own
-// loads of that stage; loads are counted by hand, the compiler does not track them).
-
-constexpr int DBK = 32;                                  // k per stage
-constexpr int kDlStages = 5;                            // 5 x 32 KB: all of a compute unit's LDS
-constexpr int kDlTileBytes = 256 * DBK * 2;              // one operand's tile of one stage
-constexpr int kDlStageBytes = 2 * kDlTileBytes;
-constexpr size_t kDlLds = ((size_t)kDlStages * kDlStageBytes > (size_t)BM * PST * sizeof(__bf16))
-                              ? (size_t)kDlStages * kDlStageBytes : (size_t)BM * PST * sizeof(__bf16);
-static_assert(kDlLds <= 160 * 1024, "LDS budget");
-// s_waitcnt with only the vector-memory counter set (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
-constexpr int vmcnt_only(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0f70; }
-
-// NWV waves: 4 (2 x 2, each 128 x 128, alone on its SIMD) or 8 (2 x 4, each 128 x 64, two per SIMD,
-// which can fill each other's waits).
-template <int EPI, int NWV>
-__global__ __launch_bounds__(64 * NWV) void gemm_dl_kernel(GemmParams p)
+// Which tile a product takes, and (fp32 result) into how many shares its contraction is cut: by what they take, us, fitted to 100 to
+// 16384 tokens at widths 256 to 2048.  256 x 256 has the best rate but needs 256 tiles to fill the chip; 128 x 128 finds two
+// places on a compute unit, and so does 64 x 64, which has the shortest steps where a few workgroups have to do (a step
+// is 1.5 / 1.1 / 0.45 us with all places taken, 1.1 / 0.45 / 0.26 us on a unit of its own).
+// 575 tokens of width 1024, 256 / 128 / 64: projection 28.0 / 12.1 / 12.0 us, dx 59 / 28 / 17; 2048 tokens, projection 29.9 / 21.2 / 30.1;
+// 16384 tokens, projection 104 / 123 / 218; width 2048 363 / 432 / 721.
+struct NtPlan { int tile, splits; };
+static double nt_time(int tile, long long tiles, double steps)
 {
-    static_assert(NWV == 4 || NWV == 8, "wave layouts: 2 x 2 or 2 x 4");
-    constexpr int THREADS = 64 * NWV;
-    constexpr int WNG = NWV / 2;                 // waves side by side
-    constexpr int TN = BN / WNG, NJ = TN / 32;   // columns of a wave's tile; its 32-column MFMA tiles
-    constexpr int LP = 16 / NWV;                 // load pairs (one instruction of A, one of B) per wave and stage
-    constexpr int WROWS = 256 / NWV;             // tile rows a wave loads
-    typedef Mma<__bf16> M;
-    typedef __attribute__((address_space(3))) void* lds_ptr;
-    typedef const __attribute__((address_space(1))) void* global_ptr;
-    extern __shared__ __align__(16) char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = w / WNG, wn = w % WNG;                           // wave tile: rows 128 wm .., columns TN wn ..
-    const int n_bn = p.N / BN, n_bm = (p.M + BM - 1) / BM;
-    int bm, bn;
-    {   // workgroup -> tile, as in gemm_kernel
-        const int grid = (int)gridDim.x, id = (int)blockIdx.x;
-        const int per = grid / kXcds, rem = grid - per * kXcds, x = id % kXcds;
-        const int t = x * per + min(x, rem) + id / kXcds;
-        const int band_tiles = kBandRows * n_bn, band = t / band_tiles, in_band = t - band * band_tiles;
-        const int rows = min(kBandRows, n_bm - band * kBandRows);
-        bn = in_band / rows;
-        bm = band * kBandRows + in_band - bn * rows;
+    if (tile == 256) {
+        const long long rest = tiles % 256;
+        return 3.5 + (double)(tiles / 256) * (1.5 * steps + 10.0) + (rest == 0 ? 0.0 : rest <= 192 ? 1.1 * steps + 9.0 : 1.5 * steps + 10.0);
     }
-    const int m0 = bm * BM, n0 = bn * BN;
-
-    // accumulators, transposed: acc[i][j][v] = C[m0 + 128 wm + 32 i + lane % 32][n0 + TN wn + 32 j + 8 (v/4) + 4 g + v%4]
-    f32x16 acc[4][NJ];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-    // Loads: instruction j of wave w fills rows WROWS w + 16 j .. + 15 of a tile (1 KB); lane l sits at
-    // row l / 4, position l % 4 and fetches piece (l % 4) ^ ((row >> 2) & 3) = (l & 3) ^ ((l >> 4) & 3).
-    // Rows past the end of A re-read its last row (never stored).
-    const int piece = (lane & 3) ^ ((lane >> 4) & 3);
-    const char* ga[LP];
-    const char* gb[LP];
-#pragma unroll
-    for (int j = 0; j < LP; ++j) {
-        const int ra = min(m0 + WROWS * w + 16 * j + (lane >> 2), p.M - 1);
-        const int rb = n0 + WROWS * w + 16 * j + (lane >> 2);
-        ga[j] = reinterpret_cast<const char*>(p.A) + ((size_t)ra * p.lda) * 2 + piece * 16;
-        gb[j] = reinterpret_cast<const char*>(p.B) + ((size_t)rb * p.ldb) * 2 + piece * 16;
+    const double full = tile == 128 ? 1.12 : 0.45, most = tile == 128 ? 0.95 : 0.45, half = tile == 128 ? 0.45 : 0.26, end = tile == 128 ? 2.0 : 1.0;
+    const long long rest = tiles % 512;
+    return 3.5 + (double)(tiles / 512) * (full * steps + end) + (rest == 0 ? 0.0 : (rest <= 256 ? half : most) * steps + end);
+}
+static NtPlan plan_nt(int M, int N, int K, bool may_split)
+{
+    NtPlan best = {256, 1};
+    double least = 1e30;
+    const int steps = K / 64;
+    for (int tile = 64; tile <= 256; tile *= 2) {
+        // (fp32 results take 192 rows instead of 256: 3 d rows are a multiple of both, and 32 x 8 tiles fill the chip at width 2048 where 24 x 8 do not)
+        const int rows = tile == 256 && may_split ? 192 : tile;
+        const long long tiles = (long long)((M + rows - 1) / rows) * (N / tile);
+        for (int s = 1; s <= 16 && (s == 1 || (may_split && steps >= 8 * s)); s *= 2) {
+            // (the shares are written and read once more, and added up by a launch of their own)
+            const double share_mb = 4e-6 * M * (double)N * s;
+            if (s > 1 && share_mb > 64.0) break;
+            const double t = nt_time(tile, tiles * s, (double)steps / s) * (rows == 192 ? 0.8 : 1.0) + (s > 1 ? 4.0 + share_mb * 0.5 : 0.0);
+            if (t < least) { least = t; best = NtPlan{tile, s}; }
+        }
     }
-    const int nk = p.K / DBK;
-    // loads j (one of A, one of B) of this wave for stage `stage`, k-step kb
-    auto issue_pair = [&](int stage, int kb, int j) {
-        const size_t ko = (size_t)min(kb, nk - 1) * (DBK * 2);       // steps past the end fetch the last one again (never read)
-        char* sa = smem + stage * kDlStageBytes + w * (WROWS * DBK * 2);
-        __builtin_amdgcn_global_load_lds((global_ptr)(ga[j] + ko), (lds_ptr)(sa + j * 1024), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((global_ptr)(gb[j] + ko), (lds_ptr)(sa + kDlTileBytes + j * 1024), 16, 0, 0);
-    };
-    auto issue = [&](int stage, int kb) {
-#pragma unroll
-        for (int j = 0; j < LP; ++j) issue_pair(stage, kb, j);
-    };
-    // fragment of 32 rows x 16 k: lane (r32, g) reads piece 2 kk + g of its row
-    const int frag_off0 = r32 * 64 + ((0 + g) ^ ((r32 >> 2) & 3)) * 16;
-    const int frag_off1 = r32 * 64 + ((2 + g) ^ ((r32 >> 2) & 3)) * 16;
-    // Fragments of k-half kk (16 of the stage's 32 k) of a stage: four of A, NJ of B.
-    auto read_frags = [&](bf16x8 (&fa)[4], bf16x8 (&fb)[NJ], int stage, int kk) {
-        const char* sa = smem + stage * kDlStageBytes + (128 * wm) * 64 + (kk ? frag_off1 : frag_off0);
-        const char* sb = smem + stage * kDlStageBytes + kDlTileBytes + (TN * wn) * 64 + (kk ? frag_off1 : frag_off0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(sa + 32 * i * 64);
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(sb + 32 * j * 64);
-    };
-    // the NM MFMAs of one k-half, in parts: the first kHead of them, then HP segments, each followed
-    // by one pair of the stage refill's loads
-    constexpr int NM = 4 * NJ, kHead = 2, HP = LP / 2, SEG = (NM - kHead) / HP;
-    auto multiply = [&](const bf16x8 (&fa)[4], const bf16x8 (&fb)[NJ], int from, int to) {
-#pragma unroll
-        for (int t = 0; t < NM; ++t)
-            if (t >= from && t < to) M::mma(acc[t / NJ][t % NJ], fb[t % NJ], fa[t / NJ]);   // rows = result columns
-    };
-    // the rest of a half-step after its first MFMAs: segments of MFMAs, each followed by load pair
-    // pair0 + h of stage `stage`, k-step kf
-    auto rest_and_refill = [&](const bf16x8 (&fa)[4], const bf16x8 (&fb)[NJ], int stage, int kf, int pair0) {
-#pragma unroll
-        for (int h = 0; h < HP; ++h) {
-            multiply(fa, fb, kHead + h * SEG, h + 1 == HP ? NM : kHead + (h + 1) * SEG);
-            __builtin_amdgcn_sched_barrier(0);
-            issue_pair(stage, kf, pair0 + h);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-
-    // The loop is software-pipelined by hand (the scheduling barriers keep the order).  The compiler
-    // waits for ALL outstanding LDS reads before an MFMA that needs any of them (the direct loads
-    // make it give up counting), so fragments are requested right after the first MFMAs of the
-    // previous batch have been issued: by the time the next batch needs them, the remaining MFMAs of
-    // this one have covered the LDS latency, and nothing else is outstanding when the wait comes.
-    //   second-half fragments of stage kb   <- during the MFMAs of its first half
-    //   first-half fragments of stage kb+1  <- during the MFMAs of the second half of stage kb
-    // In between: this wave's loads of stage kb+1 have landed (those of the stages after may be in
-    // flight), a barrier publishes stage kb+1 and retires stage kb-1, whose buffer is refilled.
-    bf16x8 fa0[4], fb0[NJ], fa1[4], fb1[NJ];
-    constexpr int S = kDlStages;
-#pragma unroll
-    for (int st = 0; st < S - 1; ++st) issue(st, st);
-    __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * LP * (S - 2)));    // stage 0 (each stage: 2 LP loads per lane)
-    __builtin_amdgcn_s_barrier();
-    read_frags(fa0, fb0, 0, 0);
-    int s_cur = 0;                                               // kb % S
-    for (int kb = 0; kb < nk; ++kb) {
-        const int s_next = s_cur + 1 == S ? 0 : s_cur + 1;
-        const int s_fill = s_cur == 0 ? S - 1 : s_cur - 1;       // (kb + S - 1) % S: the stage read before this one
-        // The refill of a retired stage goes out a pair of loads at a time between the MFMAs, spread
-        // over the two half-steps that follow the barrier (a wave that issues its loads in one burst
-        // stalls on the full memory queue, and its MFMAs with it): the first half of the pairs behind
-        // the barrier of this step, the second half in the first half of the next one.
-        multiply(fa0, fb0, 0, kHead);
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(fa1, fb1, s_cur, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        {
-            // second half of the refill begun in the step before (first step: stage S - 2 once more)
-            const int s_prev = s_fill == 0 ? S - 1 : s_fill - 1, k_prev = kb + S - 2;
-            rest_and_refill(fa0, fb0, s_prev, k_prev, HP);
-        }
-        __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * LP * (S - 3)));   // stage kb + 1 (the S - 3 younger ones may be in flight)
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(fa1, fb1, 0, kHead);
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(fa0, fb0, s_next, 0);                         // (after the last step: unused)
-        __builtin_amdgcn_sched_barrier(0);
-        rest_and_refill(fa1, fb1, s_fill, kb + S - 1, 0);
-        s_cur = s_next;
-    }
-    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));           // no load may land in what the epilogue reuses
-    __builtin_amdgcn_s_barrier();
-
-    // ---------------- epilogue: as in gemm_kernel, for this wave layout ----------------
-    // With one wave per SIMD (NWV = 4) nothing hides the latency of this part, so it does no more than it
-    // must: the activation is chosen by a wave-uniform branch around the loops (the gate's block
-    // needs none, the second pass of v's block only the bias), and the copy from the staging tile to
-    // global memory moves eight vectors per thread at a time.
-    __bf16* St = reinterpret_cast<__bf16*>(smem);
-    int which = 0;
-    if constexpr (EPI == kEpiProj) which = n0 / p.d;
-    const int n_pass = (EPI == kEpiProj && which == 1 && p.av != nullptr) ? 2 : 1;
-    for (int pass = 0; pass < n_pass; ++pass) {
-        // 0: the sum itself (plus bias in the projections); 1: SiLU; 2: sigmoid
-        const int mode = (EPI != kEpiProj || pass == 1 || which == 0) ? 0 : which;
-        auto stage_tile = [&](auto MODE) {
-            constexpr int md = decltype(MODE)::value;
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int col = TN * wn + 32 * j + 8 * c + 4 * g;
-                    f32x4 b = {0.0f, 0.0f, 0.0f, 0.0f};
-                    if constexpr (EPI == kEpiProj) b = *reinterpret_cast<const f32x4*>(p.bias + n0 + col);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int row = 128 * wm + 32 * i + r32;
-                        bf16x4 pk;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float a = acc[i][j][4 * c + e] + b[e];
-                            float y = a;
-                            if constexpr (md != 0) {
-                                const float sg = fast_rcp(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * a));
-                                y = (md == 1) ? a * sg : sg;
-                            }
-                            pk[e] = (__bf16)y;
-                        }
-                        *reinterpret_cast<bf16x4*>(St + (size_t)row * PST + col) = pk;
-                    }
-                }
-        };
-        if (mode == 0)      stage_tile(std::integral_constant<int, 0>());
-        else if (mode == 1) stage_tile(std::integral_constant<int, 1>());
-        else                stage_tile(std::integral_constant<int, 2>());
-        __syncthreads();
-        __bf16* out;
-        long long ld;
-        int c0;
-        if constexpr (EPI == kEpiProj) {
-            out = (pass == 1) ? p.av : (which == 0) ? p.z : (which == 1) ? p.v : p.q;
-            ld = p.d;
-            c0 = n0 - which * p.d;
-        } else {
-            out = p.C; ld = p.ldc; c0 = n0;
-        }
-        // 256 rows x 32 vectors of 16 bytes; a wave's 64 lanes cover two whole rows (1 KB contiguous in all)
-        constexpr int kBatch = 8;
-        for (int v0 = tid; v0 < BM * (BN / 8); v0 += THREADS * kBatch) {
-            u32x4 buf[kBatch];
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int vi = v0 + k * THREADS;
-                buf[k] = *reinterpret_cast<const u32x4*>(St + (size_t)(vi >> 5) * PST + (vi & 31) * 8);
-            }
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int vi = v0 + k * THREADS, row = vi >> 5;
-                if (m0 + row < p.M) *reinterpret_cast<u32x4*>(out + (size_t)(m0 + row) * ld + c0 + (vi & 31) * 8) = buf[k];
-            }
-        }
-        __syncthreads();
-    }
+    return best;
 }
 
-template <int EPI, int NWV>
-static hipError_t launch_gemm_dl(const GemmParams& p, hipStream_t stream)
+template <int EPI>
+static hipError_t launch_product(const GemmParams& p, const NtPlan& plan, hipStream_t stream)
 {
-    auto kern = gemm_dl_kernel<EPI, NWV>;
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)kDlLds);
-    if (e != hipSuccess) return e;
-    const unsigned grid = (unsigned)(((p.M + BM - 1) / BM) * (p.N / BN));
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NWV), kDlLds, stream, p);
-    return hipGetLastError();
+    if (plan.tile == 64) return launch_nt<EPI, 64, 64, 1, 2, 4, 9>(p, plan.splits, stream);
+    if (plan.tile == 128) return launch_nt<EPI, 128, 128, 2, 4, 1, 5>(p, plan.splits, stream);
+    if constexpr (EPI == kEpiFloat) return launch_nt<EPI, 192, 256, 2, 4, 1, 5>(p, plan.splits, stream);
+    else return launch_nt<EPI, 256, 256, 2, 4, 1, 5>(p, 1, stream);
+}
+
+// out = the sum of the shares, in order (n a multiple of 4)
+__global__ __launch_bounds__(256) void proj_sum_kernel(const float* shares, float* out, size_t n, int splits)
+{
+    const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (i >= n) return;
+    f32x4 s = *reinterpret_cast<const f32x4*>(shares + i);
+#pragma unroll 4
+    for (int k = 1; k < splits; ++k) s += *reinterpret_cast<const f32x4*>(shares + (size_t)k * n + i);
+    *reinterpret_cast<f32x4*>(out + i) = s;
 }
 
 // ---- element-wise pass of the reverse mode -------------------------------------------------------
-// dA[t][0:d] = dz, dA[t][d:2d] = dv * SiLU'(a_v), dA[t][2d:3d] = dq * q (1 - q); and per block of 128
-// rows the column sums of dA (the bias gradients are their sum over the row blocks, in order).
+// dA[t][0:d] = dz, dA[t][d:2d] = dv * SiLU'(a_v), dA[t][2d:3d] = dq * q (1 - q), in this order (dx) and transposed, tokens padded
+// with zeros to whole steps of 64 (dW3); and per block of ROWS tokens the column sums of dA (the bias gradients are
+// their sum over the row blocks, in order).
 //
-// Bound by memory (16 bytes in and out per row and column triple, one reciprocal and exponential).  A
+// Bound by memory (16 bytes in and out per row and column triple, one reciprocal and exponential, and 6 for the transposed copy).  A
 // workgroup takes 256 columns, which lie inside one of the three blocks (d is a multiple of 256), so what
 // is read is chosen by a uniform branch; a thread holds V neighbouring columns and every V-th part of the
 // rows, kActBatch rows requested at a time; the V parts' column sums meet in LDS, in order.
 // V = 8 (16-byte vectors) needs 16-byte aligned arrays; others take V = 2.
-// 16384 rows at width 2048, 540 MB: 130.8 us with one column pair a thread and one row at a time -> 94.6 us = 5.7 TB/s.
-constexpr int kActRows = 128, kActCols = 256, kActBatch = 4;
+// 16384 rows at width 2048: 540 MB 94 us without the transposed copy, 741 MB 120 us = 6.2 TB/s with it.
+constexpr int kActCols = 256, kActBatch = 4;
+constexpr int kActPitch = kActCols + 8;
 
-template <int V>
+// 8 consecutive rows (tokens) of one column of a [rows][pitch] LDS tile: lane -> column x0 + lane % 16, rows k0 + 8 (lane / 16) ..
+__device__ __forceinline__ bf16x8 column_piece(const __bf16* tile, int pitch, int k0, int x0, int lane)
+{
+    typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+    const int i16 = lane & 15;
+    const __bf16* p = tile + (k0 + 8 * (lane >> 4) + (i16 >> 2)) * pitch + x0 + 4 * (i16 & 3);
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p));
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + 4 * pitch));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+template <int V, int ROWS>
 __global__ __launch_bounds__(256) void proj_dact_kernel(const __bf16* dz, const __bf16* dv, const __bf16* dq, const __bf16* q,
-                                                         const __bf16* av, __bf16* dA, float* partial, int M, int d)
+                                                         const __bf16* av, __bf16* dA, __bf16* dAt, float* partial, int M, int Mp, int d)
 {
     typedef __bf16 vec __attribute__((ext_vector_type(V)));
-    constexpr int kPart = kActRows / V;                                   // rows of a thread
-    static_assert(kPart % kActBatch == 0, "whole batches");
+    constexpr int kPart = ROWS / V, kBatch = kPart < kActBatch ? kPart : kActBatch;      // rows of a thread; requested at a time
+    static_assert(kPart % kBatch == 0 && ROWS % 32 == 0, "whole batches");
     __shared__ float sums[V][kActCols];
+    extern __shared__ __align__(16) char smem[];
+    __bf16* tile = reinterpret_cast<__bf16*>(smem);                       // [ROWS][kActPitch]
     const int tx = (int)threadIdx.x % (kActCols / V), ty = (int)threadIdx.x / (kActCols / V);
     const int col0 = (int)blockIdx.x * kActCols, which = col0 / d;
     const int c = col0 - which * d + tx * V;                              // of the block's own arrays
-    const int r0 = (int)blockIdx.y * kActRows + ty * kPart, r1 = min(M, r0 + kPart);
+    const int t0 = (int)blockIdx.y * ROWS, r0 = t0 + ty * kPart;
     const __bf16* gsrc = which == 0 ? dz : which == 1 ? dv : dq;
     const __bf16* asrc = which == 1 ? av : q;
     float s[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) s[e] = 0.0f;
-    for (int rb = r0; rb < r1; rb += kActBatch) {
-        vec u[kActBatch], a[kActBatch];
+    for (int rb = r0; rb < r0 + kPart; rb += kBatch) {
+        vec u[kBatch], a[kBatch];
 #pragma unroll
-        for (int k = 0; k < kActBatch; ++k) {
+        for (int k = 0; k < kBatch; ++k) {
             const size_t e = (size_t)min(rb + k, M - 1) * d + c;          // rows past the end re-read the last one (never used)
             u[k] = *reinterpret_cast<const vec*>(gsrc + e);
             if (which != 0) a[k] = *reinterpret_cast<const vec*>(asrc + e);
         }
 #pragma unroll
-        for (int k = 0; k < kActBatch; ++k) {
-            if (rb + k >= M) break;
+        for (int k = 0; k < kBatch; ++k) {
             vec h;
 #pragma unroll
             for (int e = 0; e < V; ++e) {
@@ -579,10 +469,11 @@ __global__ __launch_bounds__(256) void proj_dact_kernel(const __bf16* dz, const 
                     const float x = (float)a[k][e];
                     g = g * x * (1.0f - x);
                 }
-                h[e] = (__bf16)g;
+                h[e] = rb + k < M ? (__bf16)g : (__bf16)0.0f;             // tokens past the end contribute nothing
                 s[e] += (float)h[e];                                      // the value the products will see (rounded to bf16)
             }
-            *reinterpret_cast<vec*>(dA + (size_t)(rb + k) * 3 * d + col0 + tx * V) = h;
+            if (rb + k < M) *reinterpret_cast<vec*>(dA + (size_t)(rb + k) * 3 * d + col0 + tx * V) = h;
+            *reinterpret_cast<vec*>(tile + (size_t)(rb + k - t0) * kActPitch + tx * V) = h;
         }
     }
 #pragma unroll
@@ -592,46 +483,86 @@ __global__ __launch_bounds__(256) void proj_dact_kernel(const __bf16* dz, const 
 #pragma unroll
     for (int k = 0; k < V; ++k) t += sums[k][threadIdx.x];
     partial[(size_t)blockIdx.y * 3 * d + col0 + (int)threadIdx.x] = t;
+    // the transposed copy, 64 bytes of 16 columns a store
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int k0 = 0; k0 < ROWS; k0 += 32) {
+            const bf16x8 v = column_piece(tile, kActPitch, k0, 64 * w + 16 * x, lane);
+            const int tok = t0 + k0 + 8 * (lane >> 4);
+            if (tok < Mp) *reinterpret_cast<bf16x8*>(dAt + (size_t)(col0 + 64 * w + 16 * x + (lane & 15)) * Mp + tok) = v;
+        }
 }
 
-template <int V>
-static hipError_t launch_proj_dact(const void* dz, const void* dv, const void* dq, const void* q, const void* av, __bf16* dA,
-                                   float* partial, int M, int d, hipStream_t stream)
+// Tokens of a workgroup: 64, or 32 while there are few (a workgroup's batches wait for memory one after the other: 204 tokens of
+// width 256 in 128s 10.2 us, in 32s 5.4)
+static int act_rows(int M, int d) { return (long long)(3 * d / kActCols) * ((M + 63) / 64) < 256 ? 32 : 64; }
+
+template <int V, int ROWS>
+static hipError_t launch_dact_rows(const void* dz, const void* dv, const void* dq, const void* q, const void* av, __bf16* dA,
+                                   __bf16* dAt, float* partial, int M, int Mp, int d, hipStream_t stream)
 {
-    hipLaunchKernelGGL(proj_dact_kernel<V>, dim3(3 * d / kActCols, (M + kActRows - 1) / kActRows), dim3(256), 0, stream,
+    constexpr size_t lds = (size_t)ROWS * kActPitch * sizeof(__bf16);
+    hipLaunchKernelGGL((proj_dact_kernel<V, ROWS>), dim3(3 * d / kActCols, Mp / ROWS), dim3(256), lds, stream,      // the padding of the transposed copy included
                        static_cast<const __bf16*>(dz), static_cast<const __bf16*>(dv), static_cast<const __bf16*>(dq),
-                       static_cast<const __bf16*>(q), static_cast<const __bf16*>(av), dA, partial, M, d);
+                       static_cast<const __bf16*>(q), static_cast<const __bf16*>(av), dA, dAt, partial, M, Mp, d);
     return hipGetLastError();
 }
-
-// dst [cols][rows] = src [rows][cols]^T (bf16), 64 x 64 tiles through LDS; rows and cols multiples of 64.
-__global__ __launch_bounds__(256) void proj_transpose_kernel(const __bf16* src, __bf16* dst, int rows, int cols)
+template <int V>
+static hipError_t launch_proj_dact(const void* dz, const void* dv, const void* dq, const void* q, const void* av, __bf16* dA,
+                                   __bf16* dAt, float* partial, int M, int Mp, int d, hipStream_t stream)
 {
-    __shared__ __bf16 tile[64][64 + 2];
-    const int r0 = (int)blockIdx.y * 64, c0 = (int)blockIdx.x * 64;
-    const int tx = (int)threadIdx.x & 63, ty = (int)threadIdx.x >> 6;
-    for (int r = ty; r < 64; r += 4) tile[r][tx] = src[(size_t)(r0 + r) * cols + c0 + tx];
+    return act_rows(M, d) == 32 ? launch_dact_rows<V, 32>(dz, dv, dq, q, av, dA, dAt, partial, M, Mp, d, stream)
+                                : launch_dact_rows<V, 64>(dz, dv, dq, q, av, dA, dAt, partial, M, Mp, d, stream);
+}
+
+// What the products of the reverse mode need besides dA, in one launch: workgroups 0 .. n_w3 - 1 transpose W3, the next n_x transpose x,
+// the rest add up the bias gradients.
+
+// dst [cols][ld] = src [rows][cols]^T (bf16), 64 x 64 tiles through LDS; cols and ld multiples of 64, rows past the end read as zero.
+__device__ __forceinline__ void transpose_tile(__bf16* tile, const __bf16* src, __bf16* dst, int rows, int cols, int ld, int block)
+{
+    constexpr int P = 64 + 32;                     // rows 16 banks apart for the transpose reads
+    const int r0 = block / (cols / 64) * 64, c0 = block % (cols / 64) * 64, tid = (int)threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int r = (tid >> 3) + 32 * k, c = (tid & 7) * 8;
+        u32x4 v = *reinterpret_cast<const u32x4*>(src + (size_t)min(r0 + r, rows - 1) * cols + c0 + c);
+        if (r0 + r >= rows) v = u32x4{0u, 0u, 0u, 0u};
+        *reinterpret_cast<u32x4*>(tile + r * P + c) = v;
+    }
     __syncthreads();
-    for (int c = ty; c < 64; c += 4) dst[(size_t)(c0 + c) * rows + r0 + tx] = tile[tx][c];
+    const int lane = tid & 63, w = tid >> 6;
+#pragma unroll
+    for (int k0 = 0; k0 < 64; k0 += 32)
+        *reinterpret_cast<bf16x8*>(dst + (size_t)(c0 + 16 * w + (lane & 15)) * ld + r0 + k0 + 8 * (lane >> 4)) =
+            column_piece(tile, P, k0, 16 * w, lane);
 }
 
 // db[c] = sum over the row blocks of partial[block][c], in a fixed order: 32 columns per workgroup,
 // the blocks in eight consecutive slices (one per 32 threads) that are then added in order.
 constexpr int kBiasCols = 32, kBiasSlices = 8;
 
-__global__ __launch_bounds__(kBiasCols * kBiasSlices) void proj_bias_grad_kernel(const float* partial, float* db, int n_blocks, int n)
+__global__ __launch_bounds__(kBiasCols * kBiasSlices) void proj_prepare_kernel(const __bf16* w3, __bf16* w3t, int n_w3, const __bf16* x,
+                                                                               __bf16* xt, int n_x, int M, int Mp, int d,
+                                                                               const float* partial, float* db, int n_blocks)
 {
-    __shared__ float part[kBiasSlices][kBiasCols];
-    const int tx = (int)threadIdx.x % kBiasCols, ty = (int)threadIdx.x / kBiasCols;
-    const int c = (int)blockIdx.x * kBiasCols + tx;
+    __shared__ __align__(16) __bf16 tile[64 * (64 + 32)];
+    const int id = (int)blockIdx.x;
+    if (id < n_w3) { transpose_tile(tile, w3, w3t, 3 * d, d, 3 * d, id); return; }
+    if (id < n_w3 + n_x) { transpose_tile(tile, x, xt, M, d, Mp, id - n_w3); return; }
+    float (*part)[kBiasCols] = reinterpret_cast<float (*)[kBiasCols]>(tile);
+    const int n = 3 * d, tx = (int)threadIdx.x % kBiasCols, ty = (int)threadIdx.x / kBiasCols;
+    const int c = (id - n_w3 - n_x) * kBiasCols + tx;                // n is a multiple of 32
     const int per = (n_blocks + kBiasSlices - 1) / kBiasSlices;
     const int b0 = ty * per, b1 = min(n_blocks, b0 + per);
     float s = 0.0f;
-    if (c < n)
-        for (int b = b0; b < b1; ++b) s += partial[(size_t)b * n + c];
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) s += partial[(size_t)b * n + c];
     part[ty][tx] = s;
     __syncthreads();
-    if (ty == 0 && c < n) {
+    if (ty == 0) {
         float t = 0.0f;
 #pragma unroll
         for (int k = 0; k < kBiasSlices; ++k) t += part[k][tx];
@@ -652,6 +583,30 @@ int proj_check(int32_t M, int32_t d)
     return HGRN2_OK;
 }
 size_t round256p(size_t x) { return (x + 255) & ~(size_t)255; }
+size_t padded(int32_t M) { return ((size_t)M + 63) & ~(size_t)63; }        // tokens, in whole steps of the product that contracts over them
+
+// workspace of the reverse mode: dA, row-block sums of dA, W3 transposed, dA and x transposed, the shares of dW3
+struct ProjBwdLayout {
+    size_t dA, partial, w3t, dAt, xt, shares;
+    int rows;             // of a row block
+    NtPlan plan_w;
+    size_t total() const { return dA + partial + w3t + dAt + xt + shares; }
+};
+ProjBwdLayout proj_bwd_layout(int32_t M, int32_t d)
+{
+    ProjBwdLayout l = {};
+    if (M == 0 || d == 0) return l;
+    const size_t n = 3 * (size_t)d;
+    l.rows = act_rows(M, d);
+    l.plan_w = plan_nt(3 * d, d, (int)padded(M), true);
+    l.dA = round256p((size_t)M * n * sizeof(__bf16));
+    l.partial = round256p(padded(M) / l.rows * n * sizeof(float));
+    l.w3t = round256p(n * d * sizeof(__bf16));
+    l.dAt = round256p(padded(M) * n * sizeof(__bf16));
+    l.xt = round256p(padded(M) * d * sizeof(__bf16));
+    l.shares = l.plan_w.splits > 1 ? round256p(l.plan_w.splits * n * d * sizeof(float)) : 0;
+    return l;
+}
 }   // namespace
 
 extern "C" {
@@ -659,9 +614,7 @@ extern "C" {
 size_t hgru2_proj_bwd_workspace_bytes(int32_t M, int32_t d)
 {
     if (proj_check(M, d) != HGRN2_OK) return 0;
-    const size_t blocks = ((size_t)M + kActRows - 1) / kActRows;
-    return round256p((size_t)M * 3 * d * sizeof(__bf16)) + round256p(blocks * 3 * d * sizeof(float)) +
-           round256p((size_t)3 * d * d * sizeof(__bf16));           // dA, row-block sums of dA, W3 transposed
+    return proj_bwd_layout(M, d).total();
 }
 
 int hgru2_proj_fwd(int32_t M, int32_t d, const void* x, const void* w3, const float* b3, void* z, void* v, void* q,
@@ -677,7 +630,7 @@ int hgru2_proj_fwd(int32_t M, int32_t d, const void* x, const void* w3, const fl
     p.M = M; p.N = 3 * d; p.K = d;
     p.bias = b3; p.z = static_cast<__bf16*>(z); p.v = static_cast<__bf16*>(v); p.q = static_cast<__bf16*>(q);
     p.av = static_cast<__bf16*>(av); p.d = d;
-    return launch_gemm_dl<kEpiProj, 8>(p, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? HGRN2_OK : HGRN2_ERR_HIP;
+    return launch_product<kEpiProj>(p, plan_nt(M, 3 * d, d, false), static_cast<hipStream_t>(hip_stream)) == hipSuccess ? HGRN2_OK : HGRN2_ERR_HIP;
 }
 
 int hgru2_proj_bwd(int32_t M, int32_t d, const void* x, const void* w3, const void* q, const void* av, const void* grad_z,
@@ -698,38 +651,43 @@ int hgru2_proj_bwd(int32_t M, int32_t d, const void* x, const void* w3, const vo
             return HGRN2_ERR_HIP;
         return HGRN2_OK;
     }
-    __bf16* dA = static_cast<__bf16*>(workspace);
-    float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + round256p((size_t)M * 3 * d * sizeof(__bf16)));
-    const int blocks = (M + kActRows - 1) / kActRows;
+    const ProjBwdLayout l = proj_bwd_layout(M, d);
+    char* at = static_cast<char*>(workspace);
+    auto take = [&](size_t bytes) { char* r = at; at += bytes; return r; };
+    __bf16* dA = reinterpret_cast<__bf16*>(take(l.dA));
+    float* partial = reinterpret_cast<float*>(take(l.partial));
+    __bf16* w3t = reinterpret_cast<__bf16*>(take(l.w3t));
+    __bf16* dAt = reinterpret_cast<__bf16*>(take(l.dAt));
+    __bf16* xt = reinterpret_cast<__bf16*>(take(l.xt));
+    float* shares = reinterpret_cast<float*>(take(l.shares));
+    const int Mp = (int)padded(M), blocks = Mp / l.rows;
     const bool aligned = (((uintptr_t)grad_z | (uintptr_t)grad_v | (uintptr_t)grad_q | (uintptr_t)q | (uintptr_t)av) & 15) == 0;
-    if ((aligned ? launch_proj_dact<8>(grad_z, grad_v, grad_q, q, av, dA, partial, M, d, stream)
-                 : launch_proj_dact<2>(grad_z, grad_v, grad_q, q, av, dA, partial, M, d, stream)) != hipSuccess)
+    if ((aligned ? launch_proj_dact<8>(grad_z, grad_v, grad_q, q, av, dA, dAt, partial, M, Mp, d, stream)
+                 : launch_proj_dact<2>(grad_z, grad_v, grad_q, q, av, dA, dAt, partial, M, Mp, d, stream)) != hipSuccess)
         return HGRN2_ERR_HIP;
-    hipLaunchKernelGGL(proj_bias_grad_kernel, dim3((3 * d + kBiasCols - 1) / kBiasCols), dim3(kBiasCols * kBiasSlices), 0, stream, partial, grad_b3,
-                       blocks, 3 * d);
+    const int n_w3 = 3 * d / 64 * (d / 64), n_x = Mp / 64 * (d / 64);
+    hipLaunchKernelGGL(proj_prepare_kernel, dim3(n_w3 + n_x + 3 * d / kBiasCols), dim3(kBiasCols * kBiasSlices), 0, stream,
+                       static_cast<const __bf16*>(w3), w3t, n_w3, static_cast<const __bf16*>(x), xt, n_x, M, Mp, d, partial, grad_b3, blocks);
     if (hipGetLastError() != hipSuccess) return HGRN2_ERR_HIP;
-    // dx [M][d] = dA [M][3d] . W3 [3d][d]: W3's contraction index is its slow axis, so it is transposed
-    // first (25 MB at width 2048, a few microseconds) and the product takes the kernel for k-contiguous operands
-    __bf16* w3t = reinterpret_cast<__bf16*>(reinterpret_cast<char*>(partial) + round256p((size_t)blocks * 3 * d * sizeof(float)));
-    hipLaunchKernelGGL(proj_transpose_kernel, dim3(d / 64, 3 * d / 64), dim3(256), 0, stream,
-                       static_cast<const __bf16*>(w3), w3t, 3 * d, d);
-    if (hipGetLastError() != hipSuccess) return HGRN2_ERR_HIP;
+    // dx [M][d] = dA [M][3d] . W3 [3d][d]
     GemmParams px = {};
     px.A = dA; px.lda = 3 * d;
     px.B = w3t; px.ldb = 3 * d;
     px.M = M; px.N = d; px.K = 3 * d;
     px.C = static_cast<__bf16*>(grad_x); px.ldc = d;
-    if (launch_gemm_dl<kEpiPlain, 4>(px, stream) != hipSuccess) return HGRN2_ERR_HIP;
-    // dW3 [3d][d] = dA^T [3d][M] . x [M][d]: the token index is the slow axis of both
+    if (launch_product<kEpiPlain>(px, plan_nt(M, d, 3 * d, false), stream) != hipSuccess) return HGRN2_ERR_HIP;
+    // dW3 [3d][d] = dA^T [3d][M] . x [M][d]
     GemmParams pw = {};
-    pw.A = dA; pw.lda = 3 * d;
-    pw.B = static_cast<const __bf16*>(x); pw.ldb = d;
-    pw.M = 3 * d; pw.N = d; pw.K = M;
-    pw.Cf = grad_w3; pw.ldc = d;
-    // tile height by the time it implies: rounds of 256 workgroups times the rows of a tile
-    const long long t256 = ((3LL * d / 256) * (d / 256) + 255) / 256 * 256, t192 = ((3LL * d / 192) * (d / 256) + 255) / 256 * 192;
-    if ((t192 < t256 ? launch_gemm<true, true, kEpiFloat, 192>(pw, stream) : launch_gemm<true, true, kEpiFloat, 256>(pw, stream)) != hipSuccess)
-        return HGRN2_ERR_HIP;
+    pw.A = dAt; pw.lda = Mp;
+    pw.B = xt; pw.ldb = Mp;
+    pw.M = 3 * d; pw.N = d; pw.K = Mp;
+    pw.Cf = l.plan_w.splits > 1 ? shares : grad_w3; pw.ldc = d;
+    if (launch_product<kEpiFloat>(pw, l.plan_w, stream) != hipSuccess) return HGRN2_ERR_HIP;
+    if (l.plan_w.splits > 1) {
+        const size_t n = (size_t)3 * d * d;
+        hipLaunchKernelGGL(proj_sum_kernel, dim3((unsigned)(n / 1024)), dim3(256), 0, stream, shares, grad_w3, n, l.plan_w.splits);
+        if (hipGetLastError() != hipSuccess) return HGRN2_ERR_HIP;
+    }
     return HGRN2_OK;
 }
 

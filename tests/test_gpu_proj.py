@@ -3,6 +3,8 @@ matrix product with bias and activation in its epilogue -- against the fp64 orac
 the layer Eq. 1 -> Eq. 2 -> Eq. 3 (projection, hgrn2_fwd_gated on its token-major outputs, and the
 whole reverse mode).  Inputs are rounded to bf16 once and the oracle sees the rounded values.
 Tolerance: max|x-y|/max|y| <= 2e-2 per tensor (bf16 storage, fp32 accumulation)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -147,3 +149,37 @@ def test_proj_full_width_sampled_rows():
     rz, ri, ro = oracle.hgru2_proj(xs[None], U, V, W, bu, bv, bw)
     tol = TOL["bf16"]
     check("z", host(z[rt]), rz[0], tol); check("v", host(v[rt]), ri[0], tol); check("q", host(q[rt]), ro[0], tol)
+
+
+@pytest.mark.parametrize("M,d", [(1, 256),          # one token: 63 padded ones in the product over the tokens
+                                 (1500, 512),       # a padded step; 32 tokens to a workgroup of the element-wise pass
+                                 (4100, 256),       # dW3 in 64 x 64 tiles, its contraction cut into shares
+                                 (2048, 1024),      # 128 x 128 tiles
+                                 (4097, 1280),      # 256 x 256 tiles with one row in the last
+                                 (9000, 1024)])     # dW3 in 192 x 256 or 128 x 128 tiles
+def test_proj_tiles_and_padding(M, d):
+    """Every tile size of the products, with a remainder of tokens: against fp32 products of the same rounded operands
+    (torch), the workspace filled with NaN before; bf16 outputs to 2 units in the last place of the
+    largest value, the fp32 sums to 1e-3 (see below)."""
+    print("\n[proj tiles] M=%d d=%d" % (M, d), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(9500 + M)
+    n = lambda *s: torch.randn(s, generator=g, device="cuda").bfloat16()
+    x, w3, b3 = n(M, d), (n(3 * d, d).float() / d ** 0.5).bfloat16(), torch.randn(3 * d, generator=g, device="cuda")
+    gz, gv, gq = n(M, d), n(M, d), n(M, d)
+    z, v, q, av = binding.hgru2_proj_fwd(x, w3, b3)
+    size = binding.lib().hgru2_proj_bwd_workspace_bytes
+    size.restype = ctypes.c_size_t
+    ws = torch.full((size(M, d),), 255, dtype=torch.uint8, device="cuda")
+    dx, dw, db = binding.hgru2_proj_bwd(x, w3, q, av, gz, gv, gq, workspace=ws)
+    a, qf = av.double(), q.double()
+    s = torch.sigmoid(a)
+    dA = torch.cat([gz.double(), gv.double() * s * (1 + a * (1 - s)), gq.double() * qf * (1 - qf)], 1).bfloat16().double()
+    pre = x.double() @ w3.double().t() + b3.double()
+    rv = pre[:, d:2 * d] * torch.sigmoid(pre[:, d:2 * d])
+    for name, got, ref, tol in (("z", z, pre[:, :d], 2.0 ** -7), ("av", av, pre[:, d:2 * d], 2.0 ** -7), ("v", v, rv, 2.0 ** -7),
+                                ("q", q, torch.sigmoid(pre[:, 2 * d:]), 2.0 ** -7), ("dx", dx, dA @ w3.double(), 2.0 ** -7),
+                                # (an element of dA may round the other way where it is formed in another order: 2^-9 of it, in a share of the elements)
+                                ("dw3", dw, dA.t() @ x.double(), 1e-3), ("db3", db, dA.sum(0), 1e-3)):
+        e = float((got.double() - ref).abs().max() / ref.abs().max())
+        print("   %-4s %.2e" % (name, e), flush=True)
+        assert e <= tol, (name, e)
