@@ -388,9 +388,17 @@ __device__ __forceinline__ void gate_rows(f32x2 (&rf)[RW], const float* beta_hea
     const f32x2 b = *reinterpret_cast<const f32x2*>(beta_head + col);
 #pragma unroll
     for (int i = 0; i < RW; ++i) {
-        const bool ok = lane_active && (row0 + i >= first_row) && (row0 + i < n_rows);
-        rf[i].x = ok ? lower_bounded_gate(rf[i].x, b.x) : 1.0f;
-        rf[i].y = ok ? lower_bounded_gate(rf[i].y, b.y) : 1.0f;
+        rf[i].x = lower_bounded_gate(rf[i].x, b.x);
+        rf[i].y = lower_bounded_gate(rf[i].y, b.y);
+    }
+    const bool all_rows = row0 >= first_row && row0 + RW <= n_rows;
+    if (!all_rows || !lane_active) {
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const bool ok = lane_active && (row0 + i >= first_row) && (row0 + i < n_rows);
+            rf[i].x = ok ? rf[i].x : 1.0f;
+            rf[i].y = ok ? rf[i].y : 1.0f;
+        }
     }
 }
 
