@@ -18,7 +18,12 @@
 // forward pass over 256 tokens of one head -- a sweep launch takes every chunk from zero at once, and
 // the workgroup of chunk n adds up the contributions of the chunks before it,
 //     S_n = Diag(g_{n-1}) ( ... Diag(g_0) h0 + A_0 ... ) + A_{n-1},
-// out of the cache; the last chunk's workgroup also forms the final state, h (G_m S_n) + K^^T V.
+// out of the cache.  What bounds it is the chain of one chunk, products on fp32 matrix instructions most of all
+// (64 clocks each), so a workgroup takes 64 dv columns (half of a 128-wide head's: half of the contributions to
+// add up and of the products, for P formed twice), and the final state, h (G_m S_n) + K^^T V, is a workgroup of its
+// own beside the last chunk's while all find a place at once.  us, one workgroup for all of it -> now: one head of 64 x 64,
+// 64 / 256 / 4096 tokens 11.6 / 20.6 / 31.4 -> 9.9 / 18.3 / 29.2; of 128 x 128, 64 / 256 / 1024 tokens 20.0 / 30.7 / 39.9 -> 12.0 / 20.9 /
+// 25.9; 32 heads of 128 x 128, 192 tokens 33.5 -> 26.1; 64 of 64 x 128 29.4 -> 27.7.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -43,7 +48,11 @@ struct FwdOutParams {
     size_t decay_stride;
     const float* h0;
     float* hT;
+    int chunk_items;         // workgroups of chunks (chunk, slab of dv)
+    int final_items;         // workgroups behind them that form the final states (sequence, slab); 0: the last chunks' do
 };
+
+constexpr int kAddCols = 64;     // dv columns of a workgroup that adds up contributions
 
 template <typename T, int DK, int DV> struct FwdOutLds {
     static constexpr int C = kChunk;
@@ -64,9 +73,10 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
 {
     static_assert(!ADD || !is_bf16_type<T>(), "bf16 storage takes the fused walk");
     constexpr int C = kChunk, RW = C / kWaves;
-    typedef FwdOutLds<T, DK, DV> L;
+    constexpr int DVW = ADD ? kAddCols : DV, NSPLIT = DV / DVW;      // dv columns of the workgroup
+    typedef FwdOutLds<T, DK, DVW> L;
     constexpr int PK = L::PK, PC = L::PC, PO = L::PO;
-    constexpr int NRT = C / 32, NBT = DV / 32, NKS = DK / 16;
+    constexpr int NRT = C / 32, NBT = DVW / 32, NKS = DK / 16;
     typedef Mma<T> M;
 
     extern __shared__ __align__(16) char smem[];
@@ -78,10 +88,19 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
     T* Ost = reinterpret_cast<T*>(smem + L::ost);   // output staging aliases K~ once P has been formed
 
     if (not_chosen(p.lay)) return;       // one of several chunk lengths, and not the one called for
-    int n, bh;
-    if (!locate_chunk<DENSE>(p.lay, p.BH, p.NC, blockIdx.x, bh, n)) return;
+    int n, bh, dv0 = 0;                  // dv0: first dv column of the workgroup
+    bool final_only = false;             // a workgroup that only forms a final state
+    if constexpr (ADD) {
+        int item = blockIdx.x;
+        final_only = item >= p.chunk_items;
+        if (final_only) item = ((item - p.chunk_items) / NSPLIT * p.NC + p.NC - 1) * NSPLIT + (item - p.chunk_items) % NSPLIT;
+        dv0 = item % NSPLIT * DVW;
+        if (!locate_chunk<DENSE>(p.lay, p.BH, p.NC, item / NSPLIT, bh, n)) return;
+    } else {
+        if (!locate_chunk<DENSE>(p.lay, p.BH, p.NC, blockIdx.x, bh, n)) return;
+    }
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
-    const bool k_act = 2 * lane < DK, v_act = 2 * lane < DV;
+    const bool k_act = 2 * lane < DK, v_act = 2 * lane < DVW;
     const SeqView sv = seq_view<DENSE, DK, DV>(p.lay, p.N, p.NC, bh);
     const size_t seq_k = sv.off_k, seq_v = sv.off_v;
     const int N = sv.N;
@@ -107,7 +126,7 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
     {
         RawRows<RW> raw_f, raw_q, raw_v;
         const int row0 = cr.tok0 + RW * w;
-        const int col_k = k_act ? 2 * lane : 0, col_v = v_act ? 2 * lane : 0;
+        const int col_k = k_act ? 2 * lane : 0, col_v = dv0 + (v_act ? 2 * lane : 0);
         load_rows<RW>(raw_f, p.f, seq_k, ld_k, col_k, row0, N, gate_bf16);
         load_rows<RW>(raw_q, qg, seq_k, ld_k, col_k, row0, N, is_bf16_type<T>());
         load_rows<RW>(raw_v, vg, seq_v, ld_v, col_v, row0, N, is_bf16_type<T>());
@@ -121,14 +140,15 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
         // (what one request takes -- the values come from other XCDs -- is most of what a chunk costs:
         // 5 us each when every lane fetched its fragments chunk after chunk), and reaches the fragments
         // through the memory of the tiles that are written next.
-        constexpr int NV = DK * DV / 4 / kThreads, AHEAD = NV > 8 ? 2 : 8;
+        constexpr int NV = DK * DVW / 4 / kThreads, AHEAD = NV > 4 ? 4 : 6;
         f32x4 st[NV];
         const float* h0 = p.h0 ? p.h0 + (size_t)bh * DK * DV : nullptr;
         const float* add = p.add + (size_t)bh * p.NC * DK * DV;
         const float* dec = p.decay + (size_t)bh * p.decay_stride;
-        auto at = [&](int i) { return 4 * (tid + kThreads * i); };
+        auto at = [&](int i) { return 4 * (tid + kThreads * i); };               // in the workgroup's [DK][DVW]
+        auto in_state = [&](int i) { return at(i) / DVW * DV + dv0 + at(i) % DVW; };
 #pragma unroll
-        for (int i = 0; i < NV; ++i) st[i] = h0 ? *reinterpret_cast<const f32x4*>(h0 + at(i)) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int i = 0; i < NV; ++i) st[i] = h0 ? *reinterpret_cast<const f32x4*>(h0 + in_state(i)) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         for (int j0 = 0; j0 < n; j0 += AHEAD) {
             f32x4 a[AHEAD][NV];
             float dm[AHEAD][NV];
@@ -137,8 +157,8 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
                 const int j = min(j0 + u, n - 1);
 #pragma unroll
                 for (int i = 0; i < NV; ++i) {
-                    a[u][i] = *reinterpret_cast<const f32x4*>(add + (size_t)j * DK * DV + at(i));
-                    dm[u][i] = dec[j * DK + at(i) / DV];
+                    a[u][i] = *reinterpret_cast<const f32x4*>(add + (size_t)j * DK * DV + in_state(i));
+                    dm[u][i] = dec[j * DK + at(i) / DVW];
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -152,7 +172,7 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
             }
         }
         float* sum = reinterpret_cast<float*>(smem);
-        static_assert((size_t)DK * DV * sizeof(float) <= L::tot, "the state fits the memory of the tiles");
+        static_assert((size_t)DK * DVW * sizeof(float) <= L::tot, "the state fits the memory of the tiles");
 #pragma unroll
         for (int i = 0; i < NV; ++i) *reinterpret_cast<f32x4*>(sum + at(i)) = st[i];
         __syncthreads();
@@ -160,7 +180,7 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-            for (int s = 0; s < 8; ++s) sfrag[ks].v[s] = sum[(size_t)(16 * ks + 8 * (s >> 2) + 4 * g + (s & 3)) * DV + 32 * bt + r32];
+            for (int s = 0; s < 8; ++s) sfrag[ks].v[s] = sum[(size_t)(16 * ks + 8 * (s >> 2) + 4 * g + (s & 3)) * DVW + 32 * bt + r32];
         // (the tiles are written after the next barrier)
     }
 
@@ -236,7 +256,7 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
     // ---------------- P^T blocks: (J, I) with J <= I; wave w takes block w ----------------
     {
         constexpr int NBLK = NRT * (NRT + 1) / 2;
-        for (int blk = w; blk < NBLK; blk += kWaves) {
+        for (int blk = final_only ? NBLK : w; blk < NBLK; blk += kWaves) {
             // enumerate (J, I): 0 -> (0,0), 1 -> (0,1), 2 -> (1,1)
             int I = 0, J = 0, cnt = 0;
             for (int ii = 0; ii < NRT; ++ii)
@@ -262,14 +282,14 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
             }
         }
     }
-    __syncthreads();
+    if (!final_only) __syncthreads();
 
     if constexpr (ADD) {
-        // Final state, by the last chunk's workgroup: h (G_m S_n) + K^^T V with K^_j = k_j prod_{s > j} f_s, as the sweep
+        // Final state, of the last chunk: h (G_m S_n) + K^^T V with K^_j = k_j prod_{s > j} f_s, as the sweep
         // forms it (K~ has a reciprocal in it, whose error the state would keep), in the tile the P blocks have
         // read K~ from.  Tiles (at, bt), the channel tiles dealt to the waves of a dv tile; fragments 2 at and
         // 2 at + 1 hold the state in accumulator order.
-        if (p.hT && n == p.NC - 1) {
+        if (final_only || (p.hT && p.final_items == 0 && n == p.NC - 1)) {
             if (k_act) {
                 const float p0 = block_decay(tot, DK, w, 2 * lane).post, p1 = block_decay(tot, DK, w, 2 * lane + 1).post;
 #pragma unroll
@@ -288,10 +308,11 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
 #pragma unroll
                 for (int ks = 0; ks < C / 16; ++ks)
                     M::mma(acc, M::load_kmajor(Km, PK, 16 * ks, 32 * at, lane), M::load(Vt + (32 * bt + r32) * PC + 16 * ks + 8 * g));
-                float* out = p.hT + (size_t)bh * DK * DV + (size_t)(32 * at) * DV + 32 * bt + r32;
+                float* out = p.hT + (size_t)bh * DK * DV + (size_t)(32 * at) * DV + dv0 + 32 * bt + r32;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) out[(size_t)acc_row(v, lane) * DV] = acc[v];
             }
+            if (final_only) return;
             __syncthreads();                 // (the O tiles take this memory)
         }
     }
@@ -325,21 +346,25 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
     // ---------------- coalesced store of the [C][DV] tile ----------------
     {
         constexpr int VEC = 16 / (int)sizeof(T);         // elements per 16-byte vector
-        constexpr int VPR = DV / VEC;                     // vectors per row
+        constexpr int VPR = DVW / VEC;                    // vectors per row
         T* og = static_cast<T*>(p.o);
         for (int idx = tid; idx < C * VPR; idx += kThreads) {
             const int row = idx / VPR, cv = idx % VPR;
             const int grow = cr.tok0 + row;
             if (cr.holds(row)) {
                 const uint4 val = *reinterpret_cast<const uint4*>(Ost + (size_t)row * PO + cv * VEC);
-                *reinterpret_cast<uint4*>(og + seq_v + (size_t)grow * ld_v + cv * VEC) = val;
+                *reinterpret_cast<uint4*>(og + seq_v + (size_t)grow * ld_v + dv0 + cv * VEC) = val;
             }
         }
     }
 }
 
+// Workgroups that add up contributions for heads of 64 find two places on a compute unit: six chunks' values requested at
+// a time instead of eight leave the registers for it (128 heads of 64, 192 tokens: 35.9 -> 28.7 us).
+constexpr int add_places(int dk) { return dk == 64 ? 2 : 1; }
+
 template <typename T, int DK, int DV, bool ADD>
-__global__ __launch_bounds__(kThreads) void fwd_out_kernel(FwdOutParams p)
+__global__ __launch_bounds__(kThreads, ADD ? add_places(DK) : 1) void fwd_out_kernel(FwdOutParams p)
 {
     if (p.dense) fwd_out_body<T, DK, DV, true, ADD>(p);
     else         fwd_out_body<T, DK, DV, false, ADD>(p);
@@ -348,11 +373,21 @@ __global__ __launch_bounds__(kThreads) void fwd_out_kernel(FwdOutParams p)
 template <typename T, int DK, int DV, bool ADD>
 static hipError_t launch_one(const SeqDims& d, const FwdOutParams& p, hipStream_t stream)
 {
-    typedef FwdOutLds<T, DK, DV> L;
+    constexpr int DVW = ADD ? kAddCols : DV, NSPLIT = DV / DVW;
+    typedef FwdOutLds<T, DK, DVW> L;
     auto kern = fwd_out_kernel<T, DK, DV, ADD>;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::total);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)d.total_chunks()), dim3(kThreads), L::total, stream, p);
+    FwdOutParams a = p;
+    a.chunk_items = (int)d.total_chunks() * NSPLIT;
+    a.final_items = 0;
+    if constexpr (ADD) {
+        static_assert(add_places(DK) * L::total <= 160 * 1024, "LDS budget of the workgroups of a compute unit");
+        // final states beside the chunks, if all run at once on the 256 compute units
+        const long long all = (long long)a.chunk_items + (long long)d.BH * NSPLIT;
+        if (p.hT && all <= 256 * add_places(DK)) a.final_items = d.BH * NSPLIT;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.chunk_items + a.final_items)), dim3(kThreads), L::total, stream, a);
     return hipGetLastError();
 }
 
@@ -372,7 +407,7 @@ static FwdOutParams out_params(const SeqDims& d, const void* q, const void* f, c
     p.q = q; p.f = f; p.v = v; p.ws = nullptr; p.o = o;
     p.BH = d.BH; p.N = d.N; p.NC = d.NC; p.gate_bf16 = d.gate_bf16 ? 1 : 0;
     p.beta = d.beta; p.H = d.H; p.lay = d.lay; p.dense = d.dense() ? 1 : 0; p.flag = d.domain_flag;
-    p.add = nullptr; p.decay = nullptr; p.decay_stride = 0; p.h0 = nullptr; p.hT = nullptr;
+    p.add = nullptr; p.decay = nullptr; p.decay_stride = 0; p.h0 = nullptr; p.hT = nullptr; p.chunk_items = 0; p.final_items = 0;
     return p;
 }
 

@@ -107,6 +107,21 @@ def test_forward_fp32_from_contributions(B, H, N, dk, dv, states):
         check("hT", host(hT), rhT, TOL["f32"])
 
 
+# The same, where the final states just find a place beside the chunks (256 workgroups, 512 with dk = 64) and where the last
+# chunks' workgroups form them, token-major
+@pytest.mark.parametrize("BH,NC,dk,dv", [(32, 3, 128, 128), (48, 2, 128, 128), (64, 3, 128, 64), (96, 2, 128, 64),
+                                         (128, 3, 64, 64), (192, 2, 64, 64), (64, 3, 64, 128), (96, 2, 64, 128)])
+def test_forward_fp32_final_states_beside_the_chunks(BH, NC, dk, dv):
+    print("\n[fwd f32, final states] BH=%d NC=%d dk=%d dv=%d" % (BH, NC, dk, dv), flush=True)
+    w = synth.make_sequence(3250 + BH, 2, BH // 2, 64 * NC - 7, dk, dv, io_dtype="f32", lb=0.5, with_h0=True)
+    rows = lambda x: dev(x).permute(0, 2, 1, 3).contiguous()
+    o, hT = binding.hgrn2_fwd(rows(w.q), rows(w.f), rows(w.v), dev(w.h0), layout=binding.HGRN2_LAYOUT_BNHD)
+    torch.cuda.synchronize()
+    ro, rhT = oracle.fwd(w.q, w.f, w.v, w.h0)
+    check("o", host(o.permute(0, 2, 1, 3)), ro, TOL["f32"])
+    check("hT", host(hT), rhT, TOL["f32"])
+
+
 # Two light runs of 96 and 100 sequences with the gate formed in the kernels, token-major, continued from a state, the
 # chunk length chosen on the device: ordinary gates (64 tokens) and gates for which shorter chunks are taken
 @pytest.mark.parametrize("small", [False, True])
