@@ -647,7 +647,7 @@ size_t hgrn1_ws_bytes(int B, int N, int d)
     return (h1_carry_floats(B, N, d) + (size_t)B * d + (R > 1 ? (size_t)B * R * 5 * d : 0)) * sizeof(float);
 }
 
-// in_place: the state a sequence ends in replaces the one it starts from, which every run reads: a workgroup takes the whole sequence
+// in_place: a state that a sequence leaves (hN, dh0) replaces one that every run reads (h0, dhN): a workgroup takes the whole sequence
 static H1Params h1_params(int B, int N, int d, int seg, void* ws, bool in_place)
 {
     H1Params p = {};
@@ -707,7 +707,7 @@ hipError_t launch_hgrn1_bwd(int B, int N, int d, bool gate_bf16, const void* f, 
         return hipGetLastError();
     }
     const int seg = beta ? kH1SegShort : kH1SegLong;
-    H1Params p = h1_params(B, N, d, seg, ws, dhN && dhN == dh0);
+    H1Params p = h1_params(B, N, d, seg, ws, dh0 && (dh0 == dhN || (dh0 == h0 && !states_saved)));
     p.f = f; p.i = i; p.o = o; p.beta = beta; p.dy = dy; p.h0 = h0; p.dhN = dhN; p.df = df; p.di = di; p.dout = dout; p.dh0 = dh0;
     if (p.R > 1) {
         if (!states_saved) launch_h1_ends<false>(p, seg, gate_bf16, stream);

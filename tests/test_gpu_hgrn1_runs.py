@@ -44,8 +44,14 @@ def test_states_continued_in_place():
     rc = binding.lib().hgrn1_bwd(2, 1300, 128, binding.HGRN2_BF16, binding.HGRN2_BF16, p(fd), p(idv), p(od), p(start), p(dyd), p(g),
                                  p(gf), p(gi), p(go), p(g), p(ws), need, binding._stream())
     assert rc == 0
+    # and the gradient of the initial state in that state's own place
+    other, dhN_d, gf2 = start.clone(), dev(dhN), torch.empty_like(gf)
+    rc = binding.lib().hgrn1_bwd(2, 1300, 128, binding.HGRN2_BF16, binding.HGRN2_BF16, p(fd), p(idv), p(od), p(other), p(dyd),
+                                 p(dhN_d), p(gf2), p(gi), p(go), p(other), p(ws), need, binding._stream())
+    assert rc == 0
     torch.cuda.synchronize()
     ry, rh = oracle.hgrn1_fwd(f, i, o, h0)
     rf, ri, ro, rh0 = oracle.hgrn1_bwd(f, i, o, dy, h0, dhN)
     check("y", host(y), ry, TOL["bf16"]); check("hN", host(s), rh, 3e-5)
     check("df", host(gf), rf, TOL["bf16"]); check("dh0", host(g), rh0, 3e-5)
+    assert torch.equal(gf, gf2) and torch.equal(g, other)
