@@ -31,9 +31,9 @@ KERNELS = {
     "hgrn1_fwd_kernel": "hgrn1_fwd_kernel",
     "hgrn1_bwd_kernel": "hgrn1_bwd_kernel<true, false, false>",
     "hgrn1_bwd_saved_kernel": "hgrn1_bwd_kernel<true, false, true>",
-    "proj_fwd_gemm": "gemm_dl_kernel<0,",
-    "proj_dx_gemm": "gemm_dl_kernel<1,",
-    "proj_dw_gemm": "gemm_kernel<true, true, 2",
+    "proj_fwd_gemm": "gemm_nt_kernel<0, 256",
+    "proj_dx_gemm": "gemm_nt_kernel<1, 256",
+    "proj_dw_gemm": "gemm_nt_kernel<2, 192",
     "proj_dact_kernel": "proj_dact_kernel",
 }
 
