@@ -20,10 +20,10 @@
 //     S_n = Diag(g_{n-1}) ( ... Diag(g_0) h0 + A_0 ... ) + A_{n-1},
 // out of the cache.  What bounds it is the chain of one chunk, products on fp32 matrix instructions most of all
 // (64 clocks each), so a workgroup takes 64 dv columns (half of a 128-wide head's: half of the contributions to
-// add up and of the products, for P formed twice), and the final state, h (G_m S_n) + K^^T V, is a workgroup of its
+// add up and of the products, for P formed twice; see launch_fwd_out_add()), and the final state, h (G_m S_n) + K^^T V, is a workgroup of its
 // own beside the last chunk's while all find a place at once.  us, one workgroup for all of it -> now: one head of 64 x 64,
 // 64 / 256 / 4096 tokens 11.6 / 20.6 / 31.4 -> 9.9 / 18.3 / 29.2; of 128 x 128, 64 / 256 / 1024 tokens 20.0 / 30.7 / 39.9 -> 12.0 / 20.9 /
-// 25.9; 32 heads of 128 x 128, 192 tokens 33.5 -> 26.1; 64 of 64 x 128 29.4 -> 27.7.
+// 25.9; 32 heads of 128 x 128, 192 tokens 33.5 -> 26.1; 64 of 64 x 128 29.4 -> 26.0.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -52,8 +52,6 @@ struct FwdOutParams {
     int final_items;         // workgroups behind them that form the final states (sequence, slab); 0: the last chunks' do
 };
 
-constexpr int kAddCols = 64;     // dv columns of a workgroup that adds up contributions
-
 template <typename T, int DK, int DV> struct FwdOutLds {
     static constexpr int C = kChunk;
     static constexpr int PK = DK + pad_elems<T>();
@@ -68,12 +66,13 @@ template <typename T, int DK, int DV> struct FwdOutLds {
     static constexpr size_t total = tot + (size_t)kWaves * DK * sizeof(float);
 };
 
-template <typename T, int DK, int DV, bool DENSE, bool ADD>
+// ADD: 0, or the dv columns of a workgroup that adds up contributions
+template <typename T, int DK, int DV, bool DENSE, int ADD>
 __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
 {
     static_assert(!ADD || !is_bf16_type<T>(), "bf16 storage takes the fused walk");
     constexpr int C = kChunk, RW = C / kWaves;
-    constexpr int DVW = ADD ? kAddCols : DV, NSPLIT = DV / DVW;      // dv columns of the workgroup
+    constexpr int DVW = ADD ? ADD : DV, NSPLIT = DV / DVW;           // dv columns of the workgroup
     typedef FwdOutLds<T, DK, DVW> L;
     constexpr int PK = L::PK, PC = L::PC, PO = L::PO;
     constexpr int NRT = C / 32, NBT = DVW / 32, NKS = DK / 16;
@@ -90,7 +89,7 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
     if (not_chosen(p.lay)) return;       // one of several chunk lengths, and not the one called for
     int n, bh, dv0 = 0;                  // dv0: first dv column of the workgroup
     bool final_only = false;             // a workgroup that only forms a final state
-    if constexpr (ADD) {
+    if constexpr (ADD != 0) {
         int item = blockIdx.x;
         final_only = item >= p.chunk_items;
         if (final_only) item = ((item - p.chunk_items) / NSPLIT * p.NC + p.NC - 1) * NSPLIT + (item - p.chunk_items) % NSPLIT;
@@ -116,7 +115,7 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
     static_assert(kWaves % NBT == 0 && (NRT * NBT) % kWaves == 0, "tile/wave mapping");
     const int bt = w % NBT;
     typename M::frag sfrag[NKS];
-    if constexpr (!ADD) {
+    if constexpr (ADD == 0) {
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks)
             sfrag[ks] = *reinterpret_cast<const typename M::frag*>(
@@ -135,7 +134,7 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
         convert_rows<RW>(rq, raw_q, row0, cr.end, k_act, is_bf16_type<T>(), 0.0f, cr.first);
         convert_rows<RW>(rv, raw_v, row0, cr.end, v_act, is_bf16_type<T>(), 0.0f, cr.first);
     }
-    if constexpr (ADD) {
+    if constexpr (ADD != 0) {
         // The sum goes over the whole workgroup in 16-byte vectors, several chunks' requested at a time
         // (what one request takes -- the values come from other XCDs -- is most of what a chunk costs:
         // 5 us each when every lane fetched its fragments chunk after chunk), and reaches the fragments
@@ -195,7 +194,7 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
         for (int i = RW - 1; i >= 0; --i) { z0[i] = run0; z1[i] = run1; run0 *= rf[i].x; run1 *= rf[i].y; }
     }
     float kz0[ADD ? RW : 1], kz1[ADD ? RW : 1];          // k z, for the final state
-    if constexpr (ADD) {
+    if constexpr (ADD != 0) {
 #pragma unroll
         for (int i = 0; i < RW; ++i) { kz0[i] = (1.0f - rf[i].x) * z0[i]; kz1[i] = (1.0f - rf[i].y) * z1[i]; }
     }
@@ -240,7 +239,7 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
     }
     __syncthreads();
 
-    if constexpr (ADD) {
+    if constexpr (ADD != 0) {
         // the read-out takes G_m S_n (the totals are complete since the first barrier)
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks)
@@ -284,7 +283,7 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
     }
     if (!final_only) __syncthreads();
 
-    if constexpr (ADD) {
+    if constexpr (ADD != 0) {
         // Final state, of the last chunk: h (G_m S_n) + K^^T V with K^_j = k_j prod_{s > j} f_s, as the sweep
         // forms it (K~ has a reciprocal in it, whose error the state would keep), in the tile the P blocks have
         // read K~ from.  Tiles (at, bt), the channel tiles dealt to the waves of a dv tile; fragments 2 at and
@@ -359,21 +358,23 @@ __device__ __forceinline__ void fwd_out_body(const FwdOutParams& p)
     }
 }
 
+constexpr int kUnits = 256;      // compute units
+
 // Workgroups that add up contributions for heads of 64 find two places on a compute unit: six chunks' values requested at
 // a time instead of eight leave the registers for it (128 heads of 64, 192 tokens: 35.9 -> 28.7 us).
-constexpr int add_places(int dk) { return dk == 64 ? 2 : 1; }
+constexpr int add_places(int dk, int cols) { return dk == 64 && cols == 64 ? 2 : 1; }
 
-template <typename T, int DK, int DV, bool ADD>
-__global__ __launch_bounds__(kThreads, ADD ? add_places(DK) : 1) void fwd_out_kernel(FwdOutParams p)
+template <typename T, int DK, int DV, int ADD>
+__global__ __launch_bounds__(kThreads, ADD ? add_places(DK, ADD) : 1) void fwd_out_kernel(FwdOutParams p)
 {
     if (p.dense) fwd_out_body<T, DK, DV, true, ADD>(p);
     else         fwd_out_body<T, DK, DV, false, ADD>(p);
 }
 
-template <typename T, int DK, int DV, bool ADD>
+template <typename T, int DK, int DV, int ADD>
 static hipError_t launch_one(const SeqDims& d, const FwdOutParams& p, hipStream_t stream)
 {
-    constexpr int DVW = ADD ? kAddCols : DV, NSPLIT = DV / DVW;
+    constexpr int DVW = ADD ? ADD : DV, NSPLIT = DV / DVW;
     typedef FwdOutLds<T, DK, DVW> L;
     auto kern = fwd_out_kernel<T, DK, DV, ADD>;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::total);
@@ -381,23 +382,26 @@ static hipError_t launch_one(const SeqDims& d, const FwdOutParams& p, hipStream_
     FwdOutParams a = p;
     a.chunk_items = (int)d.total_chunks() * NSPLIT;
     a.final_items = 0;
-    if constexpr (ADD) {
-        static_assert(add_places(DK) * L::total <= 160 * 1024, "LDS budget of the workgroups of a compute unit");
-        // final states beside the chunks, if all run at once on the 256 compute units
+    if constexpr (ADD != 0) {
+        constexpr int places = add_places(DK, ADD);
+        static_assert(places * L::total <= 160 * 1024, "LDS budget of the workgroups of a compute unit");
+        // Final states beside the chunks, if all run at once on the 256 compute units; where a sequence is one chunk, only on a
+        // unit each (192 heads of 64 x 64, 64 tokens: 13.4 us beside the chunks, two on a unit, 12.7 in them).
         const long long all = (long long)a.chunk_items + (long long)d.BH * NSPLIT;
-        if (p.hT && all <= 256 * add_places(DK)) a.final_items = d.BH * NSPLIT;
+        if (p.hT && all <= kUnits * (d.NC > 1 ? places : 1)) a.final_items = d.BH * NSPLIT;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)(a.chunk_items + a.final_items)), dim3(kThreads), L::total, stream, a);
     return hipGetLastError();
 }
 
-template <typename T, bool ADD>
+// COLS: 0, or the dv columns of a workgroup that adds up contributions
+template <typename T, int COLS>
 static hipError_t launch_dims(const SeqDims& d, const FwdOutParams& p, hipStream_t stream)
 {
-    if (d.dk == 128 && d.dv == 128) return launch_one<T, 128, 128, ADD>(d, p, stream);
-    if (d.dk == 64 && d.dv == 64) return launch_one<T, 64, 64, ADD>(d, p, stream);
-    if (d.dk == 128 && d.dv == 64) return launch_one<T, 128, 64, ADD>(d, p, stream);
-    if (d.dk == 64 && d.dv == 128) return launch_one<T, 64, 128, ADD>(d, p, stream);
+    if (d.dk == 128 && d.dv == 128) return launch_one<T, 128, 128, COLS>(d, p, stream);
+    if (d.dk == 64 && d.dv == 64) return launch_one<T, 64, 64, COLS>(d, p, stream);
+    if (d.dk == 128 && d.dv == 64) return launch_one<T, 128, 64, COLS>(d, p, stream);
+    if (d.dk == 64 && d.dv == 128) return launch_one<T, 64, 128, COLS>(d, p, stream);
     return hipErrorInvalidValue;
 }
 
@@ -417,7 +421,7 @@ hipError_t launch_fwd_out(const SeqDims& d, const void* q, const void* f, const 
     if (d.total_chunks() == 0) return hipSuccess;
     FwdOutParams p = out_params(d, q, f, v, o);
     p.ws = ws_state;
-    return d.io_bf16 ? launch_dims<__bf16, false>(d, p, stream) : launch_dims<float, false>(d, p, stream);
+    return d.io_bf16 ? launch_dims<__bf16, 0>(d, p, stream) : launch_dims<float, 0>(d, p, stream);
 }
 
 hipError_t launch_fwd_out_add(const SeqDims& d, const void* q, const void* f, const void* v, const float* add,
@@ -427,7 +431,10 @@ hipError_t launch_fwd_out_add(const SeqDims& d, const void* q, const void* f, co
     if (d.io_bf16 || d.packed) return hipErrorInvalidValue;
     FwdOutParams p = out_params(d, q, f, v, o);
     p.add = add; p.decay = decay; p.decay_stride = decay_stride; p.h0 = h0; p.hT = hT;
-    return launch_dims<float, true>(d, p, stream);
+    // Heads of 64 x 128 are halved only while the halves find a unit each: two of them on a unit take longer than one workgroup
+    // for all columns (us, halves / whole: 129 heads of 64 tokens 18.3 / 16.2, 192 19.2 / 16.8; 96 of 128 tokens 30.2 / 28.3, 48 of 256 tokens 29.8 / 27.5).
+    if (d.dk == 64 && d.dv == 128 && 2 * d.total_chunks() > kUnits) return launch_one<float, 64, 128, 128>(d, p, stream);
+    return launch_dims<float, 64>(d, p, stream);
 }
 
 }   // namespace hgrn2

@@ -107,10 +107,11 @@ def test_forward_fp32_from_contributions(B, H, N, dk, dv, states):
         check("hT", host(hT), rhT, TOL["f32"])
 
 
-# The same, where the final states just find a place beside the chunks (256 workgroups, 512 with dk = 64) and where the last
-# chunks' workgroups form them, token-major
+# The same, where the final states just find a place beside the chunks (256 workgroups, 512 with heads of 64 x 64) and where the
+# last chunks' workgroups form them, token-major; 64 x 128: 64 columns a workgroup up to 128 chunks, all columns beyond
 @pytest.mark.parametrize("BH,NC,dk,dv", [(32, 3, 128, 128), (48, 2, 128, 128), (64, 3, 128, 64), (96, 2, 128, 64),
-                                         (128, 3, 64, 64), (192, 2, 64, 64), (64, 3, 64, 128), (96, 2, 64, 128)])
+                                         (128, 3, 64, 64), (192, 2, 64, 64), (64, 3, 64, 128), (96, 2, 64, 128),
+                                         (128, 1, 64, 128), (130, 1, 64, 128), (10, 13, 64, 128), (128, 1, 64, 64), (192, 1, 64, 64)])
 def test_forward_fp32_final_states_beside_the_chunks(BH, NC, dk, dv):
     print("\n[fwd f32, final states] BH=%d NC=%d dk=%d dv=%d" % (BH, NC, dk, dv), flush=True)
     w = synth.make_sequence(3250 + BH, 2, BH // 2, 64 * NC - 7, dk, dv, io_dtype="f32", lb=0.5, with_h0=True)
