@@ -30,7 +30,8 @@ inline BwdFusedPlan uncut_bwd(int NC)
 // walks run while the memory system is busiest).
 constexpr double kBwdLightCost = 0.24;
 
-inline BwdFusedPlan light_bwd(int NC, int R, double* longest)
+// longest: what the longest run takes, at `cost` a light chunk.
+inline BwdFusedPlan light_bwd(int NC, int R, double cost, double* longest)
 {
     BwdFusedPlan pl = {};
     double sum = 0.0, x = 1.0;
@@ -47,7 +48,7 @@ inline BwdFusedPlan light_bwd(int NC, int R, double* longest)
     }
     *longest = 0.0;
     for (int r = 0; r < R; ++r) {
-        const double t = pl.bnd[r + 1] - pl.bnd[r] + kBwdLightCost * (NC - pl.bnd[r + 1]);
+        const double t = pl.bnd[r + 1] - pl.bnd[r] + cost * (NC - pl.bnd[r + 1]);
         if (t > *longest) *longest = t;
     }
     pl.light = 1; pl.R = R; pl.s_sub = 1;
@@ -72,43 +73,61 @@ inline BwdFusedPlan ends_bwd(int NC, int R)
     return pl;
 }
 
+// What the walks take besides the full walk of their run, in chunks of it (128 x 128: 7.5 us a chunk, 64 x 64: 5 us): a chunk of a
+// light walk; the two more launches of the walks from zero; a megabyte of states that those write and read twice.
+// Fitted with the constants of plan_bwd_runs() to 1750 timings: 1 to 250 sequences of 2 to 256 chunks, gates given and formed,
+// every cut tried at each size; the chosen cut takes 0.1 to 0.2% more than the best on average.
+struct BwdCost { double light, ends, mb; };
+inline BwdCost bwd_cost(int dk, int dv)
+{
+    if (dk == 64 && dv == 64) return {0.17, 0.49, 0.23};
+    if (dk == 128 && dv == 128) return {0.27, 2.2, 0.055};
+    if (dk == 128) return {0.29, 2.0, 0.037};
+    return {0.28, 1.3, 0.051};
+}
+
 inline BwdFusedPlan plan_bwd_runs(int BH, int NC, int dk, int dv, bool io_bf16, int places)
 {
     if (places == 1 || BH <= 0 || NC <= 1) return uncut_bwd(NC);
     const bool pairs = dk == 64 && dv == 64 && io_bf16;        // workgroups of four waves, two on a compute unit
+    double longest;
     if (places == kOnePerUnit || !io_bf16) {
         int R = kOnePerUnit / BH;
         if (R > NC / 4) R = NC / 4;
-        double longest;
-        if (R >= 2 && R <= 4) return light_bwd(NC, R, &longest);
+        if (R >= 2 && R <= 4) return light_bwd(NC, R, kBwdLightCost, &longest);
         return R < 2 ? uncut_bwd(NC) : ends_bwd(NC, R);
     }
-    // As many runs as find a place, however short: a run of one chunk costs little more than that chunk.  Light walks
-    // or walks from zero by what they take, in chunks of the full walk (128 x 128: 7.5 us a chunk, 64 x 64: 5 us, each
-    // on a compute unit of its own; two on one: 1.45 times as long).  The walks from zero and their carry are two more launches,
-    // 2.1 to 2.4 chunks, and states that are written and read twice.  1, 16 and 64 heads; us with runs of at
+    // Runs of one, two or four chunks and more, as many as find a place; light walks or walks from zero, by what they take (two
+    // workgroups on a compute unit: 1.4 times as long).  1, 16 and 64 heads; us with runs of at
     // least four chunks -> now:
     //   128 x 128:  4 chunks 34 -> 16.4, 34.8 -> 17.0, 36 -> 19.5 (light)     16 chunks 48.9 -> 29.7 (from zero), 51.1 -> 36.3 (light), 56
     //              32 chunks 55.3 -> 33.3, 60.9 -> 47.9 (from zero), 115       64 chunks 57.0 -> 40.3, 68.2 (from zero)
     //   64 x 64:    4 chunks 23.2 -> 12.2, 23.7 -> 12.5, 24.3 -> 13.1 (light)  16 chunks 34.2 -> 19.8, 34.8 -> 22.6, 35.9 -> 34.4 (from zero)
+    // Runs of one chunk only, as long as they find a place, are too many for few long sequences (one head of 256 chunks: 64 x 64 46.7 us
+    // in 64 runs, 63.0 in 256; 128 x 128 67.0 and 76.8, 61.0 in 128): every run's state is added up by one after the other.
+    const BwdCost cost = bwd_cost(dk, dv);
+    const int most = (pairs ? 2 : 1) * kOnePerUnit;
     BwdFusedPlan best = uncut_bwd(NC);
     double least = NC;
-    for (int at_once = kOnePerUnit; at_once <= (pairs ? 2 : 1) * kOnePerUnit; at_once += kOnePerUnit) {
-        int R = at_once / BH;
-        if (R > NC) R = NC;
-        if (R < 2) continue;
-        const double crowd = R * BH > kOnePerUnit ? 1.45 : 1.0;
-        double t;
-        const BwdFusedPlan light = light_bwd(NC, R < kMaxLightRuns ? R : kMaxLightRuns, &t);
-        if (crowd * t < least) { least = crowd * t; best = light; }
-        // (two or three runs per sequence: the walks from zero read most of q, f and grad_o once more while the
-        // memory system is busy already; 128 x 128, 85 heads of 128 chunks 513 us light, 537 us from zero, but 64 heads, four runs each, 424 and 400)
-        if (R < 4) continue;
-        const BwdFusedPlan ends = ends_bwd(NC, R);
-        const double mb = 4e-6 * dk * dv * (double)BH * ends.seg_tail;
-        t = crowd * ends.rc + 2.2 + 0.22 * ends.sub_chunks + 0.02 * ends.seg_tail + (dk == 128 && dv == 128 ? 0.045 : 0.07) * mb;
-        if (ends.R > 1 && t < least) { least = t; best = ends; }
-    }
+    for (int at_once = kOnePerUnit; at_once <= most; at_once += kOnePerUnit)
+        for (int shortest = 1; shortest <= 4; shortest *= 2) {
+            int R = at_once / BH;
+            if (R > NC / shortest) R = NC / shortest;
+            if (R < 2) continue;
+            const double crowd = R * BH > kOnePerUnit ? 1.4 : 1.0;
+            if (shortest == 1) {
+                const BwdFusedPlan light = light_bwd(NC, R < kMaxLightRuns ? R : kMaxLightRuns, cost.light, &longest);
+                const double t = (light.R * BH > kOnePerUnit ? 1.4 : 1.0) * longest;
+                if (t < least) { least = t; best = light; }
+            }
+            // (two or three runs per sequence: the walks from zero read most of q, f and grad_o once more while the
+            // memory system is busy already; 128 x 128, 85 heads of 128 chunks 513 us light, 537 us from zero, but 64 heads, four runs each, 424 and 400)
+            if (R < 4) continue;
+            const BwdFusedPlan ends = ends_bwd(NC, R);
+            const double mb = 4e-6 * dk * dv * (double)BH * ends.seg_tail;
+            const double t = crowd * ends.rc + cost.ends + 0.3 * ends.sub_chunks + 0.037 * ends.seg_tail + cost.mb * mb;
+            if (ends.R > 1 && t < least) { least = t; best = ends; }
+        }
     return best;
 }
 

@@ -48,3 +48,28 @@ def test_runs_cover_every_chunk_and_fit_the_chip(lib, dk, dv, bf16):
                 else:
                     assert (R - 1) * rc < NC <= R * rc and sub * s_sub == rc, case
                     assert tail == (0 if R == 1 else -(-(NC - rc) // sub)), case
+
+
+# us of the reverse walk of a training pair at some sizes, cut into light runs (L) or runs from zero (E), as measured on an MI355X
+# (one run to the next: 1%)
+MEASURED = [
+    (64, 64, 1, 256, {"E64": 46.7, "E128": 46.5, "E256": 63.0}),
+    (128, 128, 1, 256, {"E64": 67.0, "E128": 61.0, "E256": 76.8}),
+    (128, 64, 1, 256, {"E64": 55.6, "E128": 52.3, "E256": 68.4}),
+    (64, 128, 1, 256, {"E64": 61.9, "E128": 55.1, "E256": 70.3}),
+    (64, 64, 128, 12, {"L2": 40.0, "L3": 37.8, "L4": 38.6}),
+    (64, 64, 80, 20, {"L3": 50.6, "E5": 48.4, "L5": 45.9, "L6": 46.2}),
+    (64, 64, 120, 20, {"L4": 55.7, "E4": 57.4}),
+    (64, 128, 48, 32, {"L5": 87.6, "E5": 81.7}),
+    (64, 128, 1, 12, {"L12": 32.5, "E12": 25.4, "L6": 34.0, "E6": 33.1}),
+    (128, 64, 48, 32, {"L5": 71.1, "E5": 72.1}),
+    (128, 128, 56, 40, {"L4": 118.4, "E4": 122.5}),
+]
+
+
+@pytest.mark.parametrize("dk,dv,BH,NC,us", MEASURED)
+def test_the_cut_is_one_of_the_fast_ones(lib, dk, dv, BH, NC, us):
+    out = (ctypes.c_int * (7 + lib.max_runs()))()
+    lib.plan(BH, NC, dk, dv, 1, 0, out)
+    cut = "%s%d" % ("L" if out[5] else "E", out[0])
+    assert cut in us and us[cut] <= 1.03 * min(us.values()), (cut, us)
