@@ -78,7 +78,6 @@ struct BwdGradParams {
     const float* run_state;
     int R, rc, s_sub, seg_tail;
     int light;
-    int bnd[kMaxLightRuns + 1];
     int* flag;               // null, or set to 1 when a gate product falls below the floor of the reciprocals
     int beta_spans;          // row sets of partial sums per head (packed batches)
     // What bwd_ends_kernel leaves: per slot a state gradient [dk][dv] and the gate products [dk].  Spans of a
@@ -86,6 +85,7 @@ struct BwdGradParams {
     // runs of segmented sequences: slot = run.
     float* span_add;
     float* span_decay;
+    int bnd[kMaxLightRuns + 1];      // (last: whatever is read of the arguments by every walk lies close together)
 };
 
 
