@@ -186,12 +186,14 @@ __device__ __forceinline__ f32x2 h1_gate(RAW& raw, const f32x2& kept, bool again
     }
 }
 
-// Workgroup -> sequence b, 64 channels cb, run r.
+// Workgroup -> sequence b, 64 channels cb, run r.  (CUT: sequences are cut into runs.  The kernels for whole sequences have
+// nothing of it in them: 0.25 us of the 10.6 us a backward pass over 64 tokens takes.)
 struct H1Item { int b, cb, r; };
+template <bool CUT>
 __device__ __forceinline__ H1Item h1_item(const H1Params& p)
 {
-    const int id = (int)blockIdx.x, r = id % p.R, s = id / p.R;
-    return H1Item{s / p.NCB, s % p.NCB, r};
+    const int s = (int)blockIdx.x;
+    return H1Item{s / p.NCB, s % p.NCB, CUT ? (int)blockIdx.y : 0};
 }
 
 // The value with which run `it.r` starts, given the one the whole sequence starts with: the runs before it
@@ -228,7 +230,7 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_ends_kernel(H1Params p)
     constexpr int TS = kH1SegShort, BLOCK = kH1Segs * TS;
     constexpr int GS = GATE_BF16 ? 1 : 2;
     __shared__ f32x2 sA[2][kH1Segs][32], sX[2][kH1Segs][32];
-    const H1Item it = h1_item(p);
+    const H1Item it = h1_item<true>(p);
     if (it.r == (REVERSE ? 0 : p.R - 1)) return;
     const int cp = threadIdx.x & 31, vs = threadIdx.x >> 5;
     const size_t c0 = (size_t)it.cb * kH1Chan + 2 * cp;
@@ -299,7 +301,7 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_ends_kernel(H1Params p)
 // Two register sets: while one block is worked on out of one set, the loads of the next block,
 // issued in one burst before that work starts, fill the other.  (A wave can wait for "all but the
 // n youngest" of its loads only for n < 64, so a set is kept to 48 loads: 16-token segments.)
-template <bool GATE_BF16, bool ACT>
+template <bool GATE_BF16, bool ACT, bool CUT>
 __global__ __launch_bounds__(kH1Threads) void hgrn1_fwd_kernel(H1Params p)
 {
     constexpr int TS = kH1SegShort, BLOCK = kH1Segs * TS;
@@ -307,11 +309,11 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_fwd_kernel(H1Params p)
     __shared__ f32x2 sA[2][kH1Segs][32], sH[2][kH1Segs][32];
     const int cp = threadIdx.x & 31;                             // channel pair of the workgroup's 64 channels
     const int vs = threadIdx.x >> 5;                             // segment of the block: each half-wave walks its own
-    const H1Item item = h1_item(p);
+    const H1Item item = h1_item<CUT>(p);
     const int b = item.b;
     const size_t c0 = (size_t)item.cb * kH1Chan + 2 * cp;
     // the run's blocks and the token it ends before (the whole sequence, if that is not cut)
-    const int blk0 = item.r * p.rb, blk1 = min(p.NBLK, blk0 + p.rb), N = min(p.N, blk1 * BLOCK);
+    const int blk0 = CUT ? item.r * p.rb : 0, blk1 = CUT ? min(p.NBLK, blk0 + p.rb) : p.NBLK, N = CUT ? min(p.N, blk1 * BLOCK) : p.N;
     const size_t seq = (size_t)b * p.N * p.d;
     const unsigned lane_b = 2u * (unsigned)c0;                   // byte offset of this lane's pair in a bf16 row
     const f32x2 beta = ACT ? *reinterpret_cast<const f32x2*>(p.beta + c0) : f32x2{0.0f, 0.0f};
@@ -336,7 +338,7 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_fwd_kernel(H1Params p)
         }
     };
     f32x2 carry = p.h0 ? *reinterpret_cast<const f32x2*>(p.h0 + (size_t)b * p.d + c0) : f32x2{0.0f, 0.0f};
-    if (p.R > 1) carry = h1_enter<false>(p, item, c0, carry);
+    if constexpr (CUT) carry = h1_enter<false>(p, item, c0, carry);
     // one block out of one register set (a block past the end: every row neutral, every store dropped)
     auto work = [&](Rows& s, int blk) {
         const int t0 = blk * BLOCK + vs * TS;
@@ -387,7 +389,7 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_fwd_kernel(H1Params p)
         work(odd, blk + 1);
         if (blk + 2 >= blk1) break;
     }
-    if (p.hN && vs == 0 && item.r == p.R - 1) *reinterpret_cast<f32x2*>(p.hN + (size_t)b * p.d + c0) = carry;
+    if (p.hN && vs == 0 && (!CUT || item.r == p.R - 1)) *reinterpret_cast<f32x2*>(p.hN + (size_t)b * p.d + c0) = carry;
 }
 
 // ---- backward ------------------------------------------------------------------------------------
@@ -398,7 +400,7 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_fwd_kernel(H1Params p)
 //   dzf = df (f - beta)(1 - f) / (1 - beta),   dbeta = sum over batch and time of df (1 - f) / (1 - beta)
 // SAVED: the forward pass of the same step has left the state entering every 16-token segment in
 // `carry`; the forward phase below (a second pass over f and i) is then left out.
-template <bool GATE_BF16, bool ACT, bool SAVED>
+template <bool GATE_BF16, bool ACT, bool SAVED, bool CUT>
 __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
 {
     constexpr int TS = ACT ? kH1SegShort : kH1SegLong, BLOCK = kH1Segs * TS;
@@ -406,11 +408,11 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
     __shared__ f32x2 sA[2][kH1Segs][32], sX[2][kH1Segs][32];      // sX: forward H, later the reverse summary
     const int cp = threadIdx.x & 31;
     const int vs = threadIdx.x >> 5;
-    const H1Item item = h1_item(p);
+    const H1Item item = h1_item<CUT>(p);
     const int b = item.b;
     const size_t c0 = (size_t)item.cb * kH1Chan + 2 * cp;
     // the run's blocks and the token it ends before (the whole sequence, if that is not cut)
-    const int blk0 = item.r * p.rb, blk1 = min(p.NBLK, blk0 + p.rb), N = min(p.N, blk1 * BLOCK);
+    const int blk0 = CUT ? item.r * p.rb : 0, blk1 = CUT ? min(p.NBLK, blk0 + p.rb) : p.NBLK, N = CUT ? min(p.N, blk1 * BLOCK) : p.N;
     const size_t seq = (size_t)b * p.N * p.d;
     const unsigned lane_b = 2u * (unsigned)c0;
     const int last_blk = blk1 - 1;
@@ -449,7 +451,7 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
     // The last block is not followed by a refill: its gates and inputs stay in their registers,
     // which is where the reverse phase starts.
     f32x2 carry = p.h0 ? *reinterpret_cast<const f32x2*>(p.h0 + (size_t)b * p.d + c0) : f32x2{0.0f, 0.0f};
-    if (!SAVED && p.R > 1) carry = h1_enter<false>(p, item, c0, carry);
+    if constexpr (CUT && !SAVED) carry = h1_enter<false>(p, item, c0, carry);
     auto forward_block = [&](int blk, auto refill_tag) {
         constexpr bool REFILL = decltype(refill_tag)::value;
         const int t0 = blk * BLOCK + vs * TS;
@@ -498,7 +500,7 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
         }
     }
     f32x2 cr = p.dhN ? *reinterpret_cast<const f32x2*>(p.dhN + (size_t)b * p.d + c0) : f32x2{0.0f, 0.0f};
-    if (p.R > 1) cr = h1_enter<true>(p, item, c0, cr);
+    if constexpr (CUT) cr = h1_enter<true>(p, item, c0, cr);
     f32x2 dbeta = {0.0f, 0.0f};
     for (int blk = last_blk; blk >= blk0; --blk, ++it) {
         const int t0 = blk * BLOCK + vs * TS;
@@ -591,7 +593,7 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
             f32x2 t = {0.0f, 0.0f};
 #pragma unroll
             for (int j = 0; j < kH1Segs; ++j) { const f32x2 u = sX[0][j][cp]; t = f32x2{t.x + u.x, t.y + u.y}; }
-            *reinterpret_cast<f32x2*>(p.dbeta_part + ((size_t)b * p.R + item.r) * p.d + c0) = t;
+            *reinterpret_cast<f32x2*>(p.dbeta_part + (CUT ? (size_t)b * p.R + item.r : (size_t)b) * p.d + c0) = t;
         }
     }
 }
@@ -664,6 +666,13 @@ static H1Params h1_params(int B, int N, int d, int seg, void* ws, bool in_place)
     return p;
 }
 
+// f(a, b, c) with the three flags as constants
+template <typename F> static void h1_by_flags(bool a, bool b, bool c, F f)
+{
+    auto with = [](bool x, auto g) { if (x) g(std::true_type()); else g(std::false_type()); };
+    with(a, [&](auto A) { with(b, [&](auto B) { with(c, [&](auto C) { f(A, B, C); }); }); });
+}
+
 // (A, H) of every run, in segments of 16 tokens whatever the walk takes
 template <bool REVERSE>
 static void launch_h1_ends(H1Params p, int seg, bool gate_bf16, hipStream_t stream)
@@ -672,7 +681,7 @@ static void launch_h1_ends(H1Params p, int seg, bool gate_bf16, hipStream_t stre
     p.NBLK = p.NBLK16;
     auto kern = p.beta ? (gate_bf16 ? hgrn1_ends_kernel<true, true, REVERSE> : hgrn1_ends_kernel<false, true, REVERSE>)
                        : (gate_bf16 ? hgrn1_ends_kernel<true, false, REVERSE> : hgrn1_ends_kernel<false, false, REVERSE>);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(p.B * p.NCB * p.R)), dim3(kH1Threads), 0, stream, p);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.B * p.NCB), (unsigned)p.R), dim3(kH1Threads), 0, stream, p);
 }
 
 hipError_t launch_hgrn1_fwd(int B, int N, int d, bool gate_bf16, const void* f, const void* i, const void* o,
@@ -687,10 +696,10 @@ hipError_t launch_hgrn1_fwd(int B, int N, int d, bool gate_bf16, const void* f, 
     H1Params p = h1_params(B, N, d, kH1SegShort, ws, h0 && h0 == hN);
     p.f = f; p.i = i; p.o = o; p.beta = beta; p.h0 = h0; p.y = y; p.hN = hN;
     if (p.R > 1) launch_h1_ends<false>(p, kH1SegShort, gate_bf16, stream);
-    const dim3 grid((unsigned)(B * p.NCB * p.R));
-    auto kern = beta ? (gate_bf16 ? hgrn1_fwd_kernel<true, true> : hgrn1_fwd_kernel<false, true>)
-                     : (gate_bf16 ? hgrn1_fwd_kernel<true, false> : hgrn1_fwd_kernel<false, false>);
-    hipLaunchKernelGGL(kern, grid, dim3(kH1Threads), 0, stream, p);
+    const dim3 grid((unsigned)(B * p.NCB), (unsigned)p.R);
+    h1_by_flags(gate_bf16, beta != nullptr, p.R > 1, [&](auto GATE_BF16, auto ACT, auto CUT) {
+        hipLaunchKernelGGL((hgrn1_fwd_kernel<GATE_BF16, ACT, CUT>), grid, dim3(kH1Threads), 0, stream, p);
+    });
     return hipGetLastError();
 }
 
@@ -713,13 +722,11 @@ hipError_t launch_hgrn1_bwd(int B, int N, int d, bool gate_bf16, const void* f, 
         if (!states_saved) launch_h1_ends<false>(p, seg, gate_bf16, stream);
         launch_h1_ends<true>(p, seg, gate_bf16, stream);
     }
-    const dim3 grid((unsigned)(B * p.NCB * p.R));
-    auto kern = states_saved
-                    ? (beta ? (gate_bf16 ? hgrn1_bwd_kernel<true, true, true> : hgrn1_bwd_kernel<false, true, true>)
-                            : (gate_bf16 ? hgrn1_bwd_kernel<true, false, true> : hgrn1_bwd_kernel<false, false, true>))
-                    : (beta ? (gate_bf16 ? hgrn1_bwd_kernel<true, true, false> : hgrn1_bwd_kernel<false, true, false>)
-                            : (gate_bf16 ? hgrn1_bwd_kernel<true, false, false> : hgrn1_bwd_kernel<false, false, false>));
-    hipLaunchKernelGGL(kern, grid, dim3(kH1Threads), 0, stream, p);
+    const dim3 grid((unsigned)(B * p.NCB), (unsigned)p.R);
+    h1_by_flags(gate_bf16, beta != nullptr, p.R > 1, [&](auto GATE_BF16, auto ACT, auto CUT) {
+        if (states_saved) hipLaunchKernelGGL((hgrn1_bwd_kernel<GATE_BF16, ACT, true, CUT>), grid, dim3(kH1Threads), 0, stream, p);
+        else              hipLaunchKernelGGL((hgrn1_bwd_kernel<GATE_BF16, ACT, false, CUT>), grid, dim3(kH1Threads), 0, stream, p);
+    });
     if (beta && dbeta)
         hipLaunchKernelGGL(hgrn1_reduce_beta_kernel, dim3((d + 255) / 256), dim3(256), 0, stream, p.dbeta_part, dbeta, B * p.R, d);
     return hipGetLastError();
