@@ -544,8 +544,9 @@ __global__ __launch_bounds__(kH1Threads) void hgrn1_bwd_kernel(H1Params p)
             }
         }
         // gradients, last token first; every row is refilled with the previous block's token once consumed
-        // block 0 has nothing before it: a negative first token makes its refills address an empty range
-        const int pb = (blk - 1) * BLOCK, cb0 = blk * BLOCK;
+        // the run's first block is the last one walked: a negative first token makes its refills address an empty range
+        // (one block to a run: they would read every input a second time)
+        const int pb = blk > blk0 ? (blk - 1) * BLOCK : -BLOCK, cb0 = blk * BLOCK;
         const H1Rsrc rdo = h1_rows_from(p.dout, seq, cb0, N, p.d, 2), rdf = h1_rows_from(p.df, seq, cb0, N, p.d, 2),
                      rdi = h1_rows_from(p.di, seq, cb0, N, p.d, 2);
         const H1Rsrc rf = h1_rows_from(p.f, seq, pb, N, p.d, 2 * GS), ri = h1_rows_from(p.i, seq, pb, N, p.d, 2),
