@@ -1,7 +1,8 @@
 """The reverse walk of a training pair cut into runs of one or a few chunks (small batches): light walks by up to 16
 runs, and boundaries walked to from zero chunk by chunk; ragged last chunks, every head-dimension pair, both layouts,
-gates given and formed in the kernels, in bf16 and fp32, with and without states, 64 and 16 tokens per chunk.  Compared with the
-fp64 oracle: max|x-y|/max|y| <= 2e-2 per tensor (bf16 storage)."""
+gates given and formed in the kernels, in bf16 and fp32, with and without states, 64 and 16 tokens per chunk; with gates
+after which nothing of a chunk is left and with gates near one (0.985 to 1: a third after two chunks, 1% after ten), which show
+whether a run knows of all chunks after it.  Compared with the fp64 oracle: max|x-y|/max|y| <= 2e-2 per tensor (bf16 storage)."""
 import numpy as np
 import pytest
 import torch
@@ -14,6 +15,7 @@ pytestmark = pytest.mark.gpu
 BNHD = binding.HGRN2_LAYOUT_BNHD
 
 
+@pytest.mark.parametrize("slow", [False, True])
 @pytest.mark.parametrize("B,H,N,dk,dv,layout,states,gated,gate,chunk", [
     (1, 2, 65, 128, 128, 0, True, False, "bf16", 0),       # two runs of one chunk, the second of one token
     (2, 3, 640, 128, 128, 1, True, True, "bf16", 0),       # 10 chunks, 10 light runs
@@ -26,15 +28,17 @@ BNHD = binding.HGRN2_LAYOUT_BNHD
     (3, 20, 500, 64, 64, 0, True, True, "bf16", 0),        # 8 chunks, two workgroups on a compute unit
     (2, 2, 150, 64, 64, 1, True, True, "bf16", 16),        # 10 chunks of 16 tokens
 ])
-def test_bwd_saved_in_short_runs(B, H, N, dk, dv, layout, states, gated, gate, chunk):
-    print("\n[bwd short runs] B=%d H=%d N=%d dk=%d dv=%d layout=%d chunk=%d" % (B, H, N, dk, dv, layout, chunk), flush=True)
-    w = synth.make_sequence(6100 + N + dk, B, H, N, dk, dv, io_dtype="bf16", gate_dtype=gate, lb=0.3, with_h0=states,
+def test_bwd_saved_in_short_runs(B, H, N, dk, dv, layout, states, gated, gate, chunk, slow):
+    print("\n[bwd short runs] B=%d H=%d N=%d dk=%d dv=%d layout=%d chunk=%d slow=%s" % (B, H, N, dk, dv, layout, chunk, slow), flush=True)
+    if slow and not gated:
+        gate = "f32"                     # (bf16 has four values there)
+    w = synth.make_sequence(6100 + N + dk, B, H, N, dk, dv, io_dtype="bf16", gate_dtype=gate, lb=0.985 if slow else 0.3, with_h0=states,
                             with_dO=True, with_dhT=states)
     put = (lambda t: t.permute(0, 2, 1, 3).contiguous()) if layout == BNHD else (lambda t: t)
     get = (lambda t: host(t.permute(0, 2, 1, 3))) if layout == BNHD else host
     rng = np.random.default_rng(6200 + N)
     gates = synth.bf16_round(rng.standard_normal((B, H, N, dk)).astype(np.float32)) if gated else w.f
-    beta = rng.uniform(0.2, 0.9, size=(H, dk)).astype(np.float32) if gated else None
+    beta = rng.uniform(*((0.98, 0.99) if slow else (0.2, 0.9)), size=(H, dk)).astype(np.float32) if gated else None
     q, f, v, dO = put(dev(w.q, "bf16")), put(dev(gates, gate)), put(dev(w.v, "bf16")), put(dev(w.dO, "bf16"))
     h0, dhT = (dev(w.h0), dev(w.dhT)) if states else (None, None)
     bd = torch.from_numpy(beta).cuda() if gated else None
