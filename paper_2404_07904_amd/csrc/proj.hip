@@ -61,10 +61,10 @@ constexpr int vm_lgkm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; }
 // (1.9 PFLOP/s), 85 us the loads' way into LDS next to 192 KB of LDS reads a step (loads that never miss L2 save 14 us, no wait for them nothing), 38 us
 // the epilogue.  Four waves of 128 x 128, with a third fewer LDS reads but one wave per SIMD: 365 us.
 template <int EPI, int TM, int TN, int WM, int WN, int KG, int NS>
-__global__ __launch_bounds__(64 * WM * WN * KG, WM * WN * KG == 4 ? 1 : 2) void gemm_nt_kernel(GemmParams p)
+__global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_kernel(GemmParams p)
 {
     constexpr int NWV = WM * WN * KG, THREADS = 64 * NWV;
-    static_assert((NWV == 8 || NWV == 4) && 4 % KG == 0 && NS >= 5, "four or eight waves");
+    static_assert(NWV == 8 && 4 % KG == 0 && NS >= 5 && NS % 2 == 1, "eight waves, a ring of whole steps and one tile");
     constexpr int SLOT = (TM > TN ? TM : TN) * 128;               // bytes of a slot of the ring
     constexpr int LA = TM / 8 / NWV, LB = TN / 8 / NWV;           // load instructions per wave for a tile of A, of B
     constexpr int NI = TM / WM / 32, NJ = TN / WN / 32, KPW = 4 / KG;
@@ -140,25 +140,24 @@ __global__ __launch_bounds__(64 * WM * WN * KG, WM * WN * KG == 4 ? 1 : 2) void 
         for (int t = 0; t < NM; ++t)
             if (t >= from && t < to) M::mma(acc[t / NJ][t % NJ], fb[par][t % NJ], fa[par][t / NJ]);
     };
-        // halves 0 .. NS - 2 (A of step 0, B of step 0, A of step 1, ...)
+    // tiles 0 .. NS - 2 (A of step 0, B of step 0, A of step 1, ...); the first two have to be there
 #pragma unroll
     for (int h = 0; h < NS - 1; ++h)
 #pragma unroll
         for (int j = 0; j < ((h & 1) ? LB : LA); ++j) { if (h & 1) load_b(h, h >> 1, j); else load_a(h, h >> 1, j); }
-    constexpr int FIRST = (NS - 3) / 2 * (LA + LB) + ((NS - 3) % 2 ? LA : 0);
-    __builtin_amdgcn_s_waitcnt(vm_lgkm(FIRST));
+    __builtin_amdgcn_s_waitcnt(vm_lgkm((NS - 3) / 2 * (LA + LB)));
     __builtin_amdgcn_s_barrier();
     auto wrap = [](int s) { return s >= NS ? s - NS : s; };
     int s0 = 0;                                   // slot of A of the step, B behind it
     read_frags(fa[0], fb[0], 0, 1, KPW * kg);
-    // the loads that refill the two slots a step has freed: tile 2 k + NS, then 2 k + NS + 1 (even tiles are A's)
-    constexpr int L1 = (NS & 1) ? LB : LA, L2 = (NS & 1) ? LA : LB;
-    auto refill = [&](int slot, int k, int j) {   // j = 0 .. L1 + L2 - 1
-        const int sl = j < L1 ? slot : wrap(slot + 1), h = NS + (j < L1 ? 0 : 1);
-        if (h & 1) load_b(sl, k + (h >> 1), j < L1 ? j : j - L1); else load_a(sl, k + (h >> 1), j < L1 ? j : j - L1);
+    // the loads that refill the two slots a step has freed: tile 2 k + NS (of B), then 2 k + NS + 1 (of A; steps taken as half of a
+    // tile's number: written as sums, the scalar addresses cost small products 0.2 us)
+    auto refill = [&](int slot, int k, int j) {   // j = 0 .. LB + LA - 1
+        const int sl = j < LB ? slot : wrap(slot + 1), h = NS + (j < LB ? 0 : 1);
+        if (h & 1) load_b(sl, k + (h >> 1), j < LB ? j : j - LB); else load_a(sl, k + (h >> 1), j < LB ? j : j - LB);
     };
-    // a step: phases 0 .. KPW - 1; the loads behind the barrier of step k go out in its last phase and the first phases of the next
-    constexpr int NL = L1 + L2, LAST = L1;
+    // a step: phases 0 .. KPW - 1; of the loads behind the barrier of step k, B's go out in its last phase and A's in the first phase of the next
+    constexpr int NL = LB + LA, LAST = LB;
     for (int k = 0; k < nk; ++k) {
         const int sn = wrap(s0 + 2), sp = wrap(s0 + NS - 2);       // slots of the next and of the previous step
 #pragma unroll
@@ -171,7 +170,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, WM * WN * KG == 4 ? 1 : 2) void 
 #pragma unroll
                     for (int j = LAST; j < NL; ++j) refill(sp, k - 1, j);
                 }
-                __builtin_amdgcn_s_waitcnt(vm_lgkm((NS & 1) ? (NS - 5) / 2 * (LA + LB) + L2 : (NS - 4) / 2 * (LA + LB)));
+                __builtin_amdgcn_s_waitcnt(vm_lgkm((NS - 5) / 2 * (LA + LB) + LA));
                 __builtin_amdgcn_s_barrier();
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -491,7 +490,7 @@ __global__ __launch_bounds__(256) void proj_dact_kernel(const __bf16* dz, const 
         for (int k0 = 0; k0 < ROWS; k0 += 32) {
             const bf16x8 v = column_piece(tile, kActPitch, k0, 64 * w + 16 * x, lane);
             const int tok = t0 + k0 + 8 * (lane >> 4);
-            if (tok < Mp) *reinterpret_cast<bf16x8*>(dAt + (size_t)(col0 + 64 * w + 16 * x + (lane & 15)) * Mp + tok) = v;
+            *reinterpret_cast<bf16x8*>(dAt + (size_t)(col0 + 64 * w + 16 * x + (lane & 15)) * Mp + tok) = v;
         }
 }
 
