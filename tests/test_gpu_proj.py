@@ -153,12 +153,15 @@ def test_proj_full_width_sampled_rows():
 
 @pytest.mark.parametrize("M,d", [(1, 256),          # one token: 63 padded ones in the product over the tokens
                                  (1500, 512),       # a padded step; 32 tokens to a workgroup of the element-wise pass
-                                 (4100, 256),       # dW3 in 64 x 64 tiles, its contraction cut into shares
-                                 (2048, 1024),      # 128 x 128 tiles
-                                 (4097, 1280),      # 256 x 256 tiles with one row in the last
-                                 (9000, 1024)])     # dW3 in 192 x 256 or 128 x 128 tiles
+                                 (4100, 256),       # dW3 in 64 x 64 tiles, its contraction in 4 shares of 16 and 17 steps
+                                 (2048, 1024),      # 128 x 128 tiles, one share
+                                 (3500, 768), (4900, 512), (9984, 256),      # dW3 in 128 x 128 tiles and 2, 4, 16 shares
+                                 (4097, 1280),      # 256 x 256 tiles with one row in the last; dW3 in 192 x 256, one share
+                                 (5633, 1280), (14720, 1024),                # dW3 in 192 x 256 tiles and 2, 4 shares
+                                 (9000, 1024)])     # dx in 256 x 256 tiles
 def test_proj_tiles_and_padding(M, d):
-    """Every tile size of the products, with a remainder of tokens: against fp32 products of the same rounded operands
+    """Every tile size of the products and number of shares, with a remainder of tokens (tests/test_proj_plan_host.py says which
+    plan each size takes): against fp32 products of the same rounded operands
     (torch), the workspace filled with NaN before; bf16 outputs to 2 units in the last place of the
     largest value, the fp32 sums to 1e-3 (see below)."""
     print("\n[proj tiles] M=%d d=%d" % (M, d), flush=True)
