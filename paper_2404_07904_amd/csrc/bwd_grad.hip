@@ -1158,7 +1158,7 @@ static hipError_t launch_fused_one(const SeqDims& d, const BwdGradParams& p, hip
     return hipGetLastError();
 }
 
-BwdFusedPlan plan_bwd_fused(const SeqDims& d, int places) { return plan_bwd_runs(d.BH, d.NC, d.dk, d.dv, d.io_bf16, places); }
+BwdFusedPlan plan_bwd_fused(const SeqDims& d, int places) { return plan_bwd_runs(d.BH, d.NC, d.dk, d.dv, d.io_bf16, places, d.lay.sub < kChunk); }
 
 hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void* q, const void* f, const void* v,
                             const void* grad_o, const void* ws_state, const float* grad_hT, float* grad_h0,

@@ -86,7 +86,9 @@ inline BwdCost bwd_cost(int dk, int dv)
     return {0.28, 1.3, 0.051};
 }
 
-inline BwdFusedPlan plan_bwd_runs(int BH, int NC, int dk, int dv, bool io_bf16, int places)
+// fine: fewer than 64 tokens per chunk.  Where the length is chosen on the device, such a pass is enqueued behind the one of 64 and as a
+// rule returns at once; named by the caller, it has to give the same results, so it is cut the same way.
+inline BwdFusedPlan plan_bwd_runs(int BH, int NC, int dk, int dv, bool io_bf16, int places, bool fine = false)
 {
     if (places == 1 || BH <= 0 || NC <= 1) return uncut_bwd(NC);
     const bool pairs = dk == 64 && dv == 64 && io_bf16;        // workgroups of four waves, two on a compute unit
@@ -107,6 +109,9 @@ inline BwdFusedPlan plan_bwd_runs(int BH, int NC, int dk, int dv, bool io_bf16, 
     // in 64 runs, 63.0 in 256; 128 x 128 67.0 and 76.8, 61.0 in 128): every run's state is added up by one after the other.
     const BwdCost cost = bwd_cost(dk, dv);
     const int most = (pairs ? 2 : 1) * kOnePerUnit;
+    // Three launches that return at once take 6.7 us, one 1.9: where few runs have four chunks, fine lengths take light walks
+    // (length chosen on the device, ordinary gates, 128 heads of 64 x 64 and 12 chunks of 64: 57.0 -> 49.1 us).
+    const bool ends_ok = !fine || (most / BH > 4 && NC / 4 > 4);
     BwdFusedPlan best = uncut_bwd(NC);
     double least = NC;
     for (int at_once = kOnePerUnit; at_once <= most; at_once += kOnePerUnit)
@@ -122,7 +127,7 @@ inline BwdFusedPlan plan_bwd_runs(int BH, int NC, int dk, int dv, bool io_bf16, 
             }
             // (two or three runs per sequence: the walks from zero read most of q, f and grad_o once more while the
             // memory system is busy already; 128 x 128, 85 heads of 128 chunks 513 us light, 537 us from zero, but 64 heads, four runs each, 424 and 400)
-            if (R < 4) continue;
+            if (R < 4 || !ends_ok) continue;
             const BwdFusedPlan ends = ends_bwd(NC, R);
             const double mb = 4e-6 * dk * dv * (double)BH * ends.seg_tail;
             const double t = crowd * ends.rc + cost.ends + 0.3 * ends.sub_chunks + 0.037 * ends.seg_tail + cost.mb * mb;

@@ -12,9 +12,9 @@ SHIM = """
 #include "bwd_plan.hpp"
 using namespace hgrn2;
 extern "C" int max_runs() { return kMaxLightRuns; }
-extern "C" void plan(int BH, int NC, int dk, int dv, int bf16, int places, int* out)
+extern "C" void plan(int BH, int NC, int dk, int dv, int bf16, int places, int fine, int* out)
 {
-    const BwdFusedPlan p = plan_bwd_runs(BH, NC, dk, dv, bf16 != 0, places);
+    const BwdFusedPlan p = plan_bwd_runs(BH, NC, dk, dv, bf16 != 0, places, fine != 0);
     out[0] = p.R; out[1] = p.rc; out[2] = p.s_sub; out[3] = p.sub_chunks; out[4] = p.seg_tail; out[5] = p.light;
     for (int i = 0; i <= kMaxLightRuns; ++i) out[6 + i] = p.bnd[i];
 }
@@ -35,10 +35,10 @@ def test_runs_cover_every_chunk_and_fit_the_chip(lib, dk, dv, bf16):
     most = 512 if dk == dv == 64 and bf16 else 256
     for BH in [*range(1, 24), 32, 42, 43, 63, 64, 65, 85, 86, 128, 129, 170, 256, 257, 300, 512, 513, 2000]:
         for NC in [*range(1, 70), 127, 256, 511, 4095, 32768, 70000]:
-            for places in (0, 256, 1):
-                lib.plan(BH, NC, dk, dv, bf16, places, out)
+            for places, fine in ((0, 0), (0, 1), (256, 0), (1, 0)):
+                lib.plan(BH, NC, dk, dv, bf16, places, fine, out)
                 R, rc, s_sub, sub, tail, light = out[:6]
-                case = (BH, NC, dk, dv, places, list(out))
+                case = (BH, NC, dk, dv, places, fine, list(out))
                 assert R >= 1 and (R == 1 or R * BH <= most), case
                 assert places != 1 or R == 1, case
                 assert places != 256 or R <= max(1, NC // 4), case
@@ -70,6 +70,18 @@ MEASURED = [
 @pytest.mark.parametrize("dk,dv,BH,NC,us", MEASURED)
 def test_the_cut_is_one_of_the_fast_ones(lib, dk, dv, BH, NC, us):
     out = (ctypes.c_int * (7 + lib.max_runs()))()
-    lib.plan(BH, NC, dk, dv, 1, 0, out)
+    lib.plan(BH, NC, dk, dv, 1, 0, 0, out)
     cut = "%s%d" % ("L" if out[5] else "E", out[0])
     assert cut in us and us[cut] <= 1.03 * min(us.values()), (cut, us)
+
+
+def test_a_fine_length_is_one_launch_where_few_runs_have_four_chunks(lib):
+    out = (ctypes.c_int * (7 + lib.max_runs()))()
+    for dk, dv in ((64, 64), (128, 128)):
+        places = 512 if dk == 64 else 256
+        for BH in range(1, 260):
+            for NC in (1, 2, 8, 12, 16, 24, 48, 64, 100):
+                lib.plan(BH, NC, dk, dv, 1, 0, 1, out)
+                runs, light = out[0], out[5]
+                if min(places // BH, NC // 4) <= 4:
+                    assert runs == 1 or light, (dk, BH, NC, list(out))
