@@ -440,7 +440,9 @@ int hgrn2_bwd_noalloc(const hgrn2_shape* shape, const void* q, const void* f, co
  * hgru2_proj_bwd: reverse mode for L = sum(z grad_z) + sum(v grad_v) + sum(q grad_q):
  *   grad_x   out  device bf16 [M][d]
  *   grad_w3  out  device fp32 [3 d][d];   grad_b3  out  device fp32 [3 d] (summed in a fixed order)
- *   workspace     hgru2_proj_bwd_workspace_bytes(M, d) bytes, 256-byte aligned
+ *   workspace     hgru2_proj_bwd_workspace_bytes(M, d) bytes, 256-byte aligned: the gradient of the
+ *                 pre-activations in two orders and x in a second one, 14 bytes per element of x, and W3
+ *                 in a second one and shares of grad_w3 (16384 tokens of width 2048: 0.5 GB)
  * Status codes and stream semantics as everywhere in this header.
  */
 size_t hgru2_proj_bwd_workspace_bytes(int32_t M, int32_t d);

@@ -130,10 +130,12 @@ size_t run_decay_bytes(const SeqDims& d, bool backward)
 }
 
 // fp32 storage: whether the read-out adds up the chunks' contributions itself instead of waiting for a
-// sweep over the chunks in order.  It reads up to 1 MB of them per workgroup; and the sweep's chain of
-// chunks (5 us each) has to be what takes the time, which it is while all chunks' workgroups run at once and
-// the contributions they all read stay small (16 heads of 64, 128 chunks in all: 47 -> 24 us; heads of 128:
-// 80 chunks 38.5 -> 34.5 us, but 128 chunks 29 -> 34 us and 512 chunks 70 -> 95 us).
+// sweep over the chunks in order.  A sequence's contributions are up to 1 MB, which each of its workgroups reads (half of, where
+// it takes 64 of 128 columns); and the sweep's chain of chunks (5 us each) has to be what takes the time, which it is while all
+// chunks' workgroups run at once and the contributions they all read stay small.  us, sweep -> contributions: 16 heads of 64 x 64,
+// 8 / 16 chunks each 46 -> 23, 54 -> 29; 128 x 128, 96 chunks in all as 96 / 32 / 16 heads 24 -> 17, 31 -> 26, 41 -> 29.  Beyond the bounds
+// it depends on how the chunks fall: 128 x 128, 128 chunks as 64 / 32 / 16 heads 28 -> 30, 34 -> 36, 49 -> 37, 256 as 64 heads 38 -> 56; heads of
+// 64 x 64, 512 chunks as 64 / 32 / 16 heads 51 -> 40, 58 -> 38, 58 -> 41, 1024 73 -> 65 to 84.  (Within them it loses only 1 to 2 us at 96 heads of two chunks of 128 x 64 and 64 x 128.)
 bool out_from_contributions(const SeqDims& d)
 {
     return !d.io_bf16 && !d.packed && d.NC - 1 <= d.dv && (size_t)d.NC * d.dk * d.dv * sizeof(float) <= ((size_t)1 << 20) &&

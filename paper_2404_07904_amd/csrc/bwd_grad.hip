@@ -906,9 +906,11 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
 #pragma unroll
         for (int i = RW - 1; i >= 0; --i) { z0[i] = u0; z1[i] = u1; u0 *= rf[i].x; u1 *= rf[i].y; }
     }
-    // (Gradients leave with non-temporal stores: nothing here reads them again, and what the runs read twice, and the states
-    // the forward pass has just left, keep their place in the caches.  Training pair, us: 8 x 16 heads of 128, 2048 tokens 265 -> 260,
-    // 2 x 16 heads, 16384 tokens 725 -> 709.)
+    // (Gradients leave with non-temporal stores: what the runs read twice, and the states the forward pass has just left, keep their
+    // place in the caches, which is worth more than the gradients' to the projections' reverse mode, the next to read them.
+    // us, ordinary -> non-temporal, six sets of buffers in turn: training pair of 8 x 16 heads of 128, 2048 tokens 267 -> 261 (inputs just
+    // written 293 -> 290; all results read and written by kernels right behind 369 -> 370), 2 x 16 heads, 16384 tokens 727 -> 708; whole
+    // layer of 16384 tokens and width 2048 1518 -> 1511, of 64 to 4096 tokens and width 256 to 1024 1 to 4% less with these and o's.)
     // rows of this wave's block to global memory: one address and constant offsets when the
     // whole block lies inside the sequence, row by row otherwise
     auto store_block = [&](T* dst, const float (&x0)[RW], const float (&x1)[RW]) {
