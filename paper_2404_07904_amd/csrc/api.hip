@@ -183,8 +183,10 @@ BwdLayout bwd_layout(const SeqDims& d, bool gated, bool states_given = false, in
         l.fwd_run_state = run_state_bytes(d, false);
         l.fwd_run_decay = run_decay_bytes(d, false);
     }
-    if (l.plan.R > 1 && !l.plan.light) {
-        const size_t slots = (size_t)d.BH * l.plan.seg_tail;
+    // (room for as many chunks of 64 tokens: a fine length's plan is the same, or light walks, which need none)
+    const BwdFusedPlan room = plan_bwd_runs(d.BH, d.NC, d.dk, d.dv, d.io_bf16, places);
+    if (room.R > 1 && !room.light) {
+        const size_t slots = (size_t)d.BH * room.seg_tail;
         l.tail_state = round256(slots * d.dk * d.dv * sizeof(float));
         l.tail_decay = round256(slots * d.dk * sizeof(float));
         l.bound0 = round256((size_t)d.BH * d.dk * d.dv * sizeof(float));

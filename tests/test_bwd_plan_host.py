@@ -39,6 +39,10 @@ def test_runs_cover_every_chunk_and_fit_the_chip(lib, dk, dv, bf16):
                 lib.plan(BH, NC, dk, dv, bf16, places, fine, out)
                 R, rc, s_sub, sub, tail, light = out[:6]
                 case = (BH, NC, dk, dv, places, fine, list(out))
+                if fine:          # needs no other room than the plan of 64 tokens per chunk: the same plan, or light
+                    usual = (ctypes.c_int * len(out))()
+                    lib.plan(BH, NC, dk, dv, bf16, places, 0, usual)
+                    assert list(out) == list(usual) or out[0] == 1 or out[5], (case, list(usual))
                 assert R >= 1 and (R == 1 or R * BH <= most), case
                 assert places != 1 or R == 1, case
                 assert places != 256 or R <= max(1, NC // 4), case
