@@ -39,60 +39,14 @@
 // contraction index is the slow axis of their LDS tile are fetched with LDS transpose reads.
 // The final element-wise stage runs in the row-block / channel-pair layout after the
 // accumulators have been staged through LDS.
-#include "common.hpp"
-#include "kernels.hpp"
+#include "bwd_common.hpp"
 
 namespace hgrn2 {
 
 constexpr int kBwdWaves = 8;         // (and rows of partial sums of the gradient of beta per chunk or run: one per row block)
 static_assert(kBwdWaves == kRowBlocks, "a row block per wave");
 
-struct BwdGradParams {
-    const void* q;
-    const void* f;
-    const void* v;
-    const void* dO;
-    const void* ws_s;
-    const void* ws_ds;
-    void* dq;
-    void* df;
-    void* dv;
-    int BH, N, NC;
-    const float* beta;       // [H][dk] lower bounds, or null: the gate tensor holds f itself
-    float* beta_partials;    // [B*H*NC][8][dk] per-wave partial sums of the gradient w.r.t. beta
-    int H;
-    TokenLayout lay;         // used when dense == 0
-    int dense;               // sequence tensors are [B][H][N][d]
-    // Fused reverse walk (see bwd_grad_body<..., FUSED>): the state gradient is carried in registers
-    // instead of being read from ws_ds.  Every sequence is cut into R runs of rc chunks, one
-    // workgroup each; a run starts from grad_hT (the last one), from bound0[bh] (run 0) or from
-    // run_state[bh * seg_tail + r * s_sub - 1] (the state gradient at the end of run r, which a
-    // zero-start sweep over the later tokens and its carry have left there); run 0 leaves grad_h0.
-    // With light walks (`light`), no boundary states are needed: a workgroup first walks the chunks
-    // after its run, from grad_hT, doing nothing but the state-gradient recurrence (a fraction of a
-    // chunk's full work), and the runs are cut at bnd[0] = 0 < bnd[1] < ... < bnd[R] = NC so that
-    // all workgroups finish together.
-    const float* dhT;
-    float* dh0;
-    const float* bound0;
-    const float* run_state;
-    int R, rc, s_sub, seg_tail;
-    int light;
-    int* flag;               // null, or set to 1 when a gate product falls below the floor of the reciprocals
-    int beta_spans;          // row sets of partial sums per head (packed batches)
-    // What bwd_ends_kernel leaves: per slot a state gradient [dk][dv] and the gate products [dk].  Spans of a
-    // packed batch: slot span * H + head, read by the walk over spans (null: every span takes a light walk);
-    // runs of segmented sequences: slot = run.
-    float* span_add;
-    float* span_decay;
-    int bnd[kMaxLightRuns + 1];      // (last: whatever is read of the arguments by every walk lies close together)
-};
-
-
-// NW: waves of the workgroup.  Four (heads of 64, bf16): a wave owns two row blocks, one per half wave, since
-// a row has only 32 channel pairs, and two workgroups share a compute unit, which covers the latencies
-// that eight half-idle waves of one workgroup do not.
-template <typename T, int DK, int DV, int NW> struct BwdGradLds {
+template <typename T, int DK, int DV> struct BwdGradLds {
     static constexpr int C = kChunk;
     // Tiles that are also read with LDS transpose loads (Q~, K~, dO, dS) take a pitch of D + 24
     // elements: row-major 16-byte reads stay conflict-free and the transpose reads run at twice
@@ -120,30 +74,18 @@ template <typename T, int DK, int DV, int NW> struct BwdGradLds {
     static constexpr size_t blke = cks + (size_t)C * PF * sizeof(float);    // [8][DK] fp32 block sums of e'
     static constexpr size_t blkk = blke + (size_t)kRowBlocks * DK * sizeof(float);  // [8][DK] block sums of K~ Ks
     static constexpr size_t p2_end = blkk + (size_t)kRowBlocks * DK * sizeof(float);
-    // The dv staging tile [C][PVR] lies behind both phases and is written as soon as dv is formed; with two
-    // workgroups on a compute unit it lies behind the block sums and is written after the contractions.
-    static constexpr bool late_dv = NW == 4;
     // The next chunk's first stage writes the V, dO tiles and the block products while the last
     // stage of this one may still read the block sums; where those overlap, a barrier ends the chunk.
     static constexpr bool end_barrier = !(blke >= dsm && p2_end <= tot);
     // both phases
     static constexpr size_t dv_bytes = (size_t)C * PVR * sizeof(T);
-    static constexpr size_t rp = cmax(p1_end, p2_end + (late_dv ? dv_bytes : 0));   // [DK] fp32  g * rowsum(dS * S_n)
-    static constexpr size_t dvs = late_dv ? p2_end : rp + (size_t)DK * sizeof(float);
-    static constexpr size_t one = rp + (size_t)DK * sizeof(float) + (late_dv ? 0 : dv_bytes);   // [DK] fp32, all 1.0 (neutral factor)
+    static constexpr size_t rp = cmax(p1_end, p2_end);   // [DK] fp32  g * rowsum(dS * S_n)
+    static constexpr size_t dvs = rp + (size_t)DK * sizeof(float);      // dv staging tile [C][PVR], behind both phases
+    static constexpr size_t one = rp + (size_t)DK * sizeof(float) + dv_bytes;   // [DK] fp32, all 1.0 (neutral factor)
     static constexpr size_t zero = one + (size_t)DK * sizeof(float);        // [DK] fp32, all 0.0 (neutral term)
     static constexpr size_t total = zero + (size_t)DK * sizeof(float);
-    static_assert(total * (8 / NW) <= 160 * 1024, "LDS budget of the workgroups of a compute unit");
-    // the light walk alone (bwd_ends_kernel)
-    static constexpr size_t lq = 0;
-    static constexpr size_t ld = lq + (size_t)C * PK * sizeof(T);
-    static constexpr size_t lt = ld + (size_t)C * PV * sizeof(T);
-    static constexpr size_t lo = lt + (size_t)kRowBlocks * DK * sizeof(float);
-    static constexpr size_t light_total = lo + (size_t)DK * sizeof(float);
+    static_assert(total <= 160 * 1024, "LDS budget of a compute unit");
 };
-
-// A chunk of a walk: sequence and chunk within it.
-struct ChunkAt { SeqView sv; int bh, n; };
 
 // The token whose V / dO row goes to row `row` of the tiles (a row that stands for no token re-reads a
 // neighbouring one: what it holds drops out of every stored result).
@@ -153,48 +95,44 @@ __device__ __forceinline__ int tile_row_token(int sub, const ChunkAt& c, int row
 }
 
 // The raw rows of f and q of this thread's row block.
-template <typename T, int DK, bool GATE_BF16, bool DENSE, int NW>
+template <typename T, int DK, bool GATE_BF16, bool DENSE>
 __device__ __forceinline__ void load_fq(const BwdGradParams& p, RawRows<8>& cf, RawRows<8>& cq, const ChunkAt& c, int w, int lane)
 {
-    constexpr bool HALVES = NW == 4;
-    const int pair = (HALVES || 2 * lane < DK) ? lane : 0;
-    const int r0 = chunk_rows(p.lay.sub, c.n, c.sv.N).tok0 + (kChunk / NW) * w, ld = DENSE ? DK : (int)p.lay.sn_k;
-    load_block_rows<HALVES, 8, GATE_BF16>(cf, static_cast<const char*>(p.f) + c.sv.off_k * (GATE_BF16 ? 2 : 4), r0, c.sv.N - 1, ld, pair);
-    load_block_rows<HALVES, 8, is_bf16_type<T>()>(cq, reinterpret_cast<const char*>(static_cast<const T*>(p.q) + c.sv.off_k), r0, c.sv.N - 1, ld, pair);
+    const int pair = (2 * lane < DK) ? lane : 0;
+    const int r0 = chunk_rows(p.lay.sub, c.n, c.sv.N).tok0 + (kChunk / kBwdWaves) * w, ld = DENSE ? DK : (int)p.lay.sn_k;
+    load_block_rows<false, 8, GATE_BF16>(cf, static_cast<const char*>(p.f) + c.sv.off_k * (GATE_BF16 ? 2 : 4), r0, c.sv.N - 1, ld, pair);
+    load_block_rows<false, 8, is_bf16_type<T>()>(cq, reinterpret_cast<const char*>(static_cast<const T*>(p.q) + c.sv.off_k), r0, c.sv.N - 1, ld, pair);
 }
 
 // ---- light walk, last chunk to first, over `count` chunks of one sequence from chunk `cur` on:
 // dS_n = Diag(g_n) dS_{n+1} + Q^_n^T dO_n with Q^ = q G (G the gate product from the chunk start: no
 // quotient), the true state gradient in the accumulators (tiles as in bwd_grad_body).  Three barriers
 // per chunk.  Returns the chunk before the last one walked, whose f, q and dO rows are then loaded.
-// decay (null: not wanted): receives the product of the gates passed, channel 32 at + lane % 32.
-template <typename T, int DK, int DV, bool GATE_BF16, bool DENSE, int NW, int TPW>
+template <typename T, int DK, int DV, bool GATE_BF16, bool DENSE, int TPW>
 __device__ __forceinline__ ChunkAt light_walk(const BwdGradParams& p, T* Qm, T* dOm, float* tot, const float* ones, ChunkAt cur,
-                                              int count, f32x16 (&accD)[TPW], float* decay, RawRows<8>& raw_f, RawRows<8>& raw_q,
+                                              int count, f32x16 (&accD)[TPW], RawRows<8>& raw_f, RawRows<8>& raw_q,
                                               Raw16<T>& raw_d)
 {
-    typedef BwdGradLds<T, DK, DV, NW> L;
+    typedef BwdGradLds<T, DK, DV> L;
     typedef Mma<T> M;
     typedef typename M::frag frag;
     typedef T tx2 __attribute__((ext_vector_type(2)));
     constexpr int C = kChunk, RW = 8, NAT = DK / 32, NBT = DV / 32, GPR = DV / 16, PK = L::PK, PV = L::PV;
-    constexpr bool HALVES = NW == 4;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), at = w % NAT;
-    const bool has_d = (NAT * NBT) % NW == 0 || w < NAT * NBT, vd_act = tid < C * GPR;
+    const bool has_d = (NAT * NBT) % kBwdWaves == 0 || w < NAT * NBT, vd_act = tid < C * GPR;
     const int vd_row = vd_act ? tid / GPR : 0, vd_grp = tid % GPR;
     const T* dog = static_cast<const T*>(p.dO);
     auto load = [&](RawRows<RW>& cf, RawRows<RW>& cq, const ChunkAt& c, int lane) {
-        load_fq<T, DK, GATE_BF16, DENSE, NW>(p, cf, cq, c, w, lane);
+        load_fq<T, DK, GATE_BF16, DENSE>(p, cf, cq, c, w, lane);
         raw_d.load(dog + c.sv.off_v + (size_t)tile_row_token(p.lay.sub, c, vd_row) * (DENSE ? (size_t)DV : (size_t)p.lay.sn_v) + 16 * vd_grp);
     };
     load(raw_f, raw_q, cur, tid & 63);
-    float g_run = 1.0f;
     const int head = cur.bh / p.lay.seg % p.H;
     for (int li = 0; li < count; ++li) {
         int lane_opaque = threadIdx.x & 63;
         asm volatile("" : "+v"(lane_opaque));
         const int lane = lane_opaque, r32 = lane & 31;
-        const int cl = HALVES ? r32 : lane, rb = HALVES ? 2 * w + (lane >> 5) : w;     // channel pair, row block
+        const int cl = lane, rb = w;     // channel pair, row block
         const bool k_act = 2 * cl < DK;
         if (vd_act) raw_d.store_swapped(dOm + (size_t)vd_row * PV + 16 * vd_grp);
         const ChunkRows lr = chunk_rows(p.lay.sub, cur.n, cur.sv.N);
@@ -232,7 +170,6 @@ __device__ __forceinline__ ChunkAt light_walk(const BwdGradParams& p, T* Qm, T* 
         if (has_d) {
 #pragma unroll
             for (int i = 0; i < kRowBlocks; ++i) g_all *= tot[i * DK + 32 * at + r32];
-            g_run *= g_all;
         }
         __syncthreads();
         if (has_d) {
@@ -245,7 +182,7 @@ __device__ __forceinline__ ChunkAt light_walk(const BwdGradParams& p, T* Qm, T* 
                 const frag qf = M::load_kmajor(Qm, PK, 16 * ks, 32 * at, lane);
 #pragma unroll
                 for (int j = 0; j < TPW; ++j)
-                    M::mma(accD[j], M::load_kmajor_swapped(dOm, PV, 16 * ks, 32 * ((w + NW * j) / NAT), lane), qf);
+                    M::mma(accD[j], M::load_kmajor_swapped(dOm, PV, 16 * ks, 32 * ((w + kBwdWaves * j) / NAT), lane), qf);
             }
         }
         raw_f = nxt_f;
@@ -253,37 +190,24 @@ __device__ __forceinline__ ChunkAt light_walk(const BwdGradParams& p, T* Qm, T* 
         cur = nxt;
         __syncthreads();          // the tiles and totals are free for the next chunk
     }
-    if (decay && w < NAT && (tid & 63) < 32) decay[32 * at + (tid & 31)] = g_run;
     return cur;
 }
 
-// FUSED: the workgroup owns run `r` of sequence `bh` and walks its chunks from the last to the
+// FUSED (fp32 storage; bf16 has bwd_walk.hip): the workgroup owns run `r` of sequence `bh` and walks its chunks from the last to the
 // first with the state gradient in fp32 MFMA accumulators, oriented [dv][channel]:
 //     E_n = D'_n + Q~_n^T dO_n ,   D'_n = (g_n / G_m,n) dS_{n+1} ,   dS_n = G_m,n E_n
 // so that before each chunk the accumulators are scaled by (second-half gate product of this
 // chunk) x (first-half gate product of the chunk just done), published to the LDS tile the
 // contractions read D' from, and after the chunk's contractions receive Q~^T dO.  Only the forward
 // states S_n come from the workspace.
-// GROUPED (a FUSED walk over a packed batch): the chunks of one head, sequence after sequence, are
-// cut into `spans` equal pieces and the workgroup owns one, which may start and end inside a
-// sequence.  It walks its chunks from the last to the first: the state gradient starts from a
-// sequence's grad_hT (or zero) at its last chunk and leaves as its grad_h0 after its first, and the
-// rows of the next chunk of the walk -- be it of the sequence before -- are always in flight during
-// the epilogue of the current one.  A span that ends inside a sequence first takes the light walk
-// over the chunks between its end and the sequence's, which yields the state gradient it starts from; or,
-// with `span_add`, adds up what bwd_ends_kernel found for the later spans of that sequence:
-//     dS = Diag(decay_{s+1}) ( ... Diag(decay_last) grad_hT + add_last ... ) + add_{s+1}.
-template <typename T, int DK, int DV, bool GATE_BF16, bool DENSE, bool FUSED, bool GROUPED, int NW>
+template <typename T, int DK, int DV, bool GATE_BF16, bool DENSE, bool FUSED>
 __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
 {
-    static_assert(!GROUPED || (FUSED && !DENSE), "groups: fused walk over a packed batch");
-    constexpr int C = kChunk, RW = C / kRowBlocks, NT = 64 * NW;
-    constexpr bool HALVES = NW == 4;         // a row block per half wave
-    static_assert(!HALVES || (DK == 64 && DV == 64 && FUSED), "four waves: heads of 64");
-    typedef BwdGradLds<T, DK, DV, NW> L;
+    constexpr int C = kChunk, RW = C / kRowBlocks, NT = 64 * kBwdWaves;
+    typedef BwdGradLds<T, DK, DV> L;
     constexpr int PK = L::PK, PV = L::PV, PVR = L::PVR, PC = L::PC, PF = L::PF;
     constexpr int NRT = C / 32, NAT = DK / 32, NBT = DV / 32;
-    static_assert(NRT == 2 && NRT * NAT <= NW && NRT * NBT <= NW, "one tile per wave");
+    static_assert(NRT == 2 && NRT * NAT <= kBwdWaves && NRT * NBT <= kBwdWaves, "one tile per wave");
     typedef Mma<T> M;
     typedef typename M::frag frag;
     typedef T tx2 __attribute__((ext_vector_type(2)));
@@ -314,14 +238,12 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave index, in a scalar register
     constexpr bool gate_bf16 = GATE_BF16;
-    constexpr int GES = GATE_BF16 ? 2 : 4;
-    const T* qg = static_cast<const T*>(p.q);
     const T* vg = static_cast<const T*>(p.v);
     const T* dog = static_cast<const T*>(p.dO);
 
     // tile ownership (a wave without a tile of a kind skips that work)
-    const bool has_a = (NRT * NAT == NW) || w < NRT * NAT, has_b = (NRT * NBT == NW) || w < NRT * NBT;
-    const bool after = w >= NW / 2;          // rows of this wave lie after the mid-chunk reference
+    const bool has_a = (NRT * NAT == kBwdWaves) || w < NRT * NAT, has_b = (NRT * NBT == kBwdWaves) || w < NRT * NBT;
+    const bool after = w >= kBwdWaves / 2;          // rows of this wave lie after the mid-chunk reference
     const int rt_a = has_a ? w / NAT : 0, at = w % NAT;     // (row tile, channel tile) of dq / dk
     const int rt_b = has_b ? w / NBT : 0, bt = w % NBT;     // (row tile, column tile) of dv
 
@@ -350,7 +272,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     };
     auto tile_token = [&](const ChunkAt& c) { return tile_row_token(p.lay.sub, c, vd_row); };
     auto load_fq_rows = [&](RawRows<RW>& cf, RawRows<RW>& cq, const ChunkAt& c, int lane) {
-        load_fq<T, DK, GATE_BF16, DENSE, NW>(p, cf, cq, c, w, lane);
+        load_fq<T, DK, GATE_BF16, DENSE>(p, cf, cq, c, w, lane);
     };
     auto load_chunk_rows = [&](RawRows<RW>& cf, RawRows<RW>& cq, Raw16<T>& cv, Raw16<T>& cd, const ChunkAt& c, int lane) {
         load_fq_rows(cf, cq, c, lane);
@@ -373,50 +295,12 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     if constexpr (!DENSE) {
         if (p.lay.vl) n_chunks = table_read(p.lay.vl, 2 * (p.lay.B + 1) + p.lay.B) * p.lay.H;      // the table's total, not the host's bound
     }
-    // GROUPED: a span of the chunks of head g_head; chunk (e, n) of the walk as a ChunkAt
-    int g_head = 0;
-    auto chunk_en = [&](int e, int n) {
-        ChunkAt c;
-        c.bh = e * p.lay.H + g_head;
-        c.n = n;
-        c.sv = seq_view<DENSE, DK, DV>(p.lay, p.N, p.NC, c.bh);
-        return c;
-    };
-    // the chunk the walk visits after c: the one before it in its sequence, else the last chunk of
-    // the nearest earlier sequence of the group that has tokens; after the very last one, c again
-    auto walk_next = [&](const ChunkAt& c) {
-        if (c.n > 0) { ChunkAt r = c; r.n = c.n - 1; return r; }
-        for (int e = c.bh / p.lay.H - 1; e >= 0; --e) {
-            const int len = table_read(p.lay.vl, p.lay.B + 1 + e);
-            if (len > 0) return chunk_en(e, p.lay.chunks_of(len) - 1);
-        }
-        return c;
-    };
     RawRows<RW> raw_f, raw_q;
     Raw16<T> raw_v, raw_d;
     frag sS[2 * NBT], sD[2 * NBT];
     // chunks of this workgroup: every gridDim.x-th one, or (FUSED) those of its run, last to first
     int n_iter, f_bh = 0, f_run = 0, f_first = 0, f_last = 0;
-    int span_first = 0, span_end = 0, span_total = 0;    // GROUPED: the span's chunks and the number of all, counted over the head's chunks
-    if constexpr (GROUPED) {
-        if ((int)blockIdx.x >= p.lay.spans * p.lay.H) return;
-        const int grp = (int)blockIdx.x / p.lay.H;
-        g_head = (int)blockIdx.x - grp * p.lay.H;
-        const int total = table_read(p.lay.vl, 2 * (p.lay.B + 1) + p.lay.B);       // chunks of one head
-        const int span_start = (int)((long long)grp * total / p.lay.spans);
-        span_end = (int)((long long)(grp + 1) * total / p.lay.spans);
-        span_first = span_start; span_total = total;
-        n_iter = span_end - span_start;
-        // a sequence without tokens hands the gradient of its final state on to its initial state
-        // (such sequences lie in no span: they are dealt out by their number)
-        if (p.dh0)
-            for (int e = grp; e < p.lay.B; e += p.lay.spans)
-                if (table_read(p.lay.vl, p.lay.B + 1 + e) == 0)
-                    for (int i = tid; i < DK * DV; i += NT) {
-                        const size_t x = (size_t)(e * p.lay.H + g_head) * DK * DV + i;
-                        p.dh0[x] = p.dhT ? p.dhT[x] : 0.0f;
-                    }
-    } else if constexpr (FUSED) {
+    if constexpr (FUSED) {
         f_bh = (int)blockIdx.x / p.R;
         f_run = (int)blockIdx.x - f_bh * p.R;
         if (f_bh >= p.BH) return;
@@ -439,19 +323,11 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
 
     // FUSED: accumulator tiles of the state gradient owned by this wave, tile id w + 8 j -> (channel
     // tile id % NAT, which is this wave's `at`; dv tile id / NAT), as [dv][channel]
-    constexpr int NDT = NAT * NBT, TPW = (NDT + NW - 1) / NW;
-    const bool has_d = FUSED && ((NDT % NW == 0) || w < NDT);
+    constexpr int NDT = NAT * NBT, TPW = (NDT + kBwdWaves - 1) / kBwdWaves;
+    const bool has_d = FUSED && ((NDT % kBwdWaves == 0) || w < NDT);
     f32x16 accD[FUSED ? TPW : 1];
     float gm_prev = 1.0f;                 // first-half gate product of the chunk done before, channel 32 at + lane % 32
-    // Element (tile j, register v) of this lane in a [dk][dv] fp32 state: a wave-uniform address
-    // (sequence, dv tile, group of four registers) plus one per-lane 32-bit byte offset plus a small
-    // constant, so that no access needs an address register of its own (GROUPED walks read and write
-    // such states in the middle of the chunk loop, where registers are scarce).
-    const uint32_t st_lane = (uint32_t)((32 * at + (tid & 31)) * DV + 4 * ((tid >> 5) & 1)) * 4u;
-    auto state_cols = [&](const float* base, int seq, int j, int c) {
-        return reinterpret_cast<const char*>(base) + ((size_t)seq * DK * DV + (size_t)(32 * ((w + NW * j) / NAT) + 8 * c)) * 4;
-    };
-    if constexpr (FUSED && !GROUPED) {
+    if constexpr (FUSED) {
         const int r32i = tid & 31, gi = (tid >> 5) & 1;
         const float* init = (f_run == p.R - 1 || p.light) ? p.dhT : (f_run == 0) ? p.bound0 : p.run_state;
         if (init) {
@@ -460,29 +336,19 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
         }
 #pragma unroll
         for (int j = 0; j < TPW; ++j) {
-            const int btj = (w + NW * j) / NAT;
+            const int btj = (w + kBwdWaves * j) / NAT;
 #pragma unroll
             for (int v = 0; v < 16; ++v)
                 accD[j][v] = (init && has_d) ? init[(size_t)(32 * at + r32i) * DV + 32 * btj + 8 * (v >> 2) + 4 * gi + (v & 3)] : 0.0f;
         }
     }
     // FUSED walks add up their partial sums of the gradient w.r.t. beta chunk after chunk (a fixed order; a
-    // span's chunks are all of one head) and leave one row per row block and run, or span.
+    // run's chunks are all of one head) and leave one row per row block and run.
     constexpr bool RUN_BETA = FUSED;
     float run_b0 = 0.0f, run_b1 = 0.0f;
     auto store_run_beta = [&]() {
-        const int lane = threadIdx.x & 63, cl = HALVES ? lane & 31 : lane, rb = HALVES ? 2 * w + (lane >> 5) : w;
-        // (rows of a packed batch: beta_spans() per head.  More spans than that leave at most one chunk to a
-        // span: those with a chunk take the place of its number, those without fill the places behind.)
+        const int lane = threadIdx.x & 63, cl = lane, rb = w;
         int slot = f_bh * p.R + f_run;
-        if constexpr (GROUPED) {
-            const int grp = (int)blockIdx.x / p.lay.H;
-            int grp_slot;
-            if (p.lay.spans > p.beta_spans) grp_slot = span_end > span_first ? span_first : span_total + grp - span_first;
-            else grp_slot = grp;
-            if (grp_slot >= p.beta_spans) return;
-            slot = g_head * p.beta_spans + grp_slot;
-        }
         if (RUN_BETA && p.beta && 2 * cl < DK)
             *reinterpret_cast<f32x2*>(p.beta_partials + ((size_t)slot * kBwdWaves + rb) * DK + 2 * cl) = f32x2{run_b0, run_b1};
     };
@@ -496,93 +362,30 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     float below_floor = 1.0f;             // smallest product a reciprocal was taken of (reported once, at the end)
     if constexpr (FUSED) {
         int n_light = 0;
-        if constexpr (GROUPED) {
-            // the sequence the span ends in (found by the table kernel): the last one whose chunks
-            // start at or before the span's last chunk
-            const int* before = p.lay.vl + 2 * (p.lay.B + 1);
-            const int lo = min(max(table_read(p.lay.span_seq, (int)blockIdx.x / p.lay.H), 0), p.lay.B - 1);
-            const int nc_e = table_read(before, lo + 1) - table_read(before, lo);
-            cur = chunk_en(lo, nc_e - 1);                          // that sequence's last chunk
-            n_light = table_read(before, lo + 1) - span_end;       // its chunks after the span
-            const int seq_end = table_read(before, lo + 1);
-            if (n_light > 0) {
-                // the light walk starts from the sequence's grad_hT (the chunk loop does that itself
-                // for every sequence whose last chunk lies in the span)
-#pragma unroll
-                for (int j = 0; j < TPW; ++j)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const char* cols = state_cols(p.dhT, cur.bh, j, c);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            accD[j][4 * c + e] = (p.dhT && has_d) ? *reinterpret_cast<const float*>(cols + st_lane + 4 * e) : 0.0f;
-                    }
-            }
-            if (n_light > 0 && p.span_add && table_read(p.lay.span_walks, 1) != 0) {
-                // the spans from the one in which the sequence ends down to the next one, two requested at a time
-                const int span = (int)blockIdx.x / p.lay.H;
-                int k = span + 1;
-                while (k + 1 < p.lay.spans && (int)((long long)(k + 1) * span_total / p.lay.spans) < seq_end) ++k;
-                constexpr int AHEAD = 2;
-                if (has_d)
-                    for (; k > span; k -= AHEAD) {
-                        float dm[AHEAD];
-                        f32x4 add[AHEAD][TPW][4];
-#pragma unroll
-                        for (int u = 0; u < AHEAD; ++u) {
-                            const int slot = max(k - u, span + 1) * p.lay.H + g_head;
-                            dm[u] = p.span_decay[(size_t)slot * DK + 32 * at + (tid & 31)];
-#pragma unroll
-                            for (int j = 0; j < TPW; ++j)
-#pragma unroll
-                                for (int c = 0; c < 4; ++c) add[u][j][c] = *reinterpret_cast<const f32x4*>(state_cols(p.span_add, slot, j, c) + st_lane);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                        for (int u = 0; u < AHEAD; ++u) {
-                            if (k - u <= span) break;
-#pragma unroll
-                            for (int j = 0; j < TPW; ++j)
-#pragma unroll
-                                for (int v = 0; v < 16; ++v) accD[j][v] = fmaf(dm[u], accD[j][v], add[u][j][v >> 2][v & 3]);
-                        }
-                    }
-                cur.n -= n_light;                                  // the span's last chunk
-                n_light = 0;
-            }
-        } else {
-            n_light = p.light ? p.NC - 1 - f_last : 0;
-            if (n_light > 0) cur = where(f_bh * p.NC + p.NC - 1);
-        }
+        n_light = p.light ? p.NC - 1 - f_last : 0;
+        if (n_light > 0) cur = where(f_bh * p.NC + p.NC - 1);
         if (n_light > 0) {
-            cur = light_walk<T, DK, DV, GATE_BF16, DENSE, NW>(p, Qm, dOm, tot, ones, cur, n_light, accD, nullptr, raw_f, raw_q, raw_d);
+            cur = light_walk<T, DK, DV, GATE_BF16, DENSE>(p, Qm, dOm, tot, ones, cur, n_light, accD, raw_f, raw_q, raw_d);
             // what the full pass over the run's last chunk needs on top: its V rows
             const size_t vo = cur.sv.off_v + (size_t)tile_token(cur) * (DENSE ? (size_t)DV : (size_t)p.lay.sn_v) + 16 * vd_grp;
             raw_v.load(vg + vo);
             rows_loaded = true;
         }
     }
-    if constexpr (GROUPED) {
-        // Keeps the compiler from computing the chunk loop's lane-dependent values ahead of the light
-        // walk and carrying them through it in registers (which made the loop spill, and a reload in
-        // the loop waits for every load in flight, the next chunk's rows included).
-        int opaque = threadIdx.x & 63;
-        asm volatile("" : "+v"(opaque));
-    }
     if (!rows_loaded) {
-        if constexpr (!GROUPED) cur = where(chunk_of(0));     // (a span: its last chunk, found above)
+        cur = where(chunk_of(0));
         load_chunk_rows(raw_f, raw_q, raw_v, raw_d, cur, tid & 63);
     }
 
   for (int it = 0; it < n_iter; ++it) {
-    const int chunk = GROUPED ? (int)cur.sv.chunk0 + cur.n : chunk_of(it);
+    const int chunk = chunk_of(it);
     // Re-derive the lane-dependent indices inside the loop from a value the compiler cannot see
     // through: otherwise it hoists dozens of loop-invariant LDS addresses out of the loop, keeps
     // them in registers across the whole body and spills.
     int lane_opaque = threadIdx.x & 63;
     asm volatile("" : "+v"(lane_opaque));
     const int lane = lane_opaque, r32 = lane & 31, g = lane >> 5;
-    const int cl = HALVES ? r32 : lane, rb = HALVES ? 2 * w + g : w;     // channel pair and row block of the element-wise work
+    const int cl = lane, rb = w;     // channel pair and row block of the element-wise work
     const bool k_act = 2 * cl < DK;
     const int n = cur.n, bh = cur.bh;
     const size_t seq_k = cur.sv.off_k, seq_v = cur.sv.off_v;
@@ -656,21 +459,6 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     // H_m * dS_{n+1} of channel tile `at` -> LDS, row-major [channel][dv position] (the fragments hold
     // it already scaled and rounded, and in position order: their bits go to LDS as they are), and
     // R = rowsum((H_m dS) * (G_m S_n)) = g * rowsum(dS * S_n).  Once per channel tile (row tile 0).
-    if constexpr (GROUPED) {
-        // the walk enters a sequence at its last chunk: the state gradient starts from its grad_hT
-        if (cur.n == cur.sv.NC - 1) {
-            gm_prev = 1.0f;
-#pragma unroll
-            for (int j = 0; j < TPW; ++j)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const char* cols = state_cols(p.dhT, cur.bh, j, c);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        accD[j][4 * c + e] = (p.dhT && has_d) ? *reinterpret_cast<const float*>(cols + st_lane + 4 * e) : 0.0f;
-                }
-        }
-    }
     if constexpr (FUSED) {
         // scale the carried state gradient to D'_n and publish it as the bf16 tile the contractions read
         if (has_d) {
@@ -681,7 +469,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
             gm_prev = gm;
 #pragma unroll
             for (int j = 0; j < TPW; ++j) {
-                const int btj = (w + NW * j) / NAT;
+                const int btj = (w + kBwdWaves * j) / NAT;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) accD[j][v] *= c;
 #pragma unroll
@@ -715,7 +503,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
 
     if constexpr (FUSED) {
         // R on the last NAT waves, D'_n of their channel tile read back from the tile as operand fragments
-        if (w >= NW - NAT) {
+        if (w >= kBwdWaves - NAT) {
             f32x16 accR;
 #pragma unroll
             for (int v = 0; v < 16; ++v) accR[v] = 0.0f;
@@ -774,13 +562,8 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
         for (int k = 0; k < 16 / VEC; ++k)
             *reinterpret_cast<u32x4*>(dst + (size_t)(32 + (lane >> 1)) * PC + 16 * (lane & 1) + VEC * k) = z;
     };
-    if constexpr (HALVES) {
-        if (w < 3) { p_block(false, w); p_block(true, w); }
-        else { zero_block(Pt); zero_block(dPt); }
-    } else {
-        if (w < 6) p_block(w >= 3, w >= 3 ? w - 3 : w);
-        else zero_block((w == 6) ? Pt : dPt);
-    }
+    if (w < 6) p_block(w >= 3, w >= 3 ? w - 3 : w);
+    else zero_block((w == 6) ? Pt : dPt);
     __syncthreads();
 
     // ---------------- main contractions ----------------
@@ -811,7 +594,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
 #pragma unroll
         for (int ks = 0; ks < DK / 16; ++ks)
             M::mma(aV, M::load_kmajor(dSm, PV, 16 * ks, 32 * bt, lane), M::load(Km + (32 * rt_b + r32) * PK + 16 * ks + 8 * g));
-        if (!L::late_dv) stage_dv();
+        stage_dv();
     }
     // tile (rt_a, at), transposed (channel = accumulator row):
     //   X^T = K~^T dP^T + (G_m S_n) dO^T,   Y1^T = Q~^T dP,   Ks^T = (H_m dS) V^T
@@ -845,34 +628,15 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
                 const frag qf = M::load_kmajor(Qm, PK, 16 * ks, 32 * at, lane);
 #pragma unroll
                 for (int j = 0; j < TPW; ++j)
-                    M::mma(accD[j], M::load_kmajor_swapped(dOm, PV, 16 * ks, 32 * ((w + NW * j) / NAT), lane), qf);
+                    M::mma(accD[j], M::load_kmajor_swapped(dOm, PV, 16 * ks, 32 * ((w + kBwdWaves * j) / NAT), lane), qf);
             }
-        }
-    }
-    if constexpr (GROUPED) {
-        // the walk leaves a sequence after its first chunk: dS_0 = G_m E is its grad_h0 (formed in
-        // place: the next chunk of the walk starts from its own sequence's grad_hT)
-        if (cur.n == 0 && p.dh0 && has_d) {
-#pragma unroll
-            for (int j = 0; j < TPW; ++j)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    char* cols = const_cast<char*>(state_cols(p.dh0, cur.bh, j, c));
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        accD[j][4 * c + e] *= gm_prev;
-                        *reinterpret_cast<float*>(cols + st_lane + 4 * e) = accD[j][4 * c + e];
-                    }
-                }
         }
     }
     RawRows<RW> nxt_f, nxt_q;
     ChunkAt nxt;
-    if constexpr (GROUPED) nxt = walk_next(cur);
-    else nxt = where(chunk_of(it + 1));
+    nxt = where(chunk_of(it + 1));
     load_chunk_rows(nxt_f, nxt_q, raw_v, raw_d, nxt, lane);   // v, dO of this chunk are dead
     __syncthreads();     // every wave is done with the operand tiles
-    if (L::late_dv && has_b) stage_dv();
 
     // ---------------- staging: X, Y1, Ks as [row][channel] fp32, 16 bytes per store ----------------
     if (has_a) {
@@ -1001,14 +765,14 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
   }
     if (p.flag && below_floor < kTinyProduct) *p.flag = 1;
     store_run_beta();
-    if constexpr (FUSED && !GROUPED) {
+    if constexpr (FUSED) {
         // run 0 ends at the start of the sequence: dS_0 = G_m E of its first chunk is grad_h0
         if (f_run == 0 && p.dh0 && has_d) {
             const int r32i = tid & 31, gi = (tid >> 5) & 1;
             float* out = p.dh0 + (size_t)f_bh * DK * DV;
 #pragma unroll
             for (int j = 0; j < TPW; ++j) {
-                const int btj = (w + NW * j) / NAT;
+                const int btj = (w + kBwdWaves * j) / NAT;
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
                     out[(size_t)(32 * at + r32i) * DV + 32 * btj + 8 * (v >> 2) + 4 * gi + (v & 3)] = accD[j][v] * gm_prev;
@@ -1020,101 +784,21 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
 template <typename T, int DK, int DV, bool GATE_BF16>
 __global__ __launch_bounds__(64 * kBwdWaves) void bwd_grad_kernel(BwdGradParams p)
 {
-    if (p.dense) bwd_grad_body<T, DK, DV, GATE_BF16, true, false, false, kBwdWaves>(p);
-    else         bwd_grad_body<T, DK, DV, GATE_BF16, false, false, false, kBwdWaves>(p);
+    if (p.dense) bwd_grad_body<T, DK, DV, GATE_BF16, true, false>(p);
+    else         bwd_grad_body<T, DK, DV, GATE_BF16, false, false>(p);
 }
 
-// What a run of chunks adds to the state gradient from zero (the light walk alone), and the product of its
-// gates: for every run of segmented sequences, or for every span of a packed batch whose first sequence has
-// begun in an earlier span, over that sequence's chunks in the span.  Two workgroups of eight waves to a
-// compute unit (heads of 64: three of four): bound by what they read (q, f, dO), which the sweep with its four waves was not (2 x 16
-// heads of 16384 tokens in 28 runs each, fp32 gates, 537 MB: 137 us).
-template <typename T, int DK, int DV, bool GATE_BF16, bool DENSE, bool GROUPED, int NW>
-__device__ __forceinline__ void bwd_ends_body(const BwdGradParams& p)
-{
-    typedef BwdGradLds<T, DK, DV, NW> L;
-    constexpr int NAT = DK / 32, NBT = DV / 32, NDT = NAT * NBT, TPW = (NDT + NW - 1) / NW, NT = 64 * NW;
-    extern __shared__ __align__(16) char smem[];
-    T* Qm = reinterpret_cast<T*>(smem + L::lq);
-    T* dOm = reinterpret_cast<T*>(smem + L::ld);
-    float* tot = reinterpret_cast<float*>(smem + L::lt);
-    float* ones = reinterpret_cast<float*>(smem + L::lo);
-    if (not_chosen(p.lay)) return;
-    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), at = w % NAT, slot = blockIdx.x;
-    ChunkAt cur;
-    int count;
-    if constexpr (GROUPED) {
-        const int span = slot / p.lay.H, head = slot - span * p.lay.H;
-        if (span >= p.lay.spans || table_read(p.lay.span_walks, 1) == 0) return;
-        const int* before = p.lay.vl + 2 * (p.lay.B + 1);
-        const int total = table_read(before, p.lay.B);
-        const int p0 = (int)((long long)span * total / p.lay.spans), p1 = (int)((long long)(span + 1) * total / p.lay.spans);
-        if (span == 0 || p1 <= p0) return;
-        // the sequence that holds chunk p0 is the one the span before ends in, unless it starts here
-        const int e = min(max(table_read(p.lay.span_seq, span - 1), 0), p.lay.B - 1);
-        const int b0 = table_read(before, e), b1 = min(table_read(before, e + 1), p1);
-        if (b0 >= p0 || b1 <= p0) return;
-        cur.bh = e * p.lay.H + head;
-        cur.sv = seq_view<DENSE, DK, DV>(p.lay, p.N, p.NC, cur.bh);
-        cur.n = b1 - 1 - b0;
-        count = b1 - p0;
-    } else {
-        if (slot >= p.BH) return;
-        cur.bh = slot;
-        cur.sv = seq_view<DENSE, DK, DV, true>(p.lay, p.N, p.NC, slot);
-        count = cur.sv.NC;
-        cur.n = count - 1;
-        if (count <= 0) return;
-    }
-    for (int i = tid; i < DK; i += NT) ones[i] = 1.0f;          // first read after a barrier
-    f32x16 accD[TPW];
-#pragma unroll
-    for (int j = 0; j < TPW; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) accD[j][v] = 0.0f;
-    RawRows<8> raw_f, raw_q;
-    Raw16<T> raw_d;
-    light_walk<T, DK, DV, GATE_BF16, DENSE, NW>(p, Qm, dOm, tot, ones, cur, count, accD, p.span_decay + (size_t)slot * DK, raw_f, raw_q, raw_d);
-    if (NDT % NW == 0 || w < NDT) {
-        float* out = p.span_add + (size_t)slot * DK * DV + (size_t)(32 * at + (tid & 31)) * DV + 4 * ((tid >> 5) & 1);
-#pragma unroll
-        for (int j = 0; j < TPW; ++j)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                *reinterpret_cast<f32x4*>(out + 32 * ((w + NW * j) / NAT) + 8 * c) =
-                    f32x4{accD[j][4 * c], accD[j][4 * c + 1], accD[j][4 * c + 2], accD[j][4 * c + 3]};
-    }
-}
-
-template <typename T, int DK, int DV, bool GATE_BF16, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 3) void bwd_ends_kernel(BwdGradParams p)
-{
-    if (p.lay.vl && p.lay.spans > 0) bwd_ends_body<T, DK, DV, GATE_BF16, false, true, NW>(p);
-    else if (p.dense) bwd_ends_body<T, DK, DV, GATE_BF16, true, false, NW>(p);
-    else bwd_ends_body<T, DK, DV, GATE_BF16, false, false, NW>(p);
-}
-
-// Waves of the reverse walk over runs: heads of 64 (bf16) take workgroups of four, two on a compute unit.
-constexpr int fused_waves(int dk, int dv, bool bf16) { return dk == 64 && dv == 64 && bf16 ? 4 : kBwdWaves; }
-
-template <typename T, int DK, int DV, bool GATE_BF16, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void bwd_fused_kernel(BwdGradParams p)
-{
-    if (p.dense) bwd_grad_body<T, DK, DV, GATE_BF16, true, true, false, NW>(p);
-    else         bwd_grad_body<T, DK, DV, GATE_BF16, false, true, false, NW>(p);
-}
-
-// The fused reverse walk over groups of a packed batch's sequences (a kernel of its own).
 template <typename T, int DK, int DV, bool GATE_BF16>
-__global__ __launch_bounds__(64 * kBwdWaves) void bwd_fused_grouped_kernel(BwdGradParams p)
+__global__ __launch_bounds__(64 * kBwdWaves, 2) void bwd_fused_kernel(BwdGradParams p)
 {
-    bwd_grad_body<T, DK, DV, GATE_BF16, false, true, true, kBwdWaves>(p);
+    if (p.dense) bwd_grad_body<T, DK, DV, GATE_BF16, true, true>(p);
+    else         bwd_grad_body<T, DK, DV, GATE_BF16, false, true>(p);
 }
 
 template <typename T, int DK, int DV>
 static hipError_t launch_one(const SeqDims& d, const BwdGradParams& p, hipStream_t stream)
 {
-    typedef BwdGradLds<T, DK, DV, kBwdWaves> L;
+    typedef BwdGradLds<T, DK, DV> L;
     auto kern = d.gate_bf16 ? bwd_grad_kernel<T, DK, DV, true> : bwd_grad_kernel<T, DK, DV, false>;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::total);
     if (e != hipSuccess) return e;
@@ -1151,12 +835,11 @@ hipError_t launch_bwd_grad(const SeqDims& d, const void* q, const void* f, const
 template <typename T, int DK, int DV>
 static hipError_t launch_fused_one(const SeqDims& d, const BwdGradParams& p, hipStream_t stream)
 {
-    constexpr int NW = fused_waves(DK, DV, is_bf16_type<T>());
-    typedef BwdGradLds<T, DK, DV, NW> L;
-    auto kern = d.gate_bf16 ? bwd_fused_kernel<T, DK, DV, true, NW> : bwd_fused_kernel<T, DK, DV, false, NW>;
+    typedef BwdGradLds<T, DK, DV> L;
+    auto kern = d.gate_bf16 ? bwd_fused_kernel<T, DK, DV, true> : bwd_fused_kernel<T, DK, DV, false>;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::total);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(d.BH * p.R)), dim3(64 * NW), L::total, stream, p);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(d.BH * p.R)), dim3(64 * kBwdWaves), L::total, stream, p);
     return hipGetLastError();
 }
 
@@ -1182,23 +865,7 @@ hipError_t launch_bwd_fused(const SeqDims& d, const BwdFusedPlan& pl, const void
     for (int i = 0; i <= kMaxLightRuns; ++i) p.bnd[i] = pl.bnd[i];
     p.flag = d.domain_flag;
     if (!d.io_bf16) return launch_fused_one<float, 64, 64>(d, p, stream);
-    if (d.dk == 128 && d.dv == 128) return launch_fused_one<__bf16, 128, 128>(d, p, stream);
-    if (d.dk == 64 && d.dv == 64) return launch_fused_one<__bf16, 64, 64>(d, p, stream);
-    if (d.dk == 128 && d.dv == 64) return launch_fused_one<__bf16, 128, 64>(d, p, stream);
-    if (d.dk == 64 && d.dv == 128) return launch_fused_one<__bf16, 64, 128>(d, p, stream);
-    return hipErrorInvalidValue;
-}
-
-template <int DK, int DV>
-static hipError_t launch_ends_one(const SeqDims& d, const BwdGradParams& p, unsigned grid, hipStream_t stream)
-{
-    constexpr int NW = fused_waves(DK, DV, true);
-    typedef BwdGradLds<__bf16, DK, DV, NW> L;
-    auto kern = d.gate_bf16 ? bwd_ends_kernel<__bf16, DK, DV, true, NW> : bwd_ends_kernel<__bf16, DK, DV, false, NW>;
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::light_total);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NW), L::light_total, stream, p);
-    return hipGetLastError();
+    return launch_bwd_walk(d, p, false, stream);
 }
 
 hipError_t launch_bwd_ends(const SeqDims& d, const void* q, const void* f, const void* grad_o, float* add, float* decay, hipStream_t stream)
@@ -1215,25 +882,10 @@ hipError_t launch_bwd_ends(const SeqDims& d, const void* q, const void* f, const
     p.light = 0; p.beta_spans = 0; p.flag = nullptr;
     for (int i = 0; i <= kMaxLightRuns; ++i) p.bnd[i] = 0;
     p.span_add = add; p.span_decay = decay;
-    if (d.dk == 128 && d.dv == 128) return launch_ends_one<128, 128>(d, p, grid, stream);
-    if (d.dk == 64 && d.dv == 64) return launch_ends_one<64, 64>(d, p, grid, stream);
-    if (d.dk == 128 && d.dv == 64) return launch_ends_one<128, 64>(d, p, grid, stream);
-    if (d.dk == 64 && d.dv == 128) return launch_ends_one<64, 128>(d, p, grid, stream);
-    return hipErrorInvalidValue;
+    return launch_walk_ends(d, p, grid, stream);
 }
 
 int beta_spans(const SeqDims& d) { return d.lay.spans < d.NC ? d.lay.spans : d.NC; }
-
-template <int DK, int DV>
-static hipError_t launch_grouped_one(const SeqDims& d, const BwdGradParams& p, hipStream_t stream)
-{
-    typedef BwdGradLds<__bf16, DK, DV, kBwdWaves> L;
-    auto kern = d.gate_bf16 ? bwd_fused_grouped_kernel<__bf16, DK, DV, true> : bwd_fused_grouped_kernel<__bf16, DK, DV, false>;
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::total);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(d.lay.spans * d.lay.H)), dim3(64 * kBwdWaves), L::total, stream, p);
-    return hipGetLastError();
-}
 
 hipError_t launch_bwd_fused_grouped(const SeqDims& d, const void* q, const void* f, const void* v, const void* grad_o,
                                     const void* ws_state, const float* grad_hT, float* grad_h0, void* grad_q,
@@ -1254,11 +906,7 @@ hipError_t launch_bwd_fused_grouped(const SeqDims& d, const void* q, const void*
     p.span_add = const_cast<float*>(span_add); p.span_decay = const_cast<float*>(span_decay);
     for (int i = 0; i <= kMaxLightRuns; ++i) p.bnd[i] = 0;
     p.flag = d.domain_flag;
-    if (d.dk == 128 && d.dv == 128) return launch_grouped_one<128, 128>(d, p, stream);
-    if (d.dk == 64 && d.dv == 64) return launch_grouped_one<64, 64>(d, p, stream);
-    if (d.dk == 128 && d.dv == 64) return launch_grouped_one<128, 64>(d, p, stream);
-    if (d.dk == 64 && d.dv == 128) return launch_grouped_one<64, 128>(d, p, stream);
-    return hipErrorInvalidValue;
+    return launch_bwd_walk(d, p, true, stream);
 }
 
 constexpr int kRedGroups = 16;      // groups of 64 threads per workgroup, each adding every 16th row of its share

@@ -213,7 +213,7 @@ hipError_t launch_bwd_grad(const SeqDims& d, const void* q, const void* f, const
                            const void* ws_state, const void* ws_dstate, void* grad_q, void* grad_f,
                            void* grad_v, float* beta_partials, hipStream_t stream);
 // The same gradients from the forward states alone: one workgroup per run of a sequence walks the
-// run's chunks from the last to the first with the state gradient in registers (bwd_grad.hip).
+// run's chunks from the last to the first with the state gradient in registers (bwd_walk.hip; fp32 storage: bwd_grad.hip).
 // plan_bwd_fused() (bwd_plan.hpp) cuts the sequences into R runs of rc chunks; for R > 1 the caller provides the
 // state gradient at the run boundaries: a zero-start gradient sweep over the tokens after run 0, cut
 // into seg_tail sub-runs of sub_chunks chunks, and its reverse carry from grad_hT leave it in
