@@ -381,11 +381,11 @@ __device__ __forceinline__ float lower_bounded_gate(float z, float beta)
     return fmaf(1.0f - beta, s, beta);
 }
 
+// b: the bounds of the thread's channel pair.  (A caller with a loop loads them before it: a load in it, though taken only with beta,
+// makes the compiler wait for every load in flight.)
 template <int RW>
-__device__ __forceinline__ void gate_rows(f32x2 (&rf)[RW], const float* beta_head, int col, bool lane_active,
-                                          int row0, int n_rows, int first_row = 0)
+__device__ __forceinline__ void gate_rows(f32x2 (&rf)[RW], f32x2 b, bool lane_active, int row0, int n_rows, int first_row = 0)
 {
-    const f32x2 b = *reinterpret_cast<const f32x2*>(beta_head + col);
 #pragma unroll
     for (int i = 0; i < RW; ++i) {
         rf[i].x = lower_bounded_gate(rf[i].x, b.x);
@@ -400,6 +400,13 @@ __device__ __forceinline__ void gate_rows(f32x2 (&rf)[RW], const float* beta_hea
             rf[i].y = ok ? rf[i].y : 1.0f;
         }
     }
+}
+
+template <int RW>
+__device__ __forceinline__ void gate_rows(f32x2 (&rf)[RW], const float* beta_head, int col, bool lane_active,
+                                          int row0, int n_rows, int first_row = 0)
+{
+    gate_rows<RW>(rf, *reinterpret_cast<const f32x2*>(beta_head + col), lane_active, row0, n_rows, first_row);
 }
 
 // ---- matrix-core policy -------------------------------------------------------------------------

@@ -435,6 +435,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
             }
         }
     }
+    const f32x2 beta_pair = p.beta ? *reinterpret_cast<const f32x2*>(p.beta + (size_t)head * DK + 2 * cl) : f32x2{0.0f, 0.0f};
     float hprev0 = 1.0f, hprev1 = 1.0f;      // h of the previous chunk, channels 2*cl, 2*cl+1 (wave 0 only)
 
     // ---- row fetch, two chunks ahead, two register sets ----
@@ -494,7 +495,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
     auto prep_gates = [&](const RawRows<RW>& rf_raw, const RawRows<RW>& rq_raw, const FusedChunk& c) {
         f32x2 rf[RW];
         convert_rows<RW>(rf, rf_raw, c.row0 + RW * rb, c.hi, true, GATE_BF16, 1.0f, c.lo);
-        if (p.beta) gate_rows<RW>(rf, p.beta + (size_t)head * DK, 2 * cl, true, c.row0 + RW * rb, c.hi, c.lo);
+        if (p.beta) gate_rows<RW>(rf, beta_pair, true, c.row0 + RW * rb, c.hi, c.lo);
         float run0 = 1.0f, run1 = 1.0f;
 #pragma unroll
         for (int i = 0; i < RW; ++i) {
@@ -623,7 +624,7 @@ __device__ __forceinline__ void fwd_fused_body(const FwdFusedParams& p)
         auto gates = [&](const RawRows<RW>& raw, const FusedChunk& c, int par) {
             f32x2 rf[RW];
             convert_rows<RW>(rf, raw, c.row0 + RW * rb, c.hi, true, GATE_BF16, 1.0f, c.lo);
-            if (p.beta) gate_rows<RW>(rf, p.beta + (size_t)head * DK, 2 * cl, true, c.row0 + RW * rb, c.hi, c.lo);
+            if (p.beta) gate_rows<RW>(rf, beta_pair, true, c.row0 + RW * rb, c.hi, c.lo);
             float run0 = 1.0f, run1 = 1.0f;
 #pragma unroll
             for (int i = RW - 1; i >= 0; --i) {
