@@ -23,6 +23,7 @@
 
 namespace hgrn2 {
 
+constexpr int kUnits = 256;      // compute units: workgroups that walk tiles
 constexpr int kBandRows = 4;     // row blocks per band of the workgroup -> tile order
 
 enum GemmEpilogue { kEpiProj = 0, kEpiPlain = 1, kEpiFloat = 2 };
@@ -57,10 +58,82 @@ constexpr int vm_lgkm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; }
 // own loads of them; loads are counted by hand, the compiler does not track them).  With NS = 5 the tile of A is requested 1 3/4 steps
 // ahead, that of B 3/4.  Fragments are requested right after the first MFMAs of the quarter before (the compiler waits for
 // all outstanding LDS reads before an MFMA that needs one), and the refill goes out one load at a time between the MFMAs.
-//   16384 x 2048 x 6144 with bias, activations and four outputs: 350-363 us = 1.14-1.18 PFLOP/s (an earlier kernel with steps of 32, half
+//   16384 x 2048 x 6144 with bias, activations and four outputs: 342-359 us = 1.15-1.20 PFLOP/s (an earlier kernel with steps of 32, half
 // lines, 372-400); dx 315 us = 1.31 PFLOP/s (369), dW3 324 (516).  What bounds the 256 x 256 tile (builds that leave work out): 217 us are MFMAs and LDS reads
 // (1.9 PFLOP/s), 85 us the loads' way into LDS next to 192 KB of LDS reads a step (loads that never miss L2 save 14 us, no wait for them nothing), 38 us
 // the epilogue.  Four waves of 128 x 128, with a third fewer LDS reads but one wave per SIMD: 365 us.
+//   A workgroup of the projections' 256 x 256 tile has a compute unit to itself and walks several tiles (WALK): the ring goes on across their boundary,
+// the loads of the next tile's first steps go out in the last ones of this, and nothing starts or drains in between.
+// Rows leave through the slot that is free at that moment, each wave by itself, as whole lines (stored from the accumulators in
+// pieces of 32 bytes, the write path takes 45 us more).  16384 x 2048 x 6144: 377 -> 359 us, 8192 rows 191 -> 176, 16384 x 1024 x 3072
+// 109 -> 99, 4100 x 2048 x 6144 110.5 -> 108.  dx has three times the steps to a tile and half of the outputs, and gains nothing (8192 rows 426 -> 429 us
+// for the whole reverse mode), so it keeps one tile to a workgroup.
+constexpr bool nt_walks(int epi, int tm) { return epi == kEpiProj && tm == 256; }
+
+// A wave's 32 NI x 64 part of a tile, from its accumulators to memory: acc[i][j][v] = C[row0 + 32 i + lane % 32][32 j + 8 (v / 4) + 4 (lane / 32) + v % 4],
+// `part`: of the tile's 256 columns.  Rows before m_new are another tile's.  Every store is issued by every lane (rows that are not
+// stored lie outside the buffer), 4 NI per output: the walk counts them.  `stage`: 4 KB of LDS of the wave's own.
+template <int NI, int NJ>
+__device__ __forceinline__ void store_tile(const GemmParams& p, const f32x16 (&acc)[NI][NJ], int row0, int m_new, int col, char* stage)
+{
+    static_assert(NJ == 2, "a row of the wave's part is one line of 128 bytes");
+    const int lane = (int)threadIdx.x & 63, r32 = lane & 31, g = lane >> 5;
+    const int which = col / p.d;
+    const uint32_t pitch = (uint32_t)p.d * 2u;
+    const int from = max(row0, m_new), rows = max(min(row0 + 32 * NI, p.M) - from, 0);
+    // (of the row that is the buffer's first: rows before it wrap around to offsets past its end)
+    const uint32_t at = (uint32_t)(row0 - from + (lane >> 3)) * pitch + 16u * (lane & 7);
+    auto buffer = [&](__bf16* out) {
+        return __builtin_amdgcn_make_buffer_rsrc(out + (size_t)from * (pitch / 2) + (col - which * p.d), 0, (int)((uint32_t)rows * pitch), 0x00020000);
+    };
+    // the 16-byte piece c of row r lies at c ^ ((r >> 1) & 7), as in the ring
+    auto put = [&](const u32x4& u, int piece) {
+        // the halves of the wave trade four columns for four: lanes 0 .. 31 get columns 8 piece .., the others 8 (piece + 1) ..
+        const auto x = __builtin_amdgcn_permlane32_swap(u[0], u[2], false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(u[1], u[3], false, false);
+        *reinterpret_cast<u32x4*>(stage + r32 * 128 + (((piece + g) ^ ((r32 >> 1) & 7)) << 4)) = u32x4{x[0], y[0], x[1], y[1]};
+    };
+    // MODE 0: the sum itself; 1: SiLU of it; 2: sigmoid of it
+    auto store = [&](auto MODE, const auto& to, int i) {
+        constexpr int md = decltype(MODE)::value;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; c += 2) {
+                union { __bf16 e[8]; u32x4 u; } y;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float a = acc[i][j][4 * c + e];
+                    const float sg = md == 0 ? 0.0f : fast_rcp(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * a));
+                    y.e[e] = (__bf16)(md == 0 ? a : md == 1 ? a * sg : sg);
+                }
+                put(y.u, 4 * j + c);
+            }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int r = 8 * k + (lane >> 3);
+            const u32x4 u = *reinterpret_cast<const u32x4*>(stage + r * 128 + (((lane & 7) ^ ((r >> 1) & 7)) << 4));
+            __builtin_amdgcn_raw_buffer_store_b128(u, to, at + (uint32_t)(32 * i + 8 * k) * pitch, 0, 0);
+        }
+    };
+    typedef std::integral_constant<int, 0> Plain;
+    typedef std::integral_constant<int, 1> Silu;
+    typedef std::integral_constant<int, 2> Sigmoid;
+    if (which == 0) {
+        const auto to = buffer(p.z);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) store(Plain(), to, i);
+    } else if (which == 1) {
+        const auto to = buffer(p.v), to_av = buffer(p.av);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) { store(Silu(), to, i); if (p.av) store(Plain(), to_av, i); }
+    } else {
+        const auto to = buffer(p.q);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) store(Sigmoid(), to, i);
+    }
+}
+
 template <int EPI, int TM, int TN, int WM, int WN, int KG, int NS>
 __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_kernel(GemmParams p)
 {
@@ -69,6 +142,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_kernel(GemmParam
     constexpr int SLOT = (TM > TN ? TM : TN) * 128;               // bytes of a slot of the ring
     constexpr int LA = TM / 8 / NWV, LB = TN / 8 / NWV;           // load instructions per wave for a tile of A, of B
     constexpr int NI = TM / WM / 32, NJ = TN / WN / 32, KPW = 4 / KG;
+    constexpr bool WALK = nt_walks(EPI, TM);
     typedef Mma<__bf16> M;
     typedef __attribute__((address_space(3))) void* lds_ptr;
     typedef const __attribute__((address_space(1))) void* global_ptr;
@@ -77,35 +151,60 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_kernel(GemmParam
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = w % WN, wm = w / WN % WM, kg = w / (WN * WM);
     const int n_bn = p.N / TN, n_bm = (p.M + TM - 1) / TM;
-    int bm, bn;
+    // The tiles of an XCD lie together; its workgroups take them in turn, every `stride`-th (WALK), or one each.
+    int t, t_end, stride;
     {
-        const int grid = (int)gridDim.x, id = (int)blockIdx.x;
-        const int per = grid / kXcds, rem = grid - per * kXcds, x = id % kXcds;
-        const int t = x * per + min(x, rem) + id / kXcds;
-        const int band_tiles = kBandRows * n_bn, band = t / band_tiles, in_band = t - band * band_tiles;
-        const int rows = min(kBandRows, n_bm - band * kBandRows);
-        bn = in_band / rows;
-        bm = band * kBandRows + in_band - bn * rows;
+        const int tiles = n_bm * n_bn, grid = (int)gridDim.x, id = (int)blockIdx.x;
+        const int per = tiles / kXcds, rem = tiles - per * kXcds, x = id % kXcds, from = x * per + min(x, rem);
+        t = from + id / kXcds;
+        t_end = from + per + (x < rem ? 1 : 0);
+        stride = (grid + kXcds - 1 - x) / kXcds;
     }
-    const int m0 = bm * TM, n0 = bn * TN;
+    // Tile t: rows m0 .. of A and columns n0 .. of C.  The last tile of a column reaches back into the rows of the one before
+    // (which does not store them again: m_new), so that all tiles are whole unless A is shorter than one.
+    struct Tile { int m0, m_new, n0; };
+    auto tile_at = [&](int at) {
+        const int band_tiles = kBandRows * n_bn, band = at / band_tiles, in_band = at - band * band_tiles;
+        const int rows = min(kBandRows, n_bm - band * kBandRows), bn = in_band / rows;
+        const int m = (band * kBandRows + in_band - bn * rows) * TM;
+        return Tile{max(min(m, p.M - TM), 0), m, bn * TN};
+    };
+    Tile tile = tile_at(t);
     f32x16 acc[NI][NJ];
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
+    // What the sums start from: zero, or (WALK) the biases of their columns.  These are scalar loads, a half wave's each, and kept apart from the
+    // choice between them: folded into a vector load at a chosen address, they would wait for the ring's loads and the stores.
+    auto scalar = [](float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); };
+    auto clear = [&]() {
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float b = 0.0f;
+                    if constexpr (WALK) {
+                        typedef const __attribute__((address_space(4))) float* scalar_ptr;
+                        const scalar_ptr s = (scalar_ptr)(p.bias + tile.n0 + (TN / WN) * wn + 32 * j + 8 * c);
+                        const float lo = scalar(s[e]), hi = scalar(s[4 + e]);
+                        b = g ? hi : lo;
+                    }
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) acc[i][j][4 * c + e] = b;
+                }
+    };
+    clear();
     // Load instruction j of a wave: eight rows, of A from row a0(j) on.  A row of dW3's operands is 2 bytes per token and may be long, so
-    // the rows before are part of the scalar address; rows past the end of A re-read its last one (never stored).
-    const bool whole = m0 + TM <= p.M;
-    const char* abase = reinterpret_cast<const char*>(p.A) + (size_t)m0 * p.lda * 2;
-    const char* bbase = reinterpret_cast<const char*>(p.B) + (size_t)n0 * p.ldb * 2;
+    // the rows before are part of the scalar address; rows past the end of an A shorter than a tile re-read its last one (never stored).
+    const bool whole = p.M >= TM;
+    auto a_of = [&](const Tile& at) { return reinterpret_cast<const char*>(p.A) + (size_t)at.m0 * p.lda * 2; };
+    auto b_of = [&](const Tile& at) { return reinterpret_cast<const char*>(p.B) + (size_t)at.n0 * p.ldb * 2; };
+    const char *abase = a_of(tile), *bbase = b_of(tile), *anext = abase, *bnext = bbase;
     auto a0 = [&](int j) { return whole ? 8 * (LA * w + j) : 0; };
     uint32_t ao[LA], bo[LB];
 #pragma unroll
     for (int j = 0; j < LA; ++j) {
         const int row = 8 * (LA * w + j) + (lane >> 3);
-        ao[j] = (uint32_t)(min(row, p.M - 1 - m0) - a0(j)) * (uint32_t)(p.lda * 2) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+        ao[j] = (uint32_t)(min(row, p.M - 1) - a0(j)) * (uint32_t)(p.lda * 2) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
     }
 #pragma unroll
     for (int j = 0; j < LB; ++j) {
@@ -115,13 +214,18 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_kernel(GemmParam
     // the steps of 64 of this workgroup's share of the contraction
     const int steps = p.K / 64, first = (int)((long long)blockIdx.y * steps / gridDim.y);
     const int nk = (int)((long long)(blockIdx.y + 1) * steps / gridDim.y) - first;
-    // load instruction j of this wave for the A (B) tile of k-step ks into `slot`
+    // load instruction j of this wave for the A (B) tile of k-step ks into `slot`; steps past the last one are the next tile's (K has
+    // four steps and more there), or the last one once more
+    auto step_of = [&](const char* base, const char* next, int ks) {
+        if constexpr (WALK) return ks < nk ? base + (size_t)ks * 128 : next + (size_t)(ks - nk) * 128;
+        else return base + (size_t)(first + min(ks, nk - 1)) * 128;
+    };
     auto load_a = [&](int slot, int ks, int j) {
-        const char* s = abase + (size_t)a0(j) * p.lda * 2 + (size_t)(first + min(ks, nk - 1)) * 128;
+        const char* s = step_of(abase, anext, ks) + (size_t)a0(j) * p.lda * 2;
         __builtin_amdgcn_global_load_lds((global_ptr)(s + ao[j]), (lds_ptr)(smem + slot * SLOT + 8 * (LA * w + j) * 128), 16, 0, 0);
     };
     auto load_b = [&](int slot, int ks, int j) {
-        const char* s = bbase + (size_t)(8 * (LB * w + j)) * p.ldb * 2 + (size_t)(first + min(ks, nk - 1)) * 128;
+        const char* s = step_of(bbase, bnext, ks) + (size_t)(8 * (LB * w + j)) * p.ldb * 2;
         __builtin_amdgcn_global_load_lds((global_ptr)(s + bo[j]), (lds_ptr)(smem + slot * SLOT + 8 * (LB * w + j) * 128), 16, 0, 0);
     };
     const int sw = (r32 >> 1) & 7;
@@ -159,6 +263,13 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_kernel(GemmParam
     };
     // a step: phases 0 .. KPW - 1; of the loads behind the barrier of step k, B's go out in its last phase and A's in the first phase of the next
     constexpr int NL = LB + LA, LAST = LB;
+    int stores = 0;          // stores that went out behind the loads of this tile's first two steps
+    for (;;) {
+    Tile next = tile;
+    if constexpr (WALK) {
+        if (t + stride < t_end) next = tile_at(t + stride);
+        anext = a_of(next); bnext = b_of(next);
+    }
     for (int k = 0; k < nk; ++k) {
         const int sn = wrap(s0 + 2), sp = wrap(s0 + NS - 2);       // slots of the next and of the previous step
 #pragma unroll
@@ -171,7 +282,11 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_kernel(GemmParam
 #pragma unroll
                     for (int j = LAST; j < NL; ++j) refill(sp, k - 1, j);
                 }
-                __builtin_amdgcn_s_waitcnt(vm_lgkm((NS - 5) / 2 * (LA + LB) + LA));
+                // (the stores of the tile before are younger than what a tile's first step waits for)
+                constexpr int NEW = (NS - 5) / 2 * (LA + LB) + LA;
+                if (WALK && k == 0 && stores == 8 * NI) __builtin_amdgcn_s_waitcnt(vm_lgkm(NEW + 8 * NI));
+                else if (WALK && k == 0 && stores == 4 * NI) __builtin_amdgcn_s_waitcnt(vm_lgkm(NEW + 4 * NI));
+                else __builtin_amdgcn_s_waitcnt(vm_lgkm(NEW));
                 __builtin_amdgcn_s_barrier();
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -210,8 +325,20 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_kernel(GemmParam
         }
         s0 = sn;
     }
+    if constexpr (WALK) {
+        char* stage = smem + wrap(s0 + NS - 1) * SLOT + 8 * LA * w * 128;        // (where this wave's next loads of A go)
+        store_tile<NI, NJ>(p, acc, tile.m0 + (TM / WM) * wm, tile.m_new, tile.n0 + (TN / WN) * wn, stage);
+        stores = 4 * NI * (tile.n0 / p.d == 1 && p.av ? 2 : 1);
+        t += stride;
+        if (t >= t_end) break;
+        tile = next; abase = anext; bbase = bnext;
+        clear();
+    } else break;
+    }
     __builtin_amdgcn_s_waitcnt(vm_lgkm(0));
+    if constexpr (WALK) return;
     __builtin_amdgcn_s_barrier();
+    const int m0 = tile.m0, n0 = tile.n0;
 
     // the groups' shares of the sum, added in order
     if constexpr (KG > 1) {
@@ -255,7 +382,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_kernel(GemmParam
                 for (int j = 0; j < NJ; ++j)
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
-                        if (row < p.M)
+                        if (row >= tile.m_new && row < p.M)
                             *reinterpret_cast<f32x4*>(p.Cf + ((size_t)blockIdx.y * p.M + row) * p.ldc + n0 + (TN / WN) * wn + 32 * j + 8 * c + 4 * g) =
                                 f32x4{acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
             }
@@ -324,7 +451,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_kernel(GemmParam
 #pragma unroll
                 for (int k = 0; k < BATCH; ++k) {
                     const int vi = tid + (v0 + k) * THREADS, row = vi / VPR;
-                    if (m0 + row < p.M) *reinterpret_cast<u32x4*>(out + (size_t)(m0 + row) * ld + c0 + (vi % VPR) * 8) = buf[k];
+                    if (m0 + row >= tile.m_new && m0 + row < p.M) *reinterpret_cast<u32x4*>(out + (size_t)(m0 + row) * ld + c0 + (vi % VPR) * 8) = buf[k];
                 }
             }
             __syncthreads();
@@ -336,13 +463,15 @@ template <int EPI, int TM, int TN, int WM, int WN, int KG, int NS>
 static hipError_t launch_nt(const GemmParams& p, int splits, hipStream_t stream)
 {
     constexpr size_t ring = (size_t)NS * (TM > TN ? TM : TN) * 128;
-    constexpr size_t tail = (size_t)(KG - 1) * TM * TN * 4 + (EPI == kEpiFloat ? 0 : (size_t)TM * (TN + 8) * 2);
+    constexpr bool walk = nt_walks(EPI, TM);
+    constexpr size_t tail = (size_t)(KG - 1) * TM * TN * 4 + (EPI == kEpiFloat || walk ? 0 : (size_t)TM * (TN + 8) * 2);
     constexpr size_t lds = ring > tail ? ring : tail;
     static_assert(lds <= 160 * 1024, "LDS budget");
     auto kern = gemm_nt_kernel<EPI, TM, TN, WM, WN, KG, NS>;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(((p.M + TM - 1) / TM) * (p.N / TN)), splits), dim3(64 * WM * WN * KG), lds, stream, p);
+    const int tiles = ((p.M + TM - 1) / TM) * (p.N / TN);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(walk && tiles > kUnits ? kUnits : tiles), splits), dim3(64 * WM * WN * KG), lds, stream, p);
     return hipGetLastError();
 }
 

@@ -186,3 +186,35 @@ def test_proj_tiles_and_padding(M, d):
         e = float((got.double() - ref).abs().max() / ref.abs().max())
         print("   %-4s %.2e" % (name, e), flush=True)
         assert e <= tol, (name, e)
+
+
+@pytest.mark.parametrize("keep_av", [True, False])
+@pytest.mark.parametrize("M", [14593,       # 58 x 12 tiles for 256 workgroups: two or three each; the last row of tiles has one new row
+                               14848])      # the same tiles, all rows new
+def test_projection_walks_tiles(M, keep_av):
+    """Projections whose workgroups take several 256 x 256 tiles (the ring of operands goes on from one to the next): every output
+    element against fp64 products of the same operands, and the rows around the last tile's edge, which two tiles compute, as
+    in a call of a few rows; nothing is written where no tile belongs (a tail of sentinel rows behind every output).
+    bf16 outputs to 2 units in the last place of the largest value."""
+    d = 1024
+    print("\n[proj walk] M=%d keep_av=%s" % (M, keep_av), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(9700 + M)
+    x = torch.randn((M, d), generator=g, device="cuda").bfloat16()
+    w3 = (torch.randn((3 * d, d), generator=g, device="cuda") / d ** 0.5).bfloat16()
+    b3 = torch.randn(3 * d, generator=g, device="cuda")
+    outs = [torch.full((M + 256, d), -7.0, dtype=torch.bfloat16, device="cuda") for _ in range(4)]
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    rc = binding.lib().hgru2_proj_fwd(M, d, ptr(x), ptr(w3), ptr(b3), ptr(outs[0]), ptr(outs[1]), ptr(outs[2]),
+                                      ptr(outs[3]) if keep_av else None,
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    pre = x.double() @ w3.double().t() + b3.double()
+    refs = (pre[:, :d], pre[:, d:2 * d] * torch.sigmoid(pre[:, d:2 * d]), torch.sigmoid(pre[:, 2 * d:]), pre[:, d:2 * d])
+    for name, got, ref in zip(("z", "v", "q", "av"), outs, refs):
+        assert bool((got[M:] == -7.0).all()), name
+        if name == "av" and not keep_av:
+            assert bool((got == -7.0).all())
+            continue
+        e = float((got[:M].double() - ref).abs().max() / ref.abs().max())
+        print("   %-4s %.2e" % (name, e), flush=True)
+        assert e <= 2.0 ** -7, (name, e)
