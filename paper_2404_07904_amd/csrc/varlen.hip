@@ -30,9 +30,10 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 // take, the entry the span ends in, then two ints: whether the forward walk's spans, the reverse walk's spans
 // carry the state over spans by walks from zero (TokenLayout::span_walks).
 // (Called by all threads of a one-workgroup kernel, after a barrier that follows the table's writes.)
-__device__ __forceinline__ void build_groups(const int* tab, int n_entries, int G, int* groups, int heads64)
+// `before`: the table's third array, or the caller's copy of it in LDS.
+template <typename Before>
+__device__ __forceinline__ void build_groups(Before before, int n_entries, int G, int* groups, int heads64)
 {
-    const int* before = tab + 2 * (n_entries + 1);
     const long long total = before[n_entries];
     for (int grp = threadIdx.x; grp <= G; grp += kTabThreads) {
         int first = n_entries;
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(kTabThreads) void varlen_groups_kernel(const int* t
                                                                     int heads64, const int* choice, int path)
 {
     if (choice && table_read(choice, 0) != path) return;        // one of several alternatives, and not the one called for
-    build_groups(tab, n_entries, G, groups, heads64);
+    build_groups(tab + 2 * (n_entries + 1), n_entries, G, groups, heads64);
 }
 
 // Exclusive prefix (sum, or running maximum of non-negative values) of one value per thread over the
@@ -120,69 +121,77 @@ __device__ __forceinline__ int block_prefix(int v, int* wave_tot)
 }
 
 // With `groups` (null: none) the group array of the table is built in the same launch.
+// What the one workgroup takes is the chain of trips to memory: with up to kSortLds sequences (LDS) every array is also kept in LDS, where
+// the later steps read it, and the one trip left is the one that fetches `cu`.  Up to kSortMax the lengths are, for the order.  (21 sequences, 16 groups, with the profiler's 5 us a launch: 9.4 -> 7.2 us, forward of 21 sequences in 16384 tokens 93.7 -> 91.2, of 500 151 -> 121, of 2048 801 -> 302, of 2049 1396 -> 334).
+template <bool LDS>
 __global__ __launch_bounds__(kTabThreads) void varlen_table_kernel(const int* cu, int B, int T, int* tab, int G, int* groups, int heads64,
                                                                    int sub, const int* choice, int path)
 {
     if (choice && table_read(choice, 0) != path) return;        // one of several alternatives, and not the one called for
     const int shift = 31 - __builtin_clz((unsigned)sub);         // sub is a power of two
     __shared__ int wave_tot[kTabThreads / 64];
+    __shared__ __align__(16) int slen[(LDS ? kSortLds : kSortMax) + 4];
+    __shared__ int sstart[LDS ? kSortLds + 4 : 1], sbefore[LDS ? kSortLds + 4 : 1];
     const int n = B + 1, tid = threadIdx.x;
     const int per = (n + kTabThreads - 1) / kTabThreads;
     const int lo = min(tid * per, n), hi = min(lo + per, n);      // this thread's entries
     auto clamped = [&](int i) { return min(max(cu[i], 0), T); };
+    auto start_of = [&](int i) { if constexpr (LDS) return sstart[i]; else return tab[i]; };
+    const bool sorted = LDS || B <= kSortMax;
 
     // starts: running maximum of the clamped offsets
     int m = 0;
     for (int i = lo; i < hi; ++i) m = max(m, clamped(i));
     int run = block_prefix<true>(m, wave_tot);
-    for (int i = lo; i < hi; ++i) { run = max(run, clamped(i)); tab[i] = run; }
+    for (int i = lo; i < hi; ++i) {
+        run = max(run, clamped(i));
+        tab[i] = run;
+        if constexpr (LDS) sstart[i] = run;
+    }
+    if (sorted)
+        for (int j = n + tid; j < ((n + 3) & ~3); j += kTabThreads) slen[j] = -1;      // padding never counts
     __syncthreads();                                              // starts of the neighbouring slices are visible
 
     // lengths, and the chunk counts before every sequence
     int c = 0;
     for (int i = lo; i < hi; ++i) {
-        const int len = i < B ? tab[i + 1] - tab[i] : 0;
+        const int len = i < B ? start_of(i + 1) - start_of(i) : 0;
         tab[n + i] = len;
+        if (sorted) slen[i] = i < B ? len : -1;
         c += (len + sub - 1) >> shift;
     }
     run = block_prefix<false>(c, wave_tot);
     for (int i = lo; i < hi; ++i) {
         tab[2 * n + i] = run;
-        run += (tab[n + i] + sub - 1) >> shift;
+        if constexpr (LDS) sbefore[i] = run;
+        run += ((LDS ? (i < B ? slen[i] : 0) : tab[n + i]) + sub - 1) >> shift;
     }
     __syncthreads();                                              // all lengths are visible
 
     // order by falling length: the rank of sequence b is the number of sequences that come before
-    // it (longer, or as long with a smaller index), counted directly
-    const int* len = tab + n;
+    // it (longer, or as long with a smaller index), counted directly in LDS, four at a time: with whole vectors before b
+    // counting from its own length on and the others above it, what is missing is equal lengths before b in its own vector
     int* order = tab + 3 * n;
-    // (up to kSortLds sequences the lengths are compared out of LDS, four at a time)
-    __shared__ int slen[kSortLds];
-    const bool in_lds = B <= kSortLds;
-    if (in_lds) {
-        for (int j = tid; j < kSortLds; j += kTabThreads) slen[j] = j < B ? len[j] : -1;     // padding never counts
-        __syncthreads();
-    }
     for (int b = tid; b < B; b += kTabThreads) {
         int rank = b;
-        if (in_lds) {
-            rank = 0;
+        if (sorted) {
             const int mine = slen[b];
-            for (int j = 0; j < ((B + 3) & ~3); j += 4) {
-                const i32x4 l = *reinterpret_cast<const i32x4*>(slen + j);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) rank += (l[e] > mine || (l[e] == mine && j + e < b)) ? 1 : 0;
-            }
-        } else if (B <= kSortMax) {
             rank = 0;
-            const int mine = len[b];
-            for (int j = 0; j < B; ++j) rank += (len[j] > mine || (len[j] == mine && j < b)) ? 1 : 0;
+#pragma unroll 4
+            for (int j = 0; j < B; j += 4) {
+                const i32x4 l = *reinterpret_cast<const i32x4*>(slen + j);
+                const int above = j + 4 <= b ? mine - 1 : mine;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) rank += l[e] > above ? 1 : 0;
+            }
+            for (int e = b & ~3; e < b; ++e) rank += slen[e] == mine ? 1 : 0;
         }
         order[rank] = b;
     }
     if (groups) {
         __syncthreads();
-        build_groups(tab, B, G, groups, heads64);
+        if constexpr (LDS) build_groups((const int*)sbefore, B, G, groups, heads64);
+        else build_groups((const int*)(tab + 2 * n), B, G, groups, heads64);
     }
 }
 
@@ -272,8 +281,8 @@ size_t varlen_table_bytes(int B) { return 4 * ((size_t)B + 1) * sizeof(int); }
 hipError_t launch_varlen_table(const int* cu_seqlens, int B, int T, int* table, hipStream_t stream, int G, int* groups, bool heads64,
                                int sub, const int* choice, int path)
 {
-    hipLaunchKernelGGL(varlen_table_kernel, dim3(1), dim3(kTabThreads), 0, stream, cu_seqlens, B, T, table, G, groups, heads64 ? 1 : 0, sub,
-                       choice, path);
+    auto kern = B <= kSortLds ? varlen_table_kernel<true> : varlen_table_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3(1), dim3(kTabThreads), 0, stream, cu_seqlens, B, T, table, G, groups, heads64 ? 1 : 0, sub, choice, path);
     return hipGetLastError();
 }
 

@@ -296,3 +296,34 @@ def test_sequences_that_reach_over_spans(chunks, dk, dv):
     lens = [64 * c - 5 * i for i, c in enumerate(chunks)]
     print("\n[varlen, over spans] lens=%s dk=%d dv=%d" % (lens, dk, dv), flush=True)
     run(1800 + sum(lens), lens, 64, dk, dv, lb=0.9)
+
+
+@pytest.mark.parametrize("B", [1, 3, 255, 256, 257, 2047, 2048, 2049, 8191, 8192, 8193])
+def test_tables_of_many_sequences(B):
+    """As many sequences as the table kernel has ways to keep its arrays (in LDS up to 2048, their lengths up to 8192), most of
+    them as long as many others, some empty.  States continued in place take a workgroup per sequence, by the table's
+    order: a sequence that the order left out would keep its state and write no output.  With h0 and hT apart, a workgroup takes a
+    span of chunks, found through the table's other arrays.  Against fp64 steps over all sequences at once; tolerance as above."""
+    g = torch.Generator().manual_seed(8800 + B)
+    lens = torch.randint(0, 8, (B,), generator=g)
+    lens[torch.randint(0, B, (1 + B // 50,), generator=g)] = 21
+    T, H, d = int(lens.sum()), 1, 64
+    print("\n[varlen tables] B=%d T=%d" % (B, T), flush=True)
+    cu = torch.cat([torch.zeros(1, dtype=torch.long), lens.cumsum(0)])
+    q, v = [torch.randn((T, H, d), generator=g).bfloat16().cuda() for _ in range(2)]
+    f = (0.4 + 0.6 * torch.rand((T, H, d), generator=g)).bfloat16().cuda()
+    h0 = (0.5 * torch.randn((B, H, d, d), generator=g)).cuda()
+    cud = cu.int().cuda()
+    state = h0.clone()
+    o, _ = binding.hgrn2_fwd_varlen(q, f, v, cud, state, hT=state, o=torch.full_like(v, float("nan")))
+    o2, hT2 = binding.hgrn2_fwd_varlen(q, f, v, cud, h0)
+    ref, S = torch.zeros((T, d), dtype=torch.float64, device="cuda"), h0[:, 0].double()
+    start, lens = cu[:-1].cuda(), lens.cuda()
+    for t in range(int(lens.max())):
+        on = (lens > t).nonzero()[:, 0]
+        at = start[on] + t
+        ft = f[at, 0].double()
+        S[on] = ft[:, :, None] * S[on] + (1.0 - ft)[:, :, None] * v[at, 0].double()[:, None, :]
+        ref[at] = (q[at, 0].double()[:, :, None] * S[on]).sum(1)
+    for name, x, r in (("o", o[:, 0], ref), ("hT", state[:, 0], S), ("o (spans)", o2[:, 0], ref), ("hT (spans)", hT2[:, 0], S)):
+        check(name, host(x), r.cpu().numpy(), TOL["bf16"])
