@@ -210,7 +210,7 @@ def main():
         q, f, v, dO = sets[i % 2]
         binding.hgrn2_bwd(q, f, v, dO, None, None, workspace=ws, grad_q=gq, grad_f=gf, grad_v=gv)
 
-    # the backward call of the training pair is ONE kernel launch at this shape (bwd_fused_kernel: the
+    # the backward call of the training pair is ONE kernel launch at this shape (bwd_walk_kernel: the
     # reverse walk with the state gradient in registers), so its event time is that kernel's duration
     s_train_fwd, s_train_bwd = train_fwd, train_bwd
 
@@ -274,11 +274,11 @@ def main():
     dom_s = dom_all[len(dom_all) // 2]
     dom_bytes = 7 * seq_k
     achieved = dom_bytes / dom_s / 1e9
-    roofline = {"kernel": "bwd_fused_kernel (hgrn2_bwd_saved)", "bound": "hbm", "achieved": round(achieved, 1),
+    roofline = {"kernel": "bwd_walk_kernel (hgrn2_bwd_saved)", "bound": "hbm", "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "us": round(dom_s * 1e6, 2), "us_mean_min_max": [round(x * 1e6, 1) for x in (sum(dom_all) / len(dom_all), dom_all[0], dom_all[-1])],
                 "algorithmic_bytes": dom_bytes,
-                "traffic": MEASURED_TRAFFIC_BYTES.get("bwd_fused_kernel")}
+                "traffic": MEASURED_TRAFFIC_BYTES.get("bwd_walk_kernel")}
 
     flops = token_heads * ((4 * D * D + CHUNK * 2 * D) + (8 * D * D + CHUNK * 5 * D))   # fwd + bwd, algorithmic
     mfma_tflops = flops / (ms_per_step * 1e-3) / 1e12

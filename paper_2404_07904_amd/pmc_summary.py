@@ -23,7 +23,7 @@ KIB = 1024.0
 
 # kernels of interest: short name -> substring of the profiler's kernel name
 KERNELS = {
-    "bwd_fused_kernel": "bwd_fused_kernel",
+    "bwd_walk_kernel": "bwd_walk_kernel",
     "fwd_fused_kernel": "fwd_fused_kernel",
     "bwd_grad_kernel": "bwd_grad_kernel",
     "sweep_kernel_mode1": "sweep_kernelIDF16bLi128ELi128ELi64ELi1E",
