@@ -16,6 +16,7 @@
 // four tokens at once.  dq, df, dv leave from the accumulators: neighbouring lanes trade halves, so that each holds a pair of channels.
 // Chunks are addressed through buffer descriptors that cover exactly their tokens: rows that stand for no token read as
 // zero (their gates are set to one) and are not stored, in ragged chunks and in fine ones (ChunkRows), without a branch.
+// Where a chunk's rows lie too far apart for a descriptor (walk_rows.hpp), kernels of their own (FAR) take 64-bit row addresses.
 //
 // What bounds it, per chunk of 128 x 128 and compute unit (15.6 kcycles with everything in the caches, 6.6 us): 8.0 kcycles of vector
 // instructions, 6.8 of LDS, 3.2 of MFMA, of which the matrix stage and the element-wise stages overlap little; over
@@ -24,6 +25,7 @@
 // 16 x 16 heads, 512 tokens 87 -> 74; 8 x 32 heads of 64, 2000 tokens, gate formed 179 -> 173, 16 x 32, 512 tokens 66 -> 60;
 // 8 x 16 heads of 64 x 128, 1024 tokens 91 -> 70, of 128 x 64 73 -> 67.
 #include "bwd_common.hpp"
+#include "walk_rows.hpp"
 
 namespace hgrn2 {
 
@@ -69,14 +71,14 @@ typedef __amdgpu_buffer_rsrc_t WalkRsrc;
 constexpr int kWalkStream = 2 | 16;
 
 // The tokens of chunk rows cr of a tensor whose sequence starts at element `off`: row r, column c of the chunk lies at
-// byte ((r - lo) ld + c) es with lo the first row that stands for a token; rows before it wrap round to offsets that
-// are out of range, like those behind the last one.
+// byte walk_row_offset(r, lo, ld, c, es) with lo the first row that stands for a token.  (FAR: `bytes` is the number of rows.)
 struct ChunkSpan { uint32_t lo, hi, bytes; };
+template <bool FAR>
 __device__ __forceinline__ ChunkSpan chunk_span(const void* tensor, size_t off, const ChunkRows& cr, int ld, int width, int es)
 {
     const uintptr_t base = reinterpret_cast<uintptr_t>(tensor) + (off + (size_t)cr.first * (size_t)ld) * es;
     const int rows = max(cr.end - cr.first, 0);
-    return ChunkSpan{(uint32_t)base, (uint32_t)(base >> 32), rows > 0 ? ((unsigned)(rows - 1) * (unsigned)ld + (unsigned)width) * (unsigned)es : 0u};
+    return ChunkSpan{(uint32_t)base, (uint32_t)(base >> 32), FAR ? (uint32_t)rows : walk_chunk_bytes(rows, ld, width, es)};
 }
 __device__ __forceinline__ WalkRsrc span_rsrc(const ChunkSpan& s)
 {
@@ -88,7 +90,16 @@ __device__ __forceinline__ WalkRsrc span_rsrc(const ChunkSpan& s)
 }
 __device__ __forceinline__ WalkRsrc chunk_rsrc(const void* tensor, size_t off, const ChunkRows& cr, int ld, int width, int es)
 {
-    return span_rsrc(chunk_span(tensor, off, cr, ld, width, es));
+    return span_rsrc(chunk_span<false>(tensor, off, cr, ld, width, es));
+}
+// (FAR) 16 or 4 bytes at row `row`, counted from the span's first one, and column `col`; zero where no token is
+template <typename V>
+__device__ __forceinline__ V far_load(const ChunkSpan& s, int row, int ld, int col, int es)
+{
+    const uintptr_t base = (uintptr_t)s.lo | ((uintptr_t)s.hi << 32);
+    V x = {};
+    if ((uint32_t)row < s.bytes) x = *reinterpret_cast<const V*>(base + ((size_t)row * (size_t)ld + (size_t)col) * es);
+    return x;
 }
 __device__ __forceinline__ u32x4 rsrc_load16(WalkRsrc r, unsigned off)
 {
@@ -116,21 +127,36 @@ template <int NAT, int NW> __device__ __forceinline__ WalkWave walk_wave(int w)
 
 // f and q of the wave's tile: bf16 rows as four 16-byte pieces each, lane l the piece l % 4 of rows l / 4 and l / 4 + 16; fp32 gates
 // as the lane will use them, a row of 32 channels per half wave and load.
-template <int DK, bool GATE_BF16>
+template <int DK, bool GATE_BF16, bool FAR>
 __device__ __forceinline__ void load_gate_query(const BwdGradParams& p, RawGate<GATE_BF16>& rf, u32x4 (&rq)[2], const ChunkAt& c,
                                                 const WalkWave& ww, int lane)
 {
     const ChunkRows cr = chunk_rows(p.lay.sub, c.n, c.sv.N);
     const int ld = (int)p.lay.sn_k, lo = cr.first - cr.tok0;
+    if constexpr (FAR) {
+        const ChunkSpan f = chunk_span<true>(p.f, c.sv.off_k, cr, ld, DK, GATE_BF16 ? 2 : 4), q = chunk_span<true>(p.q, c.sv.off_k, cr, ld, DK, 2);
+        const int row = 32 * ww.rt + (lane >> 2) - lo, col = 32 * ww.at + 8 * (lane & 3);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            rq[i] = far_load<u32x4>(q, row + 16 * i, ld, col, 2);
+            if constexpr (GATE_BF16) rf.v[i] = far_load<u32x4>(f, row + 16 * i, ld, col, 2);
+        }
+        if constexpr (!GATE_BF16) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                rf.v[i] = far_load<float>(f, 32 * ww.rt + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3) - lo, ld, 32 * ww.at + (lane & 31), 4);
+        }
+        return;
+    }
     const WalkRsrc f = chunk_rsrc(p.f, c.sv.off_k, cr, ld, DK, GATE_BF16 ? 2 : 4), q = chunk_rsrc(p.q, c.sv.off_k, cr, ld, DK, 2);
-    const unsigned at = (unsigned)(((32 * ww.rt + (lane >> 2) - lo) * ld + 32 * ww.at + 8 * (lane & 3)) * 2), step = (unsigned)(32 * ld);
+    const unsigned at = walk_row_offset(32 * ww.rt + (lane >> 2), lo, ld, 32 * ww.at + 8 * (lane & 3), 2), step = (unsigned)(32 * ld);
     rq[0] = rsrc_load16(q, at);
     rq[1] = rsrc_load16(q, at + step);
     if constexpr (GATE_BF16) {
         rf.v[0] = rsrc_load16(f, at);
         rf.v[1] = rsrc_load16(f, at + step);
     } else {
-        const unsigned a = (unsigned)(((32 * ww.rt + 4 * (lane >> 5) - lo) * ld + 32 * ww.at + (lane & 31)) * 4);
+        const unsigned a = walk_row_offset(32 * ww.rt + 4 * (lane >> 5), lo, ld, 32 * ww.at + (lane & 31), 4);
 #pragma unroll
         for (int i = 0; i < 16; ++i)
             rf.v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(f, a + (unsigned)((8 * (i >> 2) + (i & 3)) * ld * 4), 0, 0));
@@ -138,13 +164,19 @@ __device__ __forceinline__ void load_gate_query(const BwdGradParams& p, RawGate<
 }
 
 // 16 columns of a row of V or dO per thread
-template <int DV>
+template <int DV, bool FAR>
 __device__ __forceinline__ void load_value_rows(const BwdGradParams& p, Raw16<__bf16>& r, const void* tensor, const ChunkAt& c, int tid)
 {
     const ChunkRows cr = chunk_rows(p.lay.sub, c.n, c.sv.N);
     const int ld = (int)p.lay.sn_v, row = tid / (DV / 16), grp = tid % (DV / 16);
+    if constexpr (FAR) {
+        const ChunkSpan s = chunk_span<true>(tensor, c.sv.off_v, cr, ld, DV, 2);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) r.v[i] = far_load<u32x4>(s, row - (cr.first - cr.tok0), ld, 16 * grp + 8 * i, 2);
+        return;
+    }
     const WalkRsrc d = chunk_rsrc(tensor, c.sv.off_v, cr, ld, DV, 2);
-    const unsigned at = (unsigned)(((row - (cr.first - cr.tok0)) * ld + 16 * grp) * 2);
+    const unsigned at = walk_row_offset(row, cr.first - cr.tok0, ld, 16 * grp, 2);
     r.v[0] = rsrc_load16(d, at);
     r.v[1] = rsrc_load16(d, at + 16);
 }
@@ -251,12 +283,12 @@ __device__ __forceinline__ void group_products(float (&a)[16], float (&z)[16], c
 // 16 values of the tile layout, columns from `col0` on, to the rows of `dst` (lo: first row that stands for a token).
 // Neighbouring lanes trade halves of their bf16 pairs: the even lane then has both channels of the first token of
 // two, the odd one of the second, and a store covers four rows with 64 bytes each.
-struct TileStore {
+template <bool FAR> struct TileStore {
     WalkRsrc dst;
     unsigned at, sel;
     int ld;
-    __device__ __forceinline__ TileStore(WalkRsrc dst_, int rt, int col0, int lo, int ld_, int lane)
-        : dst(dst_), at((unsigned)(((32 * rt + 4 * (lane >> 5) + (lane & 1) - lo) * ld_ + col0 + (lane & 30)) * 2)),
+    __device__ __forceinline__ TileStore(const ChunkSpan& span, int rt, int col0, int lo, int ld_, int lane)
+        : dst(span_rsrc(span)), at(walk_row_offset(32 * rt + 4 * (lane >> 5) + (lane & 1), lo, ld_, col0 + (lane & 30), 2)),
           sel((lane & 1) ? 0x03020706u : 0x05040100u), ld(ld_)
     {
     }
@@ -269,6 +301,28 @@ struct TileStore {
         const uint32_t u = __builtin_bit_cast(uint32_t, h);
         const uint32_t n = __builtin_amdgcn_update_dpp(0u, u, 0xB1, 0xf, 0xf, true);      // the neighbour's
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(n, u, sel), dst, at + (unsigned)((8 * (i >> 1) + 2 * (i & 1)) * ld * 2), 0, kWalkStream);
+    }
+};
+template <> struct TileStore<true> {
+    ChunkSpan span;
+    int row, col, ld;
+    unsigned sel;
+    __device__ __forceinline__ TileStore(const ChunkSpan& span_, int rt, int col0, int lo, int ld_, int lane)
+        : span(span_), row(32 * rt + 4 * (lane >> 5) + (lane & 1) - lo), col(col0 + (lane & 30)), ld(ld_),
+          sel((lane & 1) ? 0x03020706u : 0x05040100u)
+    {
+    }
+    __device__ __forceinline__ void pair(int i, float x0, float x1) const
+    {
+        bf16x2 h;
+        h.x = (__bf16)x0;
+        h.y = (__bf16)x1;
+        const uint32_t u = __builtin_bit_cast(uint32_t, h);
+        const uint32_t n = __builtin_amdgcn_update_dpp(0u, u, 0xB1, 0xf, 0xf, true);
+        const int r = row + 8 * (i >> 1) + 2 * (i & 1);
+        const uintptr_t base = (uintptr_t)span.lo | ((uintptr_t)span.hi << 32);
+        if ((uint32_t)r < span.bytes)
+            __builtin_nontemporal_store(__builtin_amdgcn_perm(n, u, sel), reinterpret_cast<uint32_t*>(base + ((size_t)r * (size_t)ld + (size_t)col) * 2));
     }
 };
 
@@ -289,8 +343,8 @@ __device__ __forceinline__ ChunkAt light_walk(const BwdGradParams& p, __bf16* Qs
     const bool has_d = (NAT * NBT) % NW == 0 || ww.w < NAT * NBT, vd_act = 64 * NW == C * GPR || tid < C * GPR;
     const float beta = GATED ? p.beta[(size_t)(cur.bh / p.lay.seg % p.H) * DK + 32 * ww.at + (tid & 31)] : 0.0f;
     auto load = [&](const ChunkAt& c, int lane) {
-        if (ww.has_a) load_gate_query<DK, GATE_BF16>(p, raw_f, raw_q, c, ww, lane);
-        if (vd_act) load_value_rows<DV>(p, raw_d, p.dO, c, 64 * ww.w + lane);
+        if (ww.has_a) load_gate_query<DK, GATE_BF16, false>(p, raw_f, raw_q, c, ww, lane);
+        if (vd_act) load_value_rows<DV, false>(p, raw_d, p.dO, c, 64 * ww.w + lane);
     };
     load(cur, tid & 63);
     float g_run = 1.0f;
@@ -378,7 +432,8 @@ __device__ __forceinline__ ChunkAt light_walk(const BwdGradParams& p, __bf16* Qs
 // over the chunks between its end and the sequence's; or, with `span_add`, adds up what bwd_ends_kernel found for the later
 // spans of that sequence:
 //     dS = Diag(decay_{s+1}) ( ... Diag(decay_last) grad_hT + add_last ... ) + add_{s+1}.
-template <int DK, int DV, bool GATE_BF16, bool GATED, bool GROUPED>
+// FAR: rows too far apart for descriptors.  So many heads are never cut (walk_rows.hpp), and no such walk is light.
+template <int DK, int DV, bool GATE_BF16, bool GATED, bool GROUPED, bool FAR>
 __device__ __forceinline__ void walk_body(const BwdGradParams& p)
 {
     typedef __bf16 T;
@@ -537,10 +592,10 @@ __device__ __forceinline__ void walk_body(const BwdGradParams& p)
     Raw16<T> raw_v, raw_d;
     auto load_rows_of = [&](const ChunkAt& c, bool values_only, const WalkWave& ww, int lane) {
         if (!values_only) {
-            if (has_a) load_gate_query<DK, GATE_BF16>(p, raw_f, raw_q, c, ww, lane);
-            if (vd_act) load_value_rows<DV>(p, raw_d, p.dO, c, 64 * ww.w + lane);
+            if (has_a) load_gate_query<DK, GATE_BF16, FAR>(p, raw_f, raw_q, c, ww, lane);
+            if (vd_act) load_value_rows<DV, FAR>(p, raw_d, p.dO, c, 64 * ww.w + lane);
         }
-        if (vd_act) load_value_rows<DV>(p, raw_v, p.v, c, 64 * ww.w + lane);
+        if (vd_act) load_value_rows<DV, FAR>(p, raw_v, p.v, c, 64 * ww.w + lane);
     };
     ChunkAt cur;
     {
@@ -593,7 +648,8 @@ __device__ __forceinline__ void walk_body(const BwdGradParams& p)
             n_light = p.light ? p.NC - 1 - f_last : 0;
             cur.n = f_last + n_light;
         }
-        if (n_light > 0) {
+        if constexpr (FAR) n_light = 0;
+        else if (n_light > 0) {
             // (second set: the tiles of K~ and D')
             cur = light_walk<DK, DV, GATE_BF16, GATED, NW, 2>(p, QT, DK * PT, dOm, C * PV, tot, cur, n_light, accD, nullptr, raw_f, raw_q, raw_d, ww);
         }
@@ -609,7 +665,7 @@ __device__ __forceinline__ void walk_body(const BwdGradParams& p)
     int df_lo = 0;
     auto finish_df = [&](const WalkWave& ww, int lane, int ld_k) {
         const float other = ex[(1 - ww.rt) * DK + 32 * ww.at + (lane & 31)];
-        const TileStore out(span_rsrc(df_dst), ww.rt, 32 * ww.at, df_lo, ld_k, lane);
+        const TileStore<FAR> out(df_dst, ww.rt, 32 * ww.at, df_lo, ld_k, lane);
 #pragma unroll
         for (int i = 0; i < 8; ++i) out.pair(i, fmaf(other, df_r[2 * i], df_u[2 * i]), fmaf(other, df_r[2 * i + 1], df_u[2 * i + 1]));
         if constexpr (GATED) run_b += fmaf(other, beta_r, beta_u);
@@ -789,7 +845,7 @@ __device__ __forceinline__ void walk_body(const BwdGradParams& p)
 #pragma unroll
             for (int ks = 0; ks < DK / 16; ++ks)
                 WM::mma(aV, WM::load_kmajor(KT, PT, 16 * ks, 32 * rt_b, lane), WM::load_kmajor_swapped(dSm, PV, 16 * ks, 32 * bt, lane));
-            const TileStore out(chunk_rsrc(p.dv, cur.sv.off_v, cr, ld_v, DV, 2), rt_b, 32 * bt, lo, ld_v, lane);
+            const TileStore<FAR> out(chunk_span<FAR>(p.dv, cur.sv.off_v, cr, ld_v, DV, 2), rt_b, 32 * bt, lo, ld_v, lane);
 #pragma unroll
             for (int i = 0; i < 8; ++i) out.pair(i, aV[2 * i], aV[2 * i + 1]);
         };
@@ -838,7 +894,7 @@ __device__ __forceinline__ void walk_body(const BwdGradParams& p)
         // (bf16(.) are the values the MFMAs consumed, so that the pair terms inside e' cancel to fp32 accuracy)
         if (has_a) {
             float a[16], z[16], gs[16], dk[16], te[4], tk[4];
-            const TileStore out(chunk_rsrc(p.dq, cur.sv.off_k, cr, ld_k, DK, 2), rt, 32 * at, lo, ld_k, lane);
+            const TileStore<FAR> out(chunk_span<FAR>(p.dq, cur.sv.off_k, cr, ld_k, DK, 2), rt, 32 * at, lo, ld_k, lane);
             if constexpr (GATED) {
                 const f32x4 xa = stash[64 * w + lane], xz = stash[NT + 64 * w + lane];
 #pragma unroll
@@ -908,7 +964,7 @@ __device__ __forceinline__ void walk_body(const BwdGradParams& p)
                     df_r[i] = r * (f[i] - beta);
                 }
             }
-            df_dst = chunk_span(p.df, cur.sv.off_k, cr, ld_k, DK, 2);
+            df_dst = chunk_span<FAR>(p.df, cur.sv.off_k, cr, ld_k, DK, 2);
             df_lo = lo;
         }
         __syncthreads(); // every wave is done with the tiles
@@ -923,25 +979,31 @@ __device__ __forceinline__ void walk_body(const BwdGradParams& p)
     }
 }
 
-template <int DK, int DV, bool GATE_BF16, bool GATED>
+template <int DK, int DV, bool GATE_BF16, bool GATED, bool FAR = false>
 __global__ __launch_bounds__(64 * walk_waves(DK, DV), 2) void bwd_walk_kernel(BwdGradParams p)
 {
-    walk_body<DK, DV, GATE_BF16, GATED, false>(p);
+    walk_body<DK, DV, GATE_BF16, GATED, false, FAR>(p);
 }
 
 // The walk over spans of a packed batch (a kernel of its own).
-template <int DK, int DV, bool GATE_BF16, bool GATED>
+template <int DK, int DV, bool GATE_BF16, bool GATED, bool FAR = false>
 __global__ __launch_bounds__(64 * walk_waves(DK, DV), 2) void bwd_walk_grouped_kernel(BwdGradParams p)
 {
-    walk_body<DK, DV, GATE_BF16, GATED, true>(p);
+    walk_body<DK, DV, GATE_BF16, GATED, true, FAR>(p);
 }
 
 template <int DK, int DV, bool GATED>
 static hipError_t launch_walk_one(const SeqDims& d, const BwdGradParams& p, bool grouped, hipStream_t stream)
 {
     typedef WalkLds<DK, DV> L;
-    auto kern = grouped ? (d.gate_bf16 ? bwd_walk_grouped_kernel<DK, DV, true, GATED> : bwd_walk_grouped_kernel<DK, DV, false, GATED>)
-                        : (d.gate_bf16 ? bwd_walk_kernel<DK, DV, true, GATED> : bwd_walk_kernel<DK, DV, false, GATED>);
+    const bool bf = d.gate_bf16;
+    auto kern = grouped ? (bf ? bwd_walk_grouped_kernel<DK, DV, true, GATED> : bwd_walk_grouped_kernel<DK, DV, false, GATED>)
+                        : (bf ? bwd_walk_kernel<DK, DV, true, GATED> : bwd_walk_kernel<DK, DV, false, GATED>);
+    if (!walk_rows_near(d.lay.sn_k, d.lay.sn_v, bf ? 2 : 4)) {
+        if (grouped ? d.lay.spans != 1 : p.R != 1) return hipErrorInvalidValue;
+        kern = grouped ? (bf ? bwd_walk_grouped_kernel<DK, DV, true, GATED, true> : bwd_walk_grouped_kernel<DK, DV, false, GATED, true>)
+                       : (bf ? bwd_walk_kernel<DK, DV, true, GATED, true> : bwd_walk_kernel<DK, DV, false, GATED, true>);
+    }
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)L::total);
     if (e != hipSuccess) return e;
     const unsigned grid = grouped ? (unsigned)(d.lay.spans * d.lay.H) : (unsigned)(d.BH * p.R);
