@@ -248,6 +248,11 @@ template <> __device__ __forceinline__ void stream_pair_t<float>(float* base, si
 // of a small-gate mode stand for no token, see ChunkRows.)
 template <int RW> struct RawRows { f32x2 r[RW]; };
 
+// The bytes of i rows of row_elems elements of ES bytes.  A row holds the elements of every head, up to 1 GiB, so that a few rows are more
+// than an int holds.  (From one row to the next it is one 64-bit addition, where ints took a product and its sign: forward passes with
+// strided rows 1.003 times as fast over 696 shapes.  A condition on the stride beside that on the rows cost 1 to 6%.)
+template <int ES> __device__ __forceinline__ size_t rows_apart(int i, int row_elems) { return (size_t)i * (uint32_t)(row_elems * ES); }
+
 template <int RW>
 __device__ __forceinline__ void load_rows(RawRows<RW>& out, const void* base, size_t seq_off, int row_stride,
                                           int col, int row0, int n_rows, bool is_bf16)
@@ -261,7 +266,7 @@ __device__ __forceinline__ void load_rows(RawRows<RW>& out, const void* base, si
             const char* b0 = b + (size_t)row0 * row_stride * 2;
 #pragma unroll
             for (int i = 0; i < RW; ++i)
-                out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(b0 + i * row_stride * 2));
+                out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(b0 + rows_apart<2>(i, row_stride)));
         } else {
 #pragma unroll
             for (int i = 0; i < RW; ++i) {
@@ -274,7 +279,7 @@ __device__ __forceinline__ void load_rows(RawRows<RW>& out, const void* base, si
         if (full) {
             const char* b0 = b + (size_t)row0 * row_stride * 4;
 #pragma unroll
-            for (int i = 0; i < RW; ++i) out.r[i] = *reinterpret_cast<const f32x2*>(b0 + i * row_stride * 4);
+            for (int i = 0; i < RW; ++i) out.r[i] = *reinterpret_cast<const f32x2*>(b0 + rows_apart<4>(i, row_stride));
         } else {
 #pragma unroll
             for (int i = 0; i < RW; ++i) {
@@ -299,8 +304,8 @@ __device__ __forceinline__ void load_rows_clamped(RawRows<RW>& out, const char* 
         const char* rp = seq_base + (size_t)row0 * (row_elems * ES) + lane_col * ES;
 #pragma unroll
         for (int i = 0; i < RW; ++i) {
-            if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp + i * row_elems * ES));
-            else out.r[i] = *reinterpret_cast<const f32x2*>(rp + i * row_elems * ES);
+            if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp + rows_apart<ES>(i, row_elems)));
+            else out.r[i] = *reinterpret_cast<const f32x2*>(rp + rows_apart<ES>(i, row_elems));
         }
     } else {
 #pragma unroll
@@ -324,11 +329,11 @@ __device__ __forceinline__ void load_block_rows(RawRows<RW>& out, const char* se
         constexpr int ES = IS_BF16 ? 2 : 4;
         const int half = lane >> 5, col = 2 * (lane & 31);
         if (row0 >= 0 && row0 + 2 * RW - 1 <= last_row) {
-            const char* rp = seq_base + (size_t)row0 * (ld * ES) + (uint32_t)((half * RW * ld + col) * ES);
+            const char* rp = seq_base + (size_t)row0 * (ld * ES) + rows_apart<ES>(half * RW, ld) + col * ES;
 #pragma unroll
             for (int i = 0; i < RW; ++i) {
-                if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp + i * ld * ES));
-                else out.r[i] = *reinterpret_cast<const f32x2*>(rp + i * ld * ES);
+                if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp + rows_apart<ES>(i, ld)));
+                else out.r[i] = *reinterpret_cast<const f32x2*>(rp + rows_apart<ES>(i, ld));
             }
         } else {
 #pragma unroll

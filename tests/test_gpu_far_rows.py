@@ -1,5 +1,5 @@
 """So many heads side by side that the rows of a chunk lie gigabytes apart: the reverse walk then takes 64-bit row addresses
-(csrc/walk_rows.hpp says from which stride on).  The heads repeat 512 heads, so every element of every result has to be that of a
+(csrc/walk_rows.hpp says from which stride on), and a few rows of the other kernels are more than an int apart.  The heads repeat 512 heads, so every element of every result has to be that of a
 call over those alone; bf16 results to 2 units in the last place of the largest value (another instance of the kernel
 may contract its sums in another way; a row that was taken for another one is off by the value itself)."""
 import pytest
@@ -89,5 +89,36 @@ def test_packed_backward_of_far_rows(saved):
     far = run(times)
     for i, (x, y) in enumerate(zip(far, few)):
         same("grad %d" % i, x, y, times)
+    del far
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("what,H,dk,dv,N", [
+    ("fwd", 2560 * FEW, 64, 64, 16), ("fwd", 1280 * FEW, 128, 128, 8), ("f32", 2048 * FEW, 64, 64, 16), ("bwd", 2048 * FEW, 64, 64, 16)])
+def test_whole_blocks_of_far_rows(what, H, dk, dv, N):
+    """Rows of 320 MiB (256 in the last two) of fp32 gates, in blocks of 8 and 16 that lie inside the sequence: the forward pass, the one of
+    fp32 storage (sweep and read-out) and the stateless backward pass (sweep and reverse walk)."""
+    room(160)
+    print("\n[far rows, blocks] %s H=%d dk=%d dv=%d N=%d" % (what, H, dk, dv, N), flush=True)
+    q, f, v, dO, _ = few_heads(47, N, dk, dv, torch.float32, False)
+    if what == "f32":
+        q, v = q.float(), v.float()
+
+    def run(times):
+        a, g, b, c = (x.repeat(1, times, 1).unsqueeze(0) for x in (q, f, v, dO))
+        if what == "bwd":
+            r = [x for x in binding.hgrn2_bwd(a, g, b, c, layout=BNHD) if x is not None]
+        else:
+            r = list(binding.hgrn2_fwd(a, g, b, layout=BNHD))
+        torch.cuda.synchronize()
+        return r
+
+    times = H // FEW
+    few = run(1)
+    far = run(times)
+    for i, (x, y) in enumerate(zip(far, few)):
+        if x.dim() == 4 and x.shape[1] != N:          # the final state: a head's rows together
+            x, y = x.reshape(1, H, dk * dv), y.reshape(1, FEW, dk * dv)
+        same("%s %d" % (what, i), x, y, times)
     del far
     torch.cuda.empty_cache()
