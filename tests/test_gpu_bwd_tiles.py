@@ -52,6 +52,12 @@ def test_walk_at_tile_edges(dk, dv, layout, gate, gated, chunk):
             check("dbeta", host(g[-1]), rb, TOL["bf16"])
 
 
+@pytest.mark.parametrize("dk,dv,layout,gate,gated,chunk", [
+    (64, 64, 1, "bf16", True, 16), (128, 64, 0, "f32", False, 32), (64, 128, 0, "bf16", True, 32), (128, 128, 1, "f32", True, 16)])
+def test_fine_chunks_at_tile_edges(dk, dv, layout, gate, gated, chunk):
+    test_walk_at_tile_edges(dk, dv, layout, gate, gated, chunk)
+
+
 @pytest.mark.parametrize("dk,dv,gate,gated", [(128, 128, "bf16", True), (64, 64, "f32", False), (128, 64, "bf16", False), (64, 128, "bf16", True)])
 def test_packed_walk_at_tile_edges(dk, dv, gate, gated):
     beta = np.random.default_rng(6).uniform(0.2, 0.9, size=(2, dk)).astype(np.float32) if gated else None
@@ -73,6 +79,12 @@ def test_packed_walk_at_tile_edges(dk, dv, gate, gated):
         check("dbeta", host([x for x in g if x is not None][-1]), sum(x[3] for x in refs), TOL["bf16"])
 
 
+def odd(x):
+    room = torch.zeros(x.numel() + 8, dtype=x.dtype, device="cuda")
+    room[1:1 + x.numel()] = x.flatten()
+    return room[1:1 + x.numel()].view(x.shape)
+
+
 def test_tensors_that_start_at_an_odd_element():
     B, H, N, d = 2, 2, 197, 128
     gen = torch.Generator(device="cuda").manual_seed(3)
@@ -80,14 +92,31 @@ def test_tensors_that_start_at_an_odd_element():
     xs[1] = 0.4 + 0.6 * torch.sigmoid(xs[1])
     xs = [x.bfloat16() for x in xs]
 
-    def odd(x):
-        room = torch.zeros(x.numel() + 8, dtype=x.dtype, device="cuda")
-        room[1:1 + x.numel()] = x.flatten()
-        return room[1:1 + x.numel()].view(x.shape)
-
     def run(q, f, v, dO):
         o, _, saved = binding.hgrn2_fwd_saving(q, f, v, want_hT=False)
         return [o] + [x for x in binding.hgrn2_bwd_saved(q, f, v, saved, dO) if x is not None]
 
     for a, b in zip(run(*xs), run(*[odd(x) for x in xs])):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dk,dv,layout,gate,gated,chunk", [
+    (64, 64, 1, torch.float32, True, 0), (128, 64, 1, torch.float32, False, 16), (64, 128, 0, torch.bfloat16, True, 0)])
+def test_other_shapes_that_start_at_an_odd_element(dk, dv, layout, gate, gated, chunk):
+    """Inputs and gradients alike, which a caller of the C ABI may place as it likes."""
+    B, H, N = 2, 3, 133
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    at = lambda d: (B, N, H, d) if layout == BNHD else (B, H, N, d)
+    r = lambda d: torch.randn(at(d), generator=gen, device="cuda")
+    z = r(dk)
+    xs = [r(dk).bfloat16(), (z if gated else 0.4 + 0.6 * torch.sigmoid(z)).to(gate), r(dv).bfloat16(), r(dv).bfloat16()]
+    beta = torch.full((H, dk), 0.3, device="cuda") if gated else None
+
+    def run(q, f, v, dO, place):
+        o, _, saved = binding.hgrn2_fwd_saving(q, f, v, beta=beta, want_hT=False, layout=layout, chunk=chunk)
+        g = [place(torch.zeros_like(x, dtype=torch.bfloat16)) for x in (q, f, v)]
+        out = binding.hgrn2_bwd_saved(q, f, v, saved, dO, beta=beta, layout=layout, chunk=chunk, grad_q=g[0], grad_f=g[1], grad_v=g[2])
+        return [o] + [x for x in out if x is not None]
+
+    for a, b in zip(run(*xs, lambda x: x), run(*[odd(x) for x in xs], odd)):
         assert torch.equal(a, b)
