@@ -19,8 +19,8 @@ struct BwdGradParams {
     const float* beta;       // [H][dk] lower bounds, or null: the gate tensor holds f itself
     float* beta_partials;    // [B*H*NC][8][dk] per-wave partial sums of the gradient w.r.t. beta
     int H;
-    TokenLayout lay;         // used when dense == 0
-    int dense;               // sequence tensors are [B][H][N][d]
+    TokenLayout lay;         // (always set: the walks of bwd_walk.hip take strides and offsets from it whatever the layout)
+    int dense;               // sequence tensors are [B][H][N][d]: bwd_grad.hip then has compile-time strides
     // Reverse walk (walk_body(), bwd_grad_body<..., FUSED>): the state gradient is carried in registers
     // instead of being read from ws_ds.  Every sequence is cut into R runs of rc chunks, one
     // workgroup each; a run starts from grad_hT (the last one), from bound0[bh] (run 0) or from

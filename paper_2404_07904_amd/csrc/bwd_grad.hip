@@ -193,7 +193,7 @@ __device__ __forceinline__ ChunkAt light_walk(const BwdGradParams& p, T* Qm, T* 
     return cur;
 }
 
-// FUSED (fp32 storage; bf16 has bwd_walk.hip): the workgroup owns run `r` of sequence `bh` and walks its chunks from the last to the
+// FUSED (fp32 storage, heads of 64 x 64 alone; bf16 has bwd_walk.hip): the workgroup owns run `r` of sequence `bh` and walks its chunks from the last to the
 // first with the state gradient in fp32 MFMA accumulators, oriented [dv][channel]:
 //     E_n = D'_n + Q~_n^T dO_n ,   D'_n = (g_n / G_m,n) dS_{n+1} ,   dS_n = G_m,n E_n
 // so that before each chunk the accumulators are scaled by (second-half gate product of this
@@ -521,7 +521,7 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
     // ---------------- P^T and dP^T blocks ----------------
     // Eight waves: 0..2 take the P blocks (I,J) = (0,0), (1,0), (1,1), 3..5 the same for dP, 6 and 7 zero
     // the never-computed block (rows j >= 32, columns i < 32) so that every later contraction can run
-    // over the full chunk without reading stale data.  Four waves: 0..2 take a block of both, 3 zeroes both.
+    // over the full chunk without reading stale data.
     auto p_block = [&](bool is_dp, int b) {
         const int I = (b == 0) ? 0 : 1, J = (b == 2) ? 1 : 0;
         f32x16 acc0, acc1;
@@ -670,11 +670,10 @@ __device__ __forceinline__ void bwd_grad_body(const BwdGradParams& p)
 #pragma unroll
         for (int i = RW - 1; i >= 0; --i) { z0[i] = u0; z1[i] = u1; u0 *= rf[i].x; u1 *= rf[i].y; }
     }
-    // (Gradients leave with non-temporal stores: what the runs read twice, and the states the forward pass has just left, keep their
+    // (Gradients leave with non-temporal stores: what is read twice, and the states the forward pass has just left, keep their
     // place in the caches, which is worth more than the gradients' to the projections' reverse mode, the next to read them.
-    // us, ordinary -> non-temporal, six sets of buffers in turn: training pair of 8 x 16 heads of 128, 2048 tokens 267 -> 261 (inputs just
-    // written 293 -> 290; all results read and written by kernels right behind 369 -> 370), 2 x 16 heads, 16384 tokens 727 -> 708; whole
-    // layer of 16384 tokens and width 2048 1518 -> 1511, of 64 to 4096 tokens and width 256 to 1024 1 to 4% less with these and o's.)
+    // us, ordinary -> non-temporal, six sets of buffers in turn, by the walk of bf16 storage that this body used to be as well: training pair of
+    // 8 x 16 heads of 128, 2048 tokens 267 -> 261, 2 x 16 heads, 16384 tokens 727 -> 708, whole layer of 16384 tokens and width 2048 1518 -> 1511.)
     // rows of this wave's block to global memory: one address and constant offsets when the
     // whole block lies inside the sequence, row by row otherwise
     auto store_block = [&](T* dst, const float (&x0)[RW], const float (&x1)[RW]) {

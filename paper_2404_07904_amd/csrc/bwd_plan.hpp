@@ -25,9 +25,10 @@ inline BwdFusedPlan uncut_bwd(int NC)
 
 // R runs with a light walk each, which costs `rho` of a chunk's full work per chunk; the cuts let all runs
 // take the same time T: len_r = T - rho (NC - end_r) from the last run (len = T) backwards, so T sum_{i<R} (1 - rho)^i = NC.
-// rho is set by the balance that measures best (128 sequences of 32 chunks in two runs: 14 + 18 chunks 180 us,
-// 15 + 17 185 us, 13 + 19 187 us; a light chunk alone costs 0.16 to 0.25 of a full one, but with many sequences the light
-// walks run while the memory system is busiest).
+// rho is the balance that measured best with the bf16 walk before the present one, and still does for heads of 128: 128 sequences of
+// 32 chunks in two runs, 12 + 20 chunks 157 us, 13 + 19 152, 14 + 18 (taken) 152, 15 + 17 158; 64 chunks 27 + 37 310, 28 + 36 (taken) 307, 29 + 35 310.
+// Heads of 64 x 64 would take a larger one (256 sequences of 32 chunks: 12 + 20 124 us, 14 + 18, which are taken, 130).  A light chunk alone
+// costs 0.23 to 0.26 of a full one.
 constexpr double kBwdLightCost = 0.24;
 
 // longest: what the longest run takes, at `cost` a light chunk.
@@ -73,10 +74,14 @@ inline BwdFusedPlan ends_bwd(int NC, int R)
     return pl;
 }
 
-// What the walks take besides the full walk of their run, in chunks of it (128 x 128: 7.5 us a chunk, 64 x 64: 5 us): a chunk of a
-// light walk; the two more launches of the walks from zero; a megabyte of states that those write and read twice.
-// Fitted with the constants of plan_bwd_runs() to 1750 timings: 1 to 250 sequences of 2 to 256 chunks, gates given and formed,
-// every cut tried at each size; the chosen cut takes 0.1 to 0.2% more than the best on average.
+// What the walks take besides the full walk of their run, in chunks of it: a chunk of a light walk; the two more launches of the walks
+// from zero; a megabyte of states that those write and read twice.
+// Fitted with the constants of plan_bwd_runs() to 1750 timings of the bf16 walk before the present one (7.5 us a chunk of 128 x 128, 5 us of
+// 64 x 64): 1 to 250 sequences of 2 to 256 chunks, gates given and formed, every cut tried at each size; the chosen cut took 0.1 to
+// 0.2% more than the best on average.  With the present walk (5.9 and 3.5 us a chunk) it takes 0.3% more with heads 128 channels wide, at most 1.16
+// times the best, and 1.5% with heads of 64 channels, whose light chunks now cost 0.26 of a full one: few sequences of 8 to 12 chunks are walked
+// from zero where light walks would do (8 heads of 64 x 128, 8 chunks: 20.2 us, light 15.3), and 56 to 128 heads of 64 x 64 take more runs than pay
+// (128 heads of 12 chunks in four 34.7, in two 29.9).
 struct BwdCost { double light, ends, mb; };
 inline BwdCost bwd_cost(int dk, int dv)
 {
@@ -101,16 +106,16 @@ inline BwdFusedPlan plan_bwd_runs(int BH, int NC, int dk, int dv, bool io_bf16, 
     }
     // Runs of one, two or four chunks and more, as many as find a place; light walks or walks from zero, by what they take (two
     // workgroups on a compute unit: 1.4 times as long).  1, 16 and 64 heads; us with runs of at
-    // least four chunks -> now:
-    //   128 x 128:  4 chunks 34 -> 16.4, 34.8 -> 17.0, 36 -> 19.5 (light)     16 chunks 48.9 -> 29.7 (from zero), 51.1 -> 36.3 (light), 56
-    //              32 chunks 55.3 -> 33.3, 60.9 -> 47.9 (from zero), 115       64 chunks 57.0 -> 40.3, 68.2 (from zero)
-    //   64 x 64:    4 chunks 23.2 -> 12.2, 23.7 -> 12.5, 24.3 -> 13.1 (light)  16 chunks 34.2 -> 19.8, 34.8 -> 22.6, 35.9 -> 34.4 (from zero)
-    // Runs of one chunk only, as long as they find a place, are too many for few long sequences (one head of 256 chunks: 64 x 64 46.7 us
-    // in 64 runs, 63.0 in 256; 128 x 128 67.0 and 76.8, 61.0 in 128): every run's state is added up by one after the other.
+    // least four chunks -> with these:
+    //   128 x 128:  4 chunks 26.5 -> 13.3, 27.0 -> 13.9, 27.9 -> 16.1 (light)  16 chunks 38.4 -> 26.7, 40.0 -> 34.3 (from zero; light 31.8), 47.5
+    //              32 chunks 46.8 -> 30.4, 51.8 -> 43.7 (from zero), 84        64 chunks 48.7 -> 37.3, 60.4 (from zero)
+    //   64 x 64:    4 chunks 17.1 -> 9.5, 17.6 -> 9.7, 17.8 -> 10.0 (light)    16 chunks 25.3 -> 16.9, 25.8 -> 19.8 (from zero), 28.9 -> 32.2
+    // Runs of one chunk only, as long as they find a place, are too many for few long sequences (one head of 256 chunks: 64 x 64 39.2 us
+    // in 64 runs, 60.4 in 256; 128 x 128 59.1 and 75.3, 56.1 in 128): every run's state is added up by one after the other.
     const BwdCost cost = bwd_cost(dk, dv);
     const int most = (pairs ? 2 : 1) * kOnePerUnit;
     // Three launches that return at once take 6.7 us, one 1.9: where few runs have four chunks, fine lengths take light walks
-    // (length chosen on the device, ordinary gates, 128 heads of 64 x 64 and 12 chunks of 64: 57.0 -> 49.1 us).
+    // (length chosen on the device, ordinary gates, 128 heads of 64 x 64 and 12 chunks of 64: 39.4 us, 34.8 with the length named).
     const bool ends_ok = !fine || (most / BH > 4 && NC / 4 > 4);
     BwdFusedPlan best = uncut_bwd(NC);
     double least = NC;
@@ -126,7 +131,7 @@ inline BwdFusedPlan plan_bwd_runs(int BH, int NC, int dk, int dv, bool io_bf16, 
                 if (t < least) { least = t; best = light; }
             }
             // (two or three runs per sequence: the walks from zero read most of q, f and grad_o once more while the
-            // memory system is busy already; 128 x 128, 85 heads of 128 chunks 513 us light, 537 us from zero, but 64 heads, four runs each, 424 and 400)
+            // memory system is busy already; 128 x 128, 85 heads of 128 chunks 464 us light, 474 us from zero, but 64 heads, four runs each, 370 and 352)
             if (R < 4 || !ends_ok) continue;
             const BwdFusedPlan ends = ends_bwd(NC, R);
             const double mb = 4e-6 * dk * dv * (double)BH * ends.seg_tail;

@@ -19,8 +19,9 @@
 // Where a chunk's rows lie too far apart for a descriptor (walk_rows.hpp), kernels of their own (FAR) take 64-bit row addresses.
 //
 // What bounds it, per chunk of 128 x 128 and compute unit (15.6 kcycles with everything in the caches, 6.6 us): 8.0 kcycles of vector
-// instructions, 6.8 of LDS, 3.2 of MFMA, of which the matrix stage and the element-wise stages overlap little; over
-// buffers that leave the caches, memory, at 4.3 TB/s.  us, the walk it replaced -> this one: training pair's backward
+// instructions, 6.8 of LDS, 3.2 of MFMA (SQ counters), of which the matrix stage and the element-wise stages overlap little; over
+// buffers that leave the caches, memory as much: 720 MB at 4.3 to 4.8 TB/s.  us, the walk it replaced -> this one, six sets of buffers in
+// turn (the benchmark's two: 156 to 160): training pair's backward
 // of 8 x 16 heads of 128, 2048 tokens 190 -> 173, gate formed in the walk, token-major 213 -> 197; 2 x 16 heads, 16384 tokens, fp32 gates 449 -> 404;
 // 16 x 16 heads, 512 tokens 87 -> 74; 8 x 32 heads of 64, 2000 tokens, gate formed 179 -> 173, 16 x 32, 512 tokens 66 -> 60;
 // 8 x 16 heads of 64 x 128, 1024 tokens 91 -> 70, of 128 x 64 73 -> 67.

@@ -8,8 +8,9 @@ namespace hgrn2 {
 // 16384 tokens at widths 256 to 2048.  256 x 256 has the best rate but needs 256 tiles to fill the chip; 128 x 128 finds two
 // places on a compute unit, and so does 64 x 64, which has the shortest steps where a few workgroups have to do (a step
 // is 1.5 / 1.1 / 0.45 us with all places taken, 1.1 / 0.45 / 0.26 us on a unit of its own).
-// 575 tokens of width 1024, 256 / 128 / 64: projection 28.0 / 12.1 / 12.0 us, dx 59 / 28 / 17; 2048 tokens, projection 29.9 / 21.2 / 30.1;
-// 16384 tokens, projection 104 / 123 / 218; width 2048 363 / 432 / 721.
+// 575 tokens of width 1024, 256 / 128 / 64: projection 26.7 / 12.4 / 12.2 us, dx 59 / 28 / 17; 2048 tokens, projection 27.6 / 20.1 / 29.3;
+// 16384 tokens, projection 94 / 119 / 214; width 2048 322 / 419 / 702.  (The constants of 256 are from before the projections' tiles were walked,
+// which takes up to 10% off several tiles to a workgroup: 8192 tokens of width 1024 take 128, 60.2, where 256 takes 53.5.)
 struct NtPlan { int tile, splits; };
 inline double nt_time(int tile, long long tiles, double steps)
 {

@@ -49,12 +49,13 @@ __device__ __forceinline__ void build_groups(Before before, int n_entries, int G
         groups[grp] = first;
     }
     __syncthreads();
-    // Which backward pass.  The reverse walk gives every workgroup a span of total / G chunks of a
-    // head (about 10 us a chunk) and has it first walk, at a sixth of that cost, the chunks between
-    // the end of its span and the end of the sequence the span ends in; the other pass (two sweeps,
-    // as long as the longest sequence at about 4.6 us a chunk, then the per-chunk kernel at 11 us per
-    // chunk of a compute unit's share) wins only when one sequence is several times longer than a
-    // span: the walk is chosen while the longest such tail is at most four spans long.
+    // Which backward pass of a stateless call.  The reverse walk gives every workgroup a span of total / G chunks of a
+    // head and has it first walk, at a quarter of the cost, the chunks between the end of its span and the end of the sequence
+    // the span ends in, or add up what walks from zero found there; the other pass takes two sweeps, as long as the longest
+    // sequence, then the per-chunk kernel.  The walk is chosen while the longest such tail is at most four spans long: where the two met
+    // before the walk took 7 us a chunk.  It is ahead on the other side of the line too by now; us, walk / other pass, 16 heads,
+    // 16384 tokens, one document of 4 and of 8 spans among short ones: 128 x 128 386 / 468 and 534 / 658, 64 x 64 274 / 333 and 455 / 512,
+    // 128 x 64 318 / 356 and 488 / 518, 64 x 128 297 / 431 and 446 / 601.
     int tail = 0, head = 0;
     for (int s = threadIdx.x; s < G; s += kTabThreads) {
         const long long p0 = (long long)s * total / G, p1 = (long long)(s + 1) * total / G;
@@ -80,11 +81,13 @@ __device__ __forceinline__ void build_groups(Before before, int n_entries, int G
         const long long share = (total + G - 1) / G;
         groups[G + 1] = (tail <= 4 * share) ? 1 : 0;
         // Walks from zero take a span's chunks, and some more for the states they leave; light walks the chunks of a
-        // sequence outside a span.  us, walks from zero / light, 16384 tokens, spans of 16: 16 heads of 128, 22 chunks
-        // outside forward 106 / 96, backward 222 / 215; 37 outside 101 / 113, 217 / 239; spans of 33, 32 heads of 64 x 128: 33
-        // outside 158 / 144, 339 / 329; 46 outside 158 / 148, 344 / 354; gate formed in the kernels, spans of 18, 30 outside
-        // forward 127 / 141.  Backward, heads of 64 x 64 (a light chunk takes 2.7 us, a chunk of
-        // a walk from zero with its four waves 0.9): spans of 33, 16 outside 259 / 265, of 17, 16 outside 137 / 142.
+        // sequence outside a span.  us, walks from zero / light, 16384 tokens, spans of 16, 16 heads, that many chunks outside a span:
+        //   128 x 128  forward 24: 97 to 100 / 103, 32: 96 / 112      backward 20: 200 / 189, 32: 186 to 201 / 200 to 208, 48: 198 / 234
+        //    64 x 64   forward 24: 67 / 70, 32: 67 / 75               backward 16: 89 / 88, 20: 91 / 93, 32: 90 / 105
+        //   128 x 64   forward 24: 78 / 79, 32: 78 / 84               backward 20: 149 / 120, 32: 137 to 140 / 134 to 143, 48: 141 / 152
+        //    64 x 128  forward 24: 78 to 81 / 75 to 80, 32: 78 / 80   backward 20: 144 / 119, 32: 131 / 134, 48: 135 / 152
+        // Over 392 batches of 4 to 64 heads and 8192 to 32768 tokens what is chosen takes 1% more than the better of the two, forward of heads of
+        // 64 x 128 2.7% (spans of 32: light walks are ahead up to 64 chunks outside, 133 / 151).
         // (Fewer chunks than spans: spans without one leave nothing.)
         groups[2 * G + 2] = (total >= G && head > share + 9) ? 1 : 0;
         groups[2 * G + 3] = (total >= G && tail > (heads64 ? share / 3 + 2 : share + 8)) ? 1 : 0;

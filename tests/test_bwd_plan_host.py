@@ -55,7 +55,7 @@ def test_runs_cover_every_chunk_and_fit_the_chip(lib, dk, dv, bf16):
 
 
 # us of the reverse walk of a training pair at some sizes, cut into light runs (L) or runs from zero (E), as measured on an MI355X
-# (one run to the next: 1%)
+# (one run to the next: 1%) with the walk that the plan's costs are fitted to, the one before the present walk of bf16 storage
 MEASURED = [
     (64, 64, 1, 256, {"E64": 46.7, "E128": 46.5, "E256": 63.0}),
     (128, 128, 1, 256, {"E64": 67.0, "E128": 61.0, "E256": 76.8}),
