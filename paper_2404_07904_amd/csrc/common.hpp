@@ -320,6 +320,8 @@ __device__ __forceinline__ void load_rows_clamped(RawRows<RW>& out, const char* 
 // RW rows of this lane's channel pair, row0 wave-uniform: rows row0 .. row0 + RW - 1 of pair `lane` for the
 // whole wave, or (HALVES: heads of 64, whose rows have only 32 pairs) of pair lane % 32, the upper half
 // wave taking the RW rows after those of the lower one.  Rows outside the sequence re-read a row inside it.
+// HALVES: ints hold 2 RW rows (halves_near(); 64-bit offsets spill where a lane has an address of its own).
+template <int RW> constexpr bool halves_near(long long ld, int es) { return 2 * RW * ld * es <= 0x7fffffff; }
 template <bool HALVES, int RW, bool IS_BF16>
 __device__ __forceinline__ void load_block_rows(RawRows<RW>& out, const char* seq_base, int row0, int last_row, int ld, int lane)
 {
@@ -329,11 +331,11 @@ __device__ __forceinline__ void load_block_rows(RawRows<RW>& out, const char* se
         constexpr int ES = IS_BF16 ? 2 : 4;
         const int half = lane >> 5, col = 2 * (lane & 31);
         if (row0 >= 0 && row0 + 2 * RW - 1 <= last_row) {
-            const char* rp = seq_base + (size_t)row0 * (ld * ES) + rows_apart<ES>(half * RW, ld) + col * ES;
+            const char* rp = seq_base + (size_t)row0 * (ld * ES) + (uint32_t)((half * RW * ld + col) * ES);
 #pragma unroll
             for (int i = 0; i < RW; ++i) {
-                if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp + rows_apart<ES>(i, ld)));
-                else out.r[i] = *reinterpret_cast<const f32x2*>(rp + rows_apart<ES>(i, ld));
+                if (IS_BF16) out.r[i].x = __uint_as_float(*reinterpret_cast<const uint32_t*>(rp + i * ld * ES));
+                else out.r[i] = *reinterpret_cast<const f32x2*>(rp + i * ld * ES);
             }
         } else {
 #pragma unroll

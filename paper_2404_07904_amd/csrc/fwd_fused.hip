@@ -965,7 +965,8 @@ __global__ __launch_bounds__(64 * fused_waves(DK), 2) void run_ends_kernel(FwdFu
 
 static bool fused_grouped(const SeqDims& d) { return d.lay.vl && d.lay.spans > 0; }
 
-bool fwd_fused_supported(const SeqDims& d) { return d.io_bf16; }
+// (heads of 64 so many that 16 rows are more than an int apart, 524288 with fp32 gates, take sweep and read-out)
+bool fwd_fused_supported(const SeqDims& d) { return d.io_bf16 && (d.dk != 64 || halves_near<8>(d.lay.sn_k, d.gate_bf16 ? 2 : 4)); }
 
 typedef void (*FusedKernel)(FwdFusedParams);
 

@@ -97,7 +97,7 @@ def test_packed_backward_of_far_rows(saved):
     ("fwd", 2560 * FEW, 64, 64, 16), ("fwd", 1280 * FEW, 128, 128, 8), ("f32", 2048 * FEW, 64, 64, 16), ("bwd", 2048 * FEW, 64, 64, 16)])
 def test_whole_blocks_of_far_rows(what, H, dk, dv, N):
     """Rows of 320 MiB (256 in the last two) of fp32 gates, in blocks of 8 and 16 that lie inside the sequence: the forward pass, the one of
-    fp32 storage (sweep and read-out) and the stateless backward pass (sweep and reverse walk)."""
+    fp32 storage (sweep and read-out, which so many heads of 64 take in bf16 too) and the stateless backward pass (sweep and reverse walk)."""
     room(160)
     print("\n[far rows, blocks] %s H=%d dk=%d dv=%d N=%d" % (what, H, dk, dv, N), flush=True)
     q, f, v, dO, _ = few_heads(47, N, dk, dv, torch.float32, False)
